@@ -89,7 +89,7 @@ struct d2c_ctx {
   size_t max_rows = 0;          // max_seq * max_batch: rows the row-count-sized buffers hold
   void* head_a = nullptr;       // T [head_rows, d]
   float* logits = nullptr;      // [head_rows, vocab]
-  float* conf_part = nullptr;   // per-chunk (max, argmax, sum) triples of Eq. 1 for up to max_seq rows
+  float* conf_part = nullptr;   // per-chunk (max, argmax, sum) triples of Eq. 1 for every row of a group
   int head_rows = 0;
   float* rope_cos = nullptr;    // [max_seq, head_dim/2]
   float* rope_sin = nullptr;
@@ -469,7 +469,7 @@ int d2c_init_tuned(const d2c_dims* dims, const d2c_weights* w, const d2c_tunable
       (rc = ws_alloc(c, &c->partial, pf * 4)) ||
       (rc = ws_alloc(c, &c->head_a, (size_t)c->head_rows * d * ts)) ||
       (rc = ws_alloc(c, &c->logits, (size_t)c->head_rows * D.vocab * 4)) ||
-      (rc = ws_alloc(c, &c->conf_part, confidence_scratch_floats(D.max_seq) * 4)) ||
+      (rc = ws_alloc(c, &c->conf_part, confidence_scratch_floats((int)c->max_rows) * 4)) ||
       (rc = ws_alloc(c, &c->rope_cos, Lm * (D.head_dim / 2) * 4)) ||
       (rc = ws_alloc(c, &c->rope_sin, Lm * (D.head_dim / 2) * 4)))
     return bail(rc);
@@ -628,10 +628,11 @@ int d2c_select(d2c_ctx* c, const d2c_params* p, const float* logits, const int32
   if (prompt_len < 0 || prompt_len > L) return fail(c, D2C_EINVAL, "prompt_len outside [0, L]");
   hipStream_t st = (hipStream_t)stream;
   if (n_rows > c->dims.max_seq) return fail(c, D2C_ESHAPE, "n_rows exceeds max_seq of the context");
-  D2C_HIP(c, launch_confidence(logits, logit_pos, nullptr, n_rows, c->dims.vocab, conf, pred, c->conf_part, st));
+  D2C_HIP(c, launch_confidence_chunks(logits, n_rows, c->dims.vocab, c->conf_part, st));
   SelectArgs a{p->sigma, p->k, p->p, p->block_len, p->n_unmask, p->cand_mode, p->threshold, p->conf_decode,
                tokens, is_masked, L, prompt_len,
-               conf, pred, influence, mstar, u_set, decode_idx, s_next, s_rows_next, counts, score_out};
+               conf, pred, influence, mstar, u_set, decode_idx, s_next, s_rows_next, counts, score_out,
+               c->conf_part, logit_pos, nullptr, n_rows, confidence_chunks(c->dims.vocab)};
   D2C_HIP(c, launch_select(&a, 1, st));
   return D2C_OK;
 }
@@ -659,10 +660,11 @@ int d2c_select_static(const d2c_params* p, int32_t vocab, const float* logits, c
   hipStream_t st = (hipStream_t)stream;
   // every (row, chunk) triple that the merge reads is written by the chunk kernel of this call: nothing in
   // the array has to start at zero, whatever the last call left there
-  D2C_HIP(nullptr, launch_confidence(logits, logit_pos, nullptr, n_rows, vocab, conf, pred, sp, st));
+  D2C_HIP(nullptr, launch_confidence_chunks(logits, n_rows, vocab, sp, st));
   SelectArgs a{p->sigma, p->k, p->p, p->block_len, p->n_unmask, p->cand_mode, p->threshold, p->conf_decode,
                tokens, is_masked, L, prompt_len,
-               conf, pred, influence, mstar, u_set, decode_idx, s_next, s_rows_next, counts, score_out};
+               conf, pred, influence, mstar, u_set, decode_idx, s_next, s_rows_next, counts, score_out,
+               sp, logit_pos, nullptr, n_rows, confidence_chunks(vocab)};
   D2C_HIP(nullptr, launch_select(&a, 1, st));
   return D2C_OK;
 }
@@ -870,17 +872,21 @@ int d2c_step(d2c_ctx* c, const d2c_params* p, d2c_seq_state* seqs, int32_t batch
     struct Piece { int seg, r0, nr, at; };
     std::vector<Piece> pieces;
     int fill = 0;
+    const int n_chunks = confidence_chunks(D.vocab);
+    size_t conf_rows = 0;                         // rows of the group whose chunk triples are in conf_part
     auto flush = [&]() -> int {
       if (fill == 0) return D2C_OK;
       GemmPlan pl;
       size_t stride;
       int rc2 = project(c, c->head_a, d, c->lm_head, fill, D.vocab, d, &pl, &stride, st, true, c->logits);
       if (rc2) return rc2;
+      // the chunk triples of a group's rows stay until the selection, which merges them: the rows of all pieces in order
+      D2C_TIMED(c, st, D2C_PROF_SELECT, 0.0,
+                launch_confidence_chunks(c->logits, fill, D.vocab, c->conf_part + conf_rows * n_chunks * 3, st));
+      conf_rows += fill;
       for (const Piece& pc : pieces) {
         d2c_seq_state& s = seqs[group[pc.seg]];
         const float* lg = c->logits + (size_t)pc.at * D.vocab;
-        D2C_TIMED(c, st, D2C_PROF_SELECT, 0.0,
-                  launch_confidence(lg, s.s_rows + pc.r0, s.s_idx, pc.nr, D.vocab, s.conf, s.pred, c->conf_part, st));
         if (s.logits_out)
           D2C_HIP(c, hipMemcpyAsync(s.logits_out + (size_t)pc.r0 * D.vocab, lg, (size_t)pc.nr * D.vocab * 4,
                                     hipMemcpyDeviceToDevice, st));
@@ -908,12 +914,15 @@ int d2c_step(d2c_ctx* c, const d2c_params* p, d2c_seq_state* seqs, int32_t batch
     if (side != st) D2C_HIP(c, hipStreamWaitEvent(st, c->side_done, 0));
     // the selections of the group's sequences share launches (one workgroup per sequence)
     std::vector<SelectArgs> sel;
+    conf_rows = 0;
     for (int i = 0; i < n_seg; ++i) {
       d2c_seq_state& s = seqs[group[i]];
       sel.push_back(SelectArgs{p->sigma, p->k, p->p, p->block_len, p->n_unmask, p->cand_mode, p->threshold, p->conf_decode,
                                s.tokens, s.is_masked, s.L,
                                s.prompt_len, s.conf, s.pred, s.influence, s.mstar, s.u_set, s.decode_idx, s.s_idx, s.s_rows,
-                               s.counts, s.score});
+                               s.counts, s.score,
+                               c->conf_part + conf_rows * n_chunks * 3, s.s_rows, s.s_idx, s.n_rows, n_chunks});
+      conf_rows += (size_t)s.n_rows;
       if ((int)sel.size() == select_max_batch() || i + 1 == n_seg) {
         D2C_TIMED(c, st, D2C_PROF_SELECT, 0.0, launch_select(sel.data(), (int)sel.size(), st));
         sel.clear();

@@ -166,17 +166,21 @@ hipError_t launch_influence_chain(const ChainCall* calls, int n_calls, size_t la
                                   float* u_scratch, float* g_scratch, hipStream_t st);
 
 // ---- selection
-// Eq. 1 per logits row; the row's position is via ? via[pos[row]] : pos[row]
-// scratch: confidence_scratch_floats(n_rows) floats
+// Eq. 1 in two parts: per logits row and chunk of the vocabulary (max, argmax, sum of exp), confidence_chunks(vocab)
+// triples per row in part; launch_select merges the rows' chunks into conf and pred before it selects.
+// part: confidence_scratch_floats(n_rows) floats
 size_t confidence_scratch_floats(int n_rows);
-hipError_t launch_confidence(const float* logits, const int32_t* pos, const int32_t* via, int n_rows, int vocab,
-                             float* conf, int32_t* pred, float* scratch, hipStream_t st);
+int confidence_chunks(int vocab);
+hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st);
 struct SelectArgs {
   float sigma; int k; float p; int block_len; int n_unmask; int cand_mode; float threshold; int conf_decode;
   int32_t* tokens; uint8_t* is_masked; int L; int prompt_len;
-  const float* conf; const int32_t* pred; const float* influence;
+  float* conf; int32_t* pred; const float* influence;
   int32_t *mstar, *u_set, *decode_idx, *s_next, *s_rows_next, *counts;
   float* score_out;   // nullable: D(i) * s^i of the stage-1 candidates, 0 elsewhere
+  // logit rows of this call whose chunks are still to be merged (n_rows may be 0); a row's position is
+  // via ? via[pos[row]] : pos[row].  pos and via may be the s_rows_next / s_next that the call overwrites.
+  const float* part; const int32_t *pos, *via; int n_rows, n_chunks;
 };
 int select_max_len();
 // n independent sequences (n <= select_max_batch), one workgroup each

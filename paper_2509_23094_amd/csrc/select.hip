@@ -4,9 +4,10 @@
 // (Eq. 9) and the stage-2 cumulative-mass selection (Sec. 4.2, last paragraph).
 //
 // Everything that decides an index is integer-exact and order-independent:
-// top-k ranks 64-bit keys (float bits of the non-negative score, then lower
-// index first); top-p sorts such keys with a bitonic network in LDS and scans
-// fixed-point masses floor(c * 2^32) in uint64.  Ties always go to the lowest index.
+// top-k ranks keys (float bits of the non-negative score, then lower index
+// first); top-p looks for the key at which the fixed-point masses
+// floor(c * 2^32), added up in uint64, cross the threshold.  Ties always go to
+// the lowest index.
 #include <algorithm>
 #include <cstring>
 
@@ -23,6 +24,7 @@ namespace {
 // (ties keep the lowest index) -- fixed order, bit-reproducible.
 constexpr int kConfThreads = 256;
 constexpr int kConfMaxChunks = 64;
+constexpr int kConfChunk = 8192;              // entries per chunk, as long as 64 chunks cover the vocabulary
 
 __global__ __launch_bounds__(kConfThreads) void confidence_chunk_kernel(const float* __restrict__ logits, int vocab,
                                                                         int chunk, int n_chunks,
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(kConfThreads) void confidence_chunk_kernel(const fl
 __global__ __launch_bounds__(kConfThreads) void confidence_chunk_vec_kernel(const float* __restrict__ logits,
                                                                             int vocab, int n_chunks,
                                                                             float* __restrict__ part) {
-  constexpr int kChunk = 8192, kPieces = kChunk / (4 * kConfThreads);
+  constexpr int kChunk = kConfChunk, kPieces = kChunk / (4 * kConfThreads);
   __shared__ float s_val[kConfThreads / 64];
   __shared__ int s_idx[kConfThreads / 64];
   __shared__ float s_sum[kConfThreads / 64];
@@ -449,14 +451,17 @@ __global__ void ones_kernel(float* __restrict__ x, int n) {
 }
 
 // ------------------------------------------------------------------ two-stage selection, one workgroup
-constexpr int kSelThreads = 1024;
+constexpr int kSelThreads = 1024;            // seq_reset_kernel
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelMaxL = 4096;
+constexpr int kSelT = 512;                    // threads of select_kernel: 8 waves (16 were slower: every wave scans for itself)
+constexpr int kSelNW = kSelT / 64;
+constexpr int kRankMax = 256;                // up to this many stage-1 candidates are ranked by counting
+constexpr int kMergeMaxRows = 256;           // up to this many logit rows select_kernel merges Eq. 1's chunks (200 rows
+                                             // cost it about 4 us, a launch for them 7.5; past 32 rows a wave it grows on)
 
 struct SelShared {
   int wcnt[kSelWaves];
-  int scalar[8];
-  unsigned long long total;
 };
 
 // Ordered compaction of {i in [0,n) : pred(i)} into out (ascending); returns the count (uniform).
@@ -485,217 +490,531 @@ __device__ int block_compact(int n, Pred pred, Emit emit, SelShared* sh) {
   return base;
 }
 
-__device__ __forceinline__ unsigned long long make_key(float score, int index) {
-  return ((unsigned long long)__float_as_uint(score) << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)index);
+typedef unsigned long long u64;
+
+__device__ __forceinline__ u64 make_key(uint32_t bits, int index) {
+  return ((u64)bits << 32) | (u64)(0xFFFFFFFFu - (unsigned)index);
 }
-__device__ __forceinline__ int key_index(unsigned long long key) { return (int)(0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull)); }
-__device__ __forceinline__ unsigned long long key_mass(unsigned long long key) {
+__device__ __forceinline__ u64 bits_mass(uint32_t bits) {
   // floor(c * 2^32): the scaling is exact in float, the conversion truncates a non-negative value
-  return (unsigned long long)(__uint_as_float((unsigned)(key >> 32)) * 4294967296.0f);
+  return (u64)(__uint_as_float(bits) * 4294967296.0f);
 }
+// Running totals over the wave with lane moves inside the vector ALU (no LDS round trip): lane i gets
+// op(x_0, .., x_i), `zero` being op's neutral value.  HALVES: the two halves of the wave apart.
+template <bool HALVES = false, typename Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t zero, Op op) {
+#define D2C_DPP(ctrl, rows) x = op(x, (uint32_t)__builtin_amdgcn_update_dpp((int)zero, (int)x, ctrl, rows, 0xf, false))
+  D2C_DPP(0x111, 0xf);                     // from 1, 2, 4, 8 lanes below, inside rows of 16
+  D2C_DPP(0x112, 0xf);
+  D2C_DPP(0x114, 0xf);
+  D2C_DPP(0x118, 0xf);
+  D2C_DPP(0x142, 0xa);                     // last lane of rows 0, 2 into rows 1, 3
+  if constexpr (!HALVES) D2C_DPP(0x143, 0xc);                     // lane 31 into rows 2, 3
+#undef D2C_DPP
+  return x;
+}
+__device__ __forceinline__ u64 wave_scan_add(u64 x) {
+#define D2C_DPP(ctrl, rows)                                                                                      \
+  x += (u64)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, ctrl, rows, 0xf, false) |                 \
+       (u64)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), ctrl, rows, 0xf, false) << 32
+  D2C_DPP(0x111, 0xf);
+  D2C_DPP(0x112, 0xf);
+  D2C_DPP(0x114, 0xf);
+  D2C_DPP(0x118, 0xf);
+  D2C_DPP(0x142, 0xa);
+  D2C_DPP(0x143, 0xc);
+#undef D2C_DPP
+  return x;
+}
+// Value of one lane (the same lane for the whole wave) in every lane.
+__device__ __forceinline__ uint32_t lane_of(uint32_t x, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)x, lane); }
+__device__ __forceinline__ u64 lane_of(u64 x, int lane) {
+  return (u64)lane_of((uint32_t)x, lane) | (u64)lane_of((uint32_t)(x >> 32), lane) << 32;
+}
+// Exclusive sum over the lanes below, of one value per lane; *total is the sum over the wave.
+__device__ __forceinline__ uint32_t wave_before(uint32_t v, uint32_t* total) {
+  const uint32_t incl = wave_scan(v, 0u, [](uint32_t p, uint32_t q) { return p + q; });
+  *total = lane_of(incl, 63);
+  return incl - v;
+}
+__device__ __forceinline__ u64 low_mask(int n) { return n <= 0 ? 0ull : n >= 64 ? ~0ull : (1ull << n) - 1ull; }
+
+struct SelRadix {
+  u64 hist[3][256];          // hist[*buf] is all zero between calls
+  u64 sum[kSelNW];           // per wave: weights, OR and AND of the keys
+  uint32_t any[kSelNW], all[kSelNW];
+};
+
+// Block-wide sum of w and OR / AND of kb over the live elements (one barrier; uniform results).
+template <int PER>
+__device__ void sel_reduce(const uint32_t (&kb)[PER], unsigned live, const u64 (&w)[PER], SelRadix& sh, u64* sum_out,
+                           uint32_t* any_out, uint32_t* all_out) {
+  u64 s = 0ull;
+  uint32_t any = 0u, all = 0xffffffffu;
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (live >> e & 1u) {
+      s += w[e];
+      any |= kb[e];
+      all &= kb[e];
+    }
+  s = wave_scan_add(s);
+  any = wave_scan(any, 0u, [](uint32_t p, uint32_t q) { return p | q; });
+  all = wave_scan(all, 0xffffffffu, [](uint32_t p, uint32_t q) { return p & q; });
+  if ((threadIdx.x & 63) == 63) {
+    sh.sum[threadIdx.x >> 6] = s;
+    sh.any[threadIdx.x >> 6] = any;
+    sh.all[threadIdx.x >> 6] = all;
+  }
+  __syncthreads();
+  s = 0ull;
+  any = 0u;
+  all = 0xffffffffu;
+#pragma unroll
+  for (int v = 0; v < kSelNW; ++v) {
+    s += sh.sum[v];
+    any |= sh.any[v];
+    all &= sh.all[v];
+  }
+  *sum_out = s;
+  *any_out = any;
+  *all_out = all;
+}
+
+// Weighted selection without a sort: the largest key t with sum{w : kb >= t} > thr, and above = sum{w : kb > t}
+// (so above <= thr).  Eight key bits per pass: the weights of the elements that match the bits found so far are
+// added up per digit in LDS (integer sums: the order does not matter), then every wave scans the 256 sums from the
+// top by itself, so a pass costs one barrier.  Leading bits that all keys share (any / all) are skipped.
+// Needs sum{w} > thr.  The three histograms rotate: the next pass's one is cleared before this pass's barrier.
+template <int PER>
+__device__ void sel_radix(const uint32_t (&kb)[PER], unsigned live, const u64 (&w)[PER], uint32_t any, uint32_t all,
+                          u64 thr, SelRadix& sh, int* buf_io, uint32_t* t_out, u64* above_out) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t diff = any ^ all;
+  int rem = diff ? 32 - __clz((int)diff) : 0;
+  uint32_t prefix = rem >= 32 ? 0u : (all >> rem) << rem;
+  u64 above = 0ull;
+  int buf = *buf_io;
+  while (rem > 0) {
+    const int width = min(8, rem), shift = rem - width;
+    const int next = buf == 2 ? 0 : buf + 1;
+    if (tid < 256) sh.hist[next][tid] = 0ull;
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if ((live >> e & 1u) && (rem >= 32 || ((kb[e] ^ prefix) >> rem) == 0u))
+        atomicAdd(&sh.hist[buf][(kb[e] >> shift) & ((1u << width) - 1u)], w[e]);
+    __syncthreads();
+    u64 h[4], s = 0ull;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      h[i] = sh.hist[buf][255 - 4 * lane - i];
+      s += h[i];
+    }
+    u64 run = above + wave_scan_add(s) - s;
+    int digit = -1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (digit < 0) {
+        if (run + h[i] > thr) digit = 255 - 4 * lane - i;
+        else run += h[i];
+      }
+    // the first lane that crosses; its run holds the weight above the digit
+    const u64 cross = __ballot(digit >= 0);
+    const int src = cross ? __builtin_ctzll(cross) : 0;
+    prefix |= (lane_of((uint32_t)digit, src) & 0xffu) << shift;
+    above = lane_of(run, src);
+    rem = shift;
+    buf = next;
+  }
+  *buf_io = buf;
+  *t_out = prefix;
+  *above_out = above;
+}
+
+constexpr int kKnownPad = 66;                // words: longest sequence and one window of 32 positions
 
 constexpr int kSelMaxBatch = 8;
 struct SelectBatch {
   SelectArgs seq[kSelMaxBatch];
 };
 
-// One workgroup per sequence (blockIdx.x); the sequences are independent.
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectBatch batch) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+// Eq. 1's chunks of a row -> confidence and prediction, by 32 lanes (64 with more than 32 chunks): the same
+// (max, lowest index, sum) merge as confidence_merge_kernel, two rows of a wave at a time.
+__device__ void merge_rows(const SelectArgs& a, int wave) {
+  const int lane = threadIdx.x & 63;
+  const int width = a.n_chunks <= 32 ? 32 : 64, per = 64 / width;
+  const int li = lane & (width - 1), sub = width == 32 ? lane >> 5 : 0;
+  // lane q: position of the wave's q-th row (at most kMergeMaxRows / kSelNW = 32 rows a wave), one latency for all
+  int where = 0;
+  {
+    const int row = (wave + (lane / per) * kSelNW) * per + lane % per;
+    if (row < a.n_rows) where = a.via ? a.via[a.pos[row]] : a.pos[row];
+  }
+  constexpr int U = 4;                                       // rows of a wave whose triples are requested together
+  float nm[U], np[U];
+  int ni[U];
+  auto fetch = [&](int row0) {                               // past the end: the last triple, not used
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int row = min(row0 + u * kSelNW * per + sub, a.n_rows - 1);
+      const float* p = a.part + ((size_t)row * a.n_chunks + min(li, a.n_chunks - 1)) * 3;
+      nm[u] = p[0];
+      ni[u] = __float_as_int(p[1]);
+      np[u] = p[2];
+    }
+  };
+  // a reduction over the 32 (64) lanes of a row ends in the row's last lane; every lane reads it back from there
+  auto spread = [&](uint32_t x) {
+    const uint32_t lo = lane_of(x, 31), hi = lane_of(x, 63);
+    return width == 32 && lane < 32 ? lo : hi;
+  };
+  auto reduce = [&](uint32_t x, uint32_t zero, auto op) {
+    return spread(width == 32 ? wave_scan<true>(x, zero, op) : wave_scan<false>(x, zero, op));
+  };
+  fetch(wave * per);
+  for (int row0 = wave * per, q = 0; row0 < a.n_rows; row0 += U * kSelNW * per) {
+    float cm[U], cp[U];
+    int ci[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { cm[u] = nm[u]; cp[u] = np[u]; ci[u] = ni[u]; }
+    fetch(row0 + U * kSelNW * per);                          // fly during these rows' merges
+#pragma unroll
+    for (int u = 0; u < U; ++u, q += per) {
+      const int row = row0 + u * kSelNW * per + sub;
+      const bool on = row < a.n_rows && li < a.n_chunks;
+      const float mine = on ? cm[u] : -INFINITY;
+      const float best = __uint_as_float(reduce(__float_as_uint(mine), 0xff800000u, [](uint32_t x, uint32_t y) {
+        return __float_as_uint(fmaxf(__uint_as_float(x), __uint_as_float(y)));
+      }));
+      const uint32_t bidx = reduce(on && mine == best ? (uint32_t)ci[u] : 0x7fffffffu, 0x7fffffffu,
+                                   [](uint32_t x, uint32_t y) { return min(x, y); });
+      const float sum = __uint_as_float(reduce(__float_as_uint(on ? cp[u] * expf(mine - best) : 0.f), 0u, [](uint32_t x, uint32_t y) {
+        return __float_as_uint(__uint_as_float(x) + __uint_as_float(y));
+      }));
+      const int to = __shfl(where, (q + sub) & 63, kWave);
+      if (on && li == 0) {
+        a.conf[to] = 1.0f / sum;
+        a.pred[to] = (int)bidx;
+      }
+    }
+  }
+}
+
+// One workgroup per sequence (blockIdx.x); the sequences are independent.  Latency is what bounds it (a few KB of
+// input), so it is built from few barriers: the sets live as bitmaps of 64-position words in LDS (wave w of the
+// workgroup ballots word e * waves + w for its e-th position), every wave turns a bitmap into counts and compaction
+// offsets by itself (lane = word), and both selections look for a threshold key by radix (sel_radix) instead of sorting.
+// Eq. 3's sum stops where the Gaussian is exactly zero in float.  Measured against a bitonic sort, rank counting, a
+// scan per set and 16 waves (Eq. 1's merge then took another 5 / 7.5 us launch): L 512, 16 logit rows, 32 candidates
+// 30.4 -> 14.8 us; L 3071, 200 logit rows, 737 candidates 327 -> 33 us.
+// PER positions a thread: 4 up to 2048 positions, 8 up to 4096.
+template <int PER>
+__global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) {
+  constexpr int T = kSelT, NW = kSelNW, ML = PER * T;
+  __shared__ u64 w_mask[64], w_mst[64], w_dec[64], w_u[64], w_tie[64];
+  __shared__ u64 w_known[3 * kKnownPad];                   // known positions, with kKnownPad empty words on either side
+  __shared__ __align__(16) float phi[ML + 32];
+  __shared__ float density[ML];
+  __shared__ uint16_t cand[ML];
+  __shared__ u64 rkey[kRankMax], dkey[kRankMax];
+  __shared__ SelRadix radix;
+  __shared__ int n_small;
+
   const SelectArgs& a = batch.seq[blockIdx.x];
   const int L = a.L;
-  int NP = 2;
-  while (NP < L) NP <<= 1;
-  unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);            // [NP]
-  unsigned long long* keys1 = keys + NP;                                             // [L]
-  unsigned long long* scan_a = keys1 + L;                                            // [kSelThreads]
-  unsigned long long* scan_b = scan_a + kSelThreads;                                 // [kSelThreads]
-  SelShared* sh = reinterpret_cast<SelShared*>(scan_b + kSelThreads);                // 8-byte aligned
-  float* phi = reinterpret_cast<float*>(sh + 1);                                     // [L]
-  int* cand = reinterpret_cast<int*>(phi + L);                                       // [L]
-  int* slist = cand + L;                                                             // [L]
-  unsigned char* msk = reinterpret_cast<unsigned char*>(slist + L);                  // [L]
-  unsigned char* sel = msk + L;                                                      // [L]
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const u64 below = low_mask(lane);
+  int buf = 0;
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-
-  // ---- phase 0: mask flags, first masked position, |M_t|
-  if (tid == 0) { sh->scalar[0] = 0x7fffffff; sh->scalar[1] = 0; sh->scalar[2] = 0x7fffffff; sh->total = 0ull; }
-  __syncthreads();
-  {
-    int first = 0x7fffffff, cnt = 0;
-    for (int j = tid; j < L; j += kSelThreads) {
-      const unsigned char f = a.is_masked[j] ? 1 : 0;
-      msk[j] = f;
-      sel[j] = 0;
-      if (f) { cnt++; first = min(first, j); }
-    }
-    if (first != 0x7fffffff) atomicMin(&sh->scalar[0], first);
-    if (cnt) atomicAdd(&sh->scalar[1], cnt);
+  // ---- mask flags, the Gaussian of Eq. 3, and Eq. 1's chunks of this call's logit rows
+  float inf[PER];
+  for (int i = tid; i < 64; i += T) {
+    if (i >= PER * NW) w_mask[i] = 0ull;
+    w_mst[i] = w_dec[i] = w_u[i] = w_tie[i] = 0ull;
   }
+  for (int i = tid; i < 256; i += T) radix.hist[0][i] = 0ull;
+  for (int i = tid; i < 3 * kKnownPad; i += T)
+    if (i < kKnownPad || i >= kKnownPad + PER * NW) w_known[i] = 0ull;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int j = e * T + tid;
+    const bool f = j < L && a.is_masked[j] != 0;
+    inf[e] = j < L ? a.influence[j] : 0.f;
+    const u64 word = __ballot(f), known = __ballot(j < L && !f);
+    if (lane == 0) {
+      w_mask[e * NW + wave] = word;
+      w_known[kKnownPad + e * NW + wave] = known;
+    }
+    if (j < L && a.score_out) a.score_out[j] = 0.f;
+  }
+  const float inv2s2 = 1.0f / (2.0f * a.sigma * a.sigma);
+  // exp(-x) is zero in float from x = 104 on, subnormals included: distances of cut and more add nothing
+  const int cut = (int)fminf((float)L, ceilf(sqrtf(105.0f / inv2s2)) + 1.0f);
+  const int n_win = (cut + 31) >> 5;
+  for (int d = tid; d < n_win * 32; d += T) phi[d] = d < cut ? expf(-((float)d * (float)d) * inv2s2) : 0.f;
+  if (a.part) merge_rows(a, wave);
   __syncthreads();
-  const int first_masked = sh->scalar[0];
-  const int n_masked = sh->scalar[1];
+
+  // ---- current block and its masked tokens (every wave for itself; lane = word of the bitmap)
+  const u64 mask_w = w_mask[lane];
+  uint32_t n_masked_u;
+  (void)wave_before((uint32_t)__popcll(mask_w), &n_masked_u);
+  const int n_masked = (int)n_masked_u;
   int lo = L, hi = L;
   if (n_masked > 0) {
+    const int fw = __builtin_ctzll(__ballot(mask_w != 0ull));
+    const int first_masked = fw * 64 + __builtin_ctzll(lane_of(mask_w, fw));
     // blocks are counted from the end of the prompt in both directions (floor division): a masked
     // position inside the prompt -- nothing the decoding loop produces, but a legal input -- lies in a
     // block with a negative number, cut at position 0
     const int diff = first_masked - a.prompt_len;
     const int b = diff >= 0 ? diff / a.block_len : -((-diff + a.block_len - 1) / a.block_len);
-    const int lo_raw = a.prompt_len + b * a.block_len;
-    lo = max(0, lo_raw);
-    hi = min(L, lo_raw + a.block_len);
+    const int64_t lo_raw = (int64_t)a.prompt_len + (int64_t)b * a.block_len;
+    lo = (int)max((int64_t)0, lo_raw);
+    hi = (int)min((int64_t)L, lo_raw + a.block_len);
   }
+  const u64 cand_w = mask_w & low_mask(hi - lane * 64) & ~low_mask(lo - lane * 64);
+  uint32_t n1_u;
+  const uint32_t cand_before = wave_before((uint32_t)__popcll(cand_w), &n1_u);
+  const int n1 = (int)n1_u;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int word = e * NW + wave;
+    const u64 bits = lane_of(cand_w, word);
+    const int before = (int)lane_of(cand_before, word);
+    if (bits >> lane & 1ull) cand[before + __popcll(bits & below)] = (uint16_t)(e * T + tid);
+  }
+  __syncthreads();
 
-  // ---- phase 1: Eq. 3 on the masked tokens of the current block, score = D(i) * s^i
-  const float inv2s2 = 1.0f / (2.0f * a.sigma * a.sigma);
-  for (int d = tid; d < L; d += kSelThreads) {
-    phi[d] = expf(-((float)d * (float)d) * inv2s2);
-    if (a.score_out) a.score_out[d] = 0.f;
+  // ---- phase 1: Eq. 3 on the masked tokens of the current block, score = D(i) * s^i; thread t holds candidates
+  // t, t + T, ..  A wave takes 64 candidates (one a lane) and a share of the distances, 32 at a time: the known positions
+  // at those distances are two 32-bit windows of the bitmap, phi is the same for every lane, and a term costs three
+  // instructions.  Far distances are added first (the terms grow), left and right, even and odd apart.
+  const int n1p = (n1 + 63) & ~63;
+  const int shares = n1 > 0 ? max(1, min(min(8, n_win), ML / n1p)) : 1;
+  for (int item = wave; item < (n1p >> 6) * shares; item += NW) {
+    const int q = item % shares, c = (item / shares) * 64 + lane;
+    const int i = cand[min(c, n1 - 1)];
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int w = q + ((n_win - 1 - q) / shares) * shares; w >= 0; w -= shares) {
+      const int d0 = w * 32;
+      auto window = [&](int p) {                               // known flags of positions p .. p + 31
+        const unsigned at_bit = (unsigned)(p + kKnownPad * 64);
+        const u64 lo_w = w_known[at_bit >> 6], hi_w = w_known[(at_bit >> 6) + 1];
+        const unsigned sh = at_bit & 63u;
+        return (uint32_t)(lo_w >> sh) | (sh ? (uint32_t)(hi_w << (64u - sh)) : 0u);
+      };
+      const uint32_t right = window(i + d0), left = window(i - d0 - 31);
+#pragma unroll
+      for (int b = 31; b >= 0; --b) {
+        const uint32_t f = __float_as_uint(phi[d0 + b]);
+        sum[(b & 1) * 2] += __uint_as_float(f & (uint32_t)((int32_t)(right << (31 - b)) >> 31));
+        sum[(b & 1) * 2 + 1] += __uint_as_float(f & (uint32_t)((int32_t)(left << b) >> 31));
+      }
+    }
+    density[q * n1p + c] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
   }
-  const int n1 = block_compact(hi - lo, [&](int t) { return msk[lo + t] != 0; },
-                               [&](int slot, int t) { cand[slot] = lo + t; }, sh);
-  for (int c = wave; c < n1; c += kSelWaves) {
-    const int i = cand[c];
-    float dsum = 0.f;
-    for (int j = lane; j < L; j += kWave)
-      if (!msk[j]) dsum += phi[abs(i - j)];
-    dsum = wave_sum(dsum);
-    if (lane == 0) {
-      const float score = dsum * a.conf[i];
-      keys1[c] = make_key(score, i);
-      if (a.score_out) a.score_out[i] = score;
+  int at[PER];
+  float cf[PER];
+  unsigned clive = 0u;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int c = e * T + tid;
+    at[e] = 0;
+    cf[e] = 0.f;
+    if (c < n1) {
+      clive |= 1u << e;
+      at[e] = cand[c];
+      cf[e] = a.conf[at[e]];
     }
   }
   __syncthreads();
 
-  // ---- phase 2: Eq. 4 (top-k) and the decode set by rank counting.  The decode set ranks the same
-  // scores, or the confidences alone (conf_decode), and with a threshold also takes every candidate
-  // whose confidence exceeds it.
-  if (a.conf_decode)
-    for (int c = tid; c < n1; c += kSelThreads) keys[c] = make_key(a.conf[cand[c]], cand[c]);
-  __syncthreads();
-  const unsigned long long* dkeys = a.conf_decode ? keys : keys1;
-  for (int c = tid; c < n1; c += kSelThreads) {
-    const unsigned long long mine = keys1[c], dmine = dkeys[c];
-    int rank = 0, drank = 0;
-    for (int o = 0; o < n1; ++o) {
-      rank += keys1[o] > mine ? 1 : 0;
-      drank += dkeys[o] > dmine ? 1 : 0;
+  // ---- phase 2: Eq. 4 (top-k) and the decode set.  The decode set ranks the same scores, or the confidences alone
+  // (conf_decode), and with a threshold also takes every candidate whose confidence exceeds it.
+  uint32_t sb[PER], db[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    sb[e] = db[e] = 0u;
+    if (clive >> e & 1u) {
+      float dsum = 0.f;
+      for (int q = shares - 1; q >= 0; --q) dsum += density[q * n1p + e * T + tid];
+      const float score = dsum * cf[e];
+      sb[e] = __float_as_uint(score);
+      db[e] = a.conf_decode ? __float_as_uint(cf[e]) : sb[e];
+      if (a.score_out) a.score_out[at[e]] = score;
     }
-    unsigned char f = 0;
-    if (rank < a.k) f |= 1;
-    if (drank < a.n_unmask) f |= 4;
-    if (a.threshold > 0.f && a.conf[cand[c]] > a.threshold) f |= 4;
-    sel[cand[c]] = f;
   }
-  __syncthreads();
-  const int n_mstar = block_compact(n1, [&](int c) { return (sel[cand[c]] & 1) != 0; },
-                                    [&](int slot, int c) { a.mstar[slot] = cand[c]; }, sh);
-  const int n_dec = block_compact(n1, [&](int c) { return (sel[cand[c]] & 4) != 0; },
-                                  [&](int slot, int c) { a.decode_idx[slot] = cand[c]; }, sh);
-
-  // ---- phase 3: stage-2 keys (influence bits, lower index first); non-candidates sort last as key 0
-  {
-    unsigned long long part = 0ull;
-    for (int j = tid; j < NP; j += kSelThreads) {
-      unsigned long long key = 0ull;
-      if (j < L) {
-        const bool is_cand = a.cand_mode == 0 ? (msk[j] == 0) : ((sel[j] & 1) == 0);
-        if (is_cand) {
-          key = make_key(a.influence[j], j);
-          part += key_mass(key);
+  unsigned in_m = a.k >= n1 ? clive : 0u, in_d = a.n_unmask >= n1 ? clive : 0u;
+  const bool cut_m = a.k > 0 && a.k < n1, cut_d = a.n_unmask > 0 && a.n_unmask < n1;
+  if (n1 <= kRankMax) {
+    if (cut_m || cut_d) {                                    // rank by counting (n1 <= T: at most one candidate a thread)
+      if (tid < n1) {
+        rkey[tid] = make_key(sb[0], at[0]);
+        dkey[tid] = make_key(db[0], at[0]);
+      }
+      __syncthreads();
+      if (tid < n1) {
+        const u64 mine = rkey[tid], dmine = dkey[tid];
+        int rank = 0, drank = 0;
+        for (int o = 0; o < n1; ++o) {
+          rank += rkey[o] > mine ? 1 : 0;
+          drank += dkey[o] > dmine ? 1 : 0;
         }
+        if (cut_m && rank < a.k) in_m |= 1u;
+        if (cut_d && drank < a.n_unmask) in_d |= 1u;
       }
-      keys[j] = key;
     }
-    if (part) atomicAdd(&sh->total, part);      // integer sum: order does not matter
-  }
-  __syncthreads();
-  const int n2 = block_compact(L, [&](int j) { return keys[j] != 0ull; }, [&](int, int) {}, sh);
-  const unsigned long long total = sh->total;
-
-  // bitonic network, descending
-  for (int k = 2; k <= NP; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = tid; t < (NP >> 1); t += kSelThreads) {
-        const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-        const int ixj = i | j;
-        const unsigned long long x = keys[i], y = keys[ixj];
-        const bool up = (i & k) == 0;
-        if (up ? (x < y) : (x > y)) { keys[i] = y; keys[ixj] = x; }
+  } else {
+    // the count-th largest key by radix; candidates with an equal key are taken in ascending order
+    auto top = [&](const uint32_t (&kb)[PER], int count) {
+      u64 ones[PER], sum, above;
+      uint32_t any, all, t;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) ones[e] = 1ull;
+      sel_reduce(kb, clive, ones, radix, &sum, &any, &all);
+      sel_radix(kb, clive, ones, any, all, (u64)(count - 1), radix, &buf, &t, &above);
+      const int ties = count - (int)above;                   // >= 1
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const u64 word = __ballot((clive >> e & 1u) && kb[e] == t);
+        if (lane == 0) w_tie[e * NW + wave] = word;
       }
       __syncthreads();
-    }
-  }
-
-  // ---- phase 4: smallest prefix whose mass exceeds floor(p * total)
-  int take = n2;
-  if (n2 > 0 && a.p < 1.0f) {
-    const unsigned long long thr = (unsigned long long)floor((double)a.p * __ull2double_rn(total));
-    const int per = (NP + kSelThreads - 1) / kSelThreads;
-    const int begin = tid * per;
-    unsigned long long local = 0ull;
-    for (int e = 0; e < per; ++e) {
-      const int rnk = begin + e;
-      if (rnk < n2) local += key_mass(keys[rnk]);
-    }
-    scan_a[tid] = local;
-    __syncthreads();
-    unsigned long long* src = scan_a;
-    unsigned long long* dst = scan_b;
-    for (int o = 1; o < kSelThreads; o <<= 1) {            // inclusive Hillis-Steele scan
-      dst[tid] = src[tid] + (tid >= o ? src[tid - o] : 0ull);
-      __syncthreads();
-      unsigned long long* t = src; src = dst; dst = t;
-    }
-    unsigned long long run = src[tid] - local;             // exclusive prefix of this thread's chunk
-    int found = 0x7fffffff;
-    for (int e = 0; e < per; ++e) {
-      const int rnk = begin + e;
-      if (rnk < n2) {
-        run += key_mass(keys[rnk]);
-        if (run > thr && found == 0x7fffffff) found = rnk;
+      const u64 tie_w = w_tie[lane];
+      uint32_t n_tie;
+      const uint32_t tie_before = wave_before((uint32_t)__popcll(tie_w), &n_tie);
+      unsigned f = 0u;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const int word = e * NW + wave;
+        const u64 bits = lane_of(tie_w, word);
+        const int rank = (int)lane_of(tie_before, word) + __popcll(bits & below);
+        if ((clive >> e & 1u) && (kb[e] > t || (kb[e] == t && rank < ties))) f |= 1u << e;
       }
+      __syncthreads();                                       // w_tie and the reduction slots are used again
+      return f;
+    };
+    if (cut_m) in_m = top(sb, a.k);
+    if (cut_d && !a.conf_decode && cut_m && a.n_unmask <= a.k && a.k <= kRankMax) {
+      // the same ranking, and the decode set lies inside M*: count ranks among those k
+      if (tid == 0) n_small = 0;
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < PER; ++e)
+        if (in_m >> e & 1u) rkey[atomicAdd(&n_small, 1)] = make_key(sb[e], at[e]);      // exactly k of them, in any order
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < PER; ++e)
+        if (in_m >> e & 1u) {
+          const u64 mine = make_key(sb[e], at[e]);
+          int rank = 0;
+          for (int o = 0; o < a.k; ++o) rank += rkey[o] > mine ? 1 : 0;
+          if (rank < a.n_unmask) in_d |= 1u << e;
+        }
+    } else if (cut_d) {
+      in_d = top(db, a.n_unmask);
     }
-    if (found != 0x7fffffff) atomicMin(&sh->scalar[2], found);
-    __syncthreads();
-    if (sh->scalar[2] != 0x7fffffff) take = sh->scalar[2] + 1;
   }
-  for (int rnk = tid; rnk < take; rnk += kSelThreads) sel[key_index(keys[rnk])] |= 2;
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (clive >> e & 1u) {
+      const u64 bit = 1ull << (at[e] & 63);
+      if (in_m >> e & 1u) atomicOr(&w_mst[at[e] >> 6], bit);
+      if ((in_d >> e & 1u) || (a.threshold > 0.f && cf[e] > a.threshold)) atomicOr(&w_dec[at[e] >> 6], bit);
+    }
   __syncthreads();
 
-  // ---- phase 5: unmask (Eq. 2), emit U, S_{t+1} = M* u U and its still-masked rows
-  for (int c = tid; c < n1; c += kSelThreads) {
-    const int i = cand[c];
-    if (sel[i] & 4) {
-      a.tokens[i] = a.pred[i];
-      a.is_masked[i] = 0;
-      msk[i] = 0;
+  // ---- phases 3, 4: the smallest set of stage-2 candidates, by descending influence (lowest index first among
+  // equals), whose mass exceeds floor(p * total)
+  const u64 mst_w = w_mst[lane], dec_w = w_dec[lane];
+  uint32_t kb[PER];
+  u64 mass[PER];
+  unsigned live = 0u;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int word = e * NW + wave;
+    const u64 out = lane_of(a.cand_mode == 0 ? mask_w : mst_w, word);
+    kb[e] = __float_as_uint(inf[e]);
+    mass[e] = 0ull;
+    if (e * T + tid < L && !(out >> lane & 1ull)) {
+      live |= 1u << e;
+      mass[e] = bits_mass(kb[e]);
     }
   }
-  const int n_u = block_compact(L, [&](int j) { return (sel[j] & 2) != 0; },
-                                [&](int slot, int j) { a.u_set[slot] = j; }, sh);
-  const int n_s = block_compact(L, [&](int j) { return sel[j] != 0; },
-                                [&](int slot, int j) { a.s_next[slot] = j; slist[slot] = j; }, sh);
-  const int n_rows = block_compact(n_s, [&](int rr) { return msk[slist[rr]] != 0; },
-                                   [&](int slot, int rr) { a.s_rows_next[slot] = rr; }, sh);
+  unsigned in_u = live;
+  if (a.p < 1.0f) {
+    u64 total, above;
+    uint32_t any, all, t;
+    sel_reduce(kb, live, mass, radix, &total, &any, &all);
+    const u64 thr = (u64)floor((double)a.p * __ull2double_rn(total));
+    if (total > thr) {
+      sel_radix(kb, live, mass, any, all, thr, radix, &buf, &t, &above);
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const u64 word = __ballot((live >> e & 1u) && kb[e] == t);
+        if (lane == 0) w_tie[e * NW + wave] = word;
+      }
+      __syncthreads();
+      const u64 tie_w = w_tie[lane];
+      uint32_t n_tie;
+      const uint32_t tie_before = wave_before((uint32_t)__popcll(tie_w), &n_tie);
+      u64 ties = 1ull;                                         // how many of the equal keys; a division only for a run
+      if (n_tie > 1u) ties = (thr - above) / max(bits_mass(t), (u64)1) + 1ull;
+      in_u = 0u;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const int word = e * NW + wave;
+        const u64 bits = lane_of(tie_w, word);
+        const u64 rank = (u64)(lane_of(tie_before, word) + (uint32_t)__popcll(bits & below));
+        if ((live >> e & 1u) && (kb[e] > t || (kb[e] == t && rank < ties))) in_u |= 1u << e;
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const u64 word = __ballot(in_u >> e & 1u);
+    if (lane == 0) w_u[e * NW + wave] = word;
+  }
+  __syncthreads();
+
+  // ---- phase 5: unmask (Eq. 2), emit M*, I_t, U, S_{t+1} = M* u I_t u U and its still-masked rows: all offsets from
+  // the bitmaps (two counts of at most 4096 to a register)
+  const u64 u_w = w_u[lane];
+  const u64 s_w = mst_w | dec_w | u_w, row_w = s_w & mask_w & ~dec_w;
+  uint32_t tot_a, tot_b, tot_c;
+  const uint32_t pre_a = wave_before((uint32_t)__popcll(mst_w) | (uint32_t)__popcll(dec_w) << 16, &tot_a);
+  const uint32_t pre_b = wave_before((uint32_t)__popcll(u_w) | (uint32_t)__popcll(s_w) << 16, &tot_b);
+  const uint32_t pre_c = wave_before((uint32_t)__popcll(row_w), &tot_c);
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int j = e * T + tid, word = e * NW + wave;
+    const u64 m_b = lane_of(mst_w, word), d_b = lane_of(dec_w, word), u_b = lane_of(u_w, word);
+    const u64 s_b = lane_of(s_w, word), r_b = lane_of(row_w, word);
+    const uint32_t pa = lane_of(pre_a, word), pb = lane_of(pre_b, word), pc = lane_of(pre_c, word);
+    if (m_b >> lane & 1ull) a.mstar[(pa & 0xffffu) + __popcll(m_b & below)] = j;
+    if (d_b >> lane & 1ull) {
+      a.decode_idx[(pa >> 16) + __popcll(d_b & below)] = j;
+      a.tokens[j] = a.pred[j];
+      a.is_masked[j] = 0;
+    }
+    if (u_b >> lane & 1ull) a.u_set[(pb & 0xffffu) + __popcll(u_b & below)] = j;
+    if (s_b >> lane & 1ull) {
+      const int slot = (int)(pb >> 16) + __popcll(s_b & below);
+      a.s_next[slot] = j;
+      if (r_b >> lane & 1ull) a.s_rows_next[pc + __popcll(r_b & below)] = slot;
+    }
+  }
   if (tid == 0) {
-    a.counts[0] = n_mstar;
-    a.counts[1] = n_u;
-    a.counts[2] = n_s;
-    a.counts[3] = n_dec;
-    a.counts[4] = n_rows;
-    a.counts[5] = n_masked - n_dec;
+    a.counts[0] = (int)(tot_a & 0xffffu);
+    a.counts[1] = (int)(tot_b & 0xffffu);
+    a.counts[2] = (int)(tot_b >> 16);
+    a.counts[3] = (int)(tot_a >> 16);
+    a.counts[4] = (int)tot_c;
+    a.counts[5] = n_masked - (int)(tot_a >> 16);
     a.counts[6] = lo;
     a.counts[7] = hi;
   }
-}
-
-size_t select_smem_bytes(int L, int NP) {
-  return (size_t)NP * 8 + (size_t)L * 8 + 2 * (size_t)kSelThreads * 8 + (size_t)L * 12 + sizeof(SelShared) +
-         2 * (size_t)L + 64;
 }
 
 // Step-0 state: S_0 = all rows, s_rows = masked rows, conf = 0, pred = 0.
@@ -726,23 +1045,24 @@ int select_max_len() { return kSelMaxL; }
 
 size_t confidence_scratch_floats(int n_rows) { return (size_t)n_rows * kConfMaxChunks * 3; }
 
-hipError_t launch_confidence(const float* logits, const int32_t* pos, const int32_t* via, int n_rows, int vocab,
-                             float* conf, int32_t* pred, float* scratch, hipStream_t st) {
-  if (n_rows <= 0) return hipSuccess;
-  if (vocab <= 0 || scratch == nullptr) return hipErrorInvalidValue;
-  int chunk = 8192;
+int confidence_chunks(int vocab) {
+  int chunk = kConfChunk;
   while ((vocab + chunk - 1) / chunk > kConfMaxChunks) chunk *= 2;
-  const int n_chunks = (vocab + chunk - 1) / chunk;
-  if (chunk == 8192 && vocab % 4 == 0 && vocab >= 4 && (uintptr_t)logits % 16 == 0)
+  return (vocab + chunk - 1) / chunk;
+}
+
+hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st) {
+  if (n_rows <= 0) return hipSuccess;
+  if (vocab <= 0 || part == nullptr) return hipErrorInvalidValue;
+  int chunk = kConfChunk;
+  while ((vocab + chunk - 1) / chunk > kConfMaxChunks) chunk *= 2;
+  const int n_chunks = confidence_chunks(vocab);
+  if (chunk == kConfChunk && vocab % 4 == 0 && vocab >= 4 && (uintptr_t)logits % 16 == 0)
     hipLaunchKernelGGL(confidence_chunk_vec_kernel, dim3(n_chunks, n_rows), dim3(kConfThreads), 0, st, logits, vocab,
-                       n_chunks, scratch);
+                       n_chunks, part);
   else
     hipLaunchKernelGGL(confidence_chunk_kernel, dim3(n_chunks, n_rows), dim3(kConfThreads), 0, st, logits, vocab, chunk,
-                       n_chunks, scratch);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(confidence_merge_kernel, dim3((n_rows + 63) / 64), dim3(64), 0, st, scratch, n_rows, n_chunks,
-                     pos, via, conf, pred);
+                       n_chunks, part);
   return hipGetLastError();
 }
 
@@ -821,30 +1141,30 @@ hipError_t launch_select(const SelectArgs* args, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   if (n > kSelMaxBatch) return hipErrorInvalidValue;
   SelectBatch batch;
-  size_t smem = 0;
+  int max_L = 0;
   for (int i = 0; i < n; ++i) {
     const SelectArgs& a = args[i];
     if (a.L <= 0 || a.L > kSelMaxL || a.block_len <= 0 || a.prompt_len < 0 || a.prompt_len > a.L)
       return hipErrorInvalidValue;
-    int NP = 2;
-    while (NP < a.L) NP <<= 1;
-    smem = std::max(smem, select_smem_bytes(a.L, NP));
+    if (a.n_rows < 0 || (a.n_rows > 0 && (!a.part || !a.pos || a.n_chunks <= 0 || a.n_chunks > kConfMaxChunks)))
+      return hipErrorInvalidValue;
     batch.seq[i] = a;
+    if (a.n_rows == 0) batch.seq[i].part = nullptr;
+    if (a.n_rows > kMergeMaxRows) {
+      // many logit rows: their chunks are merged by a launch of their own, spread over more than one compute unit
+      hipLaunchKernelGGL(confidence_merge_kernel, dim3((a.n_rows + 63) / 64), dim3(64), 0, st, a.part, a.n_rows, a.n_chunks,
+                         a.pos, a.via, a.conf, a.pred);
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      batch.seq[i].part = nullptr;
+    }
+    max_L = std::max(max_L, a.L);
   }
   for (int i = n; i < kSelMaxBatch; ++i) batch.seq[i] = args[0];        // never read: the grid has n workgroups
-  static int lds_limit = 0;
-  if (lds_limit == 0) {
-    int dev = 0, optin = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&optin, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, optin);
-    if (e != hipSuccess) return e;
-    lds_limit = optin;
-  }
-  if (smem > (size_t)lds_limit) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(select_kernel, dim3(n), dim3(kSelThreads), smem, st, batch);
+  if (max_L <= 4 * kSelT)
+    hipLaunchKernelGGL(select_kernel<4>, dim3(n), dim3(kSelT), 0, st, batch);
+  else
+    hipLaunchKernelGGL(select_kernel<8>, dim3(n), dim3(kSelT), 0, st, batch);
   return hipGetLastError();
 }
 

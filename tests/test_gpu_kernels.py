@@ -493,3 +493,68 @@ def test_tunables_belong_to_a_context(B):
     assert info["total_bytes"] == ctx_a.workspace_bytes() and 0 < info["pretiled_weight_bytes"] < info["total_bytes"]
     ctx_a.close()
     ctx_b.close()
+
+
+SELECT_EDGES = [
+    # as SELECT_CASES: word and workgroup edges of the bitmaps, ranking by counting / by radix (256 candidates), long and
+    # short.  Every candidate has a known token within 9 sigma (exp(-40)), so that no score is subnormal: there the
+    # relative bound of 1e-5 on the score says nothing (one unit in the last place is more)
+    (1, 0, 16, 4, 3, 1, 0.1, 10.0, 0.0, 0, False),
+    (65, 1, 16, 64, 8, 2, 0.3, 10.0, 0.2, 0, True),
+    (2048, 1024, 64, 256, 40, 3, 0.2, 30.0, 0.0, 0, True),
+    (2049, 700, 64, 1349, 300, 7, 0.5, 10.0, 0.3, 1, True),
+    (4096, 500, 64, 3596, 257, 256, 0.05, 15.0, 0.1, 0, False),
+    (4096, 500, 64, 3596, 5, 40, 0.999, 300.0, 0.1, 1, True, 0.9, 1),
+    (1500, 100, 64, 1400, 0, 0, 0.1, 1e6, 0.4, 0, True),
+]
+
+
+@pytest.mark.parametrize("case", SELECT_EDGES, ids=[str(c[0]) + "-" + str(i) for i, c in enumerate(SELECT_EDGES)])
+def test_select_parity_at_the_edges(B, case):
+    test_select_parity(B, case)
+
+
+@pytest.mark.parametrize("L,n_masked", [(640, 600), (3000, 2900)])
+def test_select_ties_beyond_the_counting_limit(B, L, n_masked):
+    """More than 256 candidates, runs of equal scores and of equal influence: the lowest index of a run goes first."""
+    say(f"select ties L={L}")
+    wd = W.ModelDims(1, 64, 4, 4, 16, 80, 64, dtype="f32")
+    ctx = B.Context(wd, W.model_weights(wd, 0), L)
+    is_masked = np.zeros(L, bool); is_masked[L - n_masked:] = True
+    y = np.where(is_masked, wd.mask_id, 3).astype(np.int32)
+    rng = np.random.default_rng(L)
+    conf = rng.integers(1, 4, size=L).astype(np.float32) / 4
+    c = rng.integers(0, 3, size=L).astype(np.float32)                       # masses 0, 1, 2: long runs, some of no mass
+    for k, nu, p, mode in ((257, 9, 0.4, 1), (n_masked - 1, 300, 0.0, 0), (1, 1, 0.99999, 1)):
+        prm = B.make_params(1e6, k, p, L, nu, mode, conf_decode=1)
+        res, _ = _run_select(B, ctx, prm, np.zeros((0, 64), np.float32), np.zeros(0, np.int32), y, is_masked, L - n_masked, conf,
+                             np.zeros(L, np.int32), c)
+        cand1 = np.flatnonzero(is_masked)
+        np.testing.assert_array_equal(res["mstar"], O.top_k_select(res["score"], cand1, k))
+        np.testing.assert_array_equal(res["decode_idx"], O.top_k_select(conf, cand1, nu))
+        cand2 = np.flatnonzero(~is_masked) if mode == 0 else np.setdiff1d(np.arange(L), res["mstar"])
+        np.testing.assert_array_equal(res["u_set"], O.top_p_select(c, cand2, p))
+    ctx.close()
+
+
+@pytest.mark.parametrize("n_rows,V", [(1, 8192), (17, 8193), (256, 40000), (257, 40000), (40, 8192 * 33)])
+def test_select_merges_every_logit_row(B, n_rows, V):
+    """Eq. 1 with the chunks merged beside the selection (up to 256 rows, up to 32 chunks or more) and by a launch of its own."""
+    say(f"select rows {n_rows} x {V}")
+    L = 600
+    wd = W.ModelDims(1, 64, 4, 4, 16, 80, V, dtype="f32")
+    mdl = W.model_weights(W.ModelDims(1, 64, 4, 4, 16, 80, 8, dtype="f32"), 0)
+    mdl["tok_emb"] = mdl["lm_head"] = np.zeros((V, 64), np.float32)
+    ctx = B.Context(wd, mdl, L)
+    is_masked = np.zeros(L, bool); is_masked[100:] = True
+    y = np.where(is_masked, wd.mask_id, 3).astype(np.int32)
+    pos = (100 + np.arange(n_rows)).astype(np.int32)
+    logits = W.logits_rows(n_rows, n_rows, V)
+    logits[0, V - 1] = logits[0, 1] = logits[0].max() + 1.0                  # tied maxima in the first and last chunk
+    prm = B.make_params(10.0, 32, 0.1, 32, 1, 0)
+    res, _ = _run_select(B, ctx, prm, logits, pos, y, is_masked, 100, np.zeros(L, np.float32), np.zeros(L, np.int32),
+                         W.skewed_influence(1, L))
+    s, xh = O.confidence(logits)
+    np.testing.assert_array_equal(res["pred"][pos], xh)
+    np.testing.assert_allclose(res["conf"][pos], s, rtol=1e-5)
+    ctx.close()
