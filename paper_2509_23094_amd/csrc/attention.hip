@@ -24,7 +24,8 @@
 //             (16-query tile, 16-key tile); its 4 waves split the heads, recompute S^T and
 //             accumulate exp(s - lse) in registers, then add their partial sums in a fixed
 //             order through LDS.
-// fp32 path (small test model only): forward and second pass, one workgroup per query row, plain FMA.
+// fp32 path: the same two kernels on the fp32 matrix cores for head dimensions 64 and 128; for other head
+// dimensions forward and second pass with one workgroup per query row, plain FMA.
 #include <algorithm>
 
 #include "common.h"
@@ -360,13 +361,15 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const bf16* __restr
 // Pass 2: one workgroup per (16-query tile, 16-key tile); its 4 waves split the heads (wave w takes
 // heads w, w+4, ..), each recomputes S^T for its heads and accumulates exp(s - lse); the four partial
 // sums are added in a fixed order through LDS.
-template <int DH>
-__global__ __launch_bounds__(kThreads) void attn_avg_bf16_kernel(const bf16* __restrict__ q,
-                                                                 const bf16* __restrict__ k_cache,
-                                                                 const float* __restrict__ lse, int m, int L,
-                                                                 int n_heads, int n_kv_heads, float scale,
-                                                                 float* __restrict__ attn_avg) {
-  constexpr int NS = DH / 32;
+__device__ __forceinline__ float exp_of(const bf16*, float x) { return __expf(x); }
+__device__ __forceinline__ float exp_of(const float*, float x) { return expf(x); }
+template <typename T, int DH>
+__global__ __launch_bounds__(kThreads) void attn_avg_kernel(const T* __restrict__ q, const T* __restrict__ k_cache,
+                                                            const float* __restrict__ lse, int m, int L, int n_heads,
+                                                            int n_kv_heads, float scale,
+                                                            float* __restrict__ attn_avg) {
+  constexpr int KS = Frag<T>::kStep, E = Frag<T>::kElems;
+  constexpr int NS = DH / KS;
   __shared__ f32x4 part[kWaves][64];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int r = lane & 15, g = lane >> 4;
@@ -377,26 +380,26 @@ __global__ __launch_bounds__(kThreads) void attn_avg_bf16_kernel(const bf16* __r
   const int group = n_heads / n_kv_heads;
   const int row = min(q0 + r, m - 1);
   const int key = min(key0 + r, L - 1);
-  const bf16* qrow = q + (size_t)row * dq + g * 8;
-  const bf16* krow = k_cache + (size_t)key * kv_pitch + g * 8;
+  const T* qrow = q + (size_t)row * dq + g * E;
+  const T* krow = k_cache + (size_t)key * kv_pitch + g * E;
 
-  auto load_head = [&](Frag<bf16> (&qf)[NS], Frag<bf16> (&kf)[NS], float& e, int head) {
+  auto load_head = [&](Frag<T> (&qf)[NS], Frag<T> (&kf)[NS], float& e, int head) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      qf[s].raw = ld16(qrow + head * DH + s * 32);
-      kf[s].raw = ld16(krow + (head / group) * DH + s * 32);
+      qf[s].raw = ld16(qrow + head * DH + s * KS);
+      kf[s].raw = ld16(krow + (head / group) * DH + s * KS);
     }
     e = lse[(size_t)head * m + row];
   };
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  auto consume = [&](const Frag<bf16> (&qf)[NS], const Frag<bf16> (&kf)[NS], float e) {
+  auto consume = [&](const Frag<T> (&qf)[NS], const Frag<T> (&kf)[NS], float e) {
     f32x4 st = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < NS; ++s) mfma16(st, kf[s], qf[s]);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] += __expf(st[j] * scale - e);
+    for (int j = 0; j < 4; ++j) acc[j] += exp_of(q, st[j] * scale - e);
   };
-  Frag<bf16> qa[NS], ka[NS], qb[NS], kb[NS];
+  Frag<T> qa[NS], ka[NS], qb[NS], kb[NS];
   float ea = 0.f, eb = 0.f;
   int h = wave;
   if (h < n_heads) load_head(qa, ka, ea, h);
@@ -423,7 +426,133 @@ __global__ __launch_bounds__(kThreads) void attn_avg_bf16_kernel(const bf16* __r
     if (key0 + 4 * g + j < L) dst[j] = sum[j] * inv_h;
 }
 
-// fp32 path (small test model): one workgroup per query row, heads in sequence, plain FMA.
+// fp32 forward for head dimensions 64 and 128: the bf16 kernel's shape (one workgroup per 16-query tile and head, 8
+// waves taking 16-key tiles round-robin with the next tile's loads in flight, online softmax per wave, merge through
+// LDS) on the fp32 matrix cores.  The accumulator of S^T = K Q^T holds 4 consecutive keys of one query per lane, which
+// is the B operand of O^T = V^T P^T for four 16x16x4 steps; a lane's 16-byte piece of a V row (4 head-dim values) feeds
+// four output tiles, tile i taking values 4r + i, so V needs no transpose.  Latency-bound at the small sizes it runs
+// at: 37 queries x 128 keys x 4 heads of 64 take 8.3 us, 119.6 in the per-row kernel below (second pass 3.5, 23.5 there).
+template <int DH>
+__global__ __launch_bounds__(kFwdThreads) void attn_fwd_f32_tile_kernel(
+    const float* __restrict__ q, const float* __restrict__ k_cache, const float* __restrict__ v_cache, int m, int L,
+    int n_heads, int n_kv_heads, float scale, float* __restrict__ out, float* __restrict__ lse) {
+  constexpr int NS = DH / 16, NB = DH / 64;
+  __shared__ float o_lds[kFwdWaves][16][DH + 1];
+  __shared__ float m_lds[kFwdWaves][16], l_lds[kFwdWaves][16], f_lds[kFwdWaves][16];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int r = lane & 15, g = lane >> 4;
+  int head, qt, dpart;
+  if (!fwd_map_decode(fwd_map(m, n_heads, n_kv_heads, 1), n_kv_heads, blockIdx.x, head, qt, dpart)) return;
+  const int q0 = qt * 16;
+  const int kvh = head / (n_heads / n_kv_heads);
+  const int dq = n_heads * DH;
+  const size_t kv_pitch = (size_t)n_kv_heads * DH;
+  const float* kbase = k_cache + (size_t)kvh * DH;
+  const float* vbase = v_cache + (size_t)kvh * DH;
+  struct Tile {
+    Frag<float> k[NS];
+    f32x4 v[NB][4];
+  };
+  auto load = [&](Tile& t, int key0) {                     // rows past the end: the last key again, masked below
+    const float* krow = kbase + (size_t)min(key0 + r, L - 1) * kv_pitch + g * 4;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) t.k[s].raw = ld16(krow + s * 16);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float* vrow = vbase + (size_t)min(key0 + 4 * g + e, L - 1) * kv_pitch + 4 * r;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) t.v[b][e] = *reinterpret_cast<const f32x4*>(vrow + b * 64);
+    }
+  };
+  Frag<float> qf[NS];
+  {
+    const float* qrow = q + (size_t)min(q0 + r, m - 1) * dq + head * DH + g * 4;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) qf[s].raw = ld16(qrow + s * 16);
+  }
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x4 acc[NB][4];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[b][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int n_tiles = (L + 15) / 16;
+  Tile cur, nxt;
+  load(cur, wave * 16);
+  for (int t = wave; t < n_tiles; t += kFwdWaves) {
+    const int key0 = t * 16;
+    load(nxt, key0 + kFwdWaves * 16);
+    f32x4 st = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) mfma16(st, cur.k[s], qf[s]);
+    float x[4], tmax = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = key0 + 4 * g + j < L;
+      x[j] = in ? st[j] * scale : -INFINITY;
+      tmax = fmaxf(tmax, x[j]);
+      if (!in) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) cur.v[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+    const float m_new = fmaxf(m_run, tmax);                // finite: a tile holds at least one key below L
+    const float alpha = expf(m_run - m_new);
+    float psum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      x[j] = expf(x[j] - m_new);
+      psum += x[j];
+    }
+    l_run = l_run * alpha + psum;
+    m_run = m_new;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        acc[b][i] *= alpha;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[b][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.v[b][e][i], x[e], acc[b][i], 0, 0, 0);
+      }
+    cur = nxt;
+  }
+  l_run += __shfl_xor(l_run, 16, kWave);
+  l_run += __shfl_xor(l_run, 32, kWave);
+  if (g == 0) {
+    m_lds[wave][r] = m_run;              // -inf, l = 0 for a wave that had no tile
+    l_lds[wave][r] = l_run;
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o_lds[wave][r][b * 64 + 16 * g + 4 * j + i] = acc[b][i][j];
+  __syncthreads();
+  if (tid < kFwdWaves * 16) {
+    const int w = tid >> 4, qi = tid & 15;
+    float mx = m_lds[0][qi];
+#pragma unroll
+    for (int u = 1; u < kFwdWaves; ++u) mx = fmaxf(mx, m_lds[u][qi]);
+    float lsum = 0.f;
+#pragma unroll
+    for (int u = 0; u < kFwdWaves; ++u) lsum += l_lds[u][qi] * expf(m_lds[u][qi] - mx);
+    f_lds[w][qi] = expf(m_lds[w][qi] - mx) / lsum;
+    if (w == 0 && q0 + qi < m) lse[(size_t)head * m + q0 + qi] = mx + logf(lsum);
+  }
+  __syncthreads();
+  for (int o = tid; o < 16 * DH; o += kFwdThreads) {
+    const int qi = o / DH, dcol = o - qi * DH;
+    float osum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kFwdWaves; ++w) osum += o_lds[w][qi][dcol] * f_lds[w][qi];
+    if (q0 + qi < m) out[(size_t)(q0 + qi) * dq + head * DH + dcol] = osum;
+  }
+}
+
+// fp32 with any other head dimension (small test models): one workgroup per query row, heads in sequence, plain FMA.
 __global__ __launch_bounds__(kThreads) void attn_fwd_f32_kernel(const float* __restrict__ q,
                                                                 const float* __restrict__ k_cache,
                                                                 const float* __restrict__ v_cache, int m, int L,
@@ -525,12 +654,25 @@ hipError_t launch_fwd_bf16(const void* q, const void* k_cache, const void* v_cac
 }
 
 template <int DH>
-hipError_t launch_avg_bf16(const void* q, const void* k_cache, const float* lse, int m, int L, int n_heads,
-                           int n_kv_heads, float* attn_avg, hipStream_t st) {
+hipError_t launch_fwd_f32(const void* q, const void* k_cache, const void* v_cache, int m, int L, int n_heads,
+                          int n_kv_heads, void* out, float* lse, hipStream_t st) {
+  hipLaunchKernelGGL(attn_fwd_f32_tile_kernel<DH>, dim3(fwd_map(m, n_heads, n_kv_heads, 1).n_wgs), dim3(kFwdThreads), 0,
+                     st, (const float*)q, (const float*)k_cache, (const float*)v_cache, m, L, n_heads, n_kv_heads,
+                     1.0f / sqrtf((float)DH), (float*)out, lse);
+  return hipGetLastError();
+}
+// the matrix-core kernels read the rows of a head in 16-byte pieces
+bool f32_tiles(int head_dim, const void* q, const void* k_cache, const void* v_cache) {
+  return (head_dim == 64 || head_dim == 128) && (((uintptr_t)q | (uintptr_t)k_cache | (uintptr_t)v_cache) & 15) == 0;
+}
+
+template <typename T, int DH>
+hipError_t launch_avg(const void* q, const void* k_cache, const float* lse, int m, int L, int n_heads,
+                      int n_kv_heads, float* attn_avg, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)DH);
   const int key_blocks = (L + 15) / 16;
-  hipLaunchKernelGGL(attn_avg_bf16_kernel<DH>, dim3((m + 15) / 16, key_blocks), dim3(kThreads), 0, st, (const bf16*)q,
-                     (const bf16*)k_cache, lse, m, L, n_heads, n_kv_heads, scale, attn_avg);
+  hipLaunchKernelGGL((attn_avg_kernel<T, DH>), dim3((m + 15) / 16, key_blocks), dim3(kThreads), 0, st, (const T*)q,
+                     (const T*)k_cache, lse, m, L, n_heads, n_kv_heads, scale, attn_avg);
   return hipGetLastError();
 }
 
@@ -592,6 +734,9 @@ hipError_t launch_attention_fwd(const Tunables& t, int dtype, const void* q, con
       return launch_fwd_bf16<64>(q, k_cache, v_cache, m, L, n_heads, n_kv_heads, out, lse, (bf16*)probs, st);
     return hipErrorInvalidValue;
   }
+  if (f32_tiles(head_dim, q, k_cache, v_cache))
+    return head_dim == 128 ? launch_fwd_f32<128>(q, k_cache, v_cache, m, L, n_heads, n_kv_heads, out, lse, st)
+                           : launch_fwd_f32<64>(q, k_cache, v_cache, m, L, n_heads, n_kv_heads, out, lse, st);
   const size_t smem = ((size_t)L + 8) * sizeof(float);
   if (smem > 64 * 1024) return hipErrorInvalidValue;   // default dynamic LDS limit
   const float scale = 1.0f / sqrtf((float)head_dim);
@@ -605,10 +750,13 @@ hipError_t launch_attention_avg(const Tunables& t, int dtype, const void* q, con
   if (m <= 0) return hipSuccess;
   if (L <= 0 || n_heads % n_kv_heads || attention_is_tiled(t, dtype, m, L)) return hipErrorInvalidValue;
   if (dtype == kBF16) {
-    if (head_dim == 128) return launch_avg_bf16<128>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st);
-    if (head_dim == 64) return launch_avg_bf16<64>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st);
+    if (head_dim == 128) return launch_avg<bf16, 128>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st);
+    if (head_dim == 64) return launch_avg<bf16, 64>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st);
     return hipErrorInvalidValue;
   }
+  if (f32_tiles(head_dim, q, k_cache, nullptr))
+    return head_dim == 128 ? launch_avg<float, 128>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st)
+                           : launch_avg<float, 64>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st);
   const float scale = 1.0f / sqrtf((float)head_dim);
   hipLaunchKernelGGL(attn_avg_f32_kernel, dim3(m), dim3(kThreads), 0, st, (const float*)q, (const float*)k_cache, lse,
                      m, L, n_heads, n_kv_heads, head_dim, scale, attn_avg);

@@ -558,3 +558,34 @@ def test_select_merges_every_logit_row(B, n_rows, V):
     np.testing.assert_array_equal(res["pred"][pos], xh)
     np.testing.assert_allclose(res["conf"][pos], s, rtol=1e-5)
     ctx.close()
+
+
+@pytest.mark.parametrize("H,Hkv,dh,L,m", [(4, 4, 64, 1, 1), (4, 2, 64, 129, 17), (6, 3, 128, 100, 33), (3, 1, 64, 1000, 129),
+                                          (2, 2, 128, 16, 16), (4, 4, 64, 143, 128)])
+def test_attention_parity_f32_tiles(B, H, Hkv, dh, L, m):
+    """fp32 on the matrix cores: one key, ragged last key and query tiles, waves without a key tile, grouped heads."""
+    say(f"attention f32 tiles H={H} Hkv={Hkv} dh={dh} L={L} m={m}")
+    _attention_parity(B, "f32", H, Hkv, dh, L, m)
+
+
+def test_attention_f32_unaligned_rows(B):
+    """Buffers that are not 16-byte aligned take the per-row kernels: the same result up to summation order."""
+    H, dh, L, m = 4, 64, 77, 19
+    say("attention f32 unaligned")
+    wd = W.ModelDims(1, H * dh, H, H, dh, 64, 64, dtype="f32")
+    ctx, _, _ = _ctx_for(B, wd, max_seq=L)
+    case = W.attention_case(1, H, H, dh, L, m, dtype="f32")
+    idx = torch.from_numpy(case["idx"]).cuda()
+    got = []
+    for off in (0, 1):
+        def put(a):
+            t = torch.zeros(a.size + 4, device="cuda")[off: off + a.size].view(a.shape)
+            t.copy_(torch.from_numpy(a))
+            return t
+        q, kc, vc = put(case["q"]), put(case["k_cache"]), put(case["v_cache"])
+        out, abar = torch.zeros_like(q), torch.zeros((m, L), device="cuda")
+        ctx.d2c_attention(q, idx, m, None, None, kc, vc, L, out, abar)
+        torch.cuda.synchronize()
+        got.append((host(out), host(abar)))
+    assert rel_l2(got[0][0], got[1][0]) < 1e-6 and rel_l2(got[0][1], got[1][1]) < 1e-6
+    ctx.close()
