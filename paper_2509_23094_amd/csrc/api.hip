@@ -76,7 +76,7 @@ struct d2c_ctx {
   size_t attn_part_floats = 0;
   float* partial = nullptr;     // split partials of the current projection
   size_t partial_floats = 0;
-  float* roll = nullptr;        // d2c_refresh_layer: the rollout block after the layer, [max_seq, max_seq]
+  float* roll = nullptr;        // d2c_refresh_layer: scratch of the rollout update, rollout_scratch_floats(max_seq)
   // d2c_step keeps every layer's head average (per batch slot: [n_layers][max_seq * max_seq]) and turns
   // them into the influence scores by a row-vector chain after the last layer
   float* abar_all = nullptr;
@@ -230,8 +230,8 @@ struct Seg {
   float* abar;                  // [m, L] out: head average of this layer (null = not wanted)
   void* probs;                  // bf16 [H, m, L] out: per-head attention rows written by the attention launch
                                 // itself (null = not wanted; only where attention_fwd_emits_probs)
-  const float* roll_in;         // rollout block before this layer (ignored at layer 0)
-  float* roll_out;              // rollout block after it; null = no rollout update
+  float* roll;                  // rollout block, updated in place (ignored on entry at layer 0; see rollout_in_place);
+                                // null = no rollout update
 };
 
 // One block on the M = sum of m compact rows of n_seg sequences.  The projections run once over all M rows
@@ -313,7 +313,7 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
   bool any_side = false;
   for (int b = 0; b < n_seg; ++b)
     any_side = any_side || (segs[b].m > 0 && segs[b].abar &&
-                            (!attention_is_tiled(c->tun, dt, segs[b].m, segs[b].L) || segs[b].roll_out));
+                            (!attention_is_tiled(c->tun, dt, segs[b].m, segs[b].L) || segs[b].roll));
   if (record_fwd && !any_side && side != st) D2C_HIP(c, hipEventRecord(c->fwd_done[layer], st));
   if (any_side) {
     if (side != st) {
@@ -327,9 +327,9 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
         D2C_TIMED(c, side, D2C_PROF_ATTN_AVG, 0.0,
                   launch_attention_avg(c->tun, dt, q + (size_t)g.off * dq * ts, g.k_cache, lse + (size_t)D.n_heads * g.off,
                                        g.m, g.L, D.n_heads, D.n_kv_heads, D.head_dim, g.abar, side));
-      if (g.roll_out)
+      if (g.roll)
         D2C_TIMED(c, side, D2C_PROF_ROLLOUT, 0.0,
-                  launch_rollout(g.abar, g.roll_in, g.roll_out, g.idx, g.m, g.L, layer == 0, side));
+                  launch_rollout(g.abar, g.roll, c->roll, g.idx, g.m, g.L, layer == 0, side));
     }
   }
   if ((rc = project(c, c->attn_o, dq, c->wo[layer], M, d, dq, &pl, &stride, st)) != D2C_OK) return rc;
@@ -451,7 +451,7 @@ int d2c_init_tuned(const d2c_dims* dims, const d2c_weights* w, const d2c_tunable
   c->head_rows = (int)std::min<size_t>(Lm, 256);
   c->attn_part_floats = need.attn_part;
   const int64_t ws0 = c->ws_bytes;
-  if ((rc = ws_alloc(c, &c->roll, Lm * Lm * 4)) ||
+  if ((rc = ws_alloc(c, &c->roll, rollout_scratch_floats(D.max_seq) * 4)) ||
       (rc = ws_alloc(c, &c->abar_all, (size_t)c->max_batch * D.n_layers * Lm * Lm * 4)))
     return bail(rc);
   c->probs_elems = attention_probs_elems(D.dtype, D.n_heads, D.max_seq);
@@ -681,10 +681,10 @@ int d2c_refresh_layer(d2c_ctx* c, int32_t layer, float* hidden, const int32_t* i
   if ((attn_avg == nullptr) != (rollout == nullptr))
     return fail(c, D2C_EINVAL, "attn_avg and rollout must both be given or both be null");
   hipStream_t st = (hipStream_t)stream;
-  const Seg seg{idx, m, 0, k_cache, v_cache, L, attn_avg, nullptr, rollout, rollout ? c->roll : nullptr};
+  const Seg seg{idx, m, 0, k_cache, v_cache, L, attn_avg, nullptr, rollout};
   rc = layer_impl(c, layer, hidden, &seg, 1, m, false, nullptr, st, st);
   if (rc) return rc;
-  if (rollout) D2C_HIP(c, launch_copy_f32(rollout, c->roll, (size_t)m * L, st));
+  if (rollout && !rollout_in_place(layer, m)) D2C_HIP(c, launch_copy_f32(rollout, c->roll, (size_t)m * L, st));
   return D2C_OK;
 }
 
@@ -815,8 +815,7 @@ int d2c_step(d2c_ctx* c, const d2c_params* p, d2c_seq_state* seqs, int32_t batch
           const bool emits = attention_fwd_emits_probs(c->tun, dt, segs[i].m, s.L);
           segs[i].probs = in_rollout && emits ? probs_slot(i, l) : nullptr;
           segs[i].abar = in_rollout && !emits ? abar_slot(i, l) : nullptr;
-          segs[i].roll_in = nullptr;               // no rollout block here: Eq. 9 comes from the chain below
-          segs[i].roll_out = nullptr;
+          segs[i].roll = nullptr;                  // no rollout block here: Eq. 9 comes from the chain below
         }
         rc = layer_impl(c, l, c->hidden, segs.data(), n_seg, M, true,
                         l + 1 < D.n_layers ? c->attn_norm[l + 1] : nullptr, st, side, l == roll_layers - 1);

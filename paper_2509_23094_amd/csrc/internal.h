@@ -143,8 +143,12 @@ size_t attention_tiled_scratch_floats(const Tunables& t, int max_m, int max_L, i
 hipError_t launch_attention_tiled(const Tunables& t, const TiledCall* calls, int n_calls, int n_heads, int n_kv_heads,
                                   int head_dim, float* scratch, size_t scratch_floats, hipStream_t st);
 
-// ---- rollout on the compact block: c_out = (A[:,S] c_in + A[:,notS] + c_in) / 2; first: c_in = one-hot rows
-hipError_t launch_rollout(const float* attn_avg, const float* c_in, float* c_out, const int32_t* idx, int m, int L,
+// ---- rollout on the compact block: c <- (A[:,S] c + A[:,notS] + c) / 2; first: c before is one-hot rows (not read).
+// Where rollout_in_place the result replaces c_block, elsewhere it is left in scratch (rollout_scratch_floats(m) and
+// at least m * L floats) and the caller copies it back.
+bool rollout_in_place(int layer, int m);
+size_t rollout_scratch_floats(int max_m);
+hipError_t launch_rollout(const float* attn_avg, float* c_block, float* scratch, const int32_t* idx, int m, int L,
                           bool first, hipStream_t st);
 hipError_t launch_influence(const float* c_block, const int32_t* idx, int m, int L, float* influence,
                             hipStream_t st);

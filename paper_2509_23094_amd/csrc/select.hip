@@ -17,6 +17,9 @@
 namespace d2c {
 namespace {
 
+typedef unsigned long long u64;
+__device__ __forceinline__ u64 low_mask(int n) { return n <= 0 ? 0ull : n >= 64 ? ~0ull : (1ull << n) - 1ull; }
+
 // ------------------------------------------------------------------ Eq. 1
 // x-hat = argmax_v, s = 1 / sum_v exp(x_v - max).  A vocabulary row (0.5 MB at V = 126464) is cut into
 // chunks, one workgroup each, so that a few dozen rows still fill the chip: per chunk (max, first index of
@@ -165,10 +168,107 @@ __global__ __launch_bounds__(kRollThreads) void rollout_first_kernel(const float
   c_out[(size_t)i * L + col] = 0.5f * (A[(size_t)i * L + col] + (idx[i] == col ? 1.f : 0.f));
 }
 
-// Later layers: the m x m by m x L product runs on the fp32 matrix cores, one wave per 16 x 16
-// output tile (4 waves = 16 rows x 64 columns per workgroup).  Per 16-long step of the
-// contraction a lane holds A[i0 + l%16][S[k0 + 4(l/16) + e]] and C[k0 + 4(l/16) + e][c0 + l%16],
-// e = 0..3, one 16x16x4 instruction per e.
+// Later layers: the m x m by m x L product on the fp32 matrix cores, in place.  One workgroup owns 16 columns: it
+// keeps its strip of c_in in LDS, so that nobody else reads what it overwrites, and its 8 waves take the 16-row tiles
+// round-robin.  Per 16-long step of the contraction a lane holds A[i0 + l%16][S[k0 + 4(l/16) + e]] and
+// C[k0 + 4(l/16) + e][c0 + l%16], e = 0..3, one 16x16x4 instruction per e.
+// DENSE: the operand A[:, S] comes from a dense copy (16 bytes a lane) instead of being gathered again by each of the
+// L / 16 workgroups (64 cache lines a load); it costs a launch, so few rows gather.  Per update, with the launches it
+// takes: 97 rows x 1823 columns 12.3 us gathered, 10.4 dense (15.5 with the copy that the tile kernel below needs);
+// 37 x 128 5.2 gathered, 6.0 dense; 600 x 3072 169 us in the tile kernel, 69 now; 1024 x 3072 413 -> 152.
+constexpr int kRollStripThreads = 512, kRollStripWaves = 8;
+constexpr int kRollPitch = 20;                 // floats per strip row: the four rows of a step fall on different banks
+constexpr int kRollFewRows = 64;               // up to this many rows the operand is gathered by the strips themselves
+constexpr int kRollStripMax = 1792;            // rows a strip of 16 columns may have in LDS (140 KB)
+template <int MAXM, bool DENSE>
+__global__ __launch_bounds__(kRollStripThreads) void rollout_strip_kernel(const float* __restrict__ A,
+                                                                          const float* __restrict__ G, int g_pitch,
+                                                                          float* __restrict__ C,
+                                                                          const int32_t* __restrict__ idx, int m, int L) {
+  __shared__ float strip[MAXM * kRollPitch];
+  __shared__ int32_t s_idx[DENSE ? 1 : MAXM];
+  __shared__ unsigned in_s;                    // bit c: column c0 + c is in S
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int r = lane & 15, g = lane >> 4;
+  const int c0 = blockIdx.x * 16, col = c0 + r;
+  const int mp = (m + 15) & ~15;
+  if (tid == 0) in_s = 0u;
+  __syncthreads();
+  for (int i = tid; i < m; i += kRollStripThreads) {
+    const int p = idx[i];
+    if constexpr (!DENSE) s_idx[i] = p;
+    if (p >= c0 && p < c0 + 16) atomicOr(&in_s, 1u << (p - c0));
+  }
+  for (int e = tid; e < mp * 16; e += kRollStripThreads) {
+    const int i = e >> 4, c = e & 15;
+    strip[i * kRollPitch + c] = i < m && c0 + c < L ? C[(size_t)i * L + c0 + c] : 0.f;
+  }
+  __syncthreads();
+  for (int i0 = wave * 16; i0 < m; i0 += kRollStripWaves * 16) {
+    const int arow = min(i0 + r, m - 1);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float direct[4];                             // requested in front of the contraction
+#pragma unroll
+    for (int j = 0; j < 4; ++j) direct[j] = A[(size_t)min(i0 + 4 * g + j, m - 1) * L + min(col, L - 1)];
+    if constexpr (DENSE) {
+      const float* grow = G + (size_t)arow * g_pitch + 4 * g;      // zero beyond column m
+      f32x4 av[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) av[u] = *reinterpret_cast<const f32x4*>(grow + min(u * 16, mp - 16));
+      for (int k0 = 0; k0 < mp; k0 += 64) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = k0 + u * 16;
+          const f32x4 a = av[u];
+          av[u] = *reinterpret_cast<const f32x4*>(grow + min(k + 64, mp - 16));
+          if (k < mp) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], strip[(k + 4 * g + e) * kRollPitch + r], acc, 0, 0, 0);
+          }
+        }
+      }
+    } else {
+      const float* a_row = A + (size_t)arow * L;
+      float av[MAXM / 16][4];                    // the whole row's share of this lane, all loads in flight
+#pragma unroll
+      for (int u = 0; u < MAXM / 16; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) av[u][e] = a_row[s_idx[min(u * 16 + 4 * g + e, m - 1)]];
+#pragma unroll
+      for (int u = 0; u < MAXM / 16; ++u)
+        if (u * 16 < mp) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int k = u * 16 + 4 * g + e;
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(k < m ? av[u][e] : 0.f, strip[k * kRollPitch + r], acc, 0, 0, 0);
+          }
+        }
+    }
+    if (col < L) {
+      const bool own = in_s >> r & 1u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = i0 + 4 * g + j;
+        if (i >= m) break;
+        C[(size_t)i * L + col] = 0.5f * (acc[j] + (own ? 0.f : direct[j]) + strip[i * kRollPitch + r]);
+      }
+    }
+  }
+}
+
+// G[i, k] = A[i, S_k], pitch g_pitch = m rounded up to 16, zero beyond column m
+__global__ __launch_bounds__(kRollThreads) void rollout_gather_kernel(const float* __restrict__ A,
+                                                                      const int32_t* __restrict__ idx, int m, int L,
+                                                                      int g_pitch, float* __restrict__ G) {
+  const size_t e = (size_t)blockIdx.x * kRollThreads + threadIdx.x;
+  if (e >= (size_t)m * g_pitch) return;
+  const int i = (int)(e / g_pitch), k = (int)(e - (size_t)i * g_pitch);
+  G[e] = k < m ? A[(size_t)i * L + idx[k]] : 0.f;
+}
+
+// More rows than a strip in LDS holds: not in place, one wave per 16 x 16 output tile (4 waves = 16 rows x 64 columns
+// per workgroup), the operand gathered.
 __global__ __launch_bounds__(kRollThreads) void rollout_kernel(const float* __restrict__ A,
                                                                const float* __restrict__ c_in,
                                                                float* __restrict__ c_out,
@@ -208,13 +308,49 @@ __global__ __launch_bounds__(kRollThreads) void rollout_kernel(const float* __re
   }
 }
 
-// Eq. 9 on the compact block: c_j = [j not in S] + sum_i C_S[i, j]
-__global__ void influence_kernel(const float* __restrict__ c_block, const int32_t* __restrict__ idx, int m, int L,
-                                 float* __restrict__ influence) {
-  const int col = blockIdx.x * blockDim.x + threadIdx.x;
-  if (col >= L) return;
-  float s = find_sorted(idx, m, col) < 0 ? 1.f : 0.f;
-  for (int i = 0; i < m; ++i) s += c_block[(size_t)i * L + col];
+// Which of the 64 columns from c0 on lie in S, as a bitmap in LDS: every thread looks at its share of the index set (one
+// memory latency instead of a search's ten).  All threads of the workgroup call it; ends on a barrier.
+template <int THREADS>
+__device__ __forceinline__ u64 columns_in_s(const int32_t* __restrict__ idx, int m, int c0, u64* word) {
+  if (threadIdx.x == 0) *word = 0ull;
+  __syncthreads();
+  for (int i = threadIdx.x; i < m; i += THREADS) {
+    const int p = idx[i];
+    if (p >= c0 && p < c0 + 64) atomicOr(word, 1ull << (p - c0));
+  }
+  __syncthreads();
+  return *word;
+}
+
+// Eq. 9 on the compact block: c_j = [j not in S] + sum_i C_S[i, j].  64 columns per workgroup, its 16 waves split the
+// rows (wave w: rows w, w + 16, ..), the waves' sums are added in wave order.  97 rows x 1823 columns: 24.6 us with a
+// thread per column, 4.0 now.
+constexpr int kInflThreads = 1024;
+__global__ __launch_bounds__(kInflThreads) void influence_kernel(const float* __restrict__ c_block,
+                                                                 const int32_t* __restrict__ idx, int m, int L,
+                                                                 float* __restrict__ influence) {
+  __shared__ float red[kInflThreads / 64][64];
+  __shared__ u64 word;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int c0 = blockIdx.x * 64, col = c0 + lane;
+  constexpr int NW = kInflThreads / 64;
+  const float* ccol = c_block + min(col, L - 1);
+  float s = 0.f;
+  int i = wave;
+  for (; i + 7 * NW < m; i += 8 * NW) {
+    float x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = ccol[(size_t)(i + t * NW) * L];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) s += x[t];
+  }
+  for (; i < m; i += NW) s += ccol[(size_t)i * L];
+  red[wave][lane] = s;
+  const u64 own = columns_in_s<kInflThreads>(idx, m, c0, &word);
+  if (wave != 0 || col >= L) return;
+  s = own >> lane & 1ull ? 0.f : 1.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) s += red[w][lane];
   influence[col] = s;
 }
 
@@ -419,8 +555,12 @@ __global__ __launch_bounds__(kChainThreads) void chain_cols_kernel(const ChainSe
   const int m = q.m, L = q.L;
   if ((int)blockIdx.x * 64 >= L) return;                  // the grid follows the longest sequence
   __shared__ float red[kChainThreads / 64][64];
+  __shared__ u64 word;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int col = blockIdx.x * 64 + lane;
+  // nothing to do where every column is in S (a first step: all of them; 24 us for 512 rows before)
+  const u64 outside = ~columns_in_s<kChainThreads>(idx, m, blockIdx.x * 64, &word) & low_mask(L - (int)blockIdx.x * 64);
+  if (outside == 0ull) return;
   const float* acol = abar + min(col, L - 1);
   float acc = 0.f;
   for (int l = wave; l < n_layers; l += kChainThreads / 64) {
@@ -438,7 +578,7 @@ __global__ __launch_bounds__(kChainThreads) void chain_cols_kernel(const ChainSe
   }
   red[wave][lane] = acc;
   __syncthreads();
-  if (wave != 0 || col >= L || find_sorted(idx, m, col) >= 0) return;
+  if (wave != 0 || !(outside >> lane & 1ull)) return;
   float sum = 0.f;
 #pragma unroll
   for (int w = 0; w < kChainThreads / 64; ++w) sum += red[w][lane];
@@ -490,8 +630,6 @@ __device__ int block_compact(int n, Pred pred, Emit emit, SelShared* sh) {
   return base;
 }
 
-typedef unsigned long long u64;
-
 __device__ __forceinline__ u64 make_key(uint32_t bits, int index) {
   return ((u64)bits << 32) | (u64)(0xFFFFFFFFu - (unsigned)index);
 }
@@ -537,7 +675,6 @@ __device__ __forceinline__ uint32_t wave_before(uint32_t v, uint32_t* total) {
   *total = lane_of(incl, 63);
   return incl - v;
 }
-__device__ __forceinline__ u64 low_mask(int n) { return n <= 0 ? 0ull : n >= 64 ? ~0ull : (1ull << n) - 1ull; }
 
 struct SelRadix {
   u64 hist[3][256];          // hist[*buf] is all zero between calls
@@ -1066,23 +1203,43 @@ hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, 
   return hipGetLastError();
 }
 
-hipError_t launch_rollout(const float* attn_avg, const float* c_in, float* c_out, const int32_t* idx, int m, int L,
+bool rollout_in_place(int layer, int m) { return layer == 0 || m <= kRollStripMax; }
+size_t rollout_scratch_floats(int max_m) { return (size_t)max_m * ((max_m + 15) & ~15); }
+
+hipError_t launch_rollout(const float* attn_avg, float* c_block, float* scratch, const int32_t* idx, int m, int L,
                           bool first, hipStream_t st) {
   if (m <= 0) return hipSuccess;
   if (first) {
     hipLaunchKernelGGL(rollout_first_kernel, dim3((L + kRollThreads - 1) / kRollThreads, m), dim3(kRollThreads), 0, st,
-                       attn_avg, c_out, idx, m, L);
+                       attn_avg, c_block, idx, m, L);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(rollout_kernel, dim3((L + 63) / 64, (m + 15) / 16), dim3(kRollThreads), 0, st, attn_avg, c_in,
-                     c_out, idx, m, L);
+  const dim3 strips((L + 15) / 16), threads(kRollStripThreads);
+  if (m <= kRollFewRows) {
+    hipLaunchKernelGGL((rollout_strip_kernel<kRollFewRows, false>), strips, threads, 0, st, attn_avg, nullptr, 0, c_block, idx, m, L);
+    return hipGetLastError();
+  }
+  if (m <= kRollStripMax) {
+    const int pitch = (m + 15) & ~15;
+    hipLaunchKernelGGL(rollout_gather_kernel, dim3((unsigned)(((size_t)m * pitch + kRollThreads - 1) / kRollThreads)),
+                       dim3(kRollThreads), 0, st, attn_avg, idx, m, L, pitch, scratch);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (m <= 768)
+      hipLaunchKernelGGL((rollout_strip_kernel<768, true>), strips, threads, 0, st, attn_avg, scratch, pitch, c_block, idx, m, L);
+    else
+      hipLaunchKernelGGL((rollout_strip_kernel<kRollStripMax, true>), strips, threads, 0, st, attn_avg, scratch, pitch, c_block, idx, m, L);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(rollout_kernel, dim3((L + 63) / 64, (m + 15) / 16), dim3(kRollThreads), 0, st, attn_avg, c_block,
+                     scratch, idx, m, L);
   return hipGetLastError();
 }
 
 hipError_t launch_influence(const float* c_block, const int32_t* idx, int m, int L, float* influence,
                             hipStream_t st) {
   if (L <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(influence_kernel, dim3((L + 255) / 256), dim3(256), 0, st, c_block, idx, m, L, influence);
+  hipLaunchKernelGGL(influence_kernel, dim3((L + 63) / 64), dim3(kInflThreads), 0, st, c_block, idx, m, L, influence);
   return hipGetLastError();
 }
 

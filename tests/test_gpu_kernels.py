@@ -589,3 +589,35 @@ def test_attention_f32_unaligned_rows(B):
         got.append((host(out), host(abar)))
     assert rel_l2(got[0][0], got[1][0]) < 1e-6 and rel_l2(got[0][1], got[1][1]) < 1e-6
     ctx.close()
+
+
+@pytest.mark.parametrize("L,m", [(1, 1), (40, 16), (131, 64), (200, 65), (791, 768), (800, 769), (1900, 1793)])
+def test_rollout_update_and_influence_at_the_size_rules(B, L, m):
+    """The second layer's rollout update for every form of it (operand gathered, dense, strip in LDS or not) and Eq. 9,
+    against the formula in fp64 on the GPU's own head averages.  Bound: sums of at most 1793 terms of a row that sums to
+    one, in fp32 (1793 roundings of 6e-8 of a value below 1, most of which cancel): 1e-5 relative to the row."""
+    say(f"rollout L={L} m={m}")
+    wd = W.ModelDims(2, 64, 4, 4, 16, 64, 64, dtype="f32")
+    ctx, _, _ = _ctx_for(B, wd, max_seq=L, n_layers=2)
+    S = W.distinct_sorted_rows(1, L, m)
+    idx = torch.from_numpy(S).cuda()
+    h = torch.from_numpy(W.hidden_rows(1, m, 64)).cuda()
+    kc, vc = (torch.from_numpy(W.hidden_rows(s, 2 * L, 64).reshape(2, L, 64)).cuda() for s in (2, 3))
+    avg, roll = torch.zeros((m, L), device="cuda"), torch.full((m, L), 7.0, device="cuda")
+    got = []
+    for l in range(2):
+        ctx.d2c_refresh_layer(l, h, idx, S, kc[l], vc[l], L, avg, roll)
+        got.append((host(avg).astype(np.float64), host(roll).astype(np.float64)))
+    c = torch.zeros(L, device="cuda")
+    ctx.d2c_influence(roll, idx, m, L, c)
+    torch.cuda.synchronize()
+    eye = np.zeros((m, L)); eye[np.arange(m), S] = 1.0
+    outside = np.ones(L); outside[S] = 0.0
+    prev = eye
+    for a, r in got:
+        ref = 0.5 * (a[:, S] @ prev + a * outside + prev)
+        for i in range(m):
+            assert rel_l2(r[i], ref[i]) < 1e-5, f"rollout row {i}"
+        prev = r
+    np.testing.assert_allclose(host(c), outside + prev.sum(0), rtol=1e-5)
+    ctx.close()
