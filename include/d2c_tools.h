@@ -62,7 +62,9 @@ int d2c_ctx_set_tunable(d2c_ctx* ctx, const char* name, int32_t value);
  * (host-side arithmetic only: no context, no GPU).  single_split != 0: the projection must not split the
  * contraction (the gate/up projection with the gated epilogue).  Writes
  * shape[0..6] = row tiles per workgroup (16 rows each), column tiles per wave, waves per workgroup, splits of
- * the contraction, contraction elements per split, row chunks, workgroups of the launch.
+ * the contraction, contraction elements per split, row chunks, workgroups of the launch (with 4 column tiles per wave two row
+ * chunks of one column block share a physical workgroup of twice the waves, which may be a quarter narrower; the
+ * nominal ones, a row chunk and 256 columns each, are counted here).
  * Returns D2C_EINVAL for a null pointer, a dtype other than D2C_F32 / D2C_BF16 or non-positive sizes. */
 int d2c_plan_projection(int32_t dtype, int32_t m, int32_t N, int32_t K, int32_t single_split, int32_t shape[7]);
 

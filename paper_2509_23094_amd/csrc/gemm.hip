@@ -15,11 +15,13 @@
 //   * the contraction axis can be split over several workgroups; every split writes
 //     its own fp32 partial and the consumer kernel sums the partials in a fixed order
 //     (deterministic, no atomics);
-//   * more than 128 rows (step 0, select-all mode) are covered by several row chunks.
+//   * more than 128 rows are covered by several row chunks (many rows in bf16: gemm_wide_kernel below).
 //     The grid is one-dimensional and workgroup ids are dealt round-robin to the 8
 //     XCDs, each with its own L2: the mapping below gives the row chunks of one weight
 //     tile consecutive slots of the SAME XCD, so the tile comes from HBM once and the
 //     other chunks hit it in L2.
+#include <algorithm>
+
 #include "common.h"
 #include "internal.h"
 
@@ -37,6 +39,12 @@ constexpr int kSuperRows = 8, kSuperCols = 4;    // many rows: block of workgrou
 // SwiGLU applied in the epilogue (single k split, one column tile per wave): act[m, N/2] = T(silu(g) * u).
 enum { kRowMajor = 0, kPre = 1, kPreSwiglu = 2 };
 
+// silu(g) * u on the exponential and reciprocal units (each within one unit in the last place in 32 bits; the result is
+// rounded to T): with a library exponential and a division the epilogue of 256 rows x 256 columns took about 7 us
+__device__ __forceinline__ float gated(float g, float u) {
+  return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896341f * g)) * u;
+}
+
 template <typename T, int MT, int NT, int WAVES, int MODE>
 __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
     const T* __restrict__ A, int lda, const T* __restrict__ W, int ldw, float* __restrict__ P, int ldp,
@@ -50,20 +58,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
   constexpr int AI = (kAFrags + kThreads - 1) / kThreads;        // of which one thread moves this many
   // workgroup id -> (weight tile, row chunk): id % 8 is the XCD, within an XCD the row chunk varies fastest
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int tile, bz;
-  if constexpr (NT >= 4) {
-    // Many rows: the 32 workgroups that run on an XCD at one time form a block of kSuperRows row chunks x
-    // kSuperCols weight tiles, so that what its L2 has to bring in per k-step (8 x 128 activation rows +
-    // 4 x 256 weight rows) is less than half of that of 32 row chunks of one weight tile.
-    const int n_row_st = (row_chunks + kSuperRows - 1) / kSuperRows;
-    const int st = slot / (kSuperRows * kSuperCols), w = slot % (kSuperRows * kSuperCols);
-    bz = (st % n_row_st) * kSuperRows + w % kSuperRows;
-    tile = ((st / n_row_st) * kSuperCols + w / kSuperRows) * 8 + xcd;
-    if (bz >= row_chunks) return;
-  } else {
-    tile = (slot / row_chunks) * 8 + xcd;
-    bz = slot % row_chunks;
-  }
+  const int tile = (slot / row_chunks) * 8 + xcd, bz = slot % row_chunks;
   if (tile >= n_blocks * n_splits) return;       // padding (whole workgroup leaves)
   const int by = tile / n_blocks, bx = tile - by * n_blocks;
   constexpr int E = Frag<T>::kElems;
@@ -164,63 +159,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
   };
 
   if (n_chunks <= 0) return;
-  if constexpr (NT >= 4) {
-    // Many rows: 128 x 64 outputs per wave, one wave per SIMD.  Nothing else hides latencies here, so the
-    // loop is pipelined by hand and the scheduler is told to keep the interleaving:
-    //   * the activation fragments are read from LDS three matrix-core groups ahead of their use;
-    //   * the weight registers of a k-step are refilled as soon as that step is done, with the same step
-    //     of the chunk two ahead (two chunks of flight time: an L2 miss costs more than one);
-    //   * the next activation chunk is requested at the top of an iteration and stored behind it.
-    // The launcher guarantees whole chunks and an even number of them per split: nothing to mask.
-    static_assert(RING == 2, "the wide loop keeps two weight chunks");
-    constexpr int NI = kSteps * MT;
-    auto load_b_step = [&](Frag<T> (&b)[NT][kSteps], int chunk, int step) {
-      const size_t off = PRE ? (size_t)(chunk_k(chunk) / KC) * kBlockElems + step * 64 * E
-                             : (size_t)(chunk_k(chunk) + step * KS + g * E);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) b[nt][step].raw = ld16(wrow[nt] + off);
-    };
-    load_a(areg[0], 0);
-    load_b(breg[0], 0);
-    load_b(breg[1], 1);
-    store_a(areg[0], 0);
-    __syncthreads();
-    for (int base = 0; base < n_chunks; base += 2) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int c = base + u;
-        load_a(areg[0], c + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        const unsigned char* abuf = lds[u];
-        auto read_af = [&](int i) {
-          Frag<T> f;
-          f.raw = *reinterpret_cast<const u32x4*>(&abuf[((i % MT) * 16 + r) * kRowStride + ((i / MT) * 4 + g) * 16]);
-          return f;
-        };
-        Frag<T> af[4];
-        af[0] = read_af(0);
-        af[1] = read_af(1);
-        af[2] = read_af(2);
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) mfma16(acc[i % MT][nt], af[i % 4], breg[u][nt][i / MT]);
-          if (i + 3 < NI) af[(i + 3) % 4] = read_af(i + 3);
-          if (i % MT == MT - 1) load_b_step(breg[u], c + 2, i / MT);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, NT, 0);                          // NT matrix-core instructions
-          if (i + 3 < NI) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);           // one LDS read
-          if (i % MT == MT - 1) __builtin_amdgcn_sched_group_barrier(0x020, NT, 0);    // the k-step's refill
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        store_a(areg[0], u ^ 1);
-        __syncthreads();
-      }
-    }
-  } else {
   // prologue: weight chunks 0..PB-1 and activation chunks 0, 1 are requested; chunk 0 reaches LDS
 #pragma unroll
   for (int u = 0; u < PB; ++u) load_b(breg[u], u);
@@ -262,8 +200,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
       __syncthreads();
     }
   }
-
-  }   // narrow loop
 
   if (MODE == kPreSwiglu && NT % 2 == 0) {
     // Column tiles alternate gate, up, gate, up ..: with an even number of tiles per wave each pair sits in one wave
@@ -326,6 +262,223 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
     }
 }
 
+// ---- many rows (bf16): two row chunks of 16*MT rows x 256 columns per workgroup.  8 waves: four take a row chunk, each with
+// 64 columns, so that two waves share a SIMD (one alone cannot issue 16x16x32 steps back to back: 1.37 PFLOP/s in a loop
+// of nothing else, 1.90 with two).  What bounds the loop is how much a compute unit gets through its L1, so the tile is
+// as large as the registers take (128 accumulators a lane; 256 x 256 outputs a workgroup) and the accesses are whole
+// 64-byte pieces (see the staging below).  The activations go from global memory straight into LDS, a chunk of 128 k
+// ahead; the weights straight into operand registers, refilled with the next chunk's step as soon as a step is done; LDS
+// reads run three matrix-core groups ahead of their use.  The scheduler is told to keep that order.  The wait in front
+// of the barrier leaves the weight refills behind the staging in flight.
+// 512 rows, LLaDA widths, against 128 x 256 tiles of 4 waves with activations through registers: gate/up (24576 x 4096)
+// 142 -> 93 us (1.10 PFLOP/s), QKV 79 -> 57, O and down together 89 -> 84.  Tried on the 256-column tile (105 us):
+// 32x32x16 steps with one wave per SIMD (119 us), operand-order staging (130 us).
+// The launcher guarantees whole chunks and an even number of them per split: nothing to mask.
+template <int MT, int NT, int MODE>
+__global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restrict__ A, int lda, const bf16* __restrict__ W,
+                                                           int ldw, float* __restrict__ P, int ldp, size_t split_stride,
+                                                           int m, int N, int K, int k_per_split, int n_blocks,
+                                                           int n_splits, int pairs, bf16* __restrict__ act) {
+  constexpr bool PRE = MODE != kRowMajor;
+  constexpr int E = 8, KS = 32, KC = 128;
+  constexpr int kBlockElems = 16 * KC;
+  constexpr int kBuf = MT * 8 * 1024;                       // bytes of one activation chunk: 2*MT row tiles x 4 steps x 1 KB
+  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * kBuf];
+  // workgroup id -> (weight tile, row pair): id % 8 is the XCD; the 32 workgroups that run on an XCD at one time form a
+  // block of up to kSuperRows row pairs x as many weight tiles, so that its L2 brings in each byte once for several
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int rows_st = min(pairs, kSuperRows);
+  const int n_row_st = (pairs + rows_st - 1) / rows_st;
+  const int cols_st = 32 / rows_st;
+  const int st = slot / (rows_st * cols_st), in_st = slot % (rows_st * cols_st);
+  const int bz = (st % n_row_st) * rows_st + in_st % rows_st;
+  const int tile = ((st / n_row_st) * cols_st + in_st / rows_st) * 8 + xcd;
+  if (bz >= pairs || tile >= n_blocks * n_splits) return;      // padding (whole workgroup leaves)
+  const int by = tile / n_blocks, bx = tile - by * n_blocks;
+
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int r = lane & 15, g = lane >> 4;
+  const int part = wave >> 2, quarter = wave & 3;             // row chunk of the pair, 64-column quarter
+  const int row0 = (bz * 2 + part) * (MT * 16);
+  const int k_begin = by * k_per_split;
+  const int k_end = min(K, k_begin + k_per_split);
+  const int n_base = (bx * 4 + quarter) * (16 * NT);
+  const int n_chunks = (k_end - k_begin) / KC;
+  if (n_chunks <= 0) return;
+  const int last_chunk = n_chunks - 1;
+
+  const bf16* wrow[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    if (PRE) {
+      const int t16 = min((n_base + nt * 16) / 16, (N + 15) / 16 - 1);
+      wrow[nt] = W + ((size_t)t16 * ldw + k_begin / KC) * kBlockElems + lane * E;
+    } else {
+      wrow[nt] = W + (size_t)min(n_base + nt * 16 + r, N - 1) * ldw + k_begin + g * E;
+    }
+  }
+  // staging: a wave brings k-step `quarter` of every other 16-row tile, 16 rows x 64 bytes an instruction (rows past m
+  // repeat row m-1 and are not stored).  Four neighbouring lanes take the 64 bytes of one row: the L1 merges only what
+  // consecutive lanes ask for, and operand order (lane = row) would cost it 64 accesses an instruction instead of 16.
+  // LDS then holds [row][piece], the pieces of a row xored with half its number: eight lanes of an operand read (rows at one
+  // k group) then touch 128 different bytes' banks.
+  unsigned aoff[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+    aoff[i] = (unsigned)(((size_t)min(bz * (MT * 32) + (2 * i + part) * 16 + (lane >> 2), m - 1) * lda + quarter * KS +
+                          ((lane & 3) ^ (lane >> 3 & 3)) * E) * 2);
+  // (through a buffer resource: a global_load .. lds counts as a flat access, behind which every LDS wait drains the queue)
+  const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16*>(A), 0, (int)(unsigned)(((size_t)(m - 1) * lda + K) * 2), 0x00020000);
+
+  Frag<bf16> b[NT][kSteps];
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  auto stage = [&](int buf, int chunk) {
+    const int soff = (k_begin + min(chunk, last_chunk) * KC) * 2;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          arsrc, (__attribute__((address_space(3))) void*)(lds + buf * kBuf + ((2 * i + part) * 4 + quarter) * 1024), 16, (int)aoff[i],
+          soff, 0, 0);
+  };
+  auto load_b_step = [&](int chunk, int step) {
+    const size_t off = (size_t)min(chunk, last_chunk) * (PRE ? kBlockElems : KC) + step * (PRE ? 64 * E : KS);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) b[nt][step].raw = ld16(wrow[nt] + off);
+  };
+  stage(0, 0);
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) load_b_step(0, s);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x70 | 0xf00);                  // vmcnt(0)
+  __syncthreads();
+  constexpr int NI = kSteps * MT;
+  for (int c = 0; c < n_chunks; ++c) {
+    stage((c & 1) ^ 1, c + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    const unsigned char* abuf = lds + (c & 1) * kBuf + part * (MT * 4096) + (r * 4 + (g ^ (r >> 1 & 3))) * 16;
+    auto read_af = [&](int i) {
+      Frag<bf16> f;
+      f.raw = *reinterpret_cast<const u32x4*>(abuf + ((i % MT) * 4 + i / MT) * 1024);
+      return f;
+    };
+    Frag<bf16> af[4];
+    af[0] = read_af(0);
+    af[1] = read_af(1);
+    af[2] = read_af(2);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) mfma16(acc[i % MT][nt], af[i % 4], b[nt][i / MT]);
+      if (i + 3 < NI) af[(i + 3) % 4] = read_af(i + 3);
+      if (i % MT == MT - 1) load_b_step(c + 1, i / MT);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, NT, 0);                          // NT matrix-core instructions
+      if (i + 3 < NI) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);           // one LDS read
+      if (i % MT == MT - 1) __builtin_amdgcn_sched_group_barrier(0x020, NT, 0);    // the k-step's refill
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // the next chunk is in LDS once all but the weight refills requested behind its staging has arrived
+    constexpr int kVm = 4 * NT;
+    __builtin_amdgcn_s_waitcnt((kVm & 15) | ((kVm >> 4) << 14) | 0x70 | 0xf00);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __builtin_amdgcn_s_waitcnt(0x70 | 0xf00);                  // no staging may write LDS after the workgroup has left
+
+  if constexpr (MODE == kPreSwiglu) {
+    // column tiles alternate gate, up, gate, up ..
+    const int F = N >> 1, first = n_base >> 4;                // first column tile of the wave
+    auto put = [&](int pair, int mt, const f32x4& gate, const f32x4& up) {
+      const int col = pair * 16 + r;
+      if (col >= F) return;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = row0 + mt * 16 + g * 4 + j;
+        if (row < m) act[(size_t)row * F + col] = (bf16)gated(gate[j], up[j]);
+      }
+    };
+    if constexpr (NT % 2 == 0) {                              // every pair sits in one wave
+#pragma unroll
+      for (int p = 0; p < NT / 2; ++p)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) put((first >> 1) + p, mt, acc[mt][2 * p], acc[mt][2 * p + 1]);
+    } else {
+      // three tiles: an even quarter holds (gate, up) and the gate of a pair whose up tile is its neighbour's first, which
+      // comes over through LDS (idle now); the neighbour's other two tiles are a pair of their own
+      f32x4* xch = reinterpret_cast<f32x4*>(lds) + (part * 2 + (quarter >> 1)) * (MT * 64);      // [MT][64]
+      __syncthreads();
+      if (quarter & 1) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) xch[mt * 64 + lane] = acc[mt][0];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        if (quarter & 1) {
+          put((first + 1) >> 1, mt, acc[mt][1], acc[mt][2]);
+        } else {
+          put(first >> 1, mt, acc[mt][0], acc[mt][1]);
+          put((first >> 1) + 1, mt, acc[mt][2], xch[mt * 64 + lane]);
+        }
+      }
+    }
+    return;
+  }
+  float* out = P + (size_t)by * split_stride;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const int col = n_base + nt * 16 + r;
+      if (col >= N) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = row0 + mt * 16 + g * 4 + j;
+        if (row < m) out[(size_t)row * ldp + col] = acc[mt][nt][j];
+      }
+    }
+}
+
+template <int MT, int NT, int MODE>
+hipError_t launch_wide_t(const GemmPlan& pl, int pairs, const void* A, int lda, const void* W, int ldw, float* P, int ldp,
+                         size_t split_stride, int m, int N, int K, hipStream_t st, void* act) {
+  const int n_blocks = (N + 64 * NT - 1) / (64 * NT);
+  const int groups = (n_blocks * pl.splits + 7) / 8;            // weight tiles are dealt to the XCDs in groups of 8
+  const int rows_st = pairs < kSuperRows ? pairs : kSuperRows;
+  const int cols_st = 32 / rows_st;
+  const dim3 grid(8 * ((groups + cols_st - 1) / cols_st) * ((pairs + rows_st - 1) / rows_st) * (rows_st * cols_st));
+  hipLaunchKernelGGL((gemm_wide_kernel<MT, NT, MODE>), grid, dim3(512), 0, st, (const bf16*)A, lda, (const bf16*)W, ldw, P,
+                     ldp, split_stride, m, N, K, pl.k_per_split, n_blocks, pl.splits, pairs, (bf16*)act);
+  return hipGetLastError();
+}
+// The row tiles are dealt evenly to the row chunks of all pairs (an odd count of chunks leaves no empty half).
+inline int wide_row_tiles(int m, int pairs) { return std::max(5, ((m + 15) / 16 + 2 * pairs - 1) / (2 * pairs)); }
+template <int MODE>
+hipError_t launch_wide(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp,
+                       size_t split_stride, int m, int N, int K, hipStream_t st, void* act) {
+  const int pairs = (pl.row_chunks + 1) / 2, mt = wide_row_tiles(m, pairs);
+#define D2C_WIDE(mt_)                                                                                                        \
+  if (mt == mt_)                                                                                                             \
+    return pl.wide_cols == 192                                                                                               \
+               ? launch_wide_t<mt_, 3, MODE>(pl, pairs, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, act)              \
+               : launch_wide_t<mt_, 4, MODE>(pl, pairs, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, act)
+  D2C_WIDE(5); D2C_WIDE(6); D2C_WIDE(7); D2C_WIDE(8);
+#undef D2C_WIDE
+  return hipErrorInvalidValue;
+}
+
 template <typename T, int MT, int NT, int WAVES, int MODE>
 hipError_t launch_t(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp,
                     size_t split_stride, int m, int N, int K, hipStream_t st, void* act) {
@@ -333,9 +486,6 @@ hipError_t launch_t(const GemmPlan& pl, const void* A, int lda, const void* W, i
   const int n_blocks = (N + cols - 1) / cols;
   const int groups = (n_blocks * pl.splits + 7) / 8;            // weight tiles are dealt to the XCDs in groups of 8
   dim3 grid(groups * 8 * pl.row_chunks);
-  if (NT >= 4)
-    grid.x = 8 * ((groups + kSuperCols - 1) / kSuperCols) * ((pl.row_chunks + kSuperRows - 1) / kSuperRows) *
-             (kSuperRows * kSuperCols);
   hipLaunchKernelGGL((gemm_rows_kernel<T, MT, NT, WAVES, MODE>), grid, dim3(WAVES * 64), 0, st, (const T*)A, lda,
                      (const T*)W, ldw, P, ldp, split_stride, m, N, K, pl.k_per_split, n_blocks, pl.splits,
                      pl.row_chunks, pl.rot, (T*)act);
@@ -380,15 +530,18 @@ hipError_t launch_nt(const GemmPlan& pl, const void* A, int lda, const void* W, 
     }
     return launch_mt<T, 1, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
   }
-  if (pl.nt == 4) {
-    // 128 rows x 64 columns per wave, one wave per SIMD: only for full row chunks in bf16
+  if (pl.wide_cols != 0) {
     if constexpr (sizeof(T) == 2) {
-      const int kc = 256 / (int)sizeof(T);
-      if (pl.waves == 4 && K % kc == 0 && pl.k_per_split % (2 * kc) == 0 && K % (2 * kc) == 0) {
-        if (pl.mt == 8) return launch_t<T, 8, 4, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
-        if (pl.mt == 7) return launch_t<T, 7, 4, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
-        if (pl.mt == 6) return launch_t<T, 6, 4, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
-      }
+      if (K % 128 || pl.k_per_split % 128) return hipErrorInvalidValue;
+      // the staging wants whole 16-byte pieces and 32-bit offsets: other callers' buffers go through registers
+      if ((uintptr_t)A % 16 == 0 && (size_t)m * lda * 2 < (1ull << 32))
+        return launch_wide<MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
+      GemmPlan other = pl;
+      other.nt = 2;
+      other.waves = 8;
+      other.mt = 8;
+      other.row_chunks = (m + 127) / 128;
+      return launch_mt<T, 2, 8, MODE>(other, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
     }
     return hipErrorInvalidValue;
   }
@@ -435,8 +588,8 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   // two column tiles per wave halve the LDS reads per matrix-core step: a gain once there are several
   // row chunks (the kernel is LDS- and L2-bound there), a loss for a handful of rows (fewer waves in flight)
   pl.nt = (N > t.gemm_nt_big_n || pl.row_chunks > 1) ? 2 : 1;
-  // several row chunks in bf16: four column tiles per wave and one wave per SIMD (128 x 64 outputs per wave)
-  // halve the LDS reads per matrix-core step once more
+  // several row chunks in bf16: gemm_wide_kernel, 128 x 64 outputs per wave; 4 waves per row chunk, and two row chunks
+  // to a workgroup
   const bool wide = pl.row_chunks > 1 && m >= t.gemm_wide_min_rows && dtype == kBF16 && t.gemm_wide_tiles &&
                     K % 256 == 0;                       // needs an even number of whole chunks
   if (wide) pl.nt = 4;
@@ -510,27 +663,40 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
     pl.mt = mt;
     pl.row_chunks = (tiles + mt - 1) / mt;
   }
-  if (wide && !single_split) {
-    // the same count of rounds, with +7 % per additional split (the partials are as large as the output and
-    // there are hundreds of rows of them)
+  pl.wide_cols = 0;
+  if (wide) {
+    // Columns per workgroup and splits by a time model in us, a workgroup taking two row chunks: a chunk of k costs a
+    // row tile 0.35 us with 256 columns and 0.8 of that with 192 (measured, 512 rows: 105 us for gate/up as 192 workgroups
+    // of 256 columns, 93 as 256 of 192: what counts is full rounds over the 256 units), and every split writes and
+    // reads m x N partial sums at about 8 TB/s.  Any count of splits: Dream's QKV at 768 rows runs 3.
+    const int pairs = (pl.row_chunks + 1) / 2;
+    const double chunk_us = 0.35 * wide_row_tiles(m, pairs), split_us = single_split ? 0.0 : (double)m * N * 8e-6 / 8.0;
     double best = 1e30;
-    for (int s = 1; s <= max_splits; s *= 2) {
-      int cps = (chunks + s - 1) / s;
-      cps += cps & 1;                                             // the wide loop takes chunks in pairs
-      if (s > 1 && cps < 4) break;
-      const int eff = (chunks + cps - 1) / cps;
-      const int wgs = blocks_of(pl.waves) * pl.row_chunks * eff;
-      const double cost = (double)((wgs + kUnits - 1) / kUnits) * cps * (1.0 + 0.07 * (eff - 1));
-      if (cost < best * 0.999) {
-        best = cost;
-        splits = s;
+    for (int cols : {256, 192})
+      for (int s = 1; s <= max_splits; ++s) {
+        int cps = (chunks + s - 1) / s;
+        cps += cps & 1;                                           // splits start on pairs of chunks
+        if (s > 1 && cps < 4) break;
+        const int eff = (chunks + cps - 1) / cps;
+        const int wgs = ((N + cols - 1) / cols) * pairs * eff;
+        const double cost = (double)((wgs + kUnits - 1) / kUnits) * cps * chunk_us * (cols == 192 ? 0.8 : 1.0) + split_us * eff;
+        if (cost < best * 0.999) {
+          best = cost;
+          splits = s;
+          pl.wide_cols = cols;
+        }
       }
-    }
   }
   int chunks_per_split = (chunks + splits - 1) / splits;
   if (wide) chunks_per_split += chunks_per_split & 1;
   pl.k_per_split = chunks_per_split * kc;
   pl.splits = (K + pl.k_per_split - 1) / pl.k_per_split;
+  // Two row chunks (193-256 rows) are one workgroup of the wide kernel as well: where that fills the chip (the head on all
+  // masked rows of a first step, 256 rows x 126464 columns: 374 -> 317 us), not for a block's matrices (96 column
+  // blocks at most).
+  if (!wide && dtype == kBF16 && pl.nt == 2 && pl.row_chunks == 2 && t.gemm_wide_tiles && K % kc == 0 &&
+      ((N + 255) / 256) * pl.splits >= 3 * kUnits / 4)
+    pl.wide_cols = 256;
   return pl;
 }
 

@@ -17,7 +17,7 @@ struct Tunables {
   int gemm_max_splits = 8;
   int gemm_wide_min_rows = 257; // the wide instantiation from this many rows on (3 row chunks)
   int gemm_tall_chunk = 1;      // 129-192 bf16 rows as ONE row chunk of 10 or 12 row tiles
-  int gemm_wide_tiles = 1;     // more than 128 rows in bf16: 128 x 64 outputs per wave, 4 waves per workgroup
+  int gemm_wide_tiles = 1;     // many bf16 rows: gemm_wide_kernel, 128 x 64 outputs per wave, two row chunks per workgroup
   int gemm_wide_mt = 0;        // row tiles per workgroup of the wide instantiation: 6, 7, 8; 0 = by shape
   int gemm_nt_big_n = 1 << 30; // N above this uses two column tiles per wave even for few rows (measured slower);
                                // more than 128 rows always do
@@ -44,6 +44,7 @@ struct GemmPlan {
   int k_per_split;
   int row_chunks;
   int rot;       // multiplier of the per-workgroup start-chunk rotation (0 = none)
+  int wide_cols; // 256 or 192: gemm_wide_kernel with so many columns per workgroup, which takes two row chunks; 0 = the others
 };
 GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split = false);
 // P must hold plan.splits * split_stride floats; split_stride >= m * ldp.

@@ -621,3 +621,35 @@ def test_rollout_update_and_influence_at_the_size_rules(B, L, m):
         prev = r
     np.testing.assert_allclose(host(c), outside + prev.sum(0), rtol=1e-5)
     ctx.close()
+
+
+@pytest.mark.parametrize("m,N,K", [(257, 40, 256), (289, 1000, 512), (385, 264, 768), (513, 256, 2304), (777, 72, 256), (1153, 520, 512)])
+def test_linear_parity_many_rows(B, m, N, K):
+    """Two row chunks per workgroup: odd counts of chunks, 5 to 8 row tiles, ragged rows and columns, one chunk pair of k."""
+    test_linear_parity(B, "bf16", m, N, K)
+
+
+@pytest.mark.parametrize("m", [257, 300, 449])
+def test_refresh_layer_parity_many_rows(B, m):
+    """The same with pre-tiled weights and the gated epilogue; widths that leave the last column block ragged."""
+    _refresh_layer_parity(B, f"bf16-{m}-rows", W.ModelDims(1, 512, 4, 4, 128, 1280, 64, dtype="bf16"), m + 30, m)
+
+
+def test_linear_many_rows_unaligned(B):
+    """Activations that are not 16-byte aligned cannot be staged straight into LDS: the same result by another kernel, up
+    to summation order in fp32 (K = 512: relative 512 * 6e-8)."""
+    m, N, K = 300, 520, 512
+    say("linear many rows, unaligned activations")
+    wd = W.ModelDims(1, 512, 4, 4, 128, 512, 64, dtype="bf16")
+    ctx, _, _ = _ctx_for(B, wd, max_seq=m)
+    a0, w = (torch.from_numpy(W.round_bf16(W.hidden_rows(s, r, K))).to(torch.bfloat16).cuda() for s, r in ((1, m), (2, N)))
+    got = []
+    for off in (0, 1):
+        a = torch.zeros(m * K + 8, dtype=torch.bfloat16, device="cuda")[off: off + m * K].view(m, K)
+        a.copy_(a0)
+        out = torch.zeros((m, N), device="cuda")
+        ctx.d2c_linear(a, w, m, N, K, out)
+        torch.cuda.synchronize()
+        got.append(host(out))
+    assert rel_l2(got[1], got[0]) < 3e-5
+    ctx.close()
