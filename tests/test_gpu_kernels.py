@@ -653,3 +653,27 @@ def test_linear_many_rows_unaligned(B):
         got.append(host(out))
     assert rel_l2(got[1], got[0]) < 3e-5
     ctx.close()
+
+
+@pytest.mark.parametrize("H,Hkv,dh,L,m", [(8, 8, 128, 1, 1), (8, 2, 128, 33, 15), (32, 32, 128, 513, 17), (28, 4, 128, 1025, 47),
+                                          (4, 4, 64, 511, 16), (40, 8, 128, 1024, 120)])
+def test_attention_parity_staged_rows(B, H, Hkv, dh, L, m):
+    """The few-row kernel with K and Q staged through LDS: one key, ragged pairs, waves without a pair, both widths of the
+    output share; and the same values with a K cache that is not 16-byte aligned (loads in operand order), bit for bit."""
+    say(f"attention staged H={H} Hkv={Hkv} dh={dh} L={L} m={m}")
+    _attention_parity(B, "bf16", H, Hkv, dh, L, m, tunables={"attn_tiled_min_m": 1 << 30})
+    wd = W.ModelDims(1, H * dh, H, Hkv, dh, 64, 64, dtype="bf16")
+    ctx, _, _ = _ctx_for(B, wd, max_seq=L, tunables={"attn_tiled_min_m": 1 << 30})
+    case = W.attention_case(1, H, Hkv, dh, L, m, dtype="bf16")
+    idx = torch.from_numpy(case["idx"]).cuda()
+    got = []
+    for off in (0, 1):
+        kc = torch.zeros(L * Hkv * dh + 8, dtype=torch.bfloat16, device="cuda")[off: off + L * Hkv * dh].view(L, Hkv * dh)
+        kc.copy_(B.to_device(case["k_cache"], "bf16"))
+        q, vc = B.to_device(case["q"], "bf16"), B.to_device(case["v_cache"], "bf16")
+        out = torch.zeros_like(q)
+        ctx.d2c_attention(q, idx, m, None, None, kc, vc, L, out, None)
+        torch.cuda.synchronize()
+        got.append(out)
+    assert torch.equal(got[0], got[1])
+    ctx.close()
