@@ -193,10 +193,14 @@ __global__ __launch_bounds__(kFwdThreads) void attn_fwd_bf16_kernel(
     const size_t off = ((size_t)min(row_first + row, row_last) * pitch + col + (size_t)(s_piece ^ (row & 7)) * 8) * 2;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(dst + i * 1024), 16, (int)off, 0, 0, 0);
   };
-  auto staged_frag = [&](const unsigned char* rows, int row, int s) {
-    Frag<bf16> f;
-    f.raw = *reinterpret_cast<const u32x4*>(rows + row * (DH * 2) + ((s * 4 + g) ^ (row & 7)) * 16);
-    return f;
+  auto staged_frags = [&](Frag<bf16> (&f)[NS], const unsigned char* rows, int row) {
+    const uint32_t base = lds_address(rows) + (uint32_t)(row * (DH * 2));
+    auto at = [&](int s) { return base + (uint32_t)(((s * 4 + g) ^ (row & 7)) * 16); };
+    u32x4 v[NS];
+    if constexpr (NS == 4) lds_read_staged(v, at(0), at(1), at(2), at(3));
+    else lds_read_staged(v, at(0), at(1));
+#pragma unroll
+    for (int s = 0; s < NS; ++s) f[s].raw = v[s];
   };
   Frag<bf16> qf[NS];
   if constexpr (STAGED) {
@@ -218,17 +222,18 @@ __global__ __launch_bounds__(kFwdThreads) void attn_fwd_bf16_kernel(
   // S^T of both tiles, one online-softmax update for the 32 keys, then O^T += V^T P^T with K = 32:
   // contraction slot (g, j) of the matrix-core step stands for key 16*(j/4) + 4g + j%4 of the pair, which
   // is how the two accumulators of S^T hold the probabilities, so P never leaves registers.
-  auto consume = [&](const KvPair<DH, NB>& t, const unsigned char* k_rows, int key0, f32x4* keep) {
+  auto consume = [&](KvPair<DH, NB>& t, const unsigned char* k_rows, int key0, f32x4* keep) {
+    if constexpr (STAGED) {
+      staged_frags(t.k[0], k_rows, r);
+      staged_frags(t.k[1], k_rows, 16 + r);
+    }
     float x[2][4];
     float tmax = -INFINITY;
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
       f32x4 st = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        if constexpr (STAGED) mfma16(st, staged_frag(k_rows, a * 16 + r, s), qf[s]);
-        else mfma16(st, t.k[a][s], qf[s]);
-      }
+      for (int s = 0; s < NS; ++s) mfma16(st, t.k[a][s], qf[s]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         x[a][j] = (key0 + a * 16 + 4 * g + j < L) ? st[j] * scale : -INFINITY;
@@ -312,8 +317,7 @@ __global__ __launch_bounds__(kFwdThreads) void attn_fwd_bf16_kernel(
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-#pragma unroll
-    for (int s = 0; s < NS; ++s) qf[s] = staged_frag(q_stage, r, s);
+    staged_frags(qf, q_stage, r);
   }
   f32x4 kept[KEEP > 0 ? 4 * KEEP : 1];
   if constexpr (KEEP > 0) {

@@ -57,6 +57,27 @@ __device__ __forceinline__ void mfma16(f32x4& acc, const Frag<float>& a, const F
 __device__ __forceinline__ u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
 __device__ __forceinline__ u32x2 ld8(const void* p) { return *reinterpret_cast<const u32x2*>(p); }
 
+// 32-bit LDS address of a shared object.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+// Operand reads of rows that were staged with buffer loads into LDS, together with their wait.  As plain loads the compiler
+// puts a wait for EVERY outstanding staging in front of them (it cannot tell the slots apart), which empties the queue
+// that the kernel wants to keep full; the kernel waits for the rows it needs by itself.
+__device__ __forceinline__ void lds_read_staged(u32x4 (&v)[4], uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+  asm volatile(
+      "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+      : "v"(a0), "v"(a1), "v"(a2), "v"(a3)
+      : "memory");
+}
+__device__ __forceinline__ void lds_read_staged(u32x4 (&v)[2], uint32_t a0, uint32_t a1) {
+  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(v[0]), "=&v"(v[1])
+               : "v"(a0), "v"(a1)
+               : "memory");
+}
+
 // Full-wave reductions in a fixed order (xor butterfly): every lane ends with
 // the same value, and the same inputs always give the same bits.
 __device__ __forceinline__ float wave_sum(float v) {

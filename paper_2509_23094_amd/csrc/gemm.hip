@@ -37,7 +37,14 @@ constexpr int kSuperRows = 8, kSuperCols = 4;    // many rows: block of workgrou
 // RING = number of weight chunks a wave keeps in registers (one being consumed, RING-1 in flight).
 // MODE: 0 = W row-major [N, K]; 1 = W pre-tiled; 2 = W pre-tiled with gate and up tiles interleaved and the
 // SwiGLU applied in the epilogue (single k split, one column tile per wave): act[m, N/2] = T(silu(g) * u).
-enum { kRowMajor = 0, kPre = 1, kPreSwiglu = 2 };
+// 3 = W row-major, its rows staged through LDS (16-byte aligned rows, one column tile per wave, where LDS holds it).
+enum { kRowMajor = 0, kPre = 1, kPreSwiglu = 2, kRowStaged = 3 };
+// weight chunks of a wave in LDS, one in use and the others on their way: 3, or 2 where three do not fit; 0 = neither
+template <int MT, int NT, int WAVES>
+constexpr int kStageSlots = NT != 1 ? 0
+                            : 2 * MT * 16 * kRowStride + WAVES * 3 * 16 * kChunkBytes <= 160 * 1024 ? 3
+                            : 2 * MT * 16 * kRowStride + WAVES * 2 * 16 * kChunkBytes <= 160 * 1024 ? 2
+                                                                                                     : 0;
 
 // silu(g) * u on the exponential and reciprocal units (each within one unit in the last place in 32 bits; the result is
 // rounded to T): with a library exponential and a division the epilogue of 256 rows x 256 columns took about 7 us
@@ -50,7 +57,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
     const T* __restrict__ A, int lda, const T* __restrict__ W, int ldw, float* __restrict__ P, int ldp,
     size_t split_stride, int m, int N, int K, int k_per_split, int n_blocks, int n_splits, int row_chunks, int rot_mul,
     T* __restrict__ act) {
-  constexpr bool PRE = MODE != kRowMajor;
+  constexpr bool PRE = MODE == kPre || MODE == kPreSwiglu, STAGED = MODE == kRowStaged;
+  static_assert(!STAGED || kStageSlots<MT, NT, WAVES> != 0, "staged weights must fit LDS");
   static_assert(MODE != kPreSwiglu || NT % 2 == 0 || WAVES % 2 == 0, "the SwiGLU epilogue pairs neighbouring waves");
   constexpr int RING = 2;
   constexpr int kThreads = WAVES * 64;
@@ -159,6 +167,95 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
   };
 
   if (n_chunks <= 0) return;
+  if constexpr (STAGED) {
+    // Row-major weights in operand order (lane = row) cost the L1, which merges only what consecutive lanes ask for, 64
+    // accesses an instruction.  A wave therefore brings its 16 rows straight into LDS, four whole 256-byte row pieces an
+    // instruction, up to two chunks ahead, and reads its operands there (the 16-byte pieces of a row are xored with its number:
+    // eight lanes of a read touch different banks).  Nobody else reads them: no barrier, but the wave's own wait.
+    // LLaDA shapes: the head on 17 rows (126464 x 4096) 242 -> 210 us, gate/up on 46 rows 49 -> 40, QKV 32 -> 27.
+    constexpr int SL = kStageSlots<MT, NT, WAVES>;
+    __shared__ __attribute__((aligned(16))) unsigned char wst[WAVES * SL * 16 * kChunkBytes];
+    unsigned char* const mine = wst + __builtin_amdgcn_readfirstlane(wave) * (SL * 16 * kChunkBytes);
+    const int first = min(__builtin_amdgcn_readfirstlane(n_base), N - 1), rows_left = N - 1 - first;
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<T*>(W) + (size_t)first * ldw, 0, (int)(((size_t)min(15, rows_left) * ldw + K) * sizeof(T)), 0x00020000);
+    int roff[4], poff[4];                                  // instruction i: row 4 i + lane / 16, its piece of the chunk
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = i * 4 + (lane >> 4);
+      roff[i] = (int)(min(row, rows_left) * (size_t)ldw * sizeof(T));
+      poff[i] = ((lane & 15) ^ (row & 7)) * E;
+    }
+    const uint32_t mine_at = lds_address(mine);
+    uint32_t woff[kSteps];                                 // this lane's operand of step s inside a slot
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) woff[s] = (uint32_t)(r * kChunkBytes + ((s * 4 + g) ^ (r & 7)) * 16);
+    auto stage_w = [&](int chunk, int slot) {
+      const int kc = chunk_k(chunk);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)                          // pieces past the end repeat the last one and meet zeros
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            wrsrc, (__attribute__((address_space(3))) void*)(mine + slot * (16 * kChunkBytes) + i * 1024), 16,
+            roff[i] + min(kc + poff[i], k_end - E) * (int)sizeof(T), 0, 0, 2 /* streaming */);
+    };
+    auto fence = [] {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    load_a(areg[0], 0);
+    fence();
+    stage_w(0, 0);
+    fence();
+    load_a(areg[1], 1);
+    fence();
+#pragma unroll
+    for (int p = 1; p + 1 < SL; ++p) stage_w(p, p);
+    fence();
+    store_a(areg[0], 0);
+    __syncthreads();
+    int slot = 0;
+    for (int base = 0; base < n_chunks; base += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int c = base + u;
+        const int refill = slot == 0 ? SL - 1 : slot - 1;  // consumed by the iteration before
+        load_a(areg[u & 1], c + 2);
+        fence();
+        stage_w(c + SL - 1, refill);
+        fence();
+        // this chunk's rows have arrived: requested behind them were SL - 1 stagings and as many activation chunks
+        constexpr int kVm = (SL - 1) * (AI + 4);
+        static_assert(kVm < 64, "vmcnt has 6 bits");
+        __builtin_amdgcn_s_waitcnt((kVm & 15) | ((kVm >> 4) << 14) | 0x70 | 0xf00);
+        fence();
+        const unsigned char* abuf = lds[u & 1];
+        const uint32_t wbuf = mine_at + (uint32_t)(slot * (16 * kChunkBytes));
+        const int kc = chunk_k(c);
+        u32x4 wv[kSteps];
+        lds_read_staged(wv, wbuf + woff[0], wbuf + woff[1], wbuf + woff[2], wbuf + woff[3]);
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+          const unsigned keep = (c < n_chunks && kc + s * KS + g * E < k_end) ? 0xffffffffu : 0u;
+          Frag<T> bf;
+          bf.raw = wv[s] & u32x4{keep, keep, keep, keep};
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            Frag<T> af;
+            af.raw = *reinterpret_cast<const u32x4*>(&abuf[(mt * 16 + r) * kRowStride + (s * 4 + g) * 16]);
+            mfma16(acc[mt][0], af, bf);
+          }
+        }
+        fence();
+        store_a(areg[(u + 1) & 1], (u + 1) & 1);
+        __builtin_amdgcn_s_waitcnt(0xc07f);                // lgkmcnt(0): the stores; what is on its way stays so
+        fence();
+        __builtin_amdgcn_s_barrier();
+        fence();
+        slot = slot == SL - 1 ? 0 : slot + 1;
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0x70 | 0xf00);              // no staging may write LDS after the workgroup has left
+  } else {
   // prologue: weight chunks 0..PB-1 and activation chunks 0, 1 are requested; chunk 0 reaches LDS
 #pragma unroll
   for (int u = 0; u < PB; ++u) load_b(breg[u], u);
@@ -200,6 +297,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
       __syncthreads();
     }
   }
+  }   // weights through registers
 
   if (MODE == kPreSwiglu && NT % 2 == 0) {
     // Column tiles alternate gate, up, gate, up ..: with an even number of tiles per wave each pair sits in one wave
@@ -486,6 +584,9 @@ hipError_t launch_t(const GemmPlan& pl, const void* A, int lda, const void* W, i
   const int n_blocks = (N + cols - 1) / cols;
   const int groups = (n_blocks * pl.splits + 7) / 8;            // weight tiles are dealt to the XCDs in groups of 8
   dim3 grid(groups * 8 * pl.row_chunks);
+  if constexpr (MODE == kRowStaged && kStageSlots<MT, NT, WAVES> == 0)
+    return launch_t<T, MT, NT, WAVES, kRowMajor>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, act);
+  else
   hipLaunchKernelGGL((gemm_rows_kernel<T, MT, NT, WAVES, MODE>), grid, dim3(WAVES * 64), 0, st, (const T*)A, lda,
                      (const T*)W, ldw, P, ldp, split_stride, m, N, K, pl.k_per_split, n_blocks, pl.splits,
                      pl.row_chunks, pl.rot, (T*)act);
@@ -547,6 +648,18 @@ hipError_t launch_nt(const GemmPlan& pl, const void* A, int lda, const void* W, 
   }
   if (pl.waves == 8) return launch_mt<T, 2, 8, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
   return launch_mt<T, 2, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
+}
+
+template <typename T>
+hipError_t launch_rows_staged(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp, size_t ss,
+                              int m, int N, int K, hipStream_t st) {
+  switch (pl.waves) {
+    case 6: return launch_mt<T, 1, 6, kRowStaged>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, nullptr);
+    case 7: return launch_mt<T, 1, 7, kRowStaged>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, nullptr);
+    case 8: return launch_mt<T, 1, 8, kRowStaged>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, nullptr);
+    case 10: return launch_mt<T, 1, 10, kRowStaged>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, nullptr);
+    default: return launch_mt<T, 1, 4, kRowStaged>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, nullptr);
+  }
 }
 
 // One 16-byte fragment per thread: dst block (tile t, chunk c) slot (step s, lane) <- src row
@@ -668,9 +781,9 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
     // Columns per workgroup and splits by a time model in us, a workgroup taking two row chunks: a chunk of k costs a
     // row tile 0.35 us with 256 columns and 0.8 of that with 192 (measured, 512 rows: 105 us for gate/up as 192 workgroups
     // of 256 columns, 93 as 256 of 192: what counts is full rounds over the 256 units), and every split writes and
-    // reads m x N partial sums at about 8 TB/s.  Any count of splits: Dream's QKV at 768 rows runs 3.
+    // reads m x N partial sums at about 5.5 TB/s.  Any count of splits: Dream's QKV at 768 rows runs 3.
     const int pairs = (pl.row_chunks + 1) / 2;
-    const double chunk_us = 0.35 * wide_row_tiles(m, pairs), split_us = single_split ? 0.0 : (double)m * N * 8e-6 / 8.0;
+    const double chunk_us = 0.35 * wide_row_tiles(m, pairs), split_us = single_split ? 0.0 : (double)m * N * 8e-6 / 5.5;
     double best = 1e30;
     for (int cols : {256, 192})
       for (int s = 1; s <= max_splits; ++s) {
@@ -715,6 +828,11 @@ hipError_t launch_gemm(int dtype, const GemmPlan& pl, const void* A, int lda, co
     if (dtype == kBF16)
       return launch_nt<bf16, kPre>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);
     return launch_nt<float, kPre>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);
+  }
+  if (pl.wide_cols == 0 && pl.nt == 1 && (uintptr_t)W % 16 == 0 && (size_t)ldw * dtype_size(dtype) * 16 < (1ull << 31)) {
+    if (dtype == kBF16)
+      return launch_rows_staged<bf16>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st);
+    return launch_rows_staged<float>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st);
   }
   if (dtype == kBF16)
     return launch_nt<bf16, kRowMajor>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);

@@ -677,3 +677,28 @@ def test_attention_parity_staged_rows(B, H, Hkv, dh, L, m):
         got.append(out)
     assert torch.equal(got[0], got[1])
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,m,N,K", [("bf16", 1, 16, 128), ("bf16", 97, 1007, 1160), ("bf16", 113, 2600, 392), ("bf16", 145, 333, 1032),
+                                         ("f32", 33, 257, 68), ("f32", 120, 1000, 516)])
+def test_linear_parity_staged_weights(B, dtype, m, N, K):
+    """Row-major weights staged through LDS: ragged last chunk and last rows, three slots, two slots (many rows, 10 waves) and
+    none; and weights that are not 16-byte aligned, which take the loads in operand order: the same bits."""
+    test_linear_parity(B, dtype, m, N, K)
+    if dtype == "bf16":
+        test_linear_parity(B, dtype, m, N, K, tunables={"gemm_waves": 10})
+    wd = W.ModelDims(1, 128, 2, 2, 64, 128, 64, dtype=dtype)
+    ctx, _, _ = _ctx_for(B, wd, max_seq=m)
+    t = B.torch_dtype(dtype)
+    a = B.to_device(W.round_bf16(W.hidden_rows(1, m, K)), dtype)
+    w0 = B.to_device(W.round_bf16(W.hidden_rows(2, N, K)), dtype)
+    got = []
+    for off in (0, 1):
+        w = torch.zeros(N * K + 8, dtype=t, device="cuda")[off: off + N * K].view(N, K)
+        w.copy_(w0)
+        out = torch.zeros((m, N), device="cuda")
+        ctx.d2c_linear(a, w, m, N, K, out)
+        torch.cuda.synchronize()
+        got.append(out)
+    assert torch.equal(got[0], got[1])
+    ctx.close()
