@@ -445,7 +445,7 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const bf16* __restr
 // sums are added in a fixed order through LDS.
 __device__ __forceinline__ float exp_of(const bf16*, float x) { return __expf(x); }
 __device__ __forceinline__ float exp_of(const float*, float x) { return expf(x); }
-template <typename T, int DH>
+template <typename T, int DH, bool STAGED>
 __global__ __launch_bounds__(kThreads) void attn_avg_kernel(const T* __restrict__ q, const T* __restrict__ k_cache,
                                                             const float* __restrict__ lse, int m, int L, int n_heads,
                                                             int n_kv_heads, float scale,
@@ -474,6 +474,69 @@ __global__ __launch_bounds__(kThreads) void attn_avg_kernel(const T* __restrict_
     e = lse[(size_t)head * m + row];
   };
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  // STAGED (bf16, 16-byte aligned rows; the offsets of a buffer load have 31 bits): as in the forward kernel, a wave brings the
+  // 16 rows of Q and of K of a head into LDS in whole pieces and reads its operands there, while the next head's rows are on
+  // their way: loads in operand order (lane = row) cost the L1 64 accesses an instruction, which bounded this pass.  Forward
+  // plus this pass, 32 heads of 128: 40 queries x 2048 keys 34.3 -> 27.6 us, 46 x 512 17.9 -> 15.2; 28 heads over 4 of K,
+  // 83 x 768 28.4 -> 20.8.  Bound now by the latency of a head's turn with two workgroups (68 KB each) on a CU.
+  constexpr int kTile = STAGED ? 16 * DH * 2 : 16, kDma = kTile / 1024;
+  __shared__ __attribute__((aligned(16))) unsigned char stage[kWaves * 2 * 2 * kTile];      // [wave][slot][Q, K]
+  if constexpr (STAGED) {
+    constexpr int kRows = 1024 / (DH * 2), kPieces = 64 / kRows;
+    unsigned char* const mine = stage + __builtin_amdgcn_readfirstlane(wave) * (4 * kTile);
+    const __amdgpu_buffer_rsrc_t q_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(q), 0, (int)((size_t)m * dq * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t k_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(k_cache), 0, (int)((size_t)L * kv_pitch * 2), 0x00020000);
+    int qoff[4], koff[4];                                   // kDma of them are used
+#pragma unroll
+    for (int i = 0; i < kDma; ++i) {
+      const int rr = i * kRows + lane / kPieces, piece = (lane % kPieces) ^ (rr & 7);
+      qoff[i] = (int)(((size_t)min(q0 + rr, m - 1) * dq + piece * 8) * 2);
+      koff[i] = (int)(((size_t)min(key0 + rr, L - 1) * kv_pitch + piece * 8) * 2);
+    }
+    auto request = [&](int head, int slot) -> float {       // past the last head: the last one again, not used
+      const int hd = min(head, n_heads - 1);
+      const float e = lse[(size_t)hd * m + row];
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < kDma; ++i) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            q_rsrc, (__attribute__((address_space(3))) void*)(mine + slot * 2 * kTile + i * 1024), 16, qoff[i], hd * DH * 2, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            k_rsrc, (__attribute__((address_space(3))) void*)(mine + slot * 2 * kTile + kTile + i * 1024), 16, koff[i],
+            (hd / group) * DH * 2, 0, 0);
+      }
+      asm volatile("" ::: "memory");
+      return e;
+    };
+    const uint32_t base = lds_address(mine) + (uint32_t)(r * (DH * 2));
+    auto read = [&](Frag<T> (&f)[NS], uint32_t at) {
+      auto piece = [&](int s) { return at + (uint32_t)(((s * 4 + g) ^ (r & 7)) * 16); };
+      u32x4 v[NS];
+      if constexpr (NS == 4) lds_read_staged(v, piece(0), piece(1), piece(2), piece(3));
+      else lds_read_staged(v, piece(0), piece(1));
+#pragma unroll
+      for (int s = 0; s < NS; ++s) f[s].raw = v[s];
+    };
+    float e = request(wave, 0);
+    int slot = 0;
+    for (int h = wave; h < n_heads; h += kWaves, slot ^= 1) {
+      const float en = request(h + kWaves, slot ^ 1);
+      __builtin_amdgcn_s_waitcnt(2 * kDma | 0x70 | 0xf00);   // all but the next head's rows
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      Frag<T> qf[NS], kf[NS];
+      read(qf, base + (uint32_t)(slot * 2 * kTile));
+      read(kf, base + (uint32_t)(slot * 2 * kTile + kTile));
+      f32x4 st = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < NS; ++s) mfma16(st, kf[s], qf[s]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] += exp_of(q, st[j] * scale - e);
+      e = en;
+    }
+    __builtin_amdgcn_s_waitcnt(0x70 | 0xf00);                // nothing is staged behind the workgroup's end
+  } else {
   auto consume = [&](const Frag<T> (&qf)[NS], const Frag<T> (&kf)[NS], float e) {
     f32x4 st = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -494,6 +557,7 @@ __global__ __launch_bounds__(kThreads) void attn_avg_kernel(const T* __restrict_
     if (h2 < n_heads) load_head(qa, ka, ea, h2);
     consume(qb, kb, eb);
     h = h2;
+  }
   }
   part[wave][lane] = acc;
   __syncthreads();
@@ -756,7 +820,15 @@ hipError_t launch_avg(const void* q, const void* k_cache, const float* lse, int 
                       int n_kv_heads, float* attn_avg, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)DH);
   const int key_blocks = (L + 15) / 16;
-  hipLaunchKernelGGL((attn_avg_kernel<T, DH>), dim3((m + 15) / 16, key_blocks), dim3(kThreads), 0, st, (const T*)q,
+  if constexpr (sizeof(T) == 2) {
+    if ((((uintptr_t)q | (uintptr_t)k_cache) & 15) == 0 && (size_t)L * n_kv_heads * DH * 2 < (1ull << 31) &&
+        (size_t)m * n_heads * DH * 2 < (1ull << 31)) {
+      hipLaunchKernelGGL((attn_avg_kernel<T, DH, true>), dim3((m + 15) / 16, key_blocks), dim3(kThreads), 0, st, (const T*)q,
+                         (const T*)k_cache, lse, m, L, n_heads, n_kv_heads, scale, attn_avg);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((attn_avg_kernel<T, DH, false>), dim3((m + 15) / 16, key_blocks), dim3(kThreads), 0, st, (const T*)q,
                      (const T*)k_cache, lse, m, L, n_heads, n_kv_heads, scale, attn_avg);
   return hipGetLastError();
 }

@@ -623,7 +623,8 @@ def test_rollout_update_and_influence_at_the_size_rules(B, L, m):
     ctx.close()
 
 
-@pytest.mark.parametrize("m,N,K", [(257, 40, 256), (289, 1000, 512), (385, 264, 768), (513, 256, 2304), (777, 72, 256), (1153, 520, 512)])
+@pytest.mark.parametrize("m,N,K", [(257, 40, 256), (289, 1000, 512), (385, 264, 768), (513, 256, 2304), (777, 72, 256), (1153, 520, 512),
+                                   (289, 16391, 2056), (513, 8200, 4104)])         # the last two: past the narrow shape's limit
 def test_linear_parity_many_rows(B, m, N, K):
     """Two row chunks per workgroup: odd counts of chunks, 5 to 8 row tiles, ragged rows and columns, one chunk pair of k."""
     test_linear_parity(B, "bf16", m, N, K)
@@ -700,5 +701,29 @@ def test_linear_parity_staged_weights(B, dtype, m, N, K):
         ctx.d2c_linear(a, w, m, N, K, out)
         torch.cuda.synchronize()
         got.append(out)
+    assert torch.equal(got[0], got[1])
+    ctx.close()
+
+
+@pytest.mark.parametrize("H,Hkv,dh,L,m", [(3, 1, 128, 1, 1), (4, 2, 64, 33, 15), (32, 32, 128, 513, 17), (28, 4, 128, 1025, 47),
+                                          (6, 3, 64, 511, 33)])
+def test_attention_average_staged_rows(B, H, Hkv, dh, L, m):
+    """The head average with Q and K staged through LDS against a K cache that is not 16-byte aligned (loads in operand order):
+    the same contraction order, so the same bits; waves without a head, heads that share K, ragged queries and keys."""
+    say(f"attention average staged H={H} Hkv={Hkv} dh={dh} L={L} m={m}")
+    _attention_parity(B, "bf16", H, Hkv, dh, L, m, tunables={"attn_tiled_min_m": 1 << 30})
+    wd = W.ModelDims(1, H * dh, H, Hkv, dh, 64, 64, dtype="bf16")
+    ctx, _, _ = _ctx_for(B, wd, max_seq=L, tunables={"attn_tiled_min_m": 1 << 30})
+    case = W.attention_case(1, H, Hkv, dh, L, m, dtype="bf16")
+    idx = torch.from_numpy(case["idx"]).cuda()
+    got = []
+    for off in (0, 1):
+        kc = torch.zeros(L * Hkv * dh + 8, dtype=torch.bfloat16, device="cuda")[off: off + L * Hkv * dh].view(L, Hkv * dh)
+        kc.copy_(B.to_device(case["k_cache"], "bf16"))
+        q, vc = B.to_device(case["q"], "bf16"), B.to_device(case["v_cache"], "bf16")
+        avg = torch.zeros((m, L), device="cuda")
+        ctx.d2c_attention(q, idx, m, None, None, kc, vc, L, torch.zeros_like(q), avg)
+        torch.cuda.synchronize()
+        got.append(avg)
     assert torch.equal(got[0], got[1])
     ctx.close()
