@@ -7,7 +7,8 @@
 //   * each wave owns 16*NT weight rows (output columns) and reads them straight
 //     from global memory into matrix-core operand registers, 16 bytes per lane,
 //     256 contiguous bytes per weight row and chunk, through a register ring that
-//     keeps RING-1 chunks in flight ahead of the one being consumed;
+//     keeps RING-1 chunks in flight ahead of the one being consumed (row-major
+//     weights come through LDS instead, see kRowStaged);
 //   * the activation rows (shared by all waves of the workgroup) are staged
 //     through LDS in 256-byte-per-row chunks, double-buffered, one barrier per chunk;
 //     a chunk is requested two iterations before it is needed in LDS, so its
@@ -32,7 +33,7 @@ namespace {
 constexpr int kChunkBytes = 256;                 // bytes of one row in one chunk
 constexpr int kRowStride = kChunkBytes + 16;     // LDS row pitch: 16-byte skew, conflict-free 16-byte reads
 constexpr int kSteps = 4;                        // matrix-core steps per chunk
-constexpr int kSuperRows = 8, kSuperCols = 4;    // many rows: block of workgroups that share an XCD's L2
+constexpr int kSuperRows = 8;                    // many rows: block of workgroups that share an XCD's L2
 
 // RING = number of weight chunks a wave keeps in registers (one being consumed, RING-1 in flight).
 // MODE: 0 = W row-major [N, K]; 1 = W pre-tiled; 2 = W pre-tiled with gate and up tiles interleaved and the
@@ -46,10 +47,13 @@ constexpr int kStageSlots = NT != 1 ? 0
                             : 2 * MT * 16 * kRowStride + WAVES * 2 * 16 * kChunkBytes <= 160 * 1024 ? 2
                                                                                                      : 0;
 
-// silu(g) * u on the exponential and reciprocal units (each within one unit in the last place in 32 bits; the result is
-// rounded to T): with a library exponential and a division the epilogue of 256 rows x 256 columns took about 7 us
+// silu(g) * u with the quotient from the reciprocal unit and one correction from its own remainder (Markstein's method), as
+// exact as the division that it replaces: relative error against 64 bits over |g| < 16 at most 1.5e-7, 4e-8 on average, both.
+// The exponential unit alone (arguments rounded after the product with log2(e)) reaches 1e-6 and is not used.
 __device__ __forceinline__ float gated(float g, float u) {
-  return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896341f * g)) * u;
+  if (!(fabsf(g) < 87.0f)) return g / (1.0f + expf(-g)) * u;   // the steps below need finite terms
+  const float d = 1.0f + expf(-g), inv = __builtin_amdgcn_rcpf(d), q = g * inv;
+  return copysignf(fmaf(fmaf(-d, q, g), inv, q), g) * u;       // the correction of -0 would lose its sign
 }
 
 template <typename T, int MT, int NT, int WAVES, int MODE>

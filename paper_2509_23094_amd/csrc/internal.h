@@ -38,8 +38,8 @@ bool set_tunable(Tunables& t, const char* name, int value);
 // ---- GEMM on a ragged handful of rows: P[s] = A[m,K] * W[N,K]^T over the k-range of split s
 struct GemmPlan {
   int mt;        // 16-row tiles per workgroup (1..8)
-  int nt;        // 16-column tiles per wave (1 or 2)
-  int waves;     // waves per workgroup (4, 8 or 16), each owning 16*nt output columns
+  int nt;        // 16-column tiles per wave (1, 2 or 4)
+  int waves;     // waves per workgroup (4, 6, 7, 8 or 10), each owning 16*nt output columns (gemm_wide_kernel: see wide_cols)
   int splits;    // k splits (partials to be summed by the consumer)
   int k_per_split;
   int row_chunks;
