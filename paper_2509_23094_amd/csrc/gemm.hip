@@ -373,7 +373,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
 // reads run three matrix-core groups ahead of their use.  The scheduler is told to keep that order.  The wait in front
 // of the barrier leaves the weight refills behind the staging in flight.
 // 512 rows, LLaDA widths, against 128 x 256 tiles of 4 waves with activations through registers: gate/up (24576 x 4096)
-// 142 -> 93 us (1.10 PFLOP/s), QKV 79 -> 57, O and down together 89 -> 84.  Tried on the 256-column tile (105 us):
+// 142 -> 93 us (1.10 PFLOP/s; the exact exponential adds about 9, by the difference of whole steps), QKV 79 -> 57, O and down together 89 -> 84.  Tried on the 256-column tile (105 us):
 // 32x32x16 steps with one wave per SIMD (119 us), operand-order staging (130 us).
 // The launcher guarantees whole chunks and an even number of them per split: nothing to mask.
 template <int MT, int NT, int MODE>
