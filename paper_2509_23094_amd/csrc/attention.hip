@@ -644,12 +644,13 @@ __global__ __launch_bounds__(kFwdThreads) void attn_fwd_f32_tile_kernel(
     }
     tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
-    const float m_new = fmaxf(m_run, tmax);                // finite: a tile holds at least one key below L
-    const float alpha = expf(m_run - m_new);
+    const float m_new = fmaxf(m_run, tmax);
+    const float ref = m_new == -INFINITY ? 0.f : m_new;    // keys whose scores are all -inf weigh nothing until one is not
+    const float alpha = expf(m_run - ref);
     float psum = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      x[j] = expf(x[j] - m_new);
+      x[j] = expf(x[j] - ref);
       psum += x[j];
     }
     l_run = l_run * alpha + psum;

@@ -591,6 +591,31 @@ def test_attention_f32_unaligned_rows(B):
     ctx.close()
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("low", [-np.inf, np.finfo(np.float32).min])
+def test_attention_f32_scores_of_minus_infinity(B, dh, low):
+    """Keys whose scores are -inf, a whole key tile and the whole of a wave's keys among them, weigh nothing: the softmax of
+    the others (K holds -inf, or the type's lowest value, which overflows in the product)."""
+    H, L, m = 2, 300, 17
+    say(f"attention f32 scores of -inf dh={dh} low={low}")
+    wd = W.ModelDims(1, H * dh, H, H, dh, 64, 64, dtype="f32")
+    ctx, _, _ = _ctx_for(B, wd, max_seq=L)
+    case = W.attention_case(5, H, H, dh, L, m, dtype="f32")
+    q, k = np.abs(case["q"]) + 1.0, case["k_cache"].copy()
+    gone = np.zeros(L, bool)
+    gone[0:40] = gone[128:144] = gone[256:272] = gone[299] = True      # tiles 0, 8 and 16: all keys of the first wave
+    k[gone, 3] = k[gone, dh + 3] = low
+    out, abar = torch.zeros((m, H * dh), device="cuda"), torch.zeros((m, L), device="cuda")
+    ctx.d2c_attention(torch.from_numpy(q).cuda(), torch.from_numpy(case["idx"]).cuda(), m, None, None, torch.from_numpy(k).cuda(),
+                      torch.from_numpy(case["v_cache"]).cuda(), L, out, abar)
+    torch.cuda.synchronize()
+    o_ref, a_ref = O.selective_attention(q, k[~gone].astype(np.float64), case["v_cache"][~gone].astype(np.float64), H, H, dh)
+    for r in range(m):
+        assert rel_l2(host(out)[r], o_ref[r]) < TOL["f32"] and rel_l2(host(abar)[r, ~gone], a_ref[r]) < TOL["f32"], f"row {r}"
+    assert (host(abar)[:, gone] == 0.0).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("L,m", [(1, 1), (40, 16), (131, 64), (200, 65), (791, 768), (800, 769), (1900, 1793)])
 def test_rollout_update_and_influence_at_the_size_rules(B, L, m):
     """The second layer's rollout update for every form of it (operand gathered, dense, strip in LDS or not) and Eq. 9,
