@@ -23,8 +23,8 @@ __device__ __forceinline__ u64 low_mask(int n) { return n <= 0 ? 0ull : n >= 64 
 // ------------------------------------------------------------------ Eq. 1
 // x-hat = argmax_v, s = 1 / sum_v exp(x_v - max).  A vocabulary row (0.5 MB at V = 126464) is cut into
 // chunks, one workgroup each, so that a few dozen rows still fill the chip: per chunk (max, first index of
-// the max, sum of exp(x - chunk max)); a second tiny launch merges the chunks of a row in ascending order
-// (ties keep the lowest index) -- fixed order, bit-reproducible.
+// the max, sum of exp(x - chunk max)); merge_rows puts the chunks of a row together (ties keep the lowest index) in an
+// order that depends on the vocabulary alone -- bit-reproducible, whatever else the call holds.
 constexpr int kConfThreads = 256;
 constexpr int kConfMaxChunks = 64;
 constexpr int kConfChunk = 8192;              // entries per chunk, as long as 64 chunks cover the vocabulary
@@ -134,23 +134,6 @@ __global__ __launch_bounds__(kConfThreads) void confidence_chunk_vec_kernel(cons
     o[1] = __int_as_float(bidx);
     o[2] = t;
   }
-}
-
-__global__ void confidence_merge_kernel(const float* __restrict__ part, int n_rows, int n_chunks,
-                                        const int32_t* __restrict__ pos, const int32_t* __restrict__ via,
-                                        float* __restrict__ conf, int32_t* __restrict__ pred) {
-  const int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= n_rows) return;
-  const float* p = part + (size_t)row * n_chunks * 3;
-  float best = p[0];
-  int bidx = __float_as_int(p[1]);
-  for (int c = 1; c < n_chunks; ++c)
-    if (p[3 * c] > best) { best = p[3 * c]; bidx = __float_as_int(p[3 * c + 1]); }   // ascending chunks: lowest index wins
-  float sum = 0.f;
-  for (int c = 0; c < n_chunks; ++c) sum += p[3 * c + 2] * expf(p[3 * c] - best);
-  const int where = via ? via[pos[row]] : pos[row];            // row -> position, directly or through S
-  conf[where] = 1.0f / sum;
-  pred[where] = bidx;
 }
 
 // ------------------------------------------------------------------ Eq. 6-8 on the compact block
@@ -599,6 +582,8 @@ constexpr int kSelNW = kSelT / 64;
 constexpr int kRankMax = 256;                // up to this many stage-1 candidates are ranked by counting
 constexpr int kMergeMaxRows = 256;           // up to this many logit rows select_kernel merges Eq. 1's chunks (200 rows
                                              // cost it about 4 us, a launch for them 7.5; past 32 rows a wave it grows on)
+constexpr int kMergeLaunchRows = 64;         // more rows: a launch of their own, so many rows a workgroup
+static_assert(kMergeMaxRows / kSelNW <= 32 && kMergeLaunchRows <= kMergeMaxRows, "merge_rows holds 32 rows a wave");
 
 struct SelShared {
   int wcnt[kSelWaves];
@@ -775,8 +760,8 @@ struct SelectBatch {
   SelectArgs seq[kSelMaxBatch];
 };
 
-// Eq. 1's chunks of a row -> confidence and prediction, by 32 lanes (64 with more than 32 chunks): the same
-// (max, lowest index, sum) merge as confidence_merge_kernel, two rows of a wave at a time.
+// Eq. 1's chunks of a row -> confidence and prediction, by 32 lanes (64 with more than 32 chunks), two rows of a wave at a
+// time; kSelT threads, at most kMergeMaxRows rows.  A row's sum is a scan over its lanes: the same bits for any number of rows.
 __device__ void merge_rows(const SelectArgs& a, int wave) {
   const int lane = threadIdx.x & 63;
   const int width = a.n_chunks <= 32 ? 32 : 64, per = 64 / width;
@@ -835,6 +820,14 @@ __device__ void merge_rows(const SelectArgs& a, int wave) {
       }
     }
   }
+}
+
+__global__ __launch_bounds__(kSelT) void confidence_merge_kernel(SelectArgs a) {
+  const int row0 = blockIdx.x * kMergeLaunchRows;
+  a.part += (size_t)row0 * a.n_chunks * 3;
+  a.pos += row0;
+  a.n_rows = min(kMergeLaunchRows, a.n_rows - row0);
+  merge_rows(a, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // One workgroup per sequence (blockIdx.x); the sequences are independent.  Latency is what bounds it (a few KB of
@@ -1309,8 +1302,7 @@ hipError_t launch_select(const SelectArgs* args, int n, hipStream_t st) {
     if (a.n_rows == 0) batch.seq[i].part = nullptr;
     if (a.n_rows > kMergeMaxRows) {
       // many logit rows: their chunks are merged by a launch of their own, spread over more than one compute unit
-      hipLaunchKernelGGL(confidence_merge_kernel, dim3((a.n_rows + 63) / 64), dim3(64), 0, st, a.part, a.n_rows, a.n_chunks,
-                         a.pos, a.via, a.conf, a.pred);
+      hipLaunchKernelGGL(confidence_merge_kernel, dim3((a.n_rows + kMergeLaunchRows - 1) / kMergeLaunchRows), dim3(kSelT), 0, st, a);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       batch.seq[i].part = nullptr;

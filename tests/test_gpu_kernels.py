@@ -537,6 +537,32 @@ def test_select_ties_beyond_the_counting_limit(B, L, n_masked):
     ctx.close()
 
 
+@pytest.mark.parametrize("V", [40000, 126464, 8192 * 33])
+def test_confidence_does_not_depend_on_the_other_rows(B, V):
+    """A row's confidence and prediction have the same bits whether the call merges them inside the selection (up to 256
+    rows) or in a launch of its own (more)."""
+    L = 640
+    say(f"confidence of the same rows in calls of 1, 256, 257 and 600 rows V={V}")
+    wd = W.ModelDims(1, 64, 4, 4, 16, 80, V, dtype="f32")
+    mdl = W.model_weights(W.ModelDims(1, 64, 4, 4, 16, 80, 8, dtype="f32"), 0)
+    mdl["tok_emb"] = mdl["lm_head"] = np.zeros((V, 64), np.float32)
+    ctx = B.Context(wd, mdl, L)
+    is_masked = np.ones(L, bool)
+    y, zero = np.full(L, wd.mask_id, np.int32), np.zeros(L, np.float32)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    logits = torch.randn((600, V), generator=g, device="cuda") * 2.0
+    got = []
+    for n in (1, 256, 257, 600):
+        res, _ = _run_select(B, ctx, B.make_params(n_unmask=0), logits[:n].cpu().numpy(), np.arange(n), y, is_masked, 0, zero,
+                             np.zeros(L, np.int32), zero + 1.0)
+        got.append((res["conf"][:n], res["pred"][:n]))
+    for conf, pred in got[:-1]:
+        np.testing.assert_array_equal(conf, got[-1][0][: len(conf)])
+        np.testing.assert_array_equal(pred, got[-1][1][: len(pred)])
+    ctx.close()
+
+
 @pytest.mark.parametrize("n_rows,V", [(1, 8192), (17, 8193), (256, 40000), (257, 40000), (40, 8192 * 33)])
 def test_select_merges_every_logit_row(B, n_rows, V):
     """Eq. 1 with the chunks merged beside the selection (up to 256 rows, up to 32 chunks or more) and by a launch of its own."""
