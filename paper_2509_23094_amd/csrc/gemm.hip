@@ -375,7 +375,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
 // 512 rows, LLaDA widths, against 128 x 256 tiles of 4 waves with activations through registers: gate/up (24576 x 4096)
 // 142 -> 93 us (1.10 PFLOP/s; the exact exponential adds about 9, by the difference of whole steps), QKV 79 -> 57, O and down together 89 -> 84.  Tried on the 256-column tile (105 us):
 // 32x32x16 steps with one wave per SIMD (119 us), operand-order staging (130 us).
-// The launcher guarantees whole chunks and an even number of them per split: nothing to mask.
+// The launcher guarantees whole chunks of k: nothing to mask.
 template <int MT, int NT, int MODE>
 __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restrict__ A, int lda, const bf16* __restrict__ W,
                                                            int ldw, float* __restrict__ P, int ldp, size_t split_stride,
@@ -565,17 +565,14 @@ hipError_t launch_wide_t(const GemmPlan& pl, int pairs, const void* A, int lda, 
                      ldp, split_stride, m, N, K, pl.k_per_split, n_blocks, pl.splits, pairs, (bf16*)act);
   return hipGetLastError();
 }
-// The row tiles are dealt evenly to the row chunks of all pairs (an odd count of chunks leaves no empty half).
-inline int wide_row_tiles(int m, int pairs) { return std::max(5, ((m + 15) / 16 + 2 * pairs - 1) / (2 * pairs)); }
 template <int MODE>
 hipError_t launch_wide(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp,
                        size_t split_stride, int m, int N, int K, hipStream_t st, void* act) {
-  const int pairs = (pl.row_chunks + 1) / 2, mt = wide_row_tiles(m, pairs);
+  const int pairs = (pl.row_chunks + 1) / 2;
 #define D2C_WIDE(mt_)                                                                                                        \
-  if (mt == mt_)                                                                                                             \
-    return pl.wide_cols == 192                                                                                               \
-               ? launch_wide_t<mt_, 3, MODE>(pl, pairs, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, act)              \
-               : launch_wide_t<mt_, 4, MODE>(pl, pairs, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, act)
+  if (pl.mt == mt_ && (pl.nt == 3 || pl.nt == 4))                                                                            \
+    return pl.nt == 3 ? launch_wide_t<mt_, 3, MODE>(pl, pairs, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, act)       \
+                      : launch_wide_t<mt_, 4, MODE>(pl, pairs, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, act)
   D2C_WIDE(5); D2C_WIDE(6); D2C_WIDE(7); D2C_WIDE(8);
 #undef D2C_WIDE
   return hipErrorInvalidValue;
@@ -635,13 +632,14 @@ hipError_t launch_nt(const GemmPlan& pl, const void* A, int lda, const void* W, 
     }
     return launch_mt<T, 1, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
   }
-  if (pl.wide_cols != 0) {
+  if (pl.wide) {
     if constexpr (sizeof(T) == 2) {
       if (K % 128 || pl.k_per_split % 128) return hipErrorInvalidValue;
       // the staging wants whole 16-byte pieces and 32-bit offsets: other callers' buffers go through registers
       if ((uintptr_t)A % 16 == 0 && (size_t)m * lda * 2 < (1ull << 32))
         return launch_wide<MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
       GemmPlan other = pl;
+      other.wide = false;
       other.nt = 2;
       other.waves = 8;
       other.mt = 8;
@@ -707,14 +705,15 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   pl.nt = (N > t.gemm_nt_big_n || pl.row_chunks > 1) ? 2 : 1;
   // several row chunks in bf16: gemm_wide_kernel, 128 x 64 outputs per wave; 4 waves per row chunk, and two row chunks
   // to a workgroup
+  // (the kernel takes any number of whole 128-element chunks, but its splits were only measured on pairs of them)
   const bool wide = pl.row_chunks > 1 && m >= t.gemm_wide_min_rows && dtype == kBF16 && t.gemm_wide_tiles &&
-                    K % 256 == 0;                       // needs an even number of whole chunks
-  if (wide) pl.nt = 4;
+                    K % 256 == 0;
+  pl.wide = false;
   pl.rot = t.gemm_rot;
   // 8 waves share one activation chunk in LDS: fewer, fatter workgroups (about 1.5 per compute unit) with
   // fewer k splits measured faster than 4-wave groups at every projection shape of the two models
   // (7 waves only where no gated epilogue can follow: it pairs neighbouring waves)
-  pl.waves = wide ? 4
+  pl.waves = wide ? 8
              : (t.gemm_waves == 4 || t.gemm_waves == 6 || t.gemm_waves == 10 || (t.gemm_waves == 7 && !single_split))
                  ? t.gemm_waves
                  : 8;
@@ -758,49 +757,43 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
       }
     }
   }
+  // row tiles per row chunk when the tiles of m rows are dealt evenly to the chunks of so many workgroup rows
+  auto dealt = [&](int pairs) { return std::max(5, (tiles + 2 * pairs - 1) / (2 * pairs)); };
   if (wide) {
-    // Rows per workgroup: 8 row tiles unless fewer do the same job better.  Measured at the LLaDA widths,
-    // 288-2048 rows: (a) fewer tiles in the SAME number of row chunks are always a gain (less matrix-core and
-    // LDS work per weight pull: 288 rows as 3 x 6 tiles -14 %); (b) MORE row chunks gain only when their count
-    // becomes a multiple of 8, the rows of the block of workgroups that shares an XCD's L2 (700 rows as
-    // 8 x 6 tiles instead of 6 x 8: -16 %; 856 rows as 8 x 7 instead of 7 x 8: -7 %; 1500 rows as 16 x 6
-    // instead of 12 x 8: -7 %), every other count lost 10-40 %.
+    // Workgroup rows of two row chunks: as many as chunks of 8 tiles (of 7 or 6 where that makes their count a multiple
+    // of 8, or keeps it) would fill.  This count was measured on a kernel with one row chunk per workgroup; on this one it is
+    // not always the best: with pre-tiled weights of the LLaDA widths the best of 4 to 8 tiles is 6 % faster on average over
+    // 257-2048 rows (777 rows x 4096 x 4096 43 us, 37 the best; 640 x 24576 x 4096 170, 129), with row-major ones 0 %.
     const int rc8 = (tiles + 7) / 8;
-    int mt = 8;
-    if (t.gemm_wide_mt != 0) {
-      mt = t.gemm_wide_mt;
-    } else {
-      if (rc8 % kSuperRows != 0)
-        for (int c : {7, 6})
-          if (mt == 8 && ((tiles + c - 1) / c) % kSuperRows == 0) mt = c;
-      if (mt == 8)
-        for (int c : {6, 7})
-          if (mt == 8 && (tiles + c - 1) / c == rc8) mt = c;
-    }
-    pl.mt = mt;
-    pl.row_chunks = (tiles + mt - 1) / mt;
-  }
-  pl.wide_cols = 0;
-  if (wide) {
+    int c = 8;
+    if (rc8 % kSuperRows != 0)
+      for (int x : {7, 6})
+        if (c == 8 && ((tiles + x - 1) / x) % kSuperRows == 0) c = x;
+    if (c == 8)
+      for (int x : {6, 7})
+        if (c == 8 && (tiles + x - 1) / x == rc8) c = x;
+    pl.wide = true;
+    pl.mt = t.gemm_wide_mt != 0 ? t.gemm_wide_mt : dealt(((tiles + c - 1) / c + 1) / 2);
+    pl.row_chunks = (tiles + pl.mt - 1) / pl.mt;
     // Columns per workgroup and splits by a time model in us, a workgroup taking two row chunks: a chunk of k costs a
     // row tile 0.35 us with 256 columns and 0.8 of that with 192 (measured, 512 rows: 105 us for gate/up as 192 workgroups
     // of 256 columns, 93 as 256 of 192: what counts is full rounds over the 256 units), and every split writes and
     // reads m x N partial sums at about 5.5 TB/s.  Any count of splits: Dream's QKV at 768 rows runs 3.
     const int pairs = (pl.row_chunks + 1) / 2;
-    const double chunk_us = 0.35 * wide_row_tiles(m, pairs), split_us = single_split ? 0.0 : (double)m * N * 8e-6 / 5.5;
+    const double chunk_us = 0.35 * pl.mt, split_us = single_split ? 0.0 : (double)m * N * 8e-6 / 5.5;
     double best = 1e30;
-    for (int cols : {256, 192})
+    for (int nt : {4, 3})
       for (int s = 1; s <= max_splits; ++s) {
         int cps = (chunks + s - 1) / s;
         cps += cps & 1;                                           // splits start on pairs of chunks
         if (s > 1 && cps < 4) break;
         const int eff = (chunks + cps - 1) / cps;
-        const int wgs = ((N + cols - 1) / cols) * pairs * eff;
-        const double cost = (double)((wgs + kUnits - 1) / kUnits) * cps * chunk_us * (cols == 192 ? 0.8 : 1.0) + split_us * eff;
+        const int wgs = ((N + 64 * nt - 1) / (64 * nt)) * pairs * eff;
+        const double cost = (double)((wgs + kUnits - 1) / kUnits) * cps * chunk_us * (nt == 3 ? 0.8 : 1.0) + split_us * eff;
         if (cost < best * 0.999) {
           best = cost;
           splits = s;
-          pl.wide_cols = cols;
+          pl.nt = nt;
         }
       }
   }
@@ -812,8 +805,12 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   // masked rows of a first step, 256 rows x 126464 columns: 374 -> 317 us), not for a block's matrices (96 column
   // blocks at most).
   if (!wide && dtype == kBF16 && pl.nt == 2 && pl.row_chunks == 2 && t.gemm_wide_tiles && K % kc == 0 &&
-      ((N + 255) / 256) * pl.splits >= 3 * kUnits / 4)
-    pl.wide_cols = 256;
+      ((N + 255) / 256) * pl.splits >= 3 * kUnits / 4) {
+    pl.wide = true;
+    pl.mt = dealt(1);
+    pl.nt = 4;
+    pl.waves = 8;
+  }
   return pl;
 }
 
@@ -833,7 +830,7 @@ hipError_t launch_gemm(int dtype, const GemmPlan& pl, const void* A, int lda, co
       return launch_nt<bf16, kPre>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);
     return launch_nt<float, kPre>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);
   }
-  if (pl.wide_cols == 0 && pl.nt == 1 && (uintptr_t)W % 16 == 0 && (size_t)ldw * dtype_size(dtype) * 16 < (1ull << 31)) {
+  if (pl.nt == 1 && (uintptr_t)W % 16 == 0 && (size_t)ldw * dtype_size(dtype) * 16 < (1ull << 31)) {
     if (dtype == kBF16)
       return launch_rows_staged<bf16>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st);
     return launch_rows_staged<float>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st);

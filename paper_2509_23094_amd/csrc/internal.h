@@ -15,10 +15,10 @@ inline size_t dtype_size(int dt) { return dt == kBF16 ? 2 : 4; }
 struct Tunables {
   int gemm_target_wgs = 384;   // aim for at least this many groups of 4 waves per GEMM
   int gemm_max_splits = 8;
-  int gemm_wide_min_rows = 257; // the wide instantiation from this many rows on (3 row chunks)
+  int gemm_wide_min_rows = 257; // gemm_wide_kernel from this many rows on (fewer: see the end of plan_gemm)
   int gemm_tall_chunk = 1;      // 129-192 bf16 rows as ONE row chunk of 10 or 12 row tiles
   int gemm_wide_tiles = 1;     // many bf16 rows: gemm_wide_kernel, 128 x 64 outputs per wave, two row chunks per workgroup
-  int gemm_wide_mt = 0;        // row tiles per workgroup of the wide instantiation: 6, 7, 8; 0 = by shape
+  int gemm_wide_mt = 0;        // row tiles per row chunk of gemm_wide_kernel: 6, 7, 8; 0 = by shape
   int gemm_nt_big_n = 1 << 30; // N above this uses two column tiles per wave even for few rows (measured slower);
                                // more than 128 rows always do
   int gemm_waves = 0;          // waves per workgroup sharing one activation chunk in LDS: 4, 6, 8, 10; 0 = by shape
@@ -37,14 +37,17 @@ bool set_tunable(Tunables& t, const char* name, int value);
 
 // ---- GEMM on a ragged handful of rows: P[s] = A[m,K] * W[N,K]^T over the k-range of split s
 struct GemmPlan {
-  int mt;        // 16-row tiles per workgroup (1..8)
-  int nt;        // 16-column tiles per wave (1, 2 or 4)
-  int waves;     // waves per workgroup (4, 6, 7, 8 or 10), each owning 16*nt output columns (gemm_wide_kernel: see wide_cols)
+  int mt;        // 16-row tiles per row chunk (1..8, 10, 12)
+  int nt;        // 16-column tiles per wave (1 or 2; wide: 3 or 4)
+  int waves;     // waves per workgroup (4, 6, 7, 8 or 10), each owning 16*nt output columns
   int splits;    // k splits (partials to be summed by the consumer)
   int k_per_split;
   int row_chunks;
   int rot;       // multiplier of the per-workgroup start-chunk rotation (0 = none)
-  int wide_cols; // 256 or 192: gemm_wide_kernel with so many columns per workgroup, which takes two row chunks; 0 = the others
+  bool wide;     // gemm_wide_kernel: two row chunks per workgroup, four of its 8 waves on each; else gemm_rows_kernel, one
+
+  int chunks_per_wg() const { return wide ? 2 : 1; }
+  int cols_per_wg() const { return 16 * nt * waves / chunks_per_wg(); }
 };
 GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split = false);
 // P must hold plan.splits * split_stride floats; split_stride >= m * ldp.

@@ -184,7 +184,7 @@ def test_refresh_layer_parity_forced_workgroup_width(B, name, waves):
 
 @pytest.mark.parametrize("mt", [6, 7, 8])
 def test_refresh_layer_parity_forced_rows_per_workgroup(B, mt):
-    """Many rows: 6, 7 or 8 row tiles per workgroup of the wide projection shape, whatever the planner's choice."""
+    """Many rows: 6, 7 or 8 row tiles for each half of a workgroup of the wide projection shape, whatever the planner would take."""
     case = [c for c in LAYER_CASES if c[0] == "bf16-330-rows"][0]
     _refresh_layer_parity(B, *case, tunables={"gemm_wide_mt": mt})
 

@@ -36,16 +36,17 @@ def test_plan_covers_rows_and_contraction_and_keeps_the_kernel_assumptions(dtype
         assert p["k_per_split"] * p["splits"] >= K and p["k_per_split"] * (p["splits"] - 1) < K, where
         assert p["k_per_split"] % elem_per_chunk == 0, where                        # splits start on chunk boundaries
         assert 1 <= p["splits"] <= 8 and (not single or p["splits"] == 1), where
-        assert p["waves"] in (4, 6, 7, 8, 10) and p["col_tiles_per_wave"] in (1, 2, 4), where
-        cols = 16 * p["col_tiles_per_wave"] * p["waves"]
+        assert p["waves"] in (4, 6, 7, 8, 10) and p["col_tiles_per_wave"] in (1, 2, 3, 4), where
+        wide = p["col_tiles_per_wave"] > 2
+        cols = 16 * p["col_tiles_per_wave"] * p["waves"] // (2 if wide else 1)
         assert p["workgroups"] == -(-N // cols) * p["splits"] * p["row_chunks"], where
-        if p["col_tiles_per_wave"] == 4:
-            # the hand-pipelined loop for many rows: bf16, 6-8 row tiles per chunk, 4 waves, chunks taken in pairs
-            assert dtype == "bf16" and p["row_tiles"] in (6, 7, 8) and p["waves"] == 4 and m >= 257, where
-            assert K % 256 == 0 and p["k_per_split"] % 256 == 0, where
-            # fewer than 8 tiles only with as many row chunks as 8 tiles need, or with whole blocks of 8 chunks
-            tiles = -(-m // 16)
-            assert p["row_tiles"] == 8 or p["row_chunks"] == -(-tiles // 8) or p["row_chunks"] % 8 == 0, where
+        if wide:
+            # the kernel for many rows: bf16, 8 waves, 5-8 row tiles for each half of them, whole chunks of k
+            assert dtype == "bf16" and p["row_tiles"] in (10, 12, 14, 16) and p["waves"] == 8 and m >= 193, where
+            assert K % 128 == 0 and (m < 257 or (K % 256 == 0 and p["k_per_split"] % 256 == 0)), where
+            if m < 257:                                # one workgroup row, where it fills three quarters of the chip
+                assert p["row_chunks"] == 1 and p["workgroups"] >= 192, where
+            continue
         if p["row_tiles"] > 8:
             # the tall single chunk: bf16 only, even tile counts up to 12, 8 waves, one column tile per wave
             assert dtype == "bf16" and p["row_tiles"] in (10, 12) and p["row_chunks"] == 1, where
@@ -55,12 +56,16 @@ def test_plan_covers_rows_and_contraction_and_keeps_the_kernel_assumptions(dtype
 
 
 def test_plan_rows_per_workgroup_for_many_rows():
-    """The measured cases of the rows-per-workgroup rule (LLaDA widths)."""
-    for m, tiles, chunks in ((288, 6, 3), (400, 7, 4), (512, 8, 4), (700, 6, 8), (856, 7, 8), (1000, 8, 8),
-                             (1100, 8, 9), (1500, 6, 16), (2048, 8, 16), (12288, 8, 96)):
+    """Rows are dealt evenly to the halves of all workgroups: (row tiles per workgroup, workgroup rows) as launched."""
+    for m, tiles, blocks in ((257, 10, 2), (288, 10, 2), (330, 12, 2), (400, 14, 2), (512, 16, 2), (700, 12, 4), (777, 14, 4),
+                             (856, 14, 4), (1000, 16, 4), (1100, 14, 5), (1500, 12, 8), (2048, 16, 8), (12288, 16, 48)):
         for (N, K) in ((12288, 4096), (4096, 12288)):
             p = _plan("bf16", m, N, K)
-            assert (p["row_tiles"], p["row_chunks"]) == (tiles, chunks), (m, N, K, p)
+            assert (p["row_tiles"], p["row_chunks"]) == (tiles, blocks), (m, N, K, p)
+    # the head on all masked rows of a first step; a block's matrices on as many rows keep two columns tiles per wave
+    p = _plan("bf16", 256, 126464, 4096, True)
+    assert (p["row_tiles"], p["row_chunks"], p["col_tiles_per_wave"], p["waves"], p["workgroups"]) == (16, 1, 4, 8, 494)
+    assert _plan("bf16", 256, 12288, 4096)["col_tiles_per_wave"] == 2
 
 
 def test_plan_at_the_benchmark_shapes():
@@ -85,7 +90,7 @@ def test_plan_at_the_benchmark_shapes():
     p = _plan("bf16", 200, 12288, 4096)
     assert (p["row_chunks"], p["col_tiles_per_wave"]) == (2, 2)
     p = _plan("bf16", 856, 12288, 4096)
-    assert (p["row_tiles"], p["row_chunks"], p["col_tiles_per_wave"], p["waves"]) == (7, 8, 4, 4)
+    assert (p["row_tiles"], p["row_chunks"], p["col_tiles_per_wave"], p["waves"]) == (14, 4, 3, 8)
     p = _plan("f32", 856, 768, 256)
     assert p["col_tiles_per_wave"] == 2 and p["row_chunks"] == 7
 
