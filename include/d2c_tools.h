@@ -34,8 +34,9 @@ int d2c_profile_end(d2c_ctx* ctx, double* ms, int64_t* launches, double* bytes);
 /* Launch-shape tunables.  Every context has its own set; two contexts may differ.  Names:
  * projection kernel: "gemm_waves" (waves per workgroup: 4, 6, 7, 8, 10; 0 = chosen by shape together with the
  * split count), "gemm_max_splits" (1..8), "gemm_target_wgs" (workgroups aimed at where the shape search does
- * not apply), "gemm_nt_big_n", "gemm_wide_tiles" (0/1: 128 x 64 outputs per wave for many bf16 rows),
- * "gemm_wide_mt" (6, 7, 8 row tiles for each half of the waves of that shape; 0 = by shape),
+ * not apply), "gemm_nt_big_n", "gemm_wide_tiles" (128 x 64 outputs per wave for many bf16 rows: 0 = never, 1 = in
+ * workgroups of 4 or of 2 x 4 waves, the faster by the planner's estimate, 2 = of 2 x 4, 3 = of 4),
+ * "gemm_wide_mt" (6, 7, 8 row tiles for each four waves of that shape; 0 = by shape),
  * "gemm_wide_min_rows" (that shape from this many rows on), "gemm_tall_chunk" (0/1: 129-192 bf16 rows
  * as one row chunk), "gemm_preshuffle" (0/1: pre-tiled weight copies; only at d2c_init_tuned), "gemm_rot";
  * attention: "attn_tiled_min_m" (bf16 attention switches to the LDS-tiled kernels from this many query rows
@@ -63,8 +64,8 @@ int d2c_ctx_set_tunable(d2c_ctx* ctx, const char* name, int32_t value);
  * contraction (the gate/up projection with the gated epilogue).  Writes
  * shape[0..6] = row tiles per workgroup (16 rows each), column tiles per wave, waves per workgroup, splits of
  * the contraction, contraction elements per split, row blocks (of the workgroup's row tiles), workgroups of the launch.
- * With 3 or 4 column tiles per wave half of the waves take the upper and half the lower half of the row tiles; else all
- * waves take all of them.
+ * Of 8 waves with 3 or 4 column tiles each, half take the upper and half the lower half of the row tiles; else all waves
+ * take all of them.
  * Returns D2C_EINVAL for a null pointer, a dtype other than D2C_F32 / D2C_BF16 or non-positive sizes. */
 int d2c_plan_projection(int32_t dtype, int32_t m, int32_t N, int32_t K, int32_t single_split, int32_t shape[7]);
 

@@ -209,7 +209,7 @@ int pre_chunks(const d2c_ctx* c, int K) { return (int)(((size_t)K * tsize(c) + 2
 // context's own projection matrices (pre-tiled when c->pre).
 int project(d2c_ctx* c, const void* A, int lda, const void* W, int m, int N, int K, GemmPlan* plan_out,
             size_t* stride_out, hipStream_t st, bool single_split = false, float* dst = nullptr) {
-  GemmPlan pl = plan_gemm(c->tun, c->dims.dtype, m, N, K, single_split);
+  GemmPlan pl = plan_gemm(c->tun, c->dims.dtype, m, N, K, single_split, !c->pre);
   const size_t stride = (size_t)m * N;
   float* P = dst ? dst : c->partial;
   if (!dst && stride * pl.splits > c->partial_floats) return fail(c, D2C_ESHAPE, "projection partials exceed workspace");
@@ -382,7 +382,7 @@ WsNeeds ws_needs(const d2c_dims& D, size_t max_rows, const Tunables& t) {
   for (int m = 1; m <= (int)max_rows; ++m)
     for (auto& s : shapes) {
       // up to 128 rows leave room for the largest split count; beyond that the planner's choice is taken
-      const GemmPlan pl = plan_gemm(t, D.dtype, m, s[0], s[1]);
+      const GemmPlan pl = plan_gemm(t, D.dtype, m, s[0], s[1], false, !t.gemm_preshuffle);
       n.partial = std::max(n.partial, (size_t)(m <= 128 ? 8 : pl.splits) * m * s[0]);
     }
   // one piece per sequence of a batched attention launch
@@ -721,14 +721,9 @@ int d2c_linear(d2c_ctx* c, const void* a, const void* w, int32_t m, int32_t N, i
   if (m == 0) return D2C_OK;
   if (!a || !w || !out) return fail(c, D2C_EINVAL, "null buffer");
   hipStream_t st = (hipStream_t)stream;
-  // The caller's weights are row-major, which the wide shape for many rows reads in operand order; a small matrix is faster in
-  // the narrow one.  Wide / narrow, us: 4096 x 4096 on 300 rows 39.4 / 33.6, on 1000 66 / 58; 4096 x 12288 75 / 84, 140 / 153;
-  // 12288 x 4096 73 / 108, 126 / 185.
-  Tunables tun = c->tun;
-  if ((size_t)N * K < ((size_t)1 << 25)) tun.gemm_wide_tiles = 0;
-  GemmPlan pl = plan_gemm(tun, c->dims.dtype, m, N, K);
+  GemmPlan pl = plan_gemm(c->tun, c->dims.dtype, m, N, K, false, true);
   const size_t stride = (size_t)m * N;
-  if (stride * pl.splits > c->partial_floats) pl = plan_gemm(tun, c->dims.dtype, m, N, K, true);   // no room for partials
+  if (stride * pl.splits > c->partial_floats) pl = plan_gemm(c->tun, c->dims.dtype, m, N, K, true, true);   // no room for partials
   if (pl.splits == 1) {
     D2C_TIMED(c, st, D2C_PROF_GEMM, (double)N * K * tsize(c),
               launch_gemm(c->dims.dtype, pl, a, K, w, K, out, N, stride, m, N, K, st));

@@ -22,6 +22,7 @@
 //     tile consecutive slots of the SAME XCD, so the tile comes from HBM once and the
 //     other chunks hit it in L2.
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "internal.h"
@@ -33,7 +34,7 @@ namespace {
 constexpr int kChunkBytes = 256;                 // bytes of one row in one chunk
 constexpr int kRowStride = kChunkBytes + 16;     // LDS row pitch: 16-byte skew, conflict-free 16-byte reads
 constexpr int kSteps = 4;                        // matrix-core steps per chunk
-constexpr int kSuperRows = 8;                    // many rows: block of workgroups that share an XCD's L2
+constexpr int kSuperRows = 8, kSuperCols = 4;    // many rows: block of workgroups that share an XCD's L2
 
 // RING = number of weight chunks a wave keeps in registers (one being consumed, RING-1 in flight).
 // MODE: 0 = W row-major [N, K]; 1 = W pre-tiled; 2 = W pre-tiled with gate and up tiles interleaved and the
@@ -70,7 +71,20 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
   constexpr int AI = (kAFrags + kThreads - 1) / kThreads;        // of which one thread moves this many
   // workgroup id -> (weight tile, row chunk): id % 8 is the XCD, within an XCD the row chunk varies fastest
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int tile = (slot / row_chunks) * 8 + xcd, bz = slot % row_chunks;
+  int tile, bz;
+  if constexpr (NT >= 4) {
+    // Many rows: the 32 workgroups that run on an XCD at one time form a block of kSuperRows row chunks x
+    // kSuperCols weight tiles, so that what its L2 has to bring in per k-step (8 x 128 activation rows +
+    // 4 x 256 weight rows) is less than half of that of 32 row chunks of one weight tile.
+    const int n_row_st = (row_chunks + kSuperRows - 1) / kSuperRows;
+    const int st = slot / (kSuperRows * kSuperCols), w = slot % (kSuperRows * kSuperCols);
+    bz = (st % n_row_st) * kSuperRows + w % kSuperRows;
+    tile = ((st / n_row_st) * kSuperCols + w / kSuperRows) * 8 + xcd;
+    if (bz >= row_chunks) return;
+  } else {
+    tile = (slot / row_chunks) * 8 + xcd;
+    bz = slot % row_chunks;
+  }
   if (tile >= n_blocks * n_splits) return;       // padding (whole workgroup leaves)
   const int by = tile / n_blocks, bx = tile - by * n_blocks;
   constexpr int E = Frag<T>::kElems;
@@ -171,7 +185,63 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
   };
 
   if (n_chunks <= 0) return;
-  if constexpr (STAGED) {
+  if constexpr (NT >= 4) {
+    // Many rows: 128 x 64 outputs per wave, one wave per SIMD.  Nothing else hides latencies here, so the
+    // loop is pipelined by hand and the scheduler is told to keep the interleaving:
+    //   * the activation fragments are read from LDS three matrix-core groups ahead of their use;
+    //   * the weight registers of a k-step are refilled as soon as that step is done, with the same step
+    //     of the chunk two ahead (two chunks of flight time: an L2 miss costs more than one);
+    //   * the next activation chunk is requested at the top of an iteration and stored behind it.
+    // The launcher guarantees whole chunks and an even number of them per split: nothing to mask.
+    static_assert(RING == 2, "the wide loop keeps two weight chunks");
+    constexpr int NI = kSteps * MT;
+    auto load_b_step = [&](Frag<T> (&b)[NT][kSteps], int chunk, int step) {
+      const size_t off = PRE ? (size_t)(chunk_k(chunk) / KC) * kBlockElems + step * 64 * E
+                             : (size_t)(chunk_k(chunk) + step * KS + g * E);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) b[nt][step].raw = ld16(wrow[nt] + off);
+    };
+    load_a(areg[0], 0);
+    load_b(breg[0], 0);
+    load_b(breg[1], 1);
+    store_a(areg[0], 0);
+    __syncthreads();
+    for (int base = 0; base < n_chunks; base += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int c = base + u;
+        load_a(areg[0], c + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned char* abuf = lds[u];
+        auto read_af = [&](int i) {
+          Frag<T> f;
+          f.raw = *reinterpret_cast<const u32x4*>(&abuf[((i % MT) * 16 + r) * kRowStride + ((i / MT) * 4 + g) * 16]);
+          return f;
+        };
+        Frag<T> af[4];
+        af[0] = read_af(0);
+        af[1] = read_af(1);
+        af[2] = read_af(2);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) mfma16(acc[i % MT][nt], af[i % 4], breg[u][nt][i / MT]);
+          if (i + 3 < NI) af[(i + 3) % 4] = read_af(i + 3);
+          if (i % MT == MT - 1) load_b_step(breg[u], c + 2, i / MT);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, NT, 0);                          // NT matrix-core instructions
+          if (i + 3 < NI) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);           // one LDS read
+          if (i % MT == MT - 1) __builtin_amdgcn_sched_group_barrier(0x020, NT, 0);    // the k-step's refill
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        store_a(areg[0], u ^ 1);
+        __syncthreads();
+      }
+    }
+  } else if constexpr (STAGED) {
     // Row-major weights in operand order (lane = row) cost the L1, which merges only what consecutive lanes ask for, 64
     // accesses an instruction.  A wave therefore brings its 16 rows straight into LDS, four whole 256-byte row pieces an
     // instruction, up to two chunks ahead, and reads its operands there (the 16-byte pieces of a row are xored with its number:
@@ -585,6 +655,9 @@ hipError_t launch_t(const GemmPlan& pl, const void* A, int lda, const void* W, i
   const int n_blocks = (N + cols - 1) / cols;
   const int groups = (n_blocks * pl.splits + 7) / 8;            // weight tiles are dealt to the XCDs in groups of 8
   dim3 grid(groups * 8 * pl.row_chunks);
+  if (NT >= 4)
+    grid.x = 8 * ((groups + kSuperCols - 1) / kSuperCols) * ((pl.row_chunks + kSuperRows - 1) / kSuperRows) *
+             (kSuperRows * kSuperCols);
   if constexpr (MODE == kRowStaged && kStageSlots<MT, NT, WAVES> == 0)
     return launch_t<T, MT, NT, WAVES, kRowMajor>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, act);
   else
@@ -640,11 +713,28 @@ hipError_t launch_nt(const GemmPlan& pl, const void* A, int lda, const void* W, 
         return launch_wide<MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
       GemmPlan other = pl;
       other.wide = false;
-      other.nt = 2;
-      other.waves = 8;
-      other.mt = 8;
-      other.row_chunks = (m + 127) / 128;
-      return launch_mt<T, 2, 8, MODE>(other, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
+      if (K % 256 == 0 && pl.k_per_split % 256 == 0) {
+        other.nt = 4;
+        other.waves = 4;
+        other.mt = std::max(6, pl.mt);
+      } else {
+        other.nt = 2;
+        other.waves = 8;
+        other.mt = 8;
+      }
+      other.row_chunks = (m + 16 * other.mt - 1) / (16 * other.mt);
+      return launch_nt<T, MODE>(other, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
+    }
+    return hipErrorInvalidValue;
+  }
+  if (pl.nt == 4) {
+    // 128 rows x 64 columns per wave, one wave per SIMD: only for full row chunks in bf16
+    if constexpr (sizeof(T) == 2) {
+      if (pl.waves == 4 && K % 256 == 0 && pl.k_per_split % 256 == 0) {
+        if (pl.mt == 8) return launch_t<T, 8, 4, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
+        if (pl.mt == 7) return launch_t<T, 7, 4, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
+        if (pl.mt == 6) return launch_t<T, 6, 4, 4, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
+      }
     }
     return hipErrorInvalidValue;
   }
@@ -687,7 +777,7 @@ __global__ __launch_bounds__(256) void preshuffle_kernel(const unsigned char* __
 
 }  // namespace
 
-GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split) {
+GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split, bool row_major) {
   GemmPlan pl;
   const int tiles = (m + 15) / 16;
   pl.mt = tiles <= 8 ? (tiles < 1 ? 1 : tiles) : 8;
@@ -703,11 +793,11 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   // two column tiles per wave halve the LDS reads per matrix-core step: a gain once there are several
   // row chunks (the kernel is LDS- and L2-bound there), a loss for a handful of rows (fewer waves in flight)
   pl.nt = (N > t.gemm_nt_big_n || pl.row_chunks > 1) ? 2 : 1;
-  // several row chunks in bf16: gemm_wide_kernel, 128 x 64 outputs per wave; 4 waves per row chunk, and two row chunks
-  // to a workgroup
-  // (the kernel takes any number of whole 128-element chunks, but its splits were only measured on pairs of them)
-  const bool wide = pl.row_chunks > 1 && m >= t.gemm_wide_min_rows && dtype == kBF16 && t.gemm_wide_tiles &&
-                    K % 256 == 0;
+  // several row chunks in bf16: 128 x 64 outputs per wave (gemm_wide_kernel or the rows kernel with four column tiles, see
+  // below).  The latter takes chunks of k in pairs, the former any number of whole ones, measured on pairs as well.
+  // Small row-major matrices are faster with two column tiles (512 rows x 1024 x 1024: 18 us, 22 and 25; 256 x 256 11, 13, 14).
+  const bool wide = pl.row_chunks > 1 && m >= t.gemm_wide_min_rows && dtype == kBF16 && t.gemm_wide_tiles != 0 &&
+                    K % 256 == 0 && !(row_major && t.gemm_wide_tiles == 1 && (size_t)N * K <= ((size_t)1 << 20));
   pl.wide = false;
   pl.rot = t.gemm_rot;
   // 8 waves share one activation chunk in LDS: fewer, fatter workgroups (about 1.5 per compute unit) with
@@ -760,10 +850,10 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   // row tiles per row chunk when the tiles of m rows are dealt evenly to the chunks of so many workgroup rows
   auto dealt = [&](int pairs) { return std::max(5, (tiles + 2 * pairs - 1) / (2 * pairs)); };
   if (wide) {
-    // Workgroup rows of two row chunks: as many as chunks of 8 tiles (of 7 or 6 where that makes their count a multiple
-    // of 8, or keeps it) would fill.  This count was measured on a kernel with one row chunk per workgroup; on this one it is
-    // not always the best: with pre-tiled weights of the LLaDA widths the best of 4 to 8 tiles is 6 % faster on average over
-    // 257-2048 rows (777 rows x 4096 x 4096 43 us, 37 the best; 640 x 24576 x 4096 170, 129), with row-major ones 0 %.
+    // Row chunks of 8 tiles, or of 7 or 6 where that makes their count a multiple of 8, the rows of the block of workgroups
+    // that shares an XCD's L2, or keeps it.  Measured on the rows kernel at the LLaDA widths, 288-2048 rows: fewer tiles in
+    // the same number of row chunks are a gain (288 rows as 3 x 6 tiles -14 %), more row chunks only up to a multiple of 8
+    // (700 rows as 8 x 6 tiles instead of 6 x 8: -16 %; every other count lost 10-40 %).
     const int rc8 = (tiles + 7) / 8;
     int c = 8;
     if (rc8 % kSuperRows != 0)
@@ -772,6 +862,31 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
     if (c == 8)
       for (int x : {6, 7})
         if (c == 8 && (tiles + x - 1) / x == rc8) c = x;
+
+    // The rows kernel: splits by rounds of workgroups over the units, +7 % per additional split (the partials are as large
+    // as the output and there are hundreds of rows of them).
+    GemmPlan one = pl;
+    one.mt = t.gemm_wide_mt != 0 ? t.gemm_wide_mt : c;
+    one.row_chunks = (tiles + one.mt - 1) / one.mt;
+    one.nt = one.waves = 4;
+    one.splits = 1;
+    double best = 1e30;
+    for (int s = 1; s <= max_splits; s *= 2) {
+      int cps = (chunks + s - 1) / s;
+      cps += cps & 1;
+      if (s > 1 && cps < 4) break;
+      const int eff = (chunks + cps - 1) / cps;
+      const int wgs = ((N + 255) / 256) * one.row_chunks * eff;
+      const double cost = (double)((wgs + kUnits - 1) / kUnits) * cps * (1.0 + 0.07 * (eff - 1));
+      if (cost < best * 0.999) {
+        best = cost;
+        one.splits = s;
+      }
+    }
+
+    // gemm_wide_kernel: as many workgroup rows as pairs of those chunks, their tiles dealt evenly.  On this kernel the count is
+    // not always the best: with pre-tiled weights of the LLaDA widths the best of 4 to 8 tiles is 6 % faster on average over
+    // 257-2048 rows (777 rows x 4096 x 4096 43 us, 37 the best; 640 x 24576 x 4096 170, 129), with row-major ones 0 %.
     pl.wide = true;
     pl.mt = t.gemm_wide_mt != 0 ? t.gemm_wide_mt : dealt(((tiles + c - 1) / c + 1) / 2);
     pl.row_chunks = (tiles + pl.mt - 1) / pl.mt;
@@ -781,7 +896,7 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
     // reads m x N partial sums at about 5.5 TB/s.  Any count of splits: Dream's QKV at 768 rows runs 3.
     const int pairs = (pl.row_chunks + 1) / 2;
     const double chunk_us = 0.35 * pl.mt, split_us = single_split ? 0.0 : (double)m * N * 8e-6 / 5.5;
-    double best = 1e30;
+    best = 1e30;
     for (int nt : {4, 3})
       for (int s = 1; s <= max_splits; ++s) {
         int cps = (chunks + s - 1) / s;
@@ -796,6 +911,39 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
           pl.nt = nt;
         }
       }
+
+    // The line between the two: time in us, fitted to both kernels on 257-12288 rows and 100 matrices from 16 x 256 to
+    // 37888 x 3584 (1926 sizes; 96 % of the predictions within 15 %).  A round of workgroups costs a start, per chunk of k a
+    // part per row tile and one for the columns (row-major weights, read in operand order, make that the larger), and per row
+    // tile the gate; a round that does not fill the chip costs `tail` and its share of the rest; a split costs a part and its
+    // partial sums.  gemm_wide_kernel has half the workgroups, so it loses where these no longer fill the chip: 1024 rows x
+    // 8192 x 4096 65 us in the rows kernel, 78 in the other, but 512 x 12288 x 4096 89 and 62.  Taking the cheaper by this
+    // gains 23 % pre-tiled over the rows kernel alone, always the faster 23.5 %, gemm_wide_kernel alone 21 %; row-major 12, 13
+    // and 7 %.  Its mistakes cost up to 8 % against the rows kernel (10 % row-major, in 12 sizes of the 1926 above 3 %).
+    struct Cost { double start, round, tile, cols, gate, tail, split, part, out; };
+    static constexpr Cost one_pre{1.6, 5.6, 0.195, 0.11, 0.25, 0.7, 4.5, 0.23, 0.10}, wide_pre{0.0, 5.1, 0.31, 0.20, 0.95, 0.7, 2.5, 0.28, 0.13},
+        one_rows{2.2, 6.9, 0.106, 1.48, 0.0, 0.8, 4.5, 0.22, 0.10}, wide_rows{0.5, 7.0, 0.166, 2.92, 0.0, 0.8, 3.0, 0.26, 0.12};
+    auto shape_us = [&](const GemmPlan& q, int s, const Cost& k) {
+      int cps = (chunks + s - 1) / s;
+      cps += cps & 1;
+      const int eff = (chunks + cps - 1) / cps;
+      const int rows = (q.row_chunks + q.chunks_per_wg() - 1) / q.chunks_per_wg(), cols = q.cols_per_wg();
+      const int per_xcd = (((N + cols - 1) / cols) * eff + 7) / 8;      // weight tiles of an XCD
+      // an XCD's workgroups go to its four groups of 8 units in turn: workgroups that leave at once (padding of the blocks of
+      // kSuperRows rows) give the groups unequal shares
+      const double full = !q.wide || rows > kSuperRows ? per_xcd * ((rows + 3) / 4) / 8.0 : per_xcd * rows / 32.0;
+      const double whole = std::floor(full), rest = full - whole;
+      const double rounds = whole < 1.0 ? 1.0 : whole + (rest > 0.0 ? k.tail + (1.0 - k.tail) * rest : 0.0);
+      const double width = q.nt == 3 ? 0.8 : 1.0, mb = 4e-6 * m * N;
+      return k.start + rounds * (k.round + width * (cps * (k.tile * q.mt + k.cols) + (single_split ? k.gate * q.mt : 0.0))) +
+             (eff > 1 ? k.split + k.part * mb * eff : 0.0) + k.out * mb * (single_split ? 0.25 : 1.0);
+    };
+    const double one_us = shape_us(one, one.splits, row_major ? one_rows : one_pre);
+    const double wide_us = shape_us(pl, splits, row_major ? wide_rows : wide_pre) * (row_major ? 1.03 : 1.0);
+    if (t.gemm_wide_tiles == 3 || (t.gemm_wide_tiles != 2 && one_us < wide_us)) {
+      pl = one;
+      splits = one.splits;
+    }
   }
   int chunks_per_split = (chunks + splits - 1) / splits;
   if (wide) chunks_per_split += chunks_per_split & 1;
@@ -804,8 +952,8 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   // Two row chunks (193-256 rows) are one workgroup of the wide kernel as well: where that fills the chip (the head on all
   // masked rows of a first step, 256 rows x 126464 columns: 374 -> 317 us), not for a block's matrices (96 column
   // blocks at most).
-  if (!wide && dtype == kBF16 && pl.nt == 2 && pl.row_chunks == 2 && t.gemm_wide_tiles && K % kc == 0 &&
-      ((N + 255) / 256) * pl.splits >= 3 * kUnits / 4) {
+  if (!wide && dtype == kBF16 && pl.nt == 2 && pl.row_chunks == 2 && K % kc == 0 &&
+      ((t.gemm_wide_tiles == 1 && ((N + 255) / 256) * pl.splits >= 3 * kUnits / 4) || t.gemm_wide_tiles == 2)) {
     pl.wide = true;
     pl.mt = dealt(1);
     pl.nt = 4;

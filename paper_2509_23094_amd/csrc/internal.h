@@ -15,10 +15,11 @@ inline size_t dtype_size(int dt) { return dt == kBF16 ? 2 : 4; }
 struct Tunables {
   int gemm_target_wgs = 384;   // aim for at least this many groups of 4 waves per GEMM
   int gemm_max_splits = 8;
-  int gemm_wide_min_rows = 257; // gemm_wide_kernel from this many rows on (fewer: see the end of plan_gemm)
+  int gemm_wide_min_rows = 257; // these from this many rows on (fewer: see the end of plan_gemm)
   int gemm_tall_chunk = 1;      // 129-192 bf16 rows as ONE row chunk of 10 or 12 row tiles
-  int gemm_wide_tiles = 1;     // many bf16 rows: gemm_wide_kernel, 128 x 64 outputs per wave, two row chunks per workgroup
-  int gemm_wide_mt = 0;        // row tiles per row chunk of gemm_wide_kernel: 6, 7, 8; 0 = by shape
+  int gemm_wide_tiles = 1;     // many bf16 rows, 128 x 64 outputs per wave: 0 = never, 1 = the faster by plan_gemm's estimate,
+                               // 2 = gemm_wide_kernel, 3 = gemm_rows_kernel with four column tiles
+  int gemm_wide_mt = 0;        // row tiles per row chunk of these: 6, 7, 8; 0 = by shape
   int gemm_nt_big_n = 1 << 30; // N above this uses two column tiles per wave even for few rows (measured slower);
                                // more than 128 rows always do
   int gemm_waves = 0;          // waves per workgroup sharing one activation chunk in LDS: 4, 6, 8, 10; 0 = by shape
@@ -38,7 +39,7 @@ bool set_tunable(Tunables& t, const char* name, int value);
 // ---- GEMM on a ragged handful of rows: P[s] = A[m,K] * W[N,K]^T over the k-range of split s
 struct GemmPlan {
   int mt;        // 16-row tiles per row chunk (1..8, 10, 12)
-  int nt;        // 16-column tiles per wave (1 or 2; wide: 3 or 4)
+  int nt;        // 16-column tiles per wave (1, 2 or 4; wide: 3 or 4)
   int waves;     // waves per workgroup (4, 6, 7, 8 or 10), each owning 16*nt output columns
   int splits;    // k splits (partials to be summed by the consumer)
   int k_per_split;
@@ -49,7 +50,8 @@ struct GemmPlan {
   int chunks_per_wg() const { return wide ? 2 : 1; }
   int cols_per_wg() const { return 16 * nt * waves / chunks_per_wg(); }
 };
-GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split = false);
+// single_split: one split, and the matrix is the gate/up pair with the gated epilogue.  row_major: W as the caller has it.
+GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split = false, bool row_major = false);
 // P must hold plan.splits * split_stride floats; split_stride >= m * ldp.
 // pre = W is a pre-tiled copy made by launch_preshuffle (then ldw = 256-byte chunks per row).
 hipError_t launch_gemm(int dtype, const GemmPlan& plan, const void* A, int lda, const void* W, int ldw,

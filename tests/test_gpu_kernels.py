@@ -674,36 +674,52 @@ def test_rollout_update_and_influence_at_the_size_rules(B, L, m):
     ctx.close()
 
 
+@pytest.mark.parametrize("kernel", [2, 3])
 @pytest.mark.parametrize("m,N,K", [(257, 40, 256), (289, 1000, 512), (385, 264, 768), (513, 256, 2304), (777, 72, 256), (1153, 520, 512),
-                                   (289, 16391, 2056), (513, 8200, 4104)])         # the last two: past the narrow shape's limit
-def test_linear_parity_many_rows(B, m, N, K):
-    """Two row chunks per workgroup: odd counts of chunks, 5 to 8 row tiles, ragged rows and columns, one chunk pair of k."""
+                                   (289, 16391, 2304), (513, 8200, 4352), (1500, 200, 1280), (900, 3000, 1536)])
+def test_linear_parity_many_rows(B, m, N, K, kernel):
+    """Row-major weights in both kernels for many rows (gemm_wide_tiles 2: two row chunks per workgroup, 3: one): odd counts of
+    row chunks, 5 to 8 row tiles, 256 and 192 columns, ragged rows and columns, one chunk pair of k and several splits."""
+    test_linear_parity(B, "bf16", m, N, K, tunables={"gemm_wide_tiles": kernel})
+
+
+@pytest.mark.parametrize("m,N,K", [(193, 40, 128), (200, 520, 640), (256, 1000, 384)])
+def test_linear_parity_two_row_chunks(B, m, N, K):
+    """193-256 rows as one workgroup row of the same kernel, counts of 128-element chunks that are odd among them."""
+    test_linear_parity(B, "bf16", m, N, K, tunables={"gemm_wide_tiles": 2})
+
+
+@pytest.mark.parametrize("m,N,K", [(300, 33000, 1280), (400, 520, 512), (256, 512 * 96, 128)])
+def test_linear_parity_many_rows_by_shape(B, m, N, K):
+    """The planner's own choice (two row chunks per workgroup, two column tiles per wave, 193-256 rows that fill the chip)."""
     test_linear_parity(B, "bf16", m, N, K)
 
 
-@pytest.mark.parametrize("m", [257, 300, 449])
-def test_refresh_layer_parity_many_rows(B, m):
+@pytest.mark.parametrize("kernel", [2, 3])
+@pytest.mark.parametrize("m", [257, 300, 449, 700])
+def test_refresh_layer_parity_many_rows(B, m, kernel):
     """The same with pre-tiled weights and the gated epilogue; widths that leave the last column block ragged."""
-    _refresh_layer_parity(B, f"bf16-{m}-rows", W.ModelDims(1, 512, 4, 4, 128, 1280, 64, dtype="bf16"), m + 30, m)
+    _refresh_layer_parity(B, f"bf16-{m}-rows", W.ModelDims(1, 512, 4, 4, 128, 1280, 64, dtype="bf16"), m + 30, m,
+                          tunables={"gemm_wide_tiles": kernel})
 
 
-def test_linear_many_rows_unaligned(B):
-    """Activations that are not 16-byte aligned cannot be staged straight into LDS: the same result by another kernel, up
-    to summation order in fp32 (K = 512: relative 512 * 6e-8)."""
-    m, N, K = 300, 520, 512
-    say("linear many rows, unaligned activations")
+@pytest.mark.parametrize("m,N,K", [(300, 520, 512), (449, 264, 2304), (230, 520, 640)])
+def test_linear_many_rows_unaligned(B, m, N, K):
+    """Activations that are not 16-byte aligned cannot be staged straight into LDS: gemm_wide_kernel's splits by another kernel
+    (one row chunk per workgroup, or two column tiles per wave where a split is no pair of chunks)."""
+    say(f"linear many rows, unaligned activations m={m} N={N} K={K}")
     wd = W.ModelDims(1, 512, 4, 4, 128, 512, 64, dtype="bf16")
-    ctx, _, _ = _ctx_for(B, wd, max_seq=m)
-    a0, w = (torch.from_numpy(W.round_bf16(W.hidden_rows(s, r, K))).to(torch.bfloat16).cuda() for s, r in ((1, m), (2, N)))
-    got = []
+    ctx, _, _ = _ctx_for(B, wd, max_seq=m, tunables={"gemm_wide_tiles": 2})
+    a_np, w_np = (W.round_bf16(W.hidden_rows(s, r, K)) for s, r in ((1, m), (2, N)))
+    a0, w = (torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (a_np, w_np))
+    ref = a_np.astype(np.float64) @ w_np.astype(np.float64).T
     for off in (0, 1):
         a = torch.zeros(m * K + 8, dtype=torch.bfloat16, device="cuda")[off: off + m * K].view(m, K)
         a.copy_(a0)
-        out = torch.zeros((m, N), device="cuda")
+        out = torch.full((m, N), 7.0, device="cuda")
         ctx.d2c_linear(a, w, m, N, K, out)
         torch.cuda.synchronize()
-        got.append(host(out))
-    assert rel_l2(got[1], got[0]) < 3e-5
+        assert rel_l2(host(out), ref) < 1e-5
     ctx.close()
 
 

@@ -37,7 +37,7 @@ def test_plan_covers_rows_and_contraction_and_keeps_the_kernel_assumptions(dtype
         assert p["k_per_split"] % elem_per_chunk == 0, where                        # splits start on chunk boundaries
         assert 1 <= p["splits"] <= 8 and (not single or p["splits"] == 1), where
         assert p["waves"] in (4, 6, 7, 8, 10) and p["col_tiles_per_wave"] in (1, 2, 3, 4), where
-        wide = p["col_tiles_per_wave"] > 2
+        wide = p["col_tiles_per_wave"] > 2 and p["waves"] == 8
         cols = 16 * p["col_tiles_per_wave"] * p["waves"] // (2 if wide else 1)
         assert p["workgroups"] == -(-N // cols) * p["splits"] * p["row_chunks"], where
         if wide:
@@ -47,6 +47,10 @@ def test_plan_covers_rows_and_contraction_and_keeps_the_kernel_assumptions(dtype
             if m < 257:                                # one workgroup row, where it fills three quarters of the chip
                 assert p["row_chunks"] == 1 and p["workgroups"] >= 192, where
             continue
+        if p["col_tiles_per_wave"] == 4:
+            # the hand-pipelined loop of one row chunk per workgroup: 6-8 row tiles, 4 waves, chunks taken in pairs
+            assert dtype == "bf16" and p["row_tiles"] in (6, 7, 8) and p["waves"] == 4 and m >= 257, where
+            assert K % 256 == 0 and p["k_per_split"] % 256 == 0, where
         if p["row_tiles"] > 8:
             # the tall single chunk: bf16 only, even tile counts up to 12, 8 waves, one column tile per wave
             assert dtype == "bf16" and p["row_tiles"] in (10, 12) and p["row_chunks"] == 1, where
@@ -66,6 +70,17 @@ def test_plan_rows_per_workgroup_for_many_rows():
     p = _plan("bf16", 256, 126464, 4096, True)
     assert (p["row_tiles"], p["row_chunks"], p["col_tiles_per_wave"], p["waves"], p["workgroups"]) == (16, 1, 4, 8, 494)
     assert _plan("bf16", 256, 12288, 4096)["col_tiles_per_wave"] == 2
+
+
+def test_plan_many_rows_one_or_two_row_chunks_per_workgroup():
+    """Sizes measured in both kernels for many rows, where they differ by 10 % and more: two row chunks per workgroup where
+    that fills the chip, one where it does not."""
+    for m, N, K, single, waves in ((777, 5632, 1024, False, 4), (1024, 8192, 4096, False, 4), (860, 8192, 3584, False, 4),
+                                   (1500, 4096, 4096, False, 4), (512, 2048, 256, True, 4), (1024, 11264, 2048, True, 8),
+                                   (512, 24576, 4096, True, 8), (512, 12288, 4096, False, 8), (300, 4096, 12288, False, 8),
+                                   (640, 3584, 18944, False, 8), (3440, 3584, 3584, False, 8), (2048, 11264, 2048, False, 8)):
+        p = _plan("bf16", m, N, K, single)
+        assert p["waves"] == waves and p["col_tiles_per_wave"] in ((4,) if waves == 4 else (3, 4)), (m, N, K, single, p)
 
 
 def test_plan_at_the_benchmark_shapes():
