@@ -450,7 +450,7 @@ template <int MT, int NT, int MODE>
 __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restrict__ A, int lda, const bf16* __restrict__ W,
                                                            int ldw, float* __restrict__ P, int ldp, size_t split_stride,
                                                            int m, int N, int K, int k_per_split, int n_blocks,
-                                                           int n_splits, int pairs, bf16* __restrict__ act) {
+                                                           int n_splits, int pairs, int rot_mul, bf16* __restrict__ act) {
   constexpr bool PRE = MODE != kRowMajor;
   constexpr int E = 8, KS = 32, KC = 128;
   constexpr int kBlockElems = 16 * KC;
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restric
     for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   auto stage = [&](int buf, int chunk) {
-    const int soff = (k_begin + min(chunk, last_chunk) * KC) * 2;
+    const int soff = (k_begin + chunk * KC) * 2;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -520,19 +520,23 @@ __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restric
           soff, 0, 0);
   };
   auto load_b_step = [&](int chunk, int step) {
-    const size_t off = (size_t)min(chunk, last_chunk) * (PRE ? kBlockElems : KC) + step * (PRE ? 64 * E : KS);
+    const size_t off = (size_t)chunk * (PRE ? kBlockElems : KC) + step * (PRE ? 64 * E : KS);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) b[nt][step].raw = ld16(wrow[nt] + off);
   };
-  stage(0, 0);
+  // the walk over the chunks starts at a multiple of the column block, as in the rows kernel; behind the last chunk it
+  // requests that one again (an L2 hit, never used)
+  int at = (int)(((unsigned)bx * (unsigned)rot_mul) % (unsigned)n_chunks);
+  stage(0, at);
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s) load_b_step(0, s);
+  for (int s = 0; s < kSteps; ++s) load_b_step(at, s);
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0x70 | 0xf00);                  // vmcnt(0)
   __syncthreads();
   constexpr int NI = kSteps * MT;
   for (int c = 0; c < n_chunks; ++c) {
-    stage((c & 1) ^ 1, c + 1);
+    if (c < last_chunk) at = at == last_chunk ? 0 : at + 1;
+    stage((c & 1) ^ 1, at);
     __builtin_amdgcn_sched_barrier(0);
     const unsigned char* abuf = lds + (c & 1) * kBuf + part * (MT * 4096) + (r * 4 + (g ^ (r >> 1 & 3))) * 16;
     auto read_af = [&](int i) {
@@ -549,7 +553,7 @@ __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restric
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) mfma16(acc[i % MT][nt], af[i % 4], b[nt][i / MT]);
       if (i + 3 < NI) af[(i + 3) % 4] = read_af(i + 3);
-      if (i % MT == MT - 1) load_b_step(c + 1, i / MT);
+      if (i % MT == MT - 1) load_b_step(at, i / MT);
     }
     __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
 #pragma unroll
@@ -632,7 +636,7 @@ hipError_t launch_wide_t(const GemmPlan& pl, int pairs, const void* A, int lda, 
   const int cols_st = 32 / rows_st;
   const dim3 grid(8 * ((groups + cols_st - 1) / cols_st) * ((pairs + rows_st - 1) / rows_st) * (rows_st * cols_st));
   hipLaunchKernelGGL((gemm_wide_kernel<MT, NT, MODE>), grid, dim3(512), 0, st, (const bf16*)A, lda, (const bf16*)W, ldw, P,
-                     ldp, split_stride, m, N, K, pl.k_per_split, n_blocks, pl.splits, pairs, (bf16*)act);
+                     ldp, split_stride, m, N, K, pl.k_per_split, n_blocks, pl.splits, pairs, pl.rot, (bf16*)act);
   return hipGetLastError();
 }
 template <int MODE>

@@ -683,6 +683,29 @@ def test_linear_parity_many_rows(B, m, N, K, kernel):
     test_linear_parity(B, "bf16", m, N, K, tunables={"gemm_wide_tiles": kernel})
 
 
+@pytest.mark.parametrize("kernel", [0, 2, 3])
+def test_linear_many_rows_start_chunk(B, kernel):
+    """gemm_rot moves the first chunk of a workgroup's walk over k in every kernel for many rows: the same sums in another
+    order, so other low bits somewhere in 300 x 1000 results of 2304 products (one in four rounds differently), same values."""
+    m, N, K = 300, 1000, 2304
+    say(f"linear many rows, start chunk, kernel {kernel}")
+    wd = W.ModelDims(1, 256, 4, 4, 64, 80, 64, dtype="bf16")
+    ctx, _, _ = _ctx_for(B, wd, max_seq=m, tunables={"gemm_wide_tiles": kernel, "gemm_max_splits": 1})
+    a, w = W.round_bf16(W.hidden_rows(11, m, K)), W.round_bf16(W.hidden_rows(12, N, K, std=0.05))
+    ad, wdv = B.to_device(a, "bf16"), B.to_device(w, "bf16")
+    ref = a.astype(np.float64) @ w.astype(np.float64).T
+    got = []
+    for rot in (0, 5):
+        ctx.set_tunable("gemm_rot", rot)
+        out = torch.full((m, N), 7.0, device="cuda")
+        ctx.d2c_linear(ad, wdv, m, N, K, out)
+        torch.cuda.synchronize()
+        assert rel_l2(host(out), ref) < 1e-5
+        got.append(out)
+    assert not torch.equal(got[0], got[1]) and torch.equal(got[0][:, :128], got[1][:, :128])     # the first column block starts at 0
+    ctx.close()
+
+
 @pytest.mark.parametrize("m,N,K", [(193, 40, 128), (200, 520, 640), (256, 1000, 384)])
 def test_linear_parity_two_row_chunks(B, m, N, K):
     """193-256 rows as one workgroup row of the same kernel, counts of 128-element chunks that are odd among them."""
