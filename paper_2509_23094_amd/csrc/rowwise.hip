@@ -322,20 +322,22 @@ __global__ void sum_splits_kernel(float* __restrict__ dst, const float* __restri
   }
 }
 
-// The same for whole 16-byte pieces: a piece per thread, its splits' loads issued together: d2c_linear on 17 rows
-// x 4096 x 4096 (eight splits) 18.9 -> 12.3 us a call.
-__global__ __launch_bounds__(kThreads) void sum_splits_vec_kernel(float* __restrict__ dst, const float* __restrict__ P,
-                                                                  int n_splits, size_t split_stride, size_t n4) {
-  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+// The same for whole 16-byte pieces: a piece per thread, the loads of its splits issued together.  Workgroups of one wave
+// take 256 floats each: where a split's columns were written in blocks of 256 (193-256 rows), they are in the L2 of the XCD
+// that reads them.  Eight splits of 17 x 4096: 9.4 us a value per thread, 2.2 now; eight of 224 x 2048: 4.9 and, with
+// four waves in a workgroup, 7.7; 2.3 now; two of 256 x 16384: 9.1, 9.7, 8.2.
+template <int SPLITS>
+__global__ __launch_bounds__(kWave) void sum_splits_vec_kernel(float* __restrict__ dst, const float* __restrict__ P,
+                                                               size_t split_stride, size_t n4) {
+  const size_t i = (size_t)blockIdx.x * kWave + threadIdx.x;
   if (i >= n4) return;
   const float* p = P + i * 4;
-  f32x4 v[8];                                            // at most 8 splits; past the end the last one again, not added
+  f32x4 v[SPLITS];
 #pragma unroll
-  for (int s = 0; s < 8; ++s) v[s] = *reinterpret_cast<const f32x4*>(p + (size_t)min(s, n_splits - 1) * split_stride);
+  for (int s = 0; s < SPLITS; ++s) v[s] = *reinterpret_cast<const f32x4*>(p + (size_t)s * split_stride);
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int s = 0; s < 8; ++s)
-    if (s < n_splits) sum += v[s];
+  for (int s = 0; s < SPLITS; ++s) sum += v[s];
   *reinterpret_cast<f32x4*>(dst + i * 4) = sum;
 }
 
@@ -503,10 +505,17 @@ hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s
 
 hipError_t launch_sum_splits(float* dst, const float* P, int n_splits, size_t split_stride, size_t n, hipStream_t st) {
   if (n == 0) return hipSuccess;
-  if (n % 4 == 0 && split_stride % 4 == 0 && (((uintptr_t)dst | (uintptr_t)P) & 15) == 0 && n_splits >= 1 && n_splits <= 8) {
-    hipLaunchKernelGGL(sum_splits_vec_kernel, dim3((unsigned)((n / 4 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, dst, P,
-                       n_splits, split_stride, n / 4);
-    return hipGetLastError();
+  if (n % 4 == 0 && split_stride % 4 == 0 && (((uintptr_t)dst | (uintptr_t)P) & 15) == 0) {
+    const dim3 grid((unsigned)((n / 4 + kWave - 1) / kWave)), wave(kWave);
+    switch (n_splits) {
+#define D2C_SUM(S_)                                                                                                   \
+  case S_:                                                                                                            \
+    hipLaunchKernelGGL(sum_splits_vec_kernel<S_>, grid, wave, 0, st, dst, P, split_stride, n / 4);                    \
+    return hipGetLastError()
+      D2C_SUM(1); D2C_SUM(2); D2C_SUM(3); D2C_SUM(4); D2C_SUM(5); D2C_SUM(6); D2C_SUM(7); D2C_SUM(8);
+#undef D2C_SUM
+      default: break;
+    }
   }
   const int blocks = (int)((n + 1023) / 1024 < 2048 ? (n + 1023) / 1024 : 2048);
   hipLaunchKernelGGL(sum_splits_kernel, dim3(blocks), dim3(256), 0, st, dst, P, n_splits, split_stride, n);

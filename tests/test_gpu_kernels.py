@@ -64,6 +64,15 @@ def test_linear_parity_every_workgroup_width(B, waves, dtype, m, N, K):
     test_linear_parity(B, dtype, m, N, K, tunables={"gemm_waves": waves})
 
 
+@pytest.mark.parametrize("N", [64, 63])
+@pytest.mark.parametrize("splits", [2, 3, 4, 5, 6, 7, 8])
+def test_linear_parity_every_split_count(B, splits, N):
+    """The partial sums of 2 to 8 splits of k added in pieces of 16 bytes (20 x 64) and value by value (21 x 63)."""
+    m, K = 20 if N == 64 else 21, 256 * splits
+    assert B.d2c_plan_projection("bf16", m, N, K)["splits"] == splits
+    test_linear_parity(B, "bf16", m, N, K)
+
+
 # ------------------------------------------------------------------ attention (config "C2" and edge shapes)
 ATTN_CASES = [
     # dtype, H, Hkv, dh, L, m, kernels ("few": the few-row kernels, "tiled": the LDS-tiled ones, "default":
