@@ -781,6 +781,20 @@ __global__ __launch_bounds__(256) void preshuffle_kernel(const unsigned char* __
 
 }  // namespace
 
+// Row-major weights through LDS or in operand order.  The slots leave room for one workgroup on a compute unit where two fit
+// without them, and a workgroup of few chunks is over before its queue is full, so short contractions lose: with 64-128
+// elements of k on 1-128 rows x 65536 columns up to 11 %, a handful of workgroups (N = 64, 256) up to 20 % of 4 us; 7 row
+// tiles (157 KB of LDS) still 11 % with 512.  From two chunks in one round of workgroups, or four in several, they gain (1-128
+// rows x 4096 x 2048 10 %).  In float they gain with 5 row tiles and more in one round (5 %; 4-16 % lost in several), with fewer
+// only where the round is full and not too long (6 %; 15 % lost on 1 and 17 rows x 16384 x 4096, 32 chunks each).
+static bool staging_pays(int dtype, const GemmPlan& pl, int N) {
+  const int wgs = ((N + 16 * pl.waves - 1) / (16 * pl.waves)) * pl.splits;
+  const int chunks = pl.k_per_split / (dtype == kBF16 ? 128 : 64);
+  if (dtype != kBF16) return wgs <= 256 && (pl.mt >= 5 || (wgs >= 200 && chunks >= 3 && chunks <= 16));
+  if (wgs > 256) return chunks >= (pl.mt == 7 ? 8 : 4);
+  return chunks >= 3 || (chunks == 2 && wgs >= 64);
+}
+
 GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split, bool row_major) {
   GemmPlan pl;
   const int tiles = (m + 15) / 16;
@@ -982,7 +996,8 @@ hipError_t launch_gemm(int dtype, const GemmPlan& pl, const void* A, int lda, co
       return launch_nt<bf16, kPre>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);
     return launch_nt<float, kPre>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);
   }
-  if (pl.nt == 1 && (uintptr_t)W % 16 == 0 && (size_t)ldw * dtype_size(dtype) * 16 < (1ull << 31)) {
+  if (pl.nt == 1 && (uintptr_t)W % 16 == 0 && (size_t)ldw * dtype_size(dtype) * 16 < (1ull << 31) &&
+      staging_pays(dtype, pl, N)) {
     if (dtype == kBF16)
       return launch_rows_staged<bf16>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st);
     return launch_rows_staged<float>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st);

@@ -779,16 +779,18 @@ def test_attention_parity_staged_rows(B, H, Hkv, dh, L, m):
     ctx.close()
 
 
-@pytest.mark.parametrize("dtype,m,N,K", [("bf16", 1, 16, 128), ("bf16", 97, 1007, 1160), ("bf16", 113, 2600, 392), ("bf16", 145, 333, 1032),
-                                         ("f32", 33, 257, 68), ("f32", 120, 1000, 516)])
+@pytest.mark.parametrize("dtype,m,N,K", [("bf16", 1, 16, 392), ("bf16", 97, 1007, 1160), ("bf16", 113, 2600, 392), ("bf16", 145, 333, 1032),
+                                         ("f32", 77, 257, 68), ("f32", 120, 1000, 516), ("f32", 33, 26001, 196)])
 def test_linear_parity_staged_weights(B, dtype, m, N, K):
-    """Row-major weights staged through LDS: ragged last chunk and last rows, three slots, two slots (many rows, 10 waves) and
-    none; and weights that are not 16-byte aligned, which take the loads in operand order: the same bits."""
-    test_linear_parity(B, dtype, m, N, K)
+    """Row-major weights staged through LDS (unsplit contractions of three chunks and more, float with five row tiles or a full
+    round of workgroups): ragged last chunk and last rows, three slots, two slots (many rows, 10 waves) and none; and weights
+    that are not 16-byte aligned, which take the loads in operand order: the same bits."""
+    tun = {"gemm_max_splits": 1}
+    test_linear_parity(B, dtype, m, N, K, tunables=tun)
     if dtype == "bf16":
-        test_linear_parity(B, dtype, m, N, K, tunables={"gemm_waves": 10})
+        test_linear_parity(B, dtype, m, N, K, tunables={"gemm_waves": 10, **tun})
     wd = W.ModelDims(1, 128, 2, 2, 64, 128, 64, dtype=dtype)
-    ctx, _, _ = _ctx_for(B, wd, max_seq=m)
+    ctx, _, _ = _ctx_for(B, wd, max_seq=m, tunables=tun)
     t = B.torch_dtype(dtype)
     a = B.to_device(W.round_bf16(W.hidden_rows(1, m, K)), dtype)
     w0 = B.to_device(W.round_bf16(W.hidden_rows(2, N, K)), dtype)
