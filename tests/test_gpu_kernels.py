@@ -756,10 +756,10 @@ def test_linear_many_rows_unaligned(B, m, N, K):
 
 
 @pytest.mark.parametrize("H,Hkv,dh,L,m", [(8, 8, 128, 1, 1), (8, 2, 128, 33, 15), (8, 8, 128, 257, 1), (8, 2, 128, 289, 15),
-                                          (32, 32, 128, 513, 17), (28, 4, 128, 1025, 47), (4, 4, 64, 511, 16), (4, 1, 64, 257, 33),
+                                          (32, 32, 128, 513, 17), (28, 4, 128, 1025, 47), (4, 4, 64, 511, 16), (4, 1, 64, 351, 33),
                                           (40, 8, 128, 1024, 120), (40, 8, 128, 351, 113), (40, 8, 128, 350, 113)])
 def test_attention_parity_staged_rows(B, H, Hkv, dh, L, m):
-    """The few-row kernel with K and Q staged through LDS (from 257 keys on, 351 where a workgroup has all columns): ragged
+    """The few-row kernel with K and Q staged through LDS (from 257 keys on where two workgroups share the columns, 351 elsewhere): ragged
     pairs, waves with one pair and with several, both widths of the output share; below it one key and waves without a pair; and
     the same values with a K cache that is not 16-byte aligned (loads in operand order), bit for bit."""
     say(f"attention staged H={H} Hkv={Hkv} dh={dh} L={L} m={m}")
