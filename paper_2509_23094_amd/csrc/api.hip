@@ -469,7 +469,7 @@ int d2c_init_tuned(const d2c_dims* dims, const d2c_weights* w, const d2c_tunable
       (rc = ws_alloc(c, &c->partial, pf * 4)) ||
       (rc = ws_alloc(c, &c->head_a, (size_t)c->head_rows * d * ts)) ||
       (rc = ws_alloc(c, &c->logits, (size_t)c->head_rows * D.vocab * 4)) ||
-      (rc = ws_alloc(c, &c->conf_part, confidence_scratch_floats((int)c->max_rows) * 4)) ||
+      (rc = ws_alloc(c, &c->conf_part, confidence_scratch_floats(c->max_rows, D.vocab) * 4)) ||
       (rc = ws_alloc(c, &c->rope_cos, Lm * (D.head_dim / 2) * 4)) ||
       (rc = ws_alloc(c, &c->rope_sin, Lm * (D.head_dim / 2) * 4)))
     return bail(rc);
@@ -654,7 +654,7 @@ int d2c_select_static(const d2c_params* p, int32_t vocab, const float* logits, c
   if (L <= 0 || L > select_max_len())
     return fail(nullptr, D2C_ESHAPE, "L outside (0, " + std::to_string(select_max_len()) + "]");
   if (prompt_len < 0 || prompt_len > L) return fail(nullptr, D2C_EINVAL, "prompt_len outside [0, L]");
-  if (confidence_scratch_floats(n_rows) > kStaticFloats) return fail(nullptr, D2C_ESHAPE, "scratch array too small");
+  if (confidence_scratch_floats(n_rows, vocab) > kStaticFloats) return fail(nullptr, D2C_ESHAPE, "scratch array too small");
   float* sp = nullptr;
   if ((rc = static_scratch(&sp))) return rc;
   hipStream_t st = (hipStream_t)stream;

@@ -178,9 +178,9 @@ hipError_t launch_influence_chain(const ChainCall* calls, int n_calls, size_t la
 // ---- selection
 // Eq. 1 in two parts: per logits row and chunk of the vocabulary (max, argmax, sum of exp), confidence_chunks(vocab)
 // triples per row in part; launch_select merges the rows' chunks into conf and pred before it selects.
-// part: confidence_scratch_floats(n_rows) floats
-size_t confidence_scratch_floats(int n_rows);
-int confidence_chunks(int vocab);
+// part: confidence_scratch_floats(n_rows, vocab) floats
+int confidence_chunks(int vocab);                       // 1..64
+size_t confidence_scratch_floats(size_t n_rows, int vocab);
 hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st);
 struct SelectArgs {
   float sigma; int k; float p; int block_len; int n_unmask; int cand_mode; float threshold; int conf_decode;

@@ -1173,13 +1173,14 @@ __global__ __launch_bounds__(kSelThreads) void seq_reset_kernel(const uint8_t* _
 
 int select_max_len() { return kSelMaxL; }
 
-size_t confidence_scratch_floats(int n_rows) { return (size_t)n_rows * kConfMaxChunks * 3; }
 
 int confidence_chunks(int vocab) {
   int chunk = kConfChunk;
   while ((vocab + chunk - 1) / chunk > kConfMaxChunks) chunk *= 2;
   return (vocab + chunk - 1) / chunk;
 }
+
+size_t confidence_scratch_floats(size_t n_rows, int vocab) { return n_rows * confidence_chunks(vocab) * 3; }
 
 hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st) {
   if (n_rows <= 0) return hipSuccess;

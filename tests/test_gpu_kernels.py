@@ -572,6 +572,23 @@ def test_confidence_does_not_depend_on_the_other_rows(B, V):
     ctx.close()
 
 
+def test_workspace_holds_the_chunk_triples_of_the_vocabulary(B):
+    """Eq. 1's chunk triples are held for every row of a group and every chunk that the vocabulary has, no more: 8192 entries
+    (one chunk) against 65536 (eight), 4 sequences of 512 positions."""
+    say("workspace of two vocabularies")
+    ws = []
+    for V in (8192, 65536):
+        wd = W.ModelDims(1, 64, 4, 4, 16, 80, V, dtype="f32")
+        mdl = W.model_weights(W.ModelDims(1, 64, 4, 4, 16, 80, 8, dtype="f32"), 0)
+        mdl["tok_emb"] = mdl["lm_head"] = np.zeros((V, 64), np.float32)
+        ctx = B.Context(wd, mdl, 512, max_batch=4)
+        info = ctx.memory_info()
+        ws.append(info["total_bytes"] - info["pretiled_weight_bytes"])
+        ctx.close()
+    head_rows = 256
+    assert ws[1] - ws[0] == head_rows * (65536 - 8192) * 4 + 4 * 512 * (8 - 1) * 3 * 4
+
+
 @pytest.mark.parametrize("n_rows,V", [(1, 8192), (17, 8193), (256, 40000), (257, 40000), (40, 8192 * 33)])
 def test_select_merges_every_logit_row(B, n_rows, V):
     """Eq. 1 with the chunks merged beside the selection (up to 256 rows, up to 32 chunks or more) and by a launch of its own."""
