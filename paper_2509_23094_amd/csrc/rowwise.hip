@@ -498,6 +498,7 @@ hipError_t launch_scatter_rows(int dtype, const void* rows_a, void* cache_a, con
 }
 
 hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t st) {
+  if (n == 0) return hipSuccess;
   const int blocks = (int)((n + 1023) / 1024 < 2048 ? (n + 1023) / 1024 : 2048);
   hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks), dim3(256), 0, st, dst, src, n);
   return hipGetLastError();

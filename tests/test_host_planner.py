@@ -117,3 +117,14 @@ def test_plan_rejects_bad_arguments():
     assert B._lib.d2c_plan_projection(1, 0, 16, 16, 0, shape) == B.D2C_EINVAL
     assert B._lib.d2c_plan_projection(5, 4, 16, 16, 0, shape) == B.D2C_EINVAL
     assert B._lib.d2c_plan_projection(1, 4, 16, 16, 0, None) == B.D2C_EINVAL
+
+
+def test_launchers_take_an_empty_array():
+    """Nothing to copy or to add is no launch and no error (a launch of no workgroups would be one)."""
+    import ctypes
+    from paper_2509_23094_amd import binding as B
+    copy = getattr(B._lib, "_ZN3d2c15launch_copy_f32EPfPKfmP12ihipStream_t")
+    copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    add = getattr(B._lib, "_ZN3d2c17launch_sum_splitsEPfPKfimmP12ihipStream_t")
+    add.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_void_p]
+    assert copy(None, None, 0, None) == 0 and add(None, None, 2, 0, 0, None) == 0
