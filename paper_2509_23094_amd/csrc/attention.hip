@@ -779,11 +779,11 @@ hipError_t launch_fwd_bf16(const void* q, const void* k_cache, const void* v_cac
   // split the output columns over two workgroups when that still fits one round of workgroups on the chip
   constexpr int kUnits = 256;
   const bool split = DH == 128 && fwd_map(m, n_heads, n_kv_heads, 2).n_wgs <= kUnits;
-  // Staging takes 135 KB of LDS with 128-wide heads (70 KB with 64), 33 KB with loads in operand order.  Up to 256 keys a wave
-  // has one pair, nothing to keep in flight, and the space only costs company on the compute unit: 80 x 128 with 64 query
-  // and 8 kv heads of 128 10.6 us, 14.1 staged, 80 x 200 with 32 heads 7.8, 8.7.  Where a workgroup has all output columns it
-  // pays from about 350 keys on (80 x 300, 32 heads: 8.9, 9.3; 80 x 400 10.3, 9.6).
-  const bool staged = L > (split ? 256 : 350) && (((uintptr_t)q | (uintptr_t)k_cache) & 15) == 0 &&
+  // Staging takes 135 KB of LDS with 128-wide heads (70 KB with 64), 33 KB with loads in operand order: where a workgroup has
+  // all output columns, so that there are many or they are small, the space costs company on the compute unit and it pays
+  // from about 350 keys on only (80 x 128 with 64 query and 8 kv heads of 128 10.6 us, 14.1 staged; 80 x 200 with 32 heads 7.8,
+  // 8.7; 80 x 300 8.9, 9.3; 80 x 400 10.3, 9.6).  Where two share them it pays always (a step's layer at 248 keys: 3 us).
+  const bool staged = (split || L > 350) && (((uintptr_t)q | (uintptr_t)k_cache) & 15) == 0 &&
                       (size_t)L * n_kv_heads * DH * 2 < (1ull << 31) && (size_t)m * n_heads * DH * 2 < (1ull << 31);
 #define D2C_FWD(KEEP_, DP_, ST_)                                                                                        \
   hipLaunchKernelGGL((attn_fwd_bf16_kernel<DH, KEEP_, DP_, ST_>), dim3(fwd_map(m, n_heads, n_kv_heads, DP_).n_wgs),     \

@@ -776,9 +776,9 @@ def test_linear_many_rows_unaligned(B, m, N, K):
                                           (32, 32, 128, 513, 17), (28, 4, 128, 1025, 47), (4, 4, 64, 511, 16), (4, 1, 64, 351, 33),
                                           (40, 8, 128, 1024, 120), (40, 8, 128, 351, 113), (40, 8, 128, 350, 113)])
 def test_attention_parity_staged_rows(B, H, Hkv, dh, L, m):
-    """The few-row kernel with K and Q staged through LDS (from 257 keys on where two workgroups share the columns, 351 elsewhere): ragged
-    pairs, waves with one pair and with several, both widths of the output share; below it one key and waves without a pair; and
-    the same values with a K cache that is not 16-byte aligned (loads in operand order), bit for bit."""
+    """The few-row kernel with K and Q staged through LDS (always where two workgroups share the columns, from 351 keys on
+    elsewhere): one key, ragged pairs, waves without a pair, with one and with several, both widths of the output share; and the
+    same values with a K cache that is not 16-byte aligned (loads in operand order), bit for bit."""
     say(f"attention staged H={H} Hkv={Hkv} dh={dh} L={L} m={m}")
     _attention_parity(B, "bf16", H, Hkv, dh, L, m, tunables={"attn_tiled_min_m": 1 << 30})
     wd = W.ModelDims(1, H * dh, H, Hkv, dh, 64, 64, dtype="bf16")
