@@ -829,8 +829,8 @@ hipError_t launch_avg(const void* q, const void* k_cache, const float* lse, int 
     // Rows past m repeat the last one, which the L1 merges in operand order but staging copies: few rows and few keys are
     // faster without (64 heads of 64, forward included, one row x 300 keys 12.1 us, 14.1 staged; 8 x 400 14.4, 15.2; 16 x 400
     // 15.8, 15.3; one row x 800 15.2, 16.0, x 1024 17.6, 16.7; 32 heads of 128, 1 x 128 11.3, 12.4; 8 x 128 12.9, 12.5;
-    // two layers with 4 x 250, K from HBM, 230.5, 227.7).
-    const bool pays = m >= (DH == 128 ? 4 : 16) || L > (DH == 128 ? 256 : 896);
+    // but two layers with 3 x 200, K from HBM, 238.0, 235.3, and with 1 x 100 220.7, 219.8).
+    const bool pays = m >= (DH == 128 ? 2 : 16) || L > (DH == 128 ? 256 : 896);
     if (pays && (((uintptr_t)q | (uintptr_t)k_cache) & 15) == 0 && (size_t)L * n_kv_heads * DH * 2 < (1ull << 31) &&
         (size_t)m * n_heads * DH * 2 < (1ull << 31)) {
       hipLaunchKernelGGL((attn_avg_kernel<T, DH, true>), dim3((m + 15) / 16, key_blocks), dim3(kThreads), 0, st, (const T*)q,
