@@ -379,12 +379,16 @@ WsNeeds ws_needs(const d2c_dims& D, size_t max_rows, const Tunables& t) {
   const int dq = D.n_heads * D.head_dim, dkv = D.n_kv_heads * D.head_dim;
   const int shapes[4][2] = {{dq + 2 * dkv, D.d_model}, {D.d_model, dq}, {2 * D.d_ffn, D.d_model}, {D.d_model, D.d_ffn}};
   WsNeeds n{0, 0};
-  for (int m = 1; m <= (int)max_rows; ++m)
+  // a tile count has one plan, or two with gemm_wide_min_rows inside it: the first and the last row count see both
+  for (size_t m0 = 1; m0 <= max_rows; m0 += 16) {
+    const size_t m1 = std::min(m0 + 15, max_rows);
     for (auto& s : shapes) {
       // up to 128 rows leave room for the largest split count; beyond that the planner's choice is taken
-      const GemmPlan pl = plan_gemm(t, D.dtype, m, s[0], s[1], false, !t.gemm_preshuffle);
-      n.partial = std::max(n.partial, (size_t)(m <= 128 ? 8 : pl.splits) * m * s[0]);
+      auto splits = [&](size_t m) { return plan_gemm(t, D.dtype, (int)m, s[0], s[1], false, !t.gemm_preshuffle).splits; };
+      const int most = m1 <= 128 ? 8 : std::max(splits(m0), splits(m1));
+      n.partial = std::max(n.partial, (size_t)most * m1 * s[0]);
     }
+  }
   // one piece per sequence of a batched attention launch
   const int batch = std::max(1, std::min((int)(max_rows / (size_t)D.max_seq), attention_tiled_max_batch()));
   n.attn_part = (size_t)batch * attention_scratch_floats(t, D.dtype, D.max_seq, D.max_seq, D.n_heads, D.head_dim);

@@ -913,7 +913,7 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
     // of 256 columns, 93 as 256 of 192: what counts is full rounds over the 256 units), and every split writes and
     // reads m x N partial sums at about 5.5 TB/s.  Any count of splits: Dream's QKV at 768 rows runs 3.
     const int pairs = (pl.row_chunks + 1) / 2;
-    const double chunk_us = 0.35 * pl.mt, split_us = single_split ? 0.0 : (double)m * N * 8e-6 / 5.5;
+    const double chunk_us = 0.35 * pl.mt, split_us = single_split ? 0.0 : (double)tiles * 16 * N * 8e-6 / 5.5;
     best = 1e30;
     for (int nt : {4, 3})
       for (int s = 1; s <= max_splits; ++s) {
@@ -952,7 +952,7 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
       const double full = !q.wide || rows > kSuperRows ? per_xcd * ((rows + 3) / 4) / 8.0 : per_xcd * rows / 32.0;
       const double whole = std::floor(full), rest = full - whole;
       const double rounds = whole < 1.0 ? 1.0 : whole + (rest > 0.0 ? k.tail + (1.0 - k.tail) * rest : 0.0);
-      const double width = q.nt == 3 ? 0.8 : 1.0, mb = 4e-6 * m * N;
+      const double width = q.nt == 3 ? 0.8 : 1.0, mb = 4e-6 * (tiles * 16) * N;
       return k.start + rounds * (k.round + width * (cps * (k.tile * q.mt + k.cols) + (single_split ? k.gate * q.mt : 0.0))) +
              (eff > 1 ? k.split + k.part * mb * eff : 0.0) + k.out * mb * (single_split ? 0.25 : 1.0);
     };

@@ -50,6 +50,7 @@ struct GemmPlan {
   int chunks_per_wg() const { return wide ? 2 : 1; }
   int cols_per_wg() const { return 16 * nt * waves / chunks_per_wg(); }
 };
+// Row counts of one tile count (16 t - 15 .. 16 t) on one side of gemm_wide_min_rows have one plan.
 // single_split: one split, and the matrix is the gate/up pair with the gated epilogue.  row_major: W as the caller has it.
 GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split = false, bool row_major = false);
 // P must hold plan.splits * split_stride floats; split_stride >= m * ldp.

@@ -198,6 +198,13 @@ def test_refresh_layer_parity_forced_rows_per_workgroup(B, mt):
     _refresh_layer_parity(B, *case, tunables={"gemm_wide_mt": mt})
 
 
+@pytest.mark.parametrize("m", [299, 300, 304])
+def test_refresh_layer_parity_many_rows_from_inside_a_tile(B, m):
+    """gemm_wide_min_rows inside a 16-row tile: two plans for one tile count, workspace for both."""
+    case = [c for c in LAYER_CASES if c[0] == "bf16-small"][0]
+    _refresh_layer_parity(B, f"bf16-{m}-rows", case[1], 304, m, tunables={"gemm_wide_min_rows": 300})
+
+
 def _refresh_layer_parity(B, name, wd, L, m, tunables=None):
     say(f"refresh_layer {name} L={L} m={m} tunables={tunables}")
     ctx, dims, mdl = _ctx_for(B, wd, max_seq=L, tiny_vocab=64, tunables=tunables)

@@ -83,6 +83,14 @@ def test_plan_many_rows_one_or_two_row_chunks_per_workgroup():
         assert p["waves"] == waves and p["col_tiles_per_wave"] in ((4,) if waves == 4 else (3, 4)), (m, N, K, single, p)
 
 
+def test_plan_depends_on_the_tile_count_alone():
+    """The workspace of a context is sized from the first and the last row count of every 16: all of them have one plan."""
+    for (N, K), single in itertools.product([s for s in SHAPES if s[1] % 8 == 0], (False, True)):
+        for t in (1, 3, 8, 9, 12, 13, 16, 17, 18, 19, 21, 25, 31, 32, 33, 40, 47, 54, 61, 64, 80, 97, 150, 215, 768):
+            first, mid, last = (_plan("bf16", 16 * t - d, N, K, single) for d in (15, 6, 0))
+            assert first == last and mid == last, (t, N, K, single, first, mid, last)
+
+
 def test_plan_at_the_benchmark_shapes():
     """One round of equal workgroups over the 256 compute units where the shape allows it (the shapes
     measured fastest on the MI355X)."""
