@@ -149,7 +149,8 @@ __device__ __forceinline__ bool fwd_map_decode(const FwdMap& f, int n_kv_heads, 
 // neighbouring lanes (16 accesses), and reads its operands there.  A row's 16-byte pieces are xored with its number, so
 // that eight lanes of a read touch different banks.  A wave reads only K rows that it staged itself: no barrier, but its
 // own wait in front of a pair.  Staged against operand order: 45 queries x 512 keys x 32 heads 10.7 -> 8.4 us, 64 x 765 with 28
-// query and 4 kv heads 17.5 -> 13.2, 33 x 1023 15.7 -> 11.6.  The loads in operand order remain for other buffers.
+// query and 4 kv heads 17.5 -> 13.2, 33 x 1023 15.7 -> 11.6.  The loads in operand order remain for
+// other buffers and for short key ranges (see launch_fwd_bf16).
 template <int DH, int KEEP, int DPARTS, bool STAGED>
 __global__ __launch_bounds__(kFwdThreads) void attn_fwd_bf16_kernel(
     const bf16* __restrict__ q, const bf16* __restrict__ k_cache, const bf16* __restrict__ v_cache, int m, int L,

@@ -16,7 +16,7 @@
 //   * the contraction axis can be split over several workgroups; every split writes
 //     its own fp32 partial and the consumer kernel sums the partials in a fixed order
 //     (deterministic, no atomics);
-//   * more than 128 rows are covered by several row chunks (many rows in bf16: gemm_wide_kernel below).
+//   * more than 128 rows are covered by several row chunks (many rows in bf16: NT = 4, or gemm_wide_kernel below).
 //     The grid is one-dimensional and workgroup ids are dealt round-robin to the 8
 //     XCDs, each with its own L2: the mapping below gives the row chunks of one weight
 //     tile consecutive slots of the SAME XCD, so the tile comes from HBM once and the
@@ -443,8 +443,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
 // reads run three matrix-core groups ahead of their use.  The scheduler is told to keep that order.  The wait in front
 // of the barrier leaves the weight refills behind the staging in flight.
 // 512 rows, LLaDA widths, against 128 x 256 tiles of 4 waves with activations through registers: gate/up (24576 x 4096)
-// 142 -> 93 us (1.10 PFLOP/s; the exact exponential adds about 9, by the difference of whole steps), QKV 79 -> 57, O and down together 89 -> 84.  Tried on the 256-column tile (105 us):
-// 32x32x16 steps with one wave per SIMD (119 us), operand-order staging (130 us).
+// 142 -> 95 us (1.09 PFLOP/s), QKV 79 -> 52.  Tried on the 256-column tile (105 us, gate/up): 32x32x16 steps with one wave
+// per SIMD (119 us), operand-order staging (130 us).  Where the workgroups are too few for the chip the other is the faster:
+// see plan_gemm.
 // The launcher guarantees whole chunks of k: nothing to mask.
 template <int MT, int NT, int MODE>
 __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restrict__ A, int lda, const bf16* __restrict__ W,
