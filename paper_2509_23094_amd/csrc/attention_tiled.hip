@@ -5,14 +5,11 @@
 // queries attend to all L cached keys without a mask, and A-bar is the head mean of the
 // normalised rows), different blocking:
 //
-//   forward   one workgroup = 64*QT query rows of one head over one range of keys.
-//             K and V blocks of 64 keys are staged through LDS once per workgroup, already
-//             in matrix-core operand order (one 16-byte fragment per lane, read back with a
-//             single conflict-free 16-byte LDS read), double-buffered with the next block's
-//             global loads in flight during the arithmetic.  Scores are computed transposed
-//             (S^T = K Q^T) so the accumulator of two 16-key tiles IS the 32-key B operand of
-//             O^T += V^T P^T; V is transposed 4x4 in registers on its way INTO LDS, once per
-//             workgroup instead of once per wave.  Both contractions use the 16x16x32 step.
+//   forward   one workgroup = 64*QT (or 128*QT) query rows of one head over one range of keys.
+//             K and V blocks of 64 keys are staged through LDS once per workgroup, in whole rows, the next
+//             block's on their way during the arithmetic; V is transposed as it is read from there.
+//             Scores are computed transposed (S^T = K Q^T) so the accumulator of two 16-key tiles IS the
+//             32-key B operand of O^T += V^T P^T.  Both contractions use the 16x16x32 step.
 //             When the grid would not fill the chip the key range is split; every split writes
 //             an unnormalised fp32 partial with its running maximum and sum, and a merge
 //             kernel combines them in a fixed order (bit-reproducible, no atomics).
@@ -81,51 +78,105 @@ __device__ __forceinline__ TileId tile_of(int bid, int q_blocks, int n_heads, in
 // reference each block was taken against (refblk [H, blocks, m]).  The head-average kernel turns them into normalised rows once the rows'
 // log-sum-exp is known: p = ptilde * 2^(refblk - lse2).
 //
-// WAVES = 4 or 8 waves per workgroup, each owning 16*QT queries; with 8 waves two waves share a SIMD, so that
-// one wave's matrix-core phase runs beside the other's vector phase (a single wave runs its phases one after
-// the other), and a K/V block staged once serves twice as many queries.
-template <int DH, int QT, int WAVES, bool EMIT>
-__global__ __launch_bounds__(WAVES * 64) void attn_tiled_fwd_kernel(const BatchArgs batch, int n_heads, int n_kv_heads,
-                                                                    float scale) {
+// WAVES = 4 or 8 waves per workgroup, each owning 16*QT queries.  Two waves share a SIMD, so that one wave's
+// matrix-core phase runs beside the other's vector phase: two workgroups of 4 waves (two LDS buffers, 64 KB) or one of
+// 8 (three buffers).
+//
+// K and V rows go from global memory straight into LDS (DMA), one or two blocks ahead, in whole rows; V is transposed on
+// its way out of LDS (ds_read_b64_tr_b16).  Loads and stores retire in one queue, which is waited for once, in the middle of a
+// block: the rows were requested at its start, the last block's probability stores behind the last wait.
+// 1024 queries x 2048 keys, 32 heads, no average: 50 us, 0.69 PFLOP/s, in 256 workgroups of 4 waves.  Rows through registers
+// took 92 us a layer for 4 x 228 x 3072 with the average (now 83) and 47 for 777 x 777 without (now 28, unsplit): the compiler
+// had moved their loads behind the scores and their wait in front of everything stored.  What is left: the probabilities
+// (half of the time of a call with the average), and 1 to 2 waves per SIMD between whose phases a third of the time is idle.
+// DMA = false brings the rows through registers: buffers that are not 16-byte aligned.
+__device__ __forceinline__ u32x2 lds_read_transposed(const unsigned char* p) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+}
+
+template <int DH, int QT, int WAVES, bool EMIT, bool DMA>
+__global__ __launch_bounds__(WAVES * 64, 2) void attn_tiled_fwd_kernel(const BatchArgs batch, int n_heads, int n_kv_heads,
+                                                                       float scale) {
   static_assert(WAVES == 4 || WAVES == 8, "4 or 8 waves");
   constexpr int NS = DH / 32;            // contraction steps of K Q^T
   constexpr int ND = DH / 16;            // head-dim tiles of O^T
-  constexpr int NB = DH / 64;            // 64-wide head-dim blocks (one V staging unit covers 64)
-  constexpr int WH = WAVES / 4;          // waves that share the staging of one key tile
-  constexpr int KF = NS / WH;            // K fragments a lane stages per block
-  constexpr int VA = 2 / WH;             // 16-key tiles of its V unit a lane stages
-  __shared__ u32x4 k_lds[2][4 * NS * 64];      // [key tile a][step s][lane]
-  __shared__ u32x4 v_lds[2][ND * 2 * 64];      // [head-dim tile][32-key step][slot]; slot = lane ^ (tile & 3)
+  constexpr int NBUF = DMA && WAVES == 8 ? 3 : 2;
+  constexpr int kRow = DH * 2;                           // bytes of a K or V row
+  constexpr int kOperand = kBlockKeys * kRow;            // bytes of a block's K (or V) rows
+  constexpr int PP = kRow / 16;                          // 16-byte pieces of a row
+  constexpr int RP = 64 / PP;                            // rows that one instruction of a wave brings
+  constexpr int LP = kBlockKeys / RP / WAVES;            // instructions per wave and operand
+  __shared__ __attribute__((aligned(16))) unsigned char lds[NBUF * 2 * kOperand];      // [buffer][K, V][key][piece]
 
   const SeqArgs& sq = batch.seq[blockIdx.y];
   const bf16* __restrict__ q = sq.q;
-  const bf16* __restrict__ k_cache = sq.k_cache;
-  const bf16* __restrict__ v_cache = sq.v_cache;
   bf16* __restrict__ out = sq.out;
   float* __restrict__ lse = sq.lse;
   float* __restrict__ o_part = sq.o_part;
   float* __restrict__ ml_part = sq.ml_part;
-  bf16* __restrict__ ptilde = sq.ptilde;
-  float* __restrict__ refblk = sq.refblk;
   const int m = sq.m, L = sq.L, keys_per_split = sq.keys_per_split, n_splits = sq.n_splits, q_blocks = sq.q_blocks;
   const TileId id = tile_of(blockIdx.x, q_blocks, n_heads, n_splits);
   if (!id.valid || id.qb >= q_blocks) return;          // the grid is sized for the largest sequence of the batch
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int r = lane & 15, g = lane >> 4;
   const int head = id.head;
   const int kvh = head / (n_heads / n_kv_heads);
   const int dq = n_heads * DH;
   const size_t kv_pitch = (size_t)n_kv_heads * DH;
-  const bf16* kbase = k_cache + (size_t)kvh * DH;
-  const bf16* vbase = v_cache + (size_t)kvh * DH;
   const int q0 = id.qb * (16 * QT * WAVES) + wave * (16 * QT);
+  const bool active = q0 < m;                          // a wave without queries only stages
   const int key_lo = id.split * keys_per_split;
   const int key_hi = min(L, key_lo + keys_per_split);
   const int n_blocks = (key_hi - key_lo + kBlockKeys - 1) / kBlockKeys;      // >= 1 by the launch plan
   const int n_blk_total = (L + kBlockKeys - 1) / kBlockKeys;
   const int Lp = n_blk_total * kBlockKeys + kPtildePad;                      // row pitch of ptilde
 
-  // this wave's queries as B operands of S^T = K Q^T (rows past m repeat row m-1 and are not stored)
+  // Staging: PP neighbouring lanes bring one row.  In LDS the 16-byte pieces of a row are permuted by an xor with the row
+  // number, so that the 16 rows of an operand read fall on different banks: single pieces of K, pairs of V (a transposed
+  // read takes 32 bytes of a row).
+  auto k_swz = [](int row) { return DH == 128 ? row & 15 : row >> 1 & 7; };
+  auto v_swz = [](int row) { return (DH == 128 ? row & 7 : row >> 1 & 3) << 1; };
+  const unsigned pitch = (unsigned)(kv_pitch * 2);
+  const int srow = wave * RP + lane / PP, spc = lane % PP;      // first row and piece of this lane; further rows 16s on
+  const int k_src = (spc ^ k_swz(srow)) * 16, v_src = (spc ^ v_swz(srow)) * 16;
+  const bf16* kbase = sq.k_cache + (size_t)key_lo * kv_pitch + (size_t)kvh * DH;
+  const bf16* vbase = sq.v_cache + (size_t)key_lo * kv_pitch + (size_t)kvh * DH;
+  const int kv_bytes = (int)(unsigned)(((size_t)(key_hi - key_lo - 1) * kv_pitch + DH) * 2);
+  const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(kbase), 0, kv_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(vbase), 0, kv_bytes, 0x00020000);
+  u32x4 reg_k[LP], reg_v[LP];                                   // !DMA only
+  auto load_block = [&](int blk, int buf) {
+    const int key0 = blk * kBlockKeys, left = key_hi - key_lo - 1 - key0;       // rows past the end repeat the last one
+    const bool whole = left >= kBlockKeys - 1;
+    unsigned char* dst = lds + buf * (2 * kOperand) + wave * 1024;
+#pragma unroll
+    for (int j = 0; j < LP; ++j) {
+      const int row = whole ? srow : min(srow + j * (RP * WAVES), left);
+      const size_t first = (size_t)(key0 + (whole ? j * (RP * WAVES) : 0)) * pitch;
+      if constexpr (DMA) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void*)(dst + j * (WAVES * 1024)), 16,
+                                                 (int)(row * pitch + k_src), (int)(unsigned)first, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vrsrc, (__attribute__((address_space(3))) void*)(dst + kOperand + j * (WAVES * 1024)),
+                                                 16, (int)(row * pitch + v_src), (int)(unsigned)first, 0, 0);
+      } else {
+        reg_k[j] = ld16(reinterpret_cast<const char*>(kbase) + first + (row * pitch + k_src));
+        reg_v[j] = ld16(reinterpret_cast<const char*>(vbase) + first + (row * pitch + v_src));
+      }
+    }
+  };
+  auto store_block = [&](int buf) {                             // !DMA
+    unsigned char* dst = lds + buf * (2 * kOperand) + wave * 1024 + lane * 16;
+#pragma unroll
+    for (int j = 0; j < LP; ++j) {
+      *reinterpret_cast<u32x4*>(dst + j * (WAVES * 1024)) = reg_k[j];
+      *reinterpret_cast<u32x4*>(dst + kOperand + j * (WAVES * 1024)) = reg_v[j];
+    }
+  };
+  load_block(0, 0);
+  if (NBUF == 3 && n_blocks > 1) load_block(1, 1);
+
+  // this wave's queries as B operands of S^T = K Q^T (rows past m repeat row m-1)
   Frag<bf16> qf[QT][NS];
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
@@ -135,89 +186,25 @@ __global__ __launch_bounds__(WAVES * 64) void attn_tiled_fwd_kernel(const BatchA
     for (int s = 0; s < NS; ++s) qf[t][s].raw = ld16(qrow + s * 32);
   }
 
-  // staging registers of the K/V block on its way from global memory to LDS: requested at the top of an
-  // iteration, stored behind its arithmetic.  Key tile kt = wave % 4 of K: its NS fragments (with 8 waves,
-  // wave / 4 picks which half of them); of V one 8-key x 4-value unit per lane (unit = 32-key step ks,
-  // 64-wide block b; with 8 waves, wave / 4 picks which 16-key tile of the unit).
-  struct Stage {
-    u32x4 k[KF];
-    u32x2 v[VA][4];
-  };
-  Stage stg;
-  const int kt = wave & 3, wh = wave >> 2;
-  const int v_b = kt % NB, v_ks = kt / NB;              // v_ks < 2 only for the waves that stage V
-  const bool stages_v = NB == 2 || v_ks < 2;            // with two 64-wide blocks every wave stages V
-  const int last_block = n_blocks - 1;
-  // Row addresses: a block that lies wholly inside [0, L) uses per-lane byte offsets fixed at launch on top
-  // of a uniform block base; only a ragged last block pays for clamping every row to L-1.
-  const unsigned koff = (unsigned)(((size_t)(kt * 16 + r) * kv_pitch + g * 8 + wh * KF * 32) * sizeof(bf16));
-  const unsigned voff =
-      (unsigned)(((size_t)((2 * v_ks + wh * VA) * 16 + 4 * g) * kv_pitch + v_b * 64 + 4 * r) * sizeof(bf16));
-  const unsigned vrow_bytes = (unsigned)(kv_pitch * sizeof(bf16));
-  auto load_block = [&](Stage& sg, int blk_req) {       // past the end: the last block again, never used
-    const int blk = min(blk_req, last_block);
-    const int key0 = key_lo + blk * kBlockKeys;
-    if (key0 + kBlockKeys <= L) {
-      const char* kblk = reinterpret_cast<const char*>(kbase + (size_t)key0 * kv_pitch);     // uniform
-      const char* vblk = reinterpret_cast<const char*>(vbase + (size_t)key0 * kv_pitch);
+  // Where the probabilities go (rows past m store what row m-1 stores, to its place)
+  const bool emits = EMIT && sq.ptilde != nullptr;              // null: a sequence of the batch whose average is not wanted
+  char* prow[QT];
+  char* rrow[QT];
+  if constexpr (EMIT) {
 #pragma unroll
-      for (int s = 0; s < KF; ++s) sg.k[s] = ld16(kblk + koff + s * 64);
-      if (stages_v) {
-#pragma unroll
-        for (int a = 0; a < VA; ++a)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) sg.v[a][e] = ld8(vblk + voff + (unsigned)(a * 16 + e) * vrow_bytes);
-      }
-    } else {
-      const int key = min(key0 + kt * 16 + r, L - 1);
-      const bf16* krow = kbase + (size_t)key * kv_pitch + g * 8 + wh * KF * 32;
-#pragma unroll
-      for (int s = 0; s < KF; ++s) sg.k[s] = ld16(krow + s * 32);
-      if (stages_v) {
-#pragma unroll
-        for (int a = 0; a < VA; ++a)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int vkey = min(key0 + (2 * v_ks + wh * VA + a) * 16 + 4 * g + e, L - 1);
-            sg.v[a][e] = ld8(vbase + (size_t)vkey * kv_pitch + v_b * 64 + 4 * r);
-          }
-      }
+    for (int t = 0; t < QT; ++t) {
+      const size_t row = (size_t)min(q0 + t * 16 + r, m - 1);
+      const size_t blk0 = (size_t)(key_lo / kBlockKeys);        // key_lo is a multiple of the block length
+      prow[t] = reinterpret_cast<char*>(sq.ptilde + ((size_t)head * m + row) * Lp + blk0 * kBlockKeys + 8 * g);
+      rrow[t] = reinterpret_cast<char*>(sq.refblk + ((size_t)head * n_blk_total + blk0) * m + row);
     }
-  };
-  // Slots of V in LDS.  The value of head-dim index b*64 + 4r + i lives in head-dim tile dt = 4b + r/4 at row
-  // 4(r%4) + i; a fragment's 8 keys are lane group g's 4 keys of tile 2ks, then of tile 2ks+1 (the order P is
-  // packed in).  Reader lane l of tile dt reads slot l ^ (dt & 3): the same 64 slots, so reads stay
-  // conflict-free, while the 64 writers of one store instruction (16 values of r for each g) now spread over
-  // all banks instead of piling 16 deep on a quarter of them.
-  const int v_dt = v_b * 4 + (r >> 2);
-  auto store_block = [&](const Stage& sg, int buf) {
-#pragma unroll
-    for (int s = 0; s < KF; ++s) k_lds[buf][(kt * NS + wh * KF + s) * 64 + lane] = sg.k[s];
-    if (stages_v) {
-      // 4x4 transposes: op[a][i] = keys 4g..4g+3 of tile 2ks+a for head-dim value 4r+i of block b
-      u32x2 op[VA][4];
-#pragma unroll
-      for (int a = 0; a < VA; ++a) {
-        op[a][0] = u32x2{pack_lo(sg.v[a][0].x, sg.v[a][1].x), pack_lo(sg.v[a][2].x, sg.v[a][3].x)};
-        op[a][1] = u32x2{pack_hi(sg.v[a][0].x, sg.v[a][1].x), pack_hi(sg.v[a][2].x, sg.v[a][3].x)};
-        op[a][2] = u32x2{pack_lo(sg.v[a][0].y, sg.v[a][1].y), pack_lo(sg.v[a][2].y, sg.v[a][3].y)};
-        op[a][3] = u32x2{pack_hi(sg.v[a][0].y, sg.v[a][1].y), pack_hi(sg.v[a][2].y, sg.v[a][3].y)};
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int slot = (g * 16 + 4 * (r & 3) + i) ^ (r >> 2);
-        u32x4* dst = &v_lds[buf][(v_dt * 2 + v_ks) * 64 + slot];
-        if constexpr (VA == 2) *dst = u32x4{op[0][i].x, op[0][i].y, op[1][i].x, op[1][i].y};
-        else reinterpret_cast<u32x2*>(dst)[wh] = op[0][i];
-      }
-    }
-  };
+  }
 
   // Online softmax in the base-2 domain: p = 2^(s*c - ref) with c = scale*log2(e).  ref is a per-row
   // reference, not necessarily the running maximum: it is only raised (and O, l rescaled) when a score
   // exceeds it by more than kRaise, so p stays below 2^kRaise.  The result is the same softmax (shift
-  // invariance); the decision depends on the data only.  Every lane checks its own 16 scores of a row
-  // against the row's reference; only when some lane of the wave finds one too large do the four lanes that
+  // invariance); the decision depends on the data only.  Every lane checks its own 16 exponents of a row; only
+  // when some lane of the wave finds one too large do the four lanes that
   // share a row exchange their maxima and raise the reference (rare after the first block).
   constexpr float kRaise = 8.f;
   const float c2 = scale * 1.44269504088896341f;
@@ -231,21 +218,30 @@ __global__ __launch_bounds__(WAVES * 64) void attn_tiled_fwd_kernel(const BatchA
     for (int d = 0; d < ND; ++d) acc[d][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   constexpr int kRing = 4;                     // LDS fragments in flight ahead of the matrix-core step that uses them
-  f32x4 st[4][QT];
-  const int vlane[4] = {lane, lane ^ 1, lane ^ 2, lane ^ 3};
+  // byte offsets of this lane's operand pieces (the step or head-dim tile enters by an xor, the key tile by an addition)
+  const unsigned k_rd = r * kRow + (g ^ k_swz(r)) * 16;
+  const int v_row = 4 * g + (r >> 2);
+  const unsigned v_rd = kOperand + v_row * kRow + (v_swz(v_row) ^ (r >> 1 & 1)) * 16 + (r & 1) * 8;
 
-  auto block = [&](int blk) {
-    const int buf = blk & 1;
+  // everything this wave has requested from memory is there (vmcnt(0))
+  auto wait_requests = [&]() {
+    __builtin_amdgcn_s_waitcnt(0x70 | 0xf00);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto block = [&](int blk, int buf) {
+    const unsigned char* kv = lds + buf * (2 * kOperand);
     const int key0 = key_lo + blk * kBlockKeys;
+    f32x4 st[4][QT];
     // ---- scores S^T = K Q^T; the first step of every tile starts from a zero accumulator operand.
     // The K fragments come from LDS through a ring of kRing registers: fragment i + kRing is requested right
     // behind the matrix-core steps of fragment i, so one LDS latency is paid per block, not one per fragment
     // (the scheduler is told to keep this order; left alone it waits for every pair of reads).
     {
       constexpr int NF = 4 * NS;
+      auto read_k = [&](int i) { return *reinterpret_cast<const u32x4*>(kv + (k_rd ^ (unsigned)(i % NS * 64)) + i / NS * (16 * kRow)); };
       Frag<bf16> kf[kRing];
 #pragma unroll
-      for (int i = 0; i < kRing; ++i) kf[i].raw = k_lds[buf][i * 64 + lane];
+      for (int i = 0; i < kRing; ++i) kf[i].raw = read_k(i);
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
 #pragma unroll
@@ -257,7 +253,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_tiled_fwd_kernel(const BatchA
           else
             mfma16(st[i / NS][t], kf[i % kRing], qf[t][i % NS]);
         }
-        if (i + kRing < NF) kf[i % kRing].raw = k_lds[buf][(i + kRing) * 64 + lane];
+        if (i + kRing < NF) kf[i % kRing].raw = read_k(i + kRing);
       }
       __builtin_amdgcn_sched_group_barrier(0x100, kRing, 0);
 #pragma unroll
@@ -276,21 +272,29 @@ __global__ __launch_bounds__(WAVES * 64) void attn_tiled_fwd_kernel(const BatchA
             for (int t = 0; t < QT; ++t) st[a][t][j] = -INFINITY;
           }
     }
-    // ---- this lane's maxima against the rows' references
-    float tmax[QT];
+    // ---- exponents against the rows' references (+inf where a row has none yet)
+    float x[QT][4][4];
     bool need = false;
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-      tmax[t] = fmaxf(fmaxf(st[0][t][0], st[0][t][1]), fmaxf(st[0][t][2], st[0][t][3]));
+      float xm[4];
 #pragma unroll
-      for (int a = 1; a < 4; ++a)
-        tmax[t] = fmaxf(tmax[t], fmaxf(fmaxf(st[a][t][0], st[a][t][1]), fmaxf(st[a][t][2], st[a][t][3])));
-      need = need || tmax[t] * c2 > ref[t] + kRaise;
+      for (int a = 0; a < 4; ++a) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[t][a][j] = fmaf(st[a][t][j], c2, -ref[t]);
+        xm[a] = fmaxf(fmaxf(x[t][a][0], x[t][a][1]), fmaxf(x[t][a][2], x[t][a][3]));
+      }
+      need = need || fmaxf(fmaxf(xm[0], xm[1]), fmaxf(xm[2], xm[3])) > kRaise;
     }
     if (__builtin_amdgcn_ballot_w64(need) != 0) {
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
-        float rmax = fmaxf(tmax[t], __shfl_xor(tmax[t], 16, kWave));
+        float rmax = -INFINITY;
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) rmax = fmaxf(rmax, st[a][t][j]);
+        rmax = fmaxf(rmax, __shfl_xor(rmax, 16, kWave));
         rmax = fmaxf(rmax, __shfl_xor(rmax, 32, kWave)) * c2;       // the row's maximum; -inf only if it has no key yet
         const float ref_new = rmax > ref[t] + kRaise ? rmax : ref[t];
         const float alpha = ref_new == ref[t] ? 1.f : __builtin_amdgcn_exp2f(ref[t] - ref_new);   // 0 on the first block
@@ -298,72 +302,103 @@ __global__ __launch_bounds__(WAVES * 64) void attn_tiled_fwd_kernel(const BatchA
 #pragma unroll
         for (int d = 0; d < ND; ++d) acc[d][t] *= alpha;
         ref[t] = ref_new;
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[t][a][j] = fmaf(st[a][t][j], c2, -ref_new);
       }
     }
     // ---- probabilities against the references, packed as the B operand of O^T += V^T P^T
     Frag<bf16> pf[2][QT];
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-      const float nref = -ref[t];
       float psum = 0.f;
-      float x[4][4];
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          x[a][j] = __builtin_amdgcn_exp2f(fmaf(st[a][t][j], c2, nref));
-          psum += x[a][j];
+          x[t][a][j] = __builtin_amdgcn_exp2f(x[t][a][j]);
+          psum += x[t][a][j];
         }
       l_run[t] += psum;                                // this lane's share; lanes are added at the end
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
-        pf[ks][t].raw = u32x4{pack_bf16(x[2 * ks][0], x[2 * ks][1]), pack_bf16(x[2 * ks][2], x[2 * ks][3]),
-                              pack_bf16(x[2 * ks + 1][0], x[2 * ks + 1][1]),
-                              pack_bf16(x[2 * ks + 1][2], x[2 * ks + 1][3])};
-      if constexpr (EMIT) {
-        // this lane holds 4 consecutive keys of each of the block's 4 key tiles for query row r of tile t
-        const int row = q0 + t * 16 + r;
-        if (row < m && ptilde != nullptr) {      // null: a sequence of the batch whose average is not wanted
-          const int gblk = (key_lo >> 6) + blk;                     // key_lo is a multiple of the block length
-          // stored as packed: the 64 values of (row, block) in the order [32-key step][lane group][tile, key]
-          bf16* prow = ptilde + ((size_t)head * m + row) * Lp + (size_t)gblk * kBlockKeys + 8 * g;
+        pf[ks][t].raw = u32x4{pack_bf16(x[t][2 * ks][0], x[t][2 * ks][1]), pack_bf16(x[t][2 * ks][2], x[t][2 * ks][3]),
+                              pack_bf16(x[t][2 * ks + 1][0], x[t][2 * ks + 1][1]),
+                              pack_bf16(x[t][2 * ks + 1][2], x[t][2 * ks + 1][3])};
+    }
+    if constexpr (DMA) wait_requests();
+    if constexpr (EMIT) {
+      // a lane holds 4 consecutive keys of each of the block's 4 key tiles for query row r of tile t, stored as packed:
+      // the 64 values of (row, block) in the order [32-key step][lane group][tile, key]
+      if (emits) {
 #pragma unroll
-          for (int ks = 0; ks < 2; ++ks) *reinterpret_cast<u32x4*>(prow + ks * 32) = pf[ks][t].raw;
-          if (g == 0) refblk[((size_t)head * n_blk_total + gblk) * m + row] = ref[t];
+        for (int t = 0; t < QT; ++t) {
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+            *reinterpret_cast<u32x4*>(prow[t] + (size_t)blk * (kBlockKeys * 2) + ks * 64) = pf[ks][t].raw;
+          *reinterpret_cast<float*>(rrow[t] + (size_t)blk * m * 4) = ref[t];       // the four lanes of a row store the same
         }
       }
     }
     // ---- O^T += V^T P^T, the V fragments through the same kind of ring
     {
       constexpr int NF = ND * 2;
+      auto read_v = [&](int i) {           // head-dim tile i / 2, 32-key step i % 2: 4 keys of either 16-key tile
+        const unsigned char* p = kv + (v_rd ^ (unsigned)(i / 2 * 32)) + i % 2 * (32 * kRow);
+        const u32x2 lo = lds_read_transposed(p), hi = lds_read_transposed(p + 16 * kRow);
+        return u32x4{lo.x, lo.y, hi.x, hi.y};
+      };
       Frag<bf16> vf[kRing];
 #pragma unroll
-      for (int i = 0; i < kRing; ++i) vf[i].raw = v_lds[buf][i * 64 + vlane[(i / 2) & 3]];
+      for (int i = 0; i < kRing; ++i) vf[i].raw = read_v(i);
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
 #pragma unroll
         for (int t = 0; t < QT; ++t) mfma16(acc[i / 2][t], vf[i % kRing], pf[i % 2][t]);
-        if (i + kRing < NF) vf[i % kRing].raw = v_lds[buf][(i + kRing) * 64 + vlane[((i + kRing) / 2) & 3]];
+        if (i + kRing < NF) vf[i % kRing].raw = read_v(i + kRing);
       }
-      __builtin_amdgcn_sched_group_barrier(0x100, kRing, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2 * kRing, 0);
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, QT, 0);
-        if (i + kRing < NF) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (i + kRing < NF) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
       }
     }
   };
 
-  load_block(stg, 0);
-  store_block(stg, 0);
-  __syncthreads();
-  for (int blk = 0; blk < n_blocks; ++blk) {
-    load_block(stg, blk + 1);                          // flies during this block's arithmetic
-    block(blk);
-    // the other buffer was last read one iteration ago, before the barrier every wave has passed
-    store_block(stg, (blk & 1) ^ 1);
+  auto barrier = [&]() {                       // without the wait for everything that __syncthreads() brings
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if constexpr (DMA) {
+    wait_requests();
+    barrier();
+  } else {
+    store_block(0);
     __syncthreads();
   }
+  for (int blk = 0, buf = 0; blk < n_blocks; ++blk) {
+    const int nxt = buf == NBUF - 1 ? 0 : buf + 1;
+    if constexpr (DMA) {
+      // the buffer that is filled now was last read one iteration ago, before the barrier every wave has passed
+      if (blk + NBUF - 1 < n_blocks) load_block(blk + NBUF - 1, NBUF == 2 ? nxt : (nxt == NBUF - 1 ? 0 : nxt + 1));
+      __builtin_amdgcn_sched_barrier(0);
+      if (active) block(blk, buf);
+      else wait_requests();
+      __builtin_amdgcn_sched_barrier(0);
+      barrier();
+    } else {
+      if (blk + 1 < n_blocks) load_block(blk + 1, nxt);
+      if (active) block(blk, buf);
+      if (blk + 1 < n_blocks) store_block(nxt);
+      __syncthreads();
+    }
+    buf = nxt;
+  }
+  if (!active) return;
 
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
@@ -527,25 +562,56 @@ __global__ __launch_bounds__(kThreads) void attn_finish_kernel(const BatchArgs b
   }
 }
 
+// Tile shape and key splits of one launch.
 struct FwdPlan {
-  int qt, waves, q_blocks, n_splits, keys_per_split;
+  int qt, waves, splits;
+  int q_per_wg() const { return 16 * qt * waves; }
 };
-FwdPlan plan_fwd(const Tunables& t, int m, int L, int n_heads) {
-  FwdPlan p;
-  const int want_qt = t.attn_qt;
-  p.qt = want_qt == 1 ? 1 : want_qt == 2 ? 2 : (m > 64 ? 2 : 1);
-  // more than 128 rows: 8 waves (two per SIMD) on 256 queries per workgroup
-  p.waves = t.attn_waves == 4 || t.attn_waves == 8 ? t.attn_waves : (p.qt == 2 && m > 128 ? 8 : 4);
-  const int q_per_wg = 16 * p.qt * p.waves;
-  p.q_blocks = (m + q_per_wg - 1) / q_per_wg;
-  const int blocks = (L + kBlockKeys - 1) / kBlockKeys;
-  int splits = 1;
-  const int max_splits = std::max(1, std::min(8, t.attn_max_splits));
-  while (splits < max_splits && p.q_blocks * n_heads * splits < t.attn_target_wgs && blocks / (splits * 2) >= 1) splits *= 2;
-  const int blocks_per_split = (blocks + splits - 1) / splits;
-  p.keys_per_split = blocks_per_split * kBlockKeys;
-  p.n_splits = (L + p.keys_per_split - 1) / p.keys_per_split;     // every split holds at least one key
-  return p;
+// A sequence whose workgroups in the largest tile shape alone fill the chip is never split (the scratch is sized by this).
+bool may_split(const Tunables& t, int m, int n_heads) { return ((m + 255) / 256) * n_heads < t.attn_target_wgs; }
+
+// The cheapest by a model of the time in us, measured at 12 shapes from 64 x 2048 to 2048 x 2048, 28 and 32 heads of 128, 1 to 8
+// splits (it names the fastest or one within 5 %).  A workgroup has a start (launch, queries, first block) and a part per
+// block of 64 keys: 1.8 for 4 waves alone on a compute unit, 2.8 where two workgroups share one, 2.6 for 8 waves (of twice
+// the queries).  Several splits write and read fp32 partials (about 3.5 TB/s both ways together).  A split thus pays only
+// while compute units are idle: 777 rows x 777 keys 22 us unsplit, 36 in two; 256 x 2048 42 us, 26 in four, 33 in eight.
+// The parts are those of calls with the head average (1.35, 2.05 and 1.95 without, and the merge is then a launch of its own);
+// the plan must not depend on it, since the output's bits may not.
+FwdPlan plan_fwd(const Tunables& t, const TiledCall* calls, int n_calls, int n_heads, int head_dim) {
+  int max_m = 0, max_L = 0;
+  double partial_us = 0.0;                        // of one split
+  for (int i = 0; i < n_calls; ++i) {
+    max_m = std::max(max_m, calls[i].m);
+    max_L = std::max(max_L, calls[i].L);
+    if (may_split(t, calls[i].m, n_heads)) partial_us += 8.0 * calls[i].m * n_heads * head_dim / 3.5e6;
+  }
+  const int qt = t.attn_qt == 1 || t.attn_qt == 2 ? t.attn_qt : (max_m > 64 ? 2 : 1);
+  const int blocks = (std::max(1, max_L) + kBlockKeys - 1) / kBlockKeys;
+  const int max_splits = std::min(std::max(1, std::min(8, t.attn_max_splits)), blocks);
+  const int units = t.attn_target_wgs;
+  const double width = qt == 1 ? 0.55 : 1.0;      // 16 queries per wave
+  const double alone = width * 1.8, shared = width * 2.8, eight = 2.6;
+  FwdPlan best{qt, t.attn_waves == 8 ? 8 : 4, 1};
+  double best_us = 1e30;
+  for (int waves : {4, 8}) {
+    if ((waves == 8 && qt == 1) || (t.attn_waves != 0 && waves != t.attn_waves)) continue;
+    for (int s = 1; s <= max_splits; ++s) {
+      FwdPlan p{qt, waves, s};
+      int wgs = 0;
+      for (int i = 0; i < n_calls; ++i)
+        wgs += (calls[i].m + p.q_per_wg() - 1) / p.q_per_wg() * n_heads * (may_split(t, calls[i].m, n_heads) ? s : 1);
+      const int room = waves == 4 ? 2 * units : units;            // workgroups on the chip at one time
+      const int rest = wgs % room;
+      const double full = waves == 4 ? shared : eight;
+      const double rounds = wgs / room * full + (rest == 0 ? 0.0 : waves == 4 && rest <= units ? alone : full);
+      const double us = (blocks + s - 1) / s * rounds + (s > 1 ? s * partial_us : 0.0);
+      if (us < best_us * 0.999) {
+        best_us = us;
+        best = p;
+      }
+    }
+  }
+  return best;
 }
 
 // Scratch of one call, in floats: partial outputs of the key splits, their (reference, sum) pairs, the
@@ -553,12 +619,12 @@ FwdPlan plan_fwd(const Tunables& t, int m, int L, int n_heads) {
 struct Scratch {
   size_t o_part, ml, ptilde, refblk, total;
 };
-Scratch scratch_of(const FwdPlan& p, int m, int L, int n_heads, int head_dim, bool emit) {
+Scratch scratch_of(int n_splits, int m, int L, int n_heads, int head_dim, bool emit) {
   Scratch s;
   const size_t hm = (size_t)n_heads * m;
   const size_t n_blk = (size_t)(L + kBlockKeys - 1) / kBlockKeys;
-  s.o_part = p.n_splits > 1 ? (size_t)p.n_splits * hm * head_dim : 0;
-  s.ml = (size_t)p.n_splits * hm * 2;
+  s.o_part = n_splits > 1 ? (size_t)n_splits * hm * head_dim : 0;
+  s.ml = (size_t)n_splits * hm * 2;
   s.ptilde = emit ? (hm * (n_blk * kBlockKeys + kPtildePad) + 1) / 2 : 0;
   s.ptilde = (s.ptilde + 3) & ~(size_t)3;                          // keep what follows 16-byte aligned
   s.refblk = emit ? hm * n_blk : 0;
@@ -569,50 +635,26 @@ Scratch scratch_of(const FwdPlan& p, int m, int L, int n_heads, int head_dim, bo
 template <int DH>
 hipError_t launch_tiled(const Tunables& t, const TiledCall* calls, int n_calls, int n_heads, int n_kv_heads,
                         float* scratch, size_t scratch_floats, hipStream_t st) {
-  // one plan for the batch: tile shape by the largest row count, key splits so that all sequences together
-  // give every compute unit a workgroup
-  int max_m = 0, max_L = 0;
+  const FwdPlan shape = plan_fwd(t, calls, n_calls, n_heads, DH);      // one for the batch
+  const int q_per_wg = shape.q_per_wg();
   bool emit = false;
-  for (int i = 0; i < n_calls; ++i) {
-    max_m = std::max(max_m, calls[i].m);
-    max_L = std::max(max_L, calls[i].L);
-    emit = emit || calls[i].attn_avg != nullptr;
-  }
-  FwdPlan shape = plan_fwd(t, max_m, max_L, n_heads);
-  const int max_splits = std::max(1, std::min(8, t.attn_max_splits));
-  const int min_blocks = (std::max(1, max_L) + kBlockKeys - 1) / kBlockKeys;
-  auto splits_for = [&](int q_per_wg) {
-    int wgs_unsplit = 0;
-    for (int i = 0; i < n_calls; ++i) wgs_unsplit += ((calls[i].m + q_per_wg - 1) / q_per_wg) * n_heads;
-    int sp = 1;
-    while (sp < max_splits && wgs_unsplit * sp < t.attn_target_wgs && min_blocks / (sp * 2) >= 1) sp *= 2;
-    return sp;
-  };
-  int splits = splits_for(16 * shape.qt * shape.waves);
-  // 8-wave workgroups halve the K/V traffic per query and overlap two waves per SIMD, but also halve the
-  // workgroup count, i.e. double the key splits a small problem needs; with fewer than 8 blocks left per
-  // split the partial outputs (written, then merged) cost more than the loop gains (measured at 256 rows x
-  // 2048 keys x 32 heads: 43 vs 47 us per call)
-  if (shape.waves == 8 && t.attn_waves == 0 && min_blocks / splits < 8) {
-    shape.waves = 4;
-    splits = splits_for(16 * shape.qt * shape.waves);
-  }
-  const int q_per_wg = 16 * shape.qt * shape.waves;
+  for (int i = 0; i < n_calls; ++i) emit = emit || calls[i].attn_avg != nullptr;
   const float scale = 1.0f / sqrtf((float)DH);
   BatchArgs args;
   memset(&args, 0, sizeof(args));
   size_t used = 0;
   int max_tiles = 0, max_fin = 0;
+  bool dma = true;                       // straight into LDS: whole 16-byte pieces, 32-bit offsets
   for (int i = 0; i < n_calls; ++i) {
     const TiledCall& c = calls[i];
-    FwdPlan p = shape;
-    p.q_blocks = (c.m + q_per_wg - 1) / q_per_wg;
+    dma = dma && ((uintptr_t)c.k_cache | (uintptr_t)c.v_cache) % 16 == 0 && (size_t)c.L * n_kv_heads * DH * 2 < (1ull << 31);
+    const int q_blocks = (c.m + q_per_wg - 1) / q_per_wg;
     const int blocks = (c.L + kBlockKeys - 1) / kBlockKeys;
-    const int s_i = std::max(1, std::min(splits, blocks));
-    p.keys_per_split = ((blocks + s_i - 1) / s_i) * kBlockKeys;
-    p.n_splits = (c.L + p.keys_per_split - 1) / p.keys_per_split;
+    const int s_i = may_split(t, c.m, n_heads) ? std::max(1, std::min(shape.splits, blocks)) : 1;
+    const int keys_per_split = ((blocks + s_i - 1) / s_i) * kBlockKeys;
+    const int n_splits = (c.L + keys_per_split - 1) / keys_per_split;      // every split holds at least one key
     const bool emit_i = c.attn_avg != nullptr;
-    const Scratch sc = scratch_of(p, c.m, c.L, n_heads, DH, emit_i);
+    const Scratch sc = scratch_of(n_splits, c.m, c.L, n_heads, DH, emit_i);
     if (sc.total > 0 && (!scratch || used + sc.total > scratch_floats)) return hipErrorInvalidValue;
     float* base = scratch ? scratch + used : nullptr;
     used += (sc.total + 3) & ~(size_t)3;
@@ -623,18 +665,24 @@ hipError_t launch_tiled(const Tunables& t, const TiledCall* calls, int n_calls, 
     a.ptilde = reinterpret_cast<bf16*>(base && emit_i ? base + sc.o_part : nullptr);
     a.ml_part = base ? base + sc.o_part + sc.ptilde : nullptr;
     a.refblk = base && emit_i ? a.ml_part + sc.ml : nullptr;
-    a.m = c.m; a.L = c.L; a.keys_per_split = p.keys_per_split; a.n_splits = p.n_splits; a.q_blocks = p.q_blocks;
+    a.m = c.m; a.L = c.L; a.keys_per_split = keys_per_split; a.n_splits = n_splits; a.q_blocks = q_blocks;
     a.avg_blocks = emit_i ? ((c.m + kFinRows - 1) / kFinRows) * ((blocks * kBlockKeys + kFinKeys - 1) / kFinKeys) : 0;
-    const int groups = (n_heads * p.n_splits + 7) / 8;
-    max_tiles = std::max(max_tiles, groups * 8 * p.q_blocks);
+    const int groups = (n_heads * n_splits + 7) / 8;
+    max_tiles = std::max(max_tiles, groups * 8 * q_blocks);
     const size_t items = (size_t)n_heads * c.m * (DH / 4);
-    const int merge_blocks = p.n_splits > 1 ? (int)((items + kThreads - 1) / kThreads) : 0;
+    const int merge_blocks = n_splits > 1 ? (int)((items + kThreads - 1) / kThreads) : 0;
     max_fin = std::max(max_fin, a.avg_blocks + merge_blocks);
   }
   const dim3 grid(max_tiles, n_calls);
-#define D2C_TILED_FWD(QT_, WAVES_, EMIT_)                                                                         \
-  hipLaunchKernelGGL((attn_tiled_fwd_kernel<DH, QT_, WAVES_, EMIT_>), grid, dim3(WAVES_ * 64), 0, st, args, n_heads, \
-                     n_kv_heads, scale)
+#define D2C_TILED_FWD(QT_, WAVES_, EMIT_)                                                                              \
+  do {                                                                                                                 \
+    if (dma)                                                                                                           \
+      hipLaunchKernelGGL((attn_tiled_fwd_kernel<DH, QT_, WAVES_, EMIT_, true>), grid, dim3(WAVES_ * 64), 0, st, args,  \
+                         n_heads, n_kv_heads, scale);                                                                  \
+    else                                                                                                               \
+      hipLaunchKernelGGL((attn_tiled_fwd_kernel<DH, QT_, WAVES_, EMIT_, false>), grid, dim3(WAVES_ * 64), 0, st, args, \
+                         n_heads, n_kv_heads, scale);                                                                  \
+  } while (0)
   if (shape.qt == 2 && shape.waves == 8 && emit) D2C_TILED_FWD(2, 8, true);
   else if (shape.qt == 2 && shape.waves == 8) D2C_TILED_FWD(2, 8, false);
   else if (shape.qt == 2 && emit) D2C_TILED_FWD(2, 4, true);
@@ -652,8 +700,7 @@ hipError_t launch_tiled(const Tunables& t, const TiledCall* calls, int n_calls, 
 }  // namespace
 
 // Most scratch ONE sequence of a batch can need, over every (m <= max_m, L <= max_L), with the head average
-// wanted.  Inside a batch the tile shape follows the largest sequence and the split count the whole batch, so
-// a sequence can be split whenever its workgroups in the largest tile shape alone would not fill the chip.
+// wanted.  The split count follows the whole batch, so a sequence counts as split wherever it may be.
 size_t attention_tiled_scratch_floats(const Tunables& t, int max_m, int max_L, int n_heads, int head_dim) {
   size_t worst = 0;
   const int max_splits = std::max(1, std::min(8, t.attn_max_splits));
@@ -661,10 +708,8 @@ size_t attention_tiled_scratch_floats(const Tunables& t, int max_m, int max_L, i
     const int Lc = std::min(L, max_L);
     const int blocks = (Lc + kBlockKeys - 1) / kBlockKeys;
     for (int m = 1; m <= max_m; ++m) {
-      FwdPlan p = plan_fwd(t, m, Lc, n_heads);
-      const bool can_split = ((m + 255) / 256) * n_heads < t.attn_target_wgs;
-      p.n_splits = can_split ? std::min(max_splits, blocks) : 1;
-      worst = std::max(worst, (scratch_of(p, m, Lc, n_heads, head_dim, true).total + 3) & ~(size_t)3);
+      const int n_splits = may_split(t, m, n_heads) ? std::min(max_splits, blocks) : 1;
+      worst = std::max(worst, (scratch_of(n_splits, m, Lc, n_heads, head_dim, true).total + 3) & ~(size_t)3);
     }
     if (L >= max_L) break;
   }

@@ -855,3 +855,34 @@ def test_attention_average_staged_rows(B, H, Hkv, dh, L, m):
         got.append(avg)
     assert torch.equal(got[0], got[1])
     ctx.close()
+
+
+@pytest.mark.parametrize("H,Hkv,dh,L,m,waves", [(4, 2, 128, 1, 1, 0), (4, 2, 128, 64, 65, 4), (3, 1, 64, 65, 129, 0), (4, 4, 128, 128, 257, 8),
+                                                (2, 1, 128, 193, 200, 8), (28, 4, 128, 777, 97, 0), (5, 5, 64, 320, 255, 8),
+                                                (2, 2, 128, 1025, 33, 4)])
+def test_attention_tiled_rows_straight_into_lds(B, H, Hkv, dh, L, m, waves):
+    """The tiled kernels at the edges of their key blocks, query tiles and buffers, K and V rows staged straight into LDS; the
+    same caches off their 16-byte alignment come through registers in the same order, so with the same bits."""
+    say(f"attention tiled staging H={H} Hkv={Hkv} dh={dh} L={L} m={m} waves={waves}")
+    m = min(m, L)
+    tun = {"attn_tiled_min_m": 1, "attn_waves": waves}
+    _attention_parity(B, "bf16", H, Hkv, dh, L, m, tunables=tun)
+    wd = W.ModelDims(1, H * dh, H, Hkv, dh, 64, 64, dtype="bf16")
+    ctx, _, _ = _ctx_for(B, wd, max_seq=L, tunables=tun)
+    case = W.attention_case(1, H, Hkv, dh, L, m, dtype="bf16")
+    idx = torch.from_numpy(case["idx"]).cuda()
+    q = B.to_device(case["q"], "bf16")
+    got = []
+    for off_k, off_v in ((0, 0), (2, 0), (0, 4)):
+        def put(a, off):
+            t = torch.zeros(a.size + 8, dtype=torch.bfloat16, device="cuda")[off: off + a.size].view(a.shape)
+            t.copy_(B.to_device(a, "bf16"))
+            return t
+        kc, vc = put(case["k_cache"], off_k), put(case["v_cache"], off_v)
+        out, avg = torch.zeros_like(q), torch.zeros((m, L), device="cuda")
+        ctx.d2c_attention(q, idx, m, None, None, kc, vc, L, out, avg)
+        torch.cuda.synchronize()
+        got.append((out, avg))
+    for out, avg in got[1:]:
+        assert torch.equal(out, got[0][0]) and torch.equal(avg, got[0][1])
+    ctx.close()
