@@ -653,6 +653,115 @@ hipError_t launch_wide(const GemmPlan& pl, const void* A, int lda, const void* W
   return hipErrorInvalidValue;
 }
 
+// ---- few rows and a short contraction in float: one 16 x 16 tile per wave, every load of its contraction (at most kTileChunks
+// chunks) requested at once.  Such a projection (37 rows x 768 x 256: 0.9 MB) is one memory latency long; gemm_rows_kernel, made
+// to stream, spent several on its double-buffered chunks and ran on 8 to 24 compute units.  The activation rows (and row-major
+// weights) come in whole rows and turn into operands in LDS, pre-tiled weights straight into registers.  Four neighbouring
+// waves (64 columns) make a workgroup; the grid has one row of workgroups per 16 rows.  37 rows, pre-tiled: 768 x 256
+// 9.8 -> 3.8 us, 1376 x 256 with the gate 9.8 -> 4.2, 256 x 256 7.1 -> 3.7, 256 x 688 6.9 -> 3.7 (activations in operand order:
+// 5.7 to 6.6).
+constexpr int kTileChunks = 4;
+// More workgroups than this gain nothing over gemm_rows_kernel, which reads the weights once for all rows (37 rows x 4096 x 512
+// in 384 workgroups 12.8 us, 10.0 there; 100 rows x 1376 x 256 in 154 7.5, 13.5 there).
+constexpr int kTileWgs = 192;
+template <int NC, int MODE>
+__global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
+                                                        float* __restrict__ P, int ldp, size_t split_stride, int m, int N, int K,
+                                                        int k_per_split, float* __restrict__ act) {
+  constexpr int E = 4, KS = 16, KC = 64;
+  constexpr int kPieces = NC * 16;                                  // 16-byte pieces of a row
+  constexpr int kPitch = kPieces + 1;                               // in LDS: neighbouring rows on other banks
+  __shared__ u32x4 a_lds[16 * kPitch];
+  __shared__ u32x4 w_lds[MODE == kRowMajor ? 64 * kPitch : 1];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4;
+  const int n_base = (blockIdx.x * 4 + wave) * 16, row0 = blockIdx.y * 16;
+  const int k_begin = blockIdx.z * k_per_split, k_end = min(K, k_begin + k_per_split);
+  // nothing is requested past the end of the contraction or of the rows (the last piece again, not used)
+  Frag<float> b[NC * kSteps];
+  u32x4 w_reg[MODE == kRowMajor ? NC * 4 : 1], a_reg[NC];
+  if constexpr (MODE == kRowMajor) {
+#pragma unroll
+    for (int i = 0; i < NC * 4; ++i) {
+      const int row = (i * 64 + lane) / kPieces, k = k_begin + (i * 64 + lane) % kPieces * E;
+      w_reg[i] = ld16(W + (size_t)min(n_base + row, N - 1) * ldw + min(k, K - E));
+    }
+  } else {
+    const float* wtile = W + ((size_t)min(n_base / 16, (N + 15) / 16 - 1) * ldw + k_begin / KC) * (16 * KC) + lane * E;
+    const int last = (k_end - k_begin - 1) / KC;
+#pragma unroll
+    for (int i = 0; i < NC * kSteps; ++i) b[i].raw = ld16(wtile + (size_t)min(i / kSteps, last) * (16 * KC) + i % kSteps * (64 * E));
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int at = i * 256 + (int)threadIdx.x, k = k_begin + at % kPieces * E;
+    a_reg[i] = ld16(A + (size_t)min(row0 + at / kPieces, m - 1) * lda + min(k, K - E));
+    if (k >= k_end) a_reg[i] = u32x4{0u, 0u, 0u, 0u};
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int at = i * 256 + (int)threadIdx.x;
+    a_lds[at / kPieces * kPitch + at % kPieces] = a_reg[i];
+  }
+  if constexpr (MODE == kRowMajor) {
+#pragma unroll
+    for (int i = 0; i < NC * 4; ++i) {
+      const int row = (i * 64 + lane) / kPieces, piece = (i * 64 + lane) % kPieces;
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      w_lds[(wave * 16 + row) * kPitch + piece] = k_begin + piece * E < k_end ? w_reg[i] : zero;
+    }
+  }
+  __syncthreads();
+  Frag<float> a[NC * kSteps];
+#pragma unroll
+  for (int i = 0; i < NC * kSteps; ++i) {
+    a[i].raw = a_lds[r * kPitch + i * 4 + g];
+    if (MODE == kRowMajor) b[i].raw = w_lds[(wave * 16 + r) * kPitch + i * 4 + g];
+  }
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int i = 0; i < NC * kSteps; ++i) mfma16(acc[i & 1], a[i], b[i]);
+  const f32x4 sum = acc[0] + acc[1];
+  if constexpr (MODE == kPreSwiglu) {
+    // column tiles alternate gate, up, gate, up ..: the odd wave of a pair hands the up values over
+    __shared__ f32x4 xch[2][64];
+    if (wave & 1) xch[wave >> 1][lane] = sum;
+    __syncthreads();
+    const int F = N >> 1, col = (n_base >> 5) * 16 + r;
+    if ((wave & 1) || col >= F) return;
+    const f32x4 u = xch[wave >> 1][lane];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = row0 + g * 4 + j;
+      if (row < m) act[(size_t)row * F + col] = sum[j] / (1.0f + expf(-sum[j])) * u[j];
+    }
+    return;
+  }
+  const int col = n_base + r;
+  if (col >= N) return;
+  float* out = P + (size_t)blockIdx.z * split_stride;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int row = row0 + g * 4 + j;
+    if (row < m) out[(size_t)row * ldp + col] = sum[j];
+  }
+}
+
+template <int MODE>
+hipError_t launch_tile(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp, size_t split_stride, int m,
+                       int N, int K, hipStream_t st, void* act) {
+  const dim3 grid((N + 63) / 64, pl.row_chunks, pl.splits);
+#define D2C_TILE(nc_)                                                                                                           \
+  if (pl.k_per_split <= nc_ * 64) {                                                                                             \
+    hipLaunchKernelGGL((gemm_tile_kernel<nc_, MODE>), grid, dim3(256), 0, st, (const float*)A, lda, (const float*)W, ldw, P, ldp, \
+                       split_stride, m, N, K, pl.k_per_split, (float*)act);                                                     \
+    return hipGetLastError();                                                                                                   \
+  }
+  D2C_TILE(1) D2C_TILE(2) D2C_TILE(3) D2C_TILE(4)
+#undef D2C_TILE
+  return hipErrorInvalidValue;
+}
+
 template <typename T, int MT, int NT, int WAVES, int MODE>
 hipError_t launch_t(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp,
                     size_t split_stride, int m, int N, int K, hipStream_t st, void* act) {
@@ -700,6 +809,10 @@ hipError_t launch_mt(const GemmPlan& pl, const void* A, int lda, const void* W, 
 template <typename T, int MODE>
 hipError_t launch_nt(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp,
                      size_t ss, int m, int N, int K, hipStream_t st, void* act) {
+  if (pl.tile) {
+    if constexpr (sizeof(T) == 4) return launch_tile<MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
+    return hipErrorInvalidValue;
+  }
   if (pl.nt == 1) {
     if (pl.waves == 8) return launch_mt<T, 1, 8, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
     if (pl.waves == 6) return launch_mt<T, 1, 6, MODE>(pl, A, lda, W, ldw, P, ldp, ss, m, N, K, st, act);
@@ -817,7 +930,7 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   // Small row-major matrices are faster with two column tiles (512 rows x 1024 x 1024: 18 us, 22 and 25; 256 x 256 11, 13, 14).
   const bool wide = pl.row_chunks > 1 && m >= t.gemm_wide_min_rows && dtype == kBF16 && t.gemm_wide_tiles != 0 &&
                     K % 256 == 0 && !(row_major && t.gemm_wide_tiles == 1 && (size_t)N * K <= ((size_t)1 << 20));
-  pl.wide = false;
+  pl.wide = pl.tile = false;
   pl.rot = t.gemm_rot;
   // 8 waves share one activation chunk in LDS: fewer, fatter workgroups (about 1.5 per compute unit) with
   // fewer k splits measured faster than 4-wave groups at every projection shape of the two models
@@ -829,6 +942,21 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   const int kc = dtype == kBF16 ? 128 : 64;                       // elements per 256-byte chunk
   const int chunks = (K + kc - 1) / kc;
   const int max_splits = single_split ? 1 : t.gemm_max_splits;
+  // Up to 128 rows in float whose contraction, or a split of it, gemm_tile_kernel holds in flight at once.  Row-major weights
+  // in several splits need the sum as a launch of its own and gain only where the other kernel reads them for many rows
+  // (256 x 688: up to 64 rows 9.5 us there, 10.4 here; 100 rows 13.3 and 10.6).
+  if (dtype != kBF16 && tiles <= 8 && t.gemm_waves == 0) {
+    const int s = (chunks + kTileChunks - 1) / kTileChunks, cps = (chunks + s - 1) / s;
+    if (s <= max_splits && (N + 63) / 64 * tiles * s <= kTileWgs && (!row_major || s == 1 || tiles > 4)) {
+      pl.tile = true;
+      pl.mt = pl.nt = 1;
+      pl.waves = 4;
+      pl.row_chunks = tiles;
+      pl.k_per_split = cps * kc;
+      pl.splits = (K + pl.k_per_split - 1) / pl.k_per_split;
+      return pl;
+    }
+  }
   auto blocks_of = [&](int waves) { return (N + 16 * pl.nt * waves - 1) / (16 * pl.nt * waves); };
   auto splits_for = [&](int waves) {
     int s = 1;
@@ -997,7 +1125,7 @@ hipError_t launch_gemm(int dtype, const GemmPlan& pl, const void* A, int lda, co
       return launch_nt<bf16, kPre>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);
     return launch_nt<float, kPre>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st, nullptr);
   }
-  if (pl.nt == 1 && (uintptr_t)W % 16 == 0 && (size_t)ldw * dtype_size(dtype) * 16 < (1ull << 31) &&
+  if (pl.nt == 1 && !pl.tile && (uintptr_t)W % 16 == 0 && (size_t)ldw * dtype_size(dtype) * 16 < (1ull << 31) &&
       staging_pays(dtype, pl, N)) {
     if (dtype == kBF16)
       return launch_rows_staged<bf16>(pl, A, lda, W, ldw, P, ldp, split_stride, m, N, K, st);

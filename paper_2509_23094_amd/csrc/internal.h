@@ -45,6 +45,7 @@ struct GemmPlan {
   int k_per_split;
   int row_chunks;
   int rot;       // multiplier of the per-workgroup start-chunk rotation (0 = none)
+  bool tile;     // gemm_tile_kernel (float): 16 rows per workgroup, one row_chunk each, whole contractions in flight
   bool wide;     // gemm_wide_kernel: two row chunks per workgroup, four of its 8 waves on each; else gemm_rows_kernel, one
 
   int chunks_per_wg() const { return wide ? 2 : 1; }

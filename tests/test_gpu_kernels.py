@@ -886,3 +886,18 @@ def test_attention_tiled_rows_straight_into_lds(B, H, Hkv, dh, L, m, waves):
     for out, avg in got[1:]:
         assert torch.equal(out, got[0][0]) and torch.equal(avg, got[0][1])
     ctx.close()
+
+
+@pytest.mark.parametrize("m,N,K", [(1, 1, 4), (15, 40, 60), (16, 63, 64), (17, 64, 68), (31, 65, 128), (33, 100, 132), (64, 250, 192),
+                                   (65, 130, 196), (128, 1376, 256), (100, 256, 260), (128, 96, 688), (81, 60, 2048), (81, 60, 2052)])
+def test_linear_f32_one_tile_per_wave(B, m, N, K):
+    """Few rows and a short contraction in float: edges of rows, columns, chunks, splits, and the first contraction past them."""
+    test_linear_parity(B, "f32", m, N, K)
+
+
+@pytest.mark.parametrize("m", [1, 17, 128])
+@pytest.mark.parametrize("wd", [W.ModelDims(1, 132, 2, 1, 32, 208, 64, dtype="f32"), W.ModelDims(1, 260, 4, 4, 16, 528, 64, dtype="f32")],
+                         ids=["132", "260"])
+def test_refresh_layer_f32_one_tile_per_wave(B, wd, m):
+    """The same with pre-tiled weights and the gated epilogue: ragged last chunks, one contraction in one split and in two."""
+    _refresh_layer_parity(B, f"f32-{wd.d_model}", wd, 131, m)
