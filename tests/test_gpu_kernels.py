@@ -901,3 +901,10 @@ def test_linear_f32_one_tile_per_wave(B, m, N, K):
 def test_refresh_layer_f32_one_tile_per_wave(B, wd, m):
     """The same with pre-tiled weights and the gated epilogue: ragged last chunks, one contraction in one split and in two."""
     _refresh_layer_parity(B, f"f32-{wd.d_model}", wd, 131, m)
+
+
+@pytest.mark.parametrize("dtype,m,N,K", [("bf16", 1, 650, 2048), ("bf16", 17, 3000, 4096), ("bf16", 70, 1000, 8192), ("bf16", 150, 520, 2048),
+                                         ("bf16", 256, 300, 4096), ("bf16", 300, 1030, 2048), ("f32", 40, 3000, 1024), ("f32", 130, 200, 2048)])
+def test_linear_rows_a_power_of_two_apart(B, dtype, m, N, K):
+    """Row-major weights whose workgroups start their walks over k at different chunks."""
+    test_linear_parity(B, dtype, m, N, K)
