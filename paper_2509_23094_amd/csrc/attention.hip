@@ -877,11 +877,18 @@ size_t attention_scratch_floats(const Tunables& t, int dtype, int max_m, int max
   return dtype == kBF16 ? attention_tiled_scratch_floats(t, max_m, max_L, n_heads, head_dim) : 0;
 }
 
-// From kLongMinM rows on the tiled kernels also take the key ranges too long for the per-head probability
-// rows: there the few-row kernels would need their second Q K^T launch for the head average.
-constexpr int kLongMinM = 48;
+// The tiled kernels also take the key ranges too long for the per-head probability rows, where the few-row kernels need a
+// second Q K^T launch for the head average: from kLongMinM rows on, up to kOneTile from kOneTileMinL keys on, and for any
+// rows from kLongMinL on.  In between the call without the average is still the faster there (us, few-row / tiled kernels, 32
+// heads of 128, without and with the average: 40 x 1100 11.5/12.7 and 18.6/16.8, 40 x 1500 13.3/14.3 and 23.1/17.5; elsewhere
+// 16 x 1500 12.8/12.1 and 19.7/14.7, 40 x 2048 16.1/16.0 and 27.0/18.9, 40 x 4096 25.7/21.1 and 45.8/25.1, 1 x 4096 25.5/19.2 and
+// 33.5/20.9; heads of 64, 17 x 1100 9.6/11.7 and 15.1/13.3, 17 x 1500 10.8/11.0 and 17.0/13.6).  The output's bits may not
+// depend on whether the average is wanted, so one line serves both.
+constexpr int kLongMinM = 48, kOneTile = 16, kOneTileMinL = 1536, kLongMinL = 1792;
 bool attention_is_tiled(const Tunables& t, int dtype, int m, int L) {
-  return dtype == kBF16 && (m >= t.attn_tiled_min_m || (m >= std::min(kLongMinM, t.attn_tiled_min_m) && L > kProbsMaxL));
+  if (dtype != kBF16) return false;
+  if (m >= t.attn_tiled_min_m) return true;
+  return L > kProbsMaxL && (m >= kLongMinM || L >= (m <= kOneTile ? kOneTileMinL : kLongMinL));
 }
 
 hipError_t launch_attention_fwd(const Tunables& t, int dtype, const void* q, const void* k_cache, const void* v_cache, int m, int L,

@@ -110,7 +110,7 @@ hipError_t launch_rope_table(float* cos_t, float* sin_t, int max_pos, int head_d
 // Two kernel families.  Few query rows (fp32, or bf16 below attn_tiled_min_m rows): a forward launch and, for
 // the head average, either per-head probability rows written by the forward launch itself (probs, see
 // attention_fwd_emits_probs) or a second launch (launch_attention_avg) that needs the forward's lse.  Many
-// rows in bf16 (attention_is_tiled: attn_tiled_min_m rows, or 48 already when the key range is too long
+// rows in bf16 (attention_is_tiled: attn_tiled_min_m rows, or fewer when the key range is too long
 // for the probability rows): K/V blocks staged through LDS, key range split over workgroups; the
 // forward launch also leaves what the head average needs, and one finishing launch merges the splits and
 // writes the average, so tiled_avg is given to launch_attention_fwd itself.

@@ -95,7 +95,7 @@ ATTN_CASES = [
     ("bf16", 5, 5, 128, 300, 16, "few"),          # 5 kv heads: plain placement
     ("bf16", 28, 4, 128, 1824, 93, "default"),    # the long-generation decode step late on: too long for the
                                                   # per-head probability rows, so the tiled kernels from 48 rows on
-    ("bf16", 28, 4, 128, 1824, 40, "default"),    # same length, fewer rows: few-row kernels and their second launch
+    ("bf16", 28, 4, 128, 1824, 40, "default"),    # same length, fewer rows
     ("f32", 4, 4, 64, 128, 73, ""),               # the small fp32 model's geometry
     ("f32", 4, 2, 8, 19, 5, ""),
 ]
@@ -908,3 +908,11 @@ def test_refresh_layer_f32_one_tile_per_wave(B, wd, m):
 def test_linear_rows_a_power_of_two_apart(B, dtype, m, N, K):
     """Row-major weights whose workgroups start their walks over k at different chunks."""
     test_linear_parity(B, dtype, m, N, K)
+
+
+@pytest.mark.parametrize("H,Hkv,dh,L,m", [(32, 32, 128, 1536, 16), (32, 32, 128, 1536, 17), (28, 4, 128, 1791, 47), (28, 4, 128, 1792, 17),
+                                          (4, 2, 64, 1535, 1), (3, 1, 64, 2050, 40), (5, 5, 128, 1537, 1)])
+def test_attention_few_rows_on_long_key_ranges(B, H, Hkv, dh, L, m):
+    """Both sides of the lines between the few-row and the tiled kernels past 1024 keys, as the library chooses by itself."""
+    say(f"attention few rows, long H={H} Hkv={Hkv} dh={dh} L={L} m={m}")
+    _attention_parity(B, "bf16", H, Hkv, dh, L, m)
