@@ -203,9 +203,10 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_tiled_fwd_kernel(const Bat
   // Online softmax in the base-2 domain: p = 2^(s*c - ref) with c = scale*log2(e).  ref is a per-row
   // reference, not necessarily the running maximum: it is only raised (and O, l rescaled) when a score
   // exceeds it by more than kRaise, so p stays below 2^kRaise.  The result is the same softmax (shift
-  // invariance); the decision depends on the data only.  Every lane checks its own 16 exponents of a row; only
-  // when some lane of the wave finds one too large do the four lanes that
-  // share a row exchange their maxima and raise the reference (rare after the first block).
+  // invariance).  Every lane checks its own 16 scores of a row against the row's reference; only when some lane
+  // of the wave finds one too large do the four lanes that share a row exchange their maxima and raise the
+  // reference (rare after the first block).  Both ask the same question in the same rounding, so that a row is
+  // raised by its own scores, whichever rows share the wave.
   constexpr float kRaise = 8.f;
   const float c2 = scale * 1.44269504088896341f;
   float ref[QT], l_run[QT];
@@ -272,29 +273,21 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_tiled_fwd_kernel(const Bat
             for (int t = 0; t < QT; ++t) st[a][t][j] = -INFINITY;
           }
     }
-    // ---- exponents against the rows' references (+inf where a row has none yet)
-    float x[QT][4][4];
+    // ---- this lane's maxima against the rows' references
+    float tmax[QT];
     bool need = false;
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-      float xm[4];
+      float am[4];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[t][a][j] = fmaf(st[a][t][j], c2, -ref[t]);
-        xm[a] = fmaxf(fmaxf(x[t][a][0], x[t][a][1]), fmaxf(x[t][a][2], x[t][a][3]));
-      }
-      need = need || fmaxf(fmaxf(xm[0], xm[1]), fmaxf(xm[2], xm[3])) > kRaise;
+      for (int a = 0; a < 4; ++a) am[a] = fmaxf(fmaxf(st[a][t][0], st[a][t][1]), fmaxf(st[a][t][2], st[a][t][3]));
+      tmax[t] = fmaxf(fmaxf(am[0], am[1]), fmaxf(am[2], am[3]));
+      need = need || tmax[t] * c2 > ref[t] + kRaise;
     }
     if (__builtin_amdgcn_ballot_w64(need) != 0) {
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
-        float rmax = -INFINITY;
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) rmax = fmaxf(rmax, st[a][t][j]);
-        rmax = fmaxf(rmax, __shfl_xor(rmax, 16, kWave));
+        float rmax = fmaxf(tmax[t], __shfl_xor(tmax[t], 16, kWave));
         rmax = fmaxf(rmax, __shfl_xor(rmax, 32, kWave)) * c2;       // the row's maximum; -inf only if it has no key yet
         const float ref_new = rmax > ref[t] + kRaise ? rmax : ref[t];
         const float alpha = ref_new == ref[t] ? 1.f : __builtin_amdgcn_exp2f(ref[t] - ref_new);   // 0 on the first block
@@ -302,30 +295,28 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_tiled_fwd_kernel(const Bat
 #pragma unroll
         for (int d = 0; d < ND; ++d) acc[d][t] *= alpha;
         ref[t] = ref_new;
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) x[t][a][j] = fmaf(st[a][t][j], c2, -ref_new);
       }
     }
     // ---- probabilities against the references, packed as the B operand of O^T += V^T P^T
     Frag<bf16> pf[2][QT];
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
+      const float nref = -ref[t];
       float psum = 0.f;
+      float x[4][4];
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          x[t][a][j] = __builtin_amdgcn_exp2f(x[t][a][j]);
-          psum += x[t][a][j];
+          x[a][j] = __builtin_amdgcn_exp2f(fmaf(st[a][t][j], c2, nref));
+          psum += x[a][j];
         }
       l_run[t] += psum;                                // this lane's share; lanes are added at the end
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
-        pf[ks][t].raw = u32x4{pack_bf16(x[t][2 * ks][0], x[t][2 * ks][1]), pack_bf16(x[t][2 * ks][2], x[t][2 * ks][3]),
-                              pack_bf16(x[t][2 * ks + 1][0], x[t][2 * ks + 1][1]),
-                              pack_bf16(x[t][2 * ks + 1][2], x[t][2 * ks + 1][3])};
+        pf[ks][t].raw = u32x4{pack_bf16(x[2 * ks][0], x[2 * ks][1]), pack_bf16(x[2 * ks][2], x[2 * ks][3]),
+                              pack_bf16(x[2 * ks + 1][0], x[2 * ks + 1][1]),
+                              pack_bf16(x[2 * ks + 1][2], x[2 * ks + 1][3])};
     }
     if constexpr (DMA) wait_requests();
     if constexpr (EMIT) {

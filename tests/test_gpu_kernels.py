@@ -916,3 +916,56 @@ def test_attention_few_rows_on_long_key_ranges(B, H, Hkv, dh, L, m):
     """Both sides of the lines between the few-row and the tiled kernels past 1024 keys, as the library chooses by itself."""
     say(f"attention few rows, long H={H} Hkv={Hkv} dh={dh} L={L} m={m}")
     _attention_parity(B, "bf16", H, Hkv, dh, L, m)
+
+
+def _f32_parts(s):
+    """float32 values as three bf16 pieces hi + mid / 2^8 + lo / 2^16, without a rounding"""
+    s = np.asarray(s, np.float32)
+    out = []
+    for _ in range(3):
+        hi = (s.view(np.uint32) & np.uint32(0xffff0000)).view(np.float32)
+        out.append(hi)
+        s = ((s - hi) * np.float32(256.0)).astype(np.float32)
+    assert not s.any()
+    return out
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+def test_attention_row_does_not_depend_on_its_neighbours(B, dh):
+    """A row's reference is raised by the row's own scores: here its second block of keys exceeds the reference by 8 within a
+    rounding of the comparison, alone and beside a row that raises its own reference there; what was decided shows in the roundings
+    of a third block 4.3 above the second."""
+    scale = np.float32(1.0) / np.sqrt(np.float32(dh))
+    c2 = np.float32(scale * np.float32(1.44269504088896341))
+    rng = np.random.default_rng(3)
+    pairs = {True: [], False: []}                            # (first block's maximum, second block's), by which rounding exceeds 8
+    while min(len(p) for p in pairs.values()) < 6:
+        s0 = np.float32(rng.uniform(20.0, 60.0))
+        ref = np.float32(s0 * c2)
+        s1 = np.float32((float(ref) + 8.0) / float(c2))
+        for _ in range(4):
+            fused = bool(np.float32(float(s1) * float(c2) - float(ref)) > 8.0)
+            if fused != bool(np.float32(s1 * c2) > np.float32(ref + np.float32(8.0))):
+                pairs[fused].append((s0, s1))
+            s1 = np.nextafter(s1, np.float32(1e9))
+    say(f"attention row beside another, head dimension {dh}")
+    ctx, _, _ = _ctx_for(B, W.ModelDims(1, dh, 1, 1, dh, 64, 64, dtype="bf16"), max_seq=192, tunables={"attn_tiled_min_m": 1, "attn_max_splits": 1})
+    q = np.zeros((2, dh), np.float32)
+    q[0, :3] = 1.0, 2.0 ** -8, 2.0 ** -16
+    q[1] = 2.0 * q[0]
+    v = B.to_device(W.round_bf16(W.hidden_rows(21, 192, dh)), "bf16")
+    for s0, s1 in pairs[True][:6] + pairs[False][:6]:
+        s = np.concatenate([rng.uniform(0.0, s0, 64), rng.uniform(s0, 0.99 * s1, 64), rng.uniform(s0, s1, 64)]).astype(np.float32)
+        s[10], s[70], s[150] = s0, s1, s1 + np.float32(4.3) / c2
+        k = np.zeros((192, dh), np.float32)
+        k[:, :3] = np.stack(_f32_parts(s), 1)
+        kc, out = B.to_device(k, "bf16"), []
+        for m in (1, 2):
+            o = torch.zeros((m, dh), dtype=torch.bfloat16, device="cuda")
+            ctx.d2c_attention(B.to_device(q[:m], "bf16"), None, m, None, None, kc, v, 192, o, None)
+            torch.cuda.synchronize()
+            out.append(o[0])
+        p = np.exp((s.astype(np.float64) - s[150]) * float(scale))
+        assert rel_l2(host(out[0]), p @ host(v).astype(np.float64) / p.sum()) < TOL["bf16"]
+        assert torch.equal(out[0], out[1]), f"scores {s0} and {s1}"
+    ctx.close()
