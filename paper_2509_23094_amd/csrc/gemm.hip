@@ -677,7 +677,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict_
   const int r = lane & 15, g = lane >> 4;
   const int n_base = (blockIdx.x * 4 + wave) * 16, row0 = blockIdx.y * 16;
   const int k_begin = blockIdx.z * k_per_split, k_end = min(K, k_begin + k_per_split);
-  // nothing is requested past the end of the contraction or of the rows (the last piece again, not used)
+  // nothing is read past the end of the contraction or of the rows (the last piece again, not used)
   Frag<float> b[NC * kSteps];
   u32x4 w_reg[MODE == kRowMajor ? NC * 4 : 1], a_reg[NC];
   if constexpr (MODE == kRowMajor) {
@@ -687,10 +687,14 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict_
       w_reg[i] = ld16(W + (size_t)min(n_base + row, N - 1) * ldw + min(k, K - E));
     }
   } else {
-    const float* wtile = W + ((size_t)min(n_base / 16, (N + 15) / 16 - 1) * ldw + k_begin / KC) * (16 * KC) + lane * E;
-    const int last = (k_end - k_begin - 1) / KC;
+    // chunks past the end of a short split lie past the end of the buffer and read as zeros: the activations are zeros there
+    // too, and an infinite weight (of the last chunk, read again) times zero would be NaN
+    const float* wtile = W + ((size_t)min(n_base / 16, (N + 15) / 16 - 1) * ldw + k_begin / KC) * (16 * KC);
+    const int bytes = (k_end - k_begin + KC - 1) / KC * (16 * KC * 4);
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wtile), 0, bytes, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < NC * kSteps; ++i) b[i].raw = ld16(wtile + (size_t)min(i / kSteps, last) * (16 * KC) + i % kSteps * (64 * E));
+    for (int i = 0; i < NC * kSteps; ++i)
+      b[i].raw = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane * 16 + i * 1024, 0, 0));
   }
 #pragma unroll
   for (int i = 0; i < NC; ++i) {

@@ -969,3 +969,29 @@ def test_attention_row_does_not_depend_on_its_neighbours(B, dh):
         assert rel_l2(host(out[0]), p @ host(v).astype(np.float64) / p.sum()) < TOL["bf16"]
         assert torch.equal(out[0], out[1]), f"scores {s0} and {s1}"
     ctx.close()
+
+
+def test_infinite_weight_in_a_short_last_split(B):
+    """A down projection of 11 chunks in splits of 4, 4 and 3 (float, pre-tiled): an infinite weight in the last chunk gives
+    infinities of the products' signs in its column, which 1e30 shows, and changes no other column."""
+    wd = W.ModelDims(1, 256, 4, 4, 64, 688, 64, dtype="f32")
+    m, L = 37, 64
+    plan = B.d2c_plan_projection("f32", m, 256, 688)
+    assert (plan["splits"], plan["k_per_split"], plan["waves"]) == (3, 256, 4)
+    say("infinite weight in a short last split")
+    dims = W.with_layers(wd, 1)
+    idx_host = np.arange(m, dtype=np.int32)
+    got = []
+    for value in (1e30, np.inf):
+        mdl = W.model_weights(dims, 0)
+        mdl["layers"][0]["w_down"][5, 680] = value
+        ctx = B.Context(dims, mdl, L)
+        h = torch.from_numpy(W.hidden_rows(4, m, 256, std=0.5)).cuda()
+        kc, vc = torch.zeros((L, 256), device="cuda"), torch.zeros((L, 256), device="cuda")
+        ctx.d2c_refresh_layer(0, h, torch.from_numpy(idx_host).cuda(), idx_host, kc, vc, L)
+        torch.cuda.synchronize()
+        got.append(host(h))
+        ctx.close()
+    large, inf = got
+    np.testing.assert_array_equal(inf[:, 5], np.copysign(np.inf, large[:, 5]).astype(np.float32))
+    np.testing.assert_array_equal(np.delete(inf, 5, 1), np.delete(large, 5, 1))
