@@ -888,7 +888,11 @@ constexpr int kLongMinM = 48, kOneTile = 16, kOneTileMinL = 1536, kLongMinL = 17
 bool attention_is_tiled(const Tunables& t, int dtype, int m, int L) {
   if (dtype != kBF16) return false;
   if (m >= t.attn_tiled_min_m) return true;
-  return L > kProbsMaxL && (m >= kLongMinM || L >= (m <= kOneTile ? kOneTileMinL : kLongMinL));
+  if (L <= kProbsMaxL) return false;
+  if (m >= kLongMinM) return true;
+  // 8 waves, if asked for, take two query tiles each, and so few rows one unless two are asked for: no such shape
+  if (t.attn_waves == 8 && t.attn_qt != 2) return false;
+  return L >= (m <= kOneTile ? kOneTileMinL : kLongMinL);
 }
 
 hipError_t launch_attention_fwd(const Tunables& t, int dtype, const void* q, const void* k_cache, const void* v_cache, int m, int L,

@@ -995,3 +995,14 @@ def test_infinite_weight_in_a_short_last_split(B):
     large, inf = got
     np.testing.assert_array_equal(inf[:, 5], np.copysign(np.inf, large[:, 5]).astype(np.float32))
     np.testing.assert_array_equal(np.delete(inf, 5, 1), np.delete(large, 5, 1))
+
+
+@pytest.mark.parametrize("tun", [{"attn_waves": 8}, {"attn_waves": 8, "attn_qt": 1}], ids=["by-rows", "one-tile"])
+@pytest.mark.parametrize("L,m", [(1536, 16), (1792, 1), (1792, 40), (2050, 47)])
+def test_attention_few_rows_with_eight_waves_asked_for(B, L, m, tun):
+    """attn_waves = 8 is a shape of more than 64 rows: fewer rows on long key ranges stay with the few-row kernels, and where the
+    tiled ones are asked for as well the call is refused."""
+    say(f"attention few rows, long, L={L} m={m} {tun}")
+    _attention_parity(B, "bf16", 4, 2, 128, L, m, tunables=tun)
+    with pytest.raises(B.D2CError):
+        _attention_parity(B, "bf16", 4, 2, 128, L, m, tunables={"attn_tiled_min_m": 1, **tun})
