@@ -890,6 +890,7 @@ bool attention_is_tiled(const Tunables& t, int dtype, int m, int L) {
   if (m >= t.attn_tiled_min_m) return true;
   if (L <= kProbsMaxL) return false;
   if (m >= kLongMinM) return true;
+  if (t.attn_tiled_min_m > Tunables{}.attn_tiled_min_m) return false;      // the few-row kernels are asked for
   // 8 waves, if asked for, take two query tiles each, and so few rows one unless two are asked for: no such shape
   if (t.attn_waves == 8 && t.attn_qt != 2) return false;
   return L >= (m <= kOneTile ? kOneTileMinL : kLongMinL);

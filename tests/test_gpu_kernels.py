@@ -1006,3 +1006,20 @@ def test_attention_few_rows_with_eight_waves_asked_for(B, L, m, tun):
     _attention_parity(B, "bf16", 4, 2, 128, L, m, tunables=tun)
     with pytest.raises(B.D2CError):
         _attention_parity(B, "bf16", 4, 2, 128, L, m, tunables={"attn_tiled_min_m": 1, **tun})
+
+
+@pytest.mark.parametrize("min_m,L,m,few", [(1 << 30, 1792, 40, True), (97, 1536, 16, True), (97, 3000, 47, True), (97, 1100, 48, False),
+                                           (96, 1792, 40, False), (64, 1536, 1, False), (1, 1100, 1, False)])
+def test_attention_few_rows_asked_for_on_long_key_ranges(B, min_m, L, m, few):
+    """attn_tiled_min_m above its default keeps calls of fewer than 48 rows in the few-row kernels, whose head average is a
+    launch of its own, on every key range."""
+    say(f"attention families min_m={min_m} L={L} m={m}")
+    tun = {"attn_tiled_min_m": min_m}
+    _attention_parity(B, "bf16", 4, 2, 64, L, m, tunables=tun)
+    ctx, _, _ = _ctx_for(B, W.ModelDims(1, 256, 4, 2, 64, 64, 64, dtype="bf16"), max_seq=L, tunables=tun)
+    case = W.attention_case(1, 4, 2, 64, L, m, dtype="bf16")
+    q, kc, vc = (B.to_device(case[n], "bf16") for n in ("q", "k_cache", "v_cache"))
+    ctx.d2c_profile_begin()
+    ctx.d2c_attention(q, None, m, None, None, kc, vc, L, torch.zeros_like(q), torch.zeros((m, L), device="cuda"))
+    assert ctx.d2c_profile_end()["attn_avg"]["launches"] == (1 if few else 0)
+    ctx.close()
