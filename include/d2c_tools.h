@@ -39,7 +39,8 @@ int d2c_profile_end(d2c_ctx* ctx, double* ms, int64_t* launches, double* bytes);
  * "gemm_wide_mt" (6, 7, 8 row tiles for each four waves of that shape; 0 = by shape),
  * "gemm_wide_min_rows" (that shape from this many rows on), "gemm_tall_chunk" (0/1: 129-192 bf16 rows
  * as one row chunk), "gemm_preshuffle" (0/1: pre-tiled weight copies; only at d2c_init_tuned), "gemm_rot"
- * (chunks of the contraction between the starts of neighbouring workgroups; 0 = by the row pitch);
+ * (chunks of the contraction between the starts of neighbouring workgroups, 0 = all start where k starts; not
+ * set: by the row pitch);
  * attention: "attn_tiled_min_m" (bf16 attention switches to the LDS-tiled kernels from this many query rows on,
  * past 1024 keys from 48 on; unless it is above its default of 96, fewer rows do on longer key ranges),
  * "attn_max_splits" (1..8, key-range splits of one attention launch), "attn_qt", "attn_waves" (4, 8; with 8 the

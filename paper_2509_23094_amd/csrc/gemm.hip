@@ -940,7 +940,7 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   // 12288 x 4096 24.1 -> 20.4, 65536 x 2048 62 -> 49, x 8192 253 -> 168; one apart gains less (65536 x 2048 56), two less still;
   // nothing at other pitches (152064 x 3584, 4096 x 12288, 30000 x 1024).
   const size_t pitch = (size_t)K * dtype_size(dtype);
-  pl.rot = t.gemm_rot != 0 ? t.gemm_rot : row_major && pitch >= 4096 && (pitch & (pitch - 1)) == 0 ? 3 : 0;
+  pl.rot = t.gemm_rot >= 0 ? t.gemm_rot : row_major && pitch >= 4096 && (pitch & (pitch - 1)) == 0 ? 3 : 0;
   // 8 waves share one activation chunk in LDS: fewer, fatter workgroups (about 1.5 per compute unit) with
   // fewer k splits measured faster than 4-wave groups at every projection shape of the two models
   // (7 waves only where no gated epilogue can follow: it pairs neighbouring waves)

@@ -24,7 +24,7 @@ struct Tunables {
                                // more than 128 rows always do
   int gemm_waves = 0;          // waves per workgroup sharing one activation chunk in LDS: 4, 6, 8, 10; 0 = by shape
   bool gemm_preshuffle = true; // d2c_init keeps pre-tiled copies of the projection matrices (costs their size again)
-  int gemm_rot = 0;            // start chunk of a workgroup's k walk = (column block * this) % chunks; 0 = by the row pitch
+  int gemm_rot = -1;           // start chunk of a workgroup's k walk = (column block * this) % chunks; -1 = by the row pitch
   int attn_tiled_min_m = 96;   // bf16 attention: from this many query rows on, the LDS-tiled kernels
   int attn_max_splits = 8;     // key-range splits of one attention launch (1..8)
   int attn_qt = 0;             // 16-row query tiles per wave in the tiled forward kernel: 1, 2; 0 = by m

@@ -1023,3 +1023,26 @@ def test_attention_few_rows_asked_for_on_long_key_ranges(B, min_m, L, m, few):
     ctx.d2c_attention(q, None, m, None, None, kc, vc, L, torch.zeros_like(q), torch.zeros((m, L), device="cuda"))
     assert ctx.d2c_profile_end()["attn_avg"]["launches"] == (1 if few else 0)
     ctx.close()
+
+
+def _start_chunks(B, dtype, m, N, K, rots, tunables=None):
+    """d2c_linear's results under each gemm_rot (None: as the library chooses)"""
+    ctxs = {rot: _ctx_for(B, W.ModelDims(1, 256, 4, 4, 64, 80, 64, dtype=dtype), max_seq=max(m, 16),
+                          tunables={**(tunables or {}), **({} if rot is None else {"gemm_rot": rot})})[0] for rot in rots}
+    a, w = (B.to_device(W.round_bf16(W.hidden_rows(s, r, K)), dtype) for s, r in ((11, m), (12, N)))
+    got = {}
+    for rot, ctx in ctxs.items():
+        got[rot] = torch.full((m, N), 7.0, device="cuda")
+        ctx.d2c_linear(a, w, m, N, K, got[rot])
+        torch.cuda.synchronize()
+        ctx.close()
+    return got
+
+
+@pytest.mark.parametrize("dtype,m,N,K,chunks", [("bf16", 17, 1000, 4096, 32), ("f32", 17, 1000, 2048, 32), ("bf16", 70, 1000, 8192, 64)])
+def test_linear_no_start_chunk_asked_for(B, dtype, m, N, K, chunks):
+    """gemm_rot = 0: every workgroup starts where k starts, as with a whole turn (a multiple of the chunks), also where the library
+    moves the starts by itself."""
+    say(f"linear gemm_rot=0 {dtype} m={m} N={N} K={K}")
+    got = _start_chunks(B, dtype, m, N, K, (None, 0, chunks), {"gemm_max_splits": 1})
+    assert torch.equal(got[0], got[chunks]) and not torch.equal(got[0], got[None])
