@@ -913,6 +913,33 @@ static bool staging_pays(int dtype, const GemmPlan& pl, int N) {
   return chunks >= 3 || (chunks == 2 && wgs >= 64);
 }
 
+// Chunks of k between the starts of neighbouring workgroups on row-major weights whose rows begin a power of two of 4 KB and
+// more apart: workgroups that walk such rows in step ask for the same few memory channels.  Measured on 1-600 rows x 1024-126464
+// columns, pitches of 4 to 64 KB, weights from memory, 976 sizes: geometric mean 1.04 over no moved starts, none below 0.98:
+//   17 rows x 126464 x 4096 211 -> 178 us, 12288 x 4096 25 -> 21, 65536 x 8192 252 -> 167, 65536 x 2048 65 -> 52; 64 rows gain
+//   10-45 % where 17 do, 100 rows 1-13 %, 256 x 126464 x 4096 412 -> 349, 512 x 126464 x 4096 685 -> 640; nothing at other
+//   pitches (152064 x 3584, 4096 x 12288, 30000 x 1024).
+// One apart does it, except at 4 KB (17 rows x 65536 x 2048: three 52 us, one 58).  Three apart meet again at 16 KB where a
+// workgroup has 96 columns (17 rows x 24576 x 8192: none 79 us, one 68, three 82; 12288 x 8192 44, 37, 49).
+// Where it loses: fewer than 16 chunks per workgroup are over before they fall into step (1 row x 8192 x 4096 in 8 chunks 17.0 ->
+// 18.3 us); activations that fill an XCD's L2 (4 MB) stay there only while all workgroups read the same part of them (64 rows x 16384 x
+// 32768 164 -> 228).  From 129 rows on the matrix cores weigh more: gains only on the widest matrices and, up to 192 rows, splits of
+// 16 and 32 KB rows (150 x 12288 x 16384 152 -> 138), losses elsewhere (150 x 49152 x 4096 in two splits 131 -> 137, 200 x 4096 x
+// 8192 1-2 %, 512 x 12288 x 32768 4 %, 1024 x 8192 x 4096 6 %).
+static int start_chunks(const GemmPlan& pl, int dtype, int m, int N, int K) {
+  const size_t pitch = (size_t)K * dtype_size(dtype);
+  if (pitch < 4096 || (pitch & (pitch - 1)) != 0) return 0;
+  const int chunks = pl.k_per_split / (dtype == kBF16 ? 128 : 64);
+  bool pays;
+  if (pl.row_chunks > 1)
+    pays = pl.wide && pl.splits == 1 && (pl.row_chunks == 2 || (pl.row_chunks <= 4 && chunks >= 32 && pitch <= 32768));
+  else if (pl.mt > 8)
+    pays = chunks >= 16 && pitch <= 32768 && (pl.splits > 1 ? pitch >= 16384 : N >= 49152);
+  else
+    pays = chunks >= 16 && m * pitch < ((size_t)4 << 20);
+  return !pays ? 0 : pitch == 4096 ? 3 : 1;
+}
+
 GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool single_split, bool row_major) {
   GemmPlan pl;
   const int tiles = (m + 15) / 16;
@@ -935,12 +962,7 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   const bool wide = pl.row_chunks > 1 && m >= t.gemm_wide_min_rows && dtype == kBF16 && t.gemm_wide_tiles != 0 &&
                     K % 256 == 0 && !(row_major && t.gemm_wide_tiles == 1 && (size_t)N * K <= ((size_t)1 << 20));
   pl.wide = pl.tile = false;
-  // Row-major rows that start a power of two of 4 KB and more apart: workgroups that walk them in step ask for the same few
-  // memory channels, so they start three chunks apart.  17 rows: 126464 x 4096 210 -> 174 us (and 1-256 rows alike),
-  // 12288 x 4096 24.1 -> 20.4, 65536 x 2048 62 -> 49, x 8192 253 -> 168; one apart gains less (65536 x 2048 56), two less still;
-  // nothing at other pitches (152064 x 3584, 4096 x 12288, 30000 x 1024).
-  const size_t pitch = (size_t)K * dtype_size(dtype);
-  pl.rot = t.gemm_rot >= 0 ? t.gemm_rot : row_major && pitch >= 4096 && (pitch & (pitch - 1)) == 0 ? 3 : 0;
+  pl.rot = 0;
   // 8 waves share one activation chunk in LDS: fewer, fatter workgroups (about 1.5 per compute unit) with
   // fewer k splits measured faster than 4-wave groups at every projection shape of the two models
   // (7 waves only where no gated epilogue can follow: it pairs neighbouring waves)
@@ -1115,6 +1137,7 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
     pl.nt = 4;
     pl.waves = 8;
   }
+  pl.rot = t.gemm_rot >= 0 ? t.gemm_rot : row_major ? start_chunks(pl, dtype, m, N, K) : 0;
   return pl;
 }
 

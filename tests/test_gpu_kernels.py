@@ -1027,15 +1027,18 @@ def test_attention_few_rows_asked_for_on_long_key_ranges(B, min_m, L, m, few):
 
 def _start_chunks(B, dtype, m, N, K, rots, tunables=None):
     """d2c_linear's results under each gemm_rot (None: as the library chooses)"""
-    ctxs = {rot: _ctx_for(B, W.ModelDims(1, 256, 4, 4, 64, 80, 64, dtype=dtype), max_seq=max(m, 16),
+    ctxs = {rot: _ctx_for(B, W.ModelDims(1, 4096, 4, 4, 64, 80, 64, dtype=dtype), max_seq=1024,
                           tunables={**(tunables or {}), **({} if rot is None else {"gemm_rot": rot})})[0] for rot in rots}
-    a, w = (B.to_device(W.round_bf16(W.hidden_rows(s, r, K)), dtype) for s, r in ((11, m), (12, N)))
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    a, w = (torch.empty((r, K), dtype=B.torch_dtype(dtype), device="cuda").normal_(generator=gen) for r in (m, N))
     got = {}
     for rot, ctx in ctxs.items():
         got[rot] = torch.full((m, N), 7.0, device="cuda")
         ctx.d2c_linear(a, w, m, N, K, got[rot])
         torch.cuda.synchronize()
         ctx.close()
+        ref = a.double() @ w.double().T
+        assert ((got[rot].double() - ref).norm() / ref.norm()).item() < 1e-5
     return got
 
 
@@ -1046,3 +1049,16 @@ def test_linear_no_start_chunk_asked_for(B, dtype, m, N, K, chunks):
     say(f"linear gemm_rot=0 {dtype} m={m} N={N} K={K}")
     got = _start_chunks(B, dtype, m, N, K, (None, 0, chunks), {"gemm_max_splits": 1})
     assert torch.equal(got[0], got[chunks]) and not torch.equal(got[0], got[None])
+
+
+@pytest.mark.parametrize("dtype,m,N,K,starts", [
+    ("bf16", 17, 24576, 2048, 3), ("bf16", 17, 12288, 2048, 0), ("bf16", 1, 8192, 4096, 0), ("bf16", 40, 12288, 4096, 1), ("bf16", 17, 12288, 8192, 1),
+    ("bf16", 40, 4096, 32768, 1), ("bf16", 64, 4096, 32768, 0), ("bf16", 150, 8192, 8192, 1), ("bf16", 192, 16384, 4096, 0), ("bf16", 192, 4096, 32768, 0),
+    ("bf16", 192, 65536, 2048, 3),
+    ("bf16", 200, 1024, 4096, 0), ("bf16", 256, 49152, 2048, 3), ("bf16", 300, 24576, 4096, 1), ("bf16", 300, 12288, 4096, 0),
+    ("bf16", 600, 24576, 4096, 0), ("f32", 1, 33000, 1024, 0), ("f32", 17, 12288, 4096, 1)])
+def test_linear_start_chunks_by_shape(B, dtype, m, N, K, starts):
+    """Row-major weights a power of two apart: how many chunks apart the library lets neighbouring workgroups start."""
+    say(f"linear start chunks {dtype} m={m} N={N} K={K}")
+    got = _start_chunks(B, dtype, m, N, K, (None, 0, 1, 3))
+    assert [rot for rot in (0, 1, 3) if torch.equal(got[rot], got[None])] == [starts]
