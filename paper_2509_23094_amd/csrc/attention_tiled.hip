@@ -561,13 +561,15 @@ struct FwdPlan {
 // A sequence whose workgroups in the largest tile shape alone fill the chip is never split (the scratch is sized by this).
 bool may_split(const Tunables& t, int m, int n_heads) { return ((m + 255) / 256) * n_heads < t.attn_target_wgs; }
 
-// The cheapest by a model of the time in us, measured at 12 shapes from 64 x 2048 to 2048 x 2048, 28 and 32 heads of 128, 1 to 8
-// splits (it names the fastest or one within 5 %).  A workgroup has a start (launch, queries, first block) and a part per
-// block of 64 keys: 1.8 for 4 waves alone on a compute unit, 2.8 where two workgroups share one, 2.6 for 8 waves (of twice
-// the queries).  Several splits write and read fp32 partials (about 3.5 TB/s both ways together).  A split thus pays only
-// while compute units are idle: 777 rows x 777 keys 22 us unsplit, 36 in two; 256 x 2048 42 us, 26 in four, 33 in eight.
+// The cheapest by a model of the time in us.  A workgroup has a part per block of 64 keys, of the width of the heads: of 128, 1.8 for
+// 4 waves alone on a compute unit, 2.8 where two workgroups share one, 2.6 for 8 waves (of twice the queries); of 64, 0.75 of that
+// (1.30 / 1.73 measured alone, 0.96 / 1.40 without the head average).  Several splits write and read fp32 partials (about 3.5 TB/s
+// both ways together), so a split pays only while compute units are idle: 777 rows x 777 keys, 32 heads of 128, 22 us unsplit, 36 in
+// two; 256 x 2048 42 us, 26 in four, 33 in eight; heads of 64, 200 x 2048 18 us in four, 22 in eight by 8 waves.
 // The parts are those of calls with the head average (1.35, 2.05 and 1.95 without, and the merge is then a launch of its own);
-// the plan must not depend on it, since the output's bits may not.
+// the plan must not depend on it, since the output's bits may not.  Against the best of 1 to 8 splits by 4 and 8 waves, over 202 sizes of
+// 16-1024 rows x 512-4096 keys, 16 to 32 heads: heads of 128 1.2 % above it on average (9 % of the sizes by more than 5, the worst
+// 12 %), without the average 5 % (33 %, 51 %); heads of 64 0.8 % (4 %, 12 %) and 7 % (43 %, 55 %).
 FwdPlan plan_fwd(const Tunables& t, const TiledCall* calls, int n_calls, int n_heads, int head_dim) {
   int max_m = 0, max_L = 0;
   double partial_us = 0.0;                        // of one split
@@ -580,8 +582,8 @@ FwdPlan plan_fwd(const Tunables& t, const TiledCall* calls, int n_calls, int n_h
   const int blocks = (std::max(1, max_L) + kBlockKeys - 1) / kBlockKeys;
   const int max_splits = std::min(std::max(1, std::min(8, t.attn_max_splits)), blocks);
   const int units = t.attn_target_wgs;
-  const double width = qt == 1 ? 0.55 : 1.0;      // 16 queries per wave
-  const double alone = width * 1.8, shared = width * 2.8, eight = 2.6;
+  const double heads = head_dim == 64 ? 0.75 : 1.0, width = heads * (qt == 1 ? 0.55 : 1.0);      // 16 queries per wave
+  const double alone = width * 1.8, shared = width * 2.8, eight = heads * 2.6;
   FwdPlan best{qt, t.attn_waves == 8 ? 8 : 4, 1};
   double best_us = 1e30;
   for (int waves : {4, 8}) {

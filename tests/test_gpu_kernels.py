@@ -1062,3 +1062,21 @@ def test_linear_start_chunks_by_shape(B, dtype, m, N, K, starts):
     say(f"linear start chunks {dtype} m={m} N={N} K={K}")
     got = _start_chunks(B, dtype, m, N, K, (None, 0, 1, 3))
     assert [rot for rot in (0, 1, 3) if torch.equal(got[rot], got[None])] == [starts]
+
+
+@pytest.mark.parametrize("H,Hkv,L,m,splits", [(32, 32, 1024, 400, 2), (32, 32, 2048, 200, 4), (16, 2, 2048, 400, 4), (32, 32, 777, 130, 4)])
+def test_attention_key_splits_of_64_wide_heads(B, H, Hkv, L, m, splits):
+    """Heads of 64: the tiled kernels take the shape that was measured the faster (4 waves and the fewer splits)."""
+    say(f"attention key splits H={H} Hkv={Hkv} L={L} m={m}")
+    wd = W.ModelDims(1, H * 64, H, Hkv, 64, 64, 64, dtype="bf16")
+    case = W.attention_case(1, H, Hkv, 64, L, m, dtype="bf16")
+    q, kc, vc = (B.to_device(case[n], "bf16") for n in ("q", "k_cache", "v_cache"))
+    got = []
+    for tun in (None, {"attn_waves": 4, "attn_max_splits": splits}, {"attn_waves": 4, "attn_max_splits": splits - 1}):
+        ctx, _, _ = _ctx_for(B, wd, max_seq=L, tunables=tun)
+        out = torch.zeros_like(q)
+        ctx.d2c_attention(q, None, m, None, None, kc, vc, L, out, None)
+        torch.cuda.synchronize()
+        got.append(out)
+        ctx.close()
+    assert torch.equal(got[0], got[1]) and not torch.equal(got[0], got[2])
