@@ -581,7 +581,7 @@ FwdPlan plan_fwd(const Tunables& t, const TiledCall* calls, int n_calls, int n_h
   const int qt = t.attn_qt == 1 || t.attn_qt == 2 ? t.attn_qt : (max_m > 64 ? 2 : 1);
   const int blocks = (std::max(1, max_L) + kBlockKeys - 1) / kBlockKeys;
   const int max_splits = std::min(std::max(1, std::min(8, t.attn_max_splits)), blocks);
-  const int units = t.attn_target_wgs;
+  const int units = std::min(t.attn_target_wgs, 1 << 20);         // more than any launch has; twice this fits an int
   const double heads = head_dim == 64 ? 0.75 : 1.0, width = heads * (qt == 1 ? 0.55 : 1.0);      // 16 queries per wave
   const double alone = width * 1.8, shared = width * 2.8, eight = heads * 2.6;
   FwdPlan best{qt, t.attn_waves == 8 ? 8 : 4, 1};

@@ -1080,3 +1080,19 @@ def test_attention_key_splits_of_64_wide_heads(B, H, Hkv, L, m, splits):
         got.append(out)
         ctx.close()
     assert torch.equal(got[0], got[1]) and not torch.equal(got[0], got[2])
+
+
+def test_attention_key_splits_with_units_without_end(B):
+    """attn_target_wgs at the largest value an int holds plans as any value does that no launch reaches."""
+    say("attention key splits, attn_target_wgs = 2^31 - 1")
+    case = W.attention_case(1, 4, 4, 128, 2048, 200, dtype="bf16")
+    q, kc, vc = (B.to_device(case[n], "bf16") for n in ("q", "k_cache", "v_cache"))
+    got = []
+    for units in (1 << 20, (1 << 31) - 1):
+        ctx, _, _ = _ctx_for(B, W.ModelDims(1, 512, 4, 4, 128, 64, 64, dtype="bf16"), max_seq=2048, tunables={"attn_target_wgs": units})
+        out = torch.zeros_like(q)
+        ctx.d2c_attention(q, None, 200, None, None, kc, vc, 2048, out, None)
+        torch.cuda.synchronize()
+        got.append(out)
+        ctx.close()
+    assert torch.equal(got[0], got[1])
