@@ -79,11 +79,10 @@ __device__ __forceinline__ TileId tile_of(int bid, int q_blocks, int n_heads, in
 // log-sum-exp is known: p = ptilde * 2^(refblk - lse2).
 //
 // WAVES = 4 or 8 waves per workgroup, each owning 16*QT queries.  Two waves share a SIMD, so that one wave's
-// matrix-core phase runs beside the other's vector phase: two workgroups of 4 waves (two LDS buffers, 64 KB) or one of
-// 8 (three buffers).
+// matrix-core phase runs beside the other's vector phase: two workgroups of 4 waves or one of 8 (two LDS buffers, 64 KB).
 //
-// K and V rows go from global memory straight into LDS (DMA), one or two blocks ahead, in whole rows; V is transposed on
-// its way out of LDS (ds_read_b64_tr_b16).  Loads and stores retire in one queue, which is waited for once, in the middle of a
+// K and V rows go from global memory straight into LDS (DMA), one block ahead, in whole rows; V is transposed on its way out of
+// LDS (ds_read_b64_tr_b16).  Loads and stores retire in one queue, which is waited for once, in the middle of a
 // block: the rows were requested at its start, the last block's probability stores behind the last wait.
 // 1024 queries x 2048 keys, 32 heads, no average: 50 us, 0.69 PFLOP/s, in 256 workgroups of 4 waves.  Rows through registers
 // took 92 us a layer for 4 x 228 x 3072 with the average (now 83) and 47 for 777 x 777 without (now 28, unsplit): the compiler
@@ -101,13 +100,12 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_tiled_fwd_kernel(const Bat
   static_assert(WAVES == 4 || WAVES == 8, "4 or 8 waves");
   constexpr int NS = DH / 32;            // contraction steps of K Q^T
   constexpr int ND = DH / 16;            // head-dim tiles of O^T
-  constexpr int NBUF = DMA && WAVES == 8 ? 3 : 2;
   constexpr int kRow = DH * 2;                           // bytes of a K or V row
   constexpr int kOperand = kBlockKeys * kRow;            // bytes of a block's K (or V) rows
   constexpr int PP = kRow / 16;                          // 16-byte pieces of a row
   constexpr int RP = 64 / PP;                            // rows that one instruction of a wave brings
   constexpr int LP = kBlockKeys / RP / WAVES;            // instructions per wave and operand
-  __shared__ __attribute__((aligned(16))) unsigned char lds[NBUF * 2 * kOperand];      // [buffer][K, V][key][piece]
+  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * 2 * kOperand];         // [buffer][K, V][key][piece]
 
   const SeqArgs& sq = batch.seq[blockIdx.y];
   const bf16* __restrict__ q = sq.q;
@@ -174,7 +172,6 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_tiled_fwd_kernel(const Bat
     }
   };
   load_block(0, 0);
-  if (NBUF == 3 && n_blocks > 1) load_block(1, 1);
 
   // this wave's queries as B operands of S^T = K Q^T (rows past m repeat row m-1)
   Frag<bf16> qf[QT][NS];
@@ -371,23 +368,21 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_tiled_fwd_kernel(const Bat
     store_block(0);
     __syncthreads();
   }
-  for (int blk = 0, buf = 0; blk < n_blocks; ++blk) {
-    const int nxt = buf == NBUF - 1 ? 0 : buf + 1;
+  for (int blk = 0; blk < n_blocks; ++blk) {
+    const int buf = blk & 1;
+    // the buffer that is filled now was last read one iteration ago, before the barrier every wave has passed
+    if (blk + 1 < n_blocks) load_block(blk + 1, buf ^ 1);
     if constexpr (DMA) {
-      // the buffer that is filled now was last read one iteration ago, before the barrier every wave has passed
-      if (blk + NBUF - 1 < n_blocks) load_block(blk + NBUF - 1, NBUF == 2 ? nxt : (nxt == NBUF - 1 ? 0 : nxt + 1));
       __builtin_amdgcn_sched_barrier(0);
       if (active) block(blk, buf);
       else wait_requests();
       __builtin_amdgcn_sched_barrier(0);
       barrier();
     } else {
-      if (blk + 1 < n_blocks) load_block(blk + 1, nxt);
       if (active) block(blk, buf);
-      if (blk + 1 < n_blocks) store_block(nxt);
+      if (blk + 1 < n_blocks) store_block(buf ^ 1);
       __syncthreads();
     }
-    buf = nxt;
   }
   if (!active) return;
 
