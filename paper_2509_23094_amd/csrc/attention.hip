@@ -879,11 +879,12 @@ size_t attention_scratch_floats(const Tunables& t, int dtype, int max_m, int max
 
 // The tiled kernels also take the key ranges too long for the per-head probability rows, where the few-row kernels need a
 // second Q K^T launch for the head average: from kLongMinM rows on, up to kOneTile from kOneTileMinL keys on, and for any
-// rows from kLongMinL on.  In between the call without the average is still the faster there (us, few-row / tiled kernels, 32
-// heads of 128, without and with the average: 40 x 1100 11.5/12.7 and 18.6/16.8, 40 x 1500 13.3/14.3 and 23.1/17.5; elsewhere
-// 16 x 1500 12.8/12.1 and 19.7/14.7, 40 x 2048 16.1/16.0 and 27.0/18.9, 40 x 4096 25.7/21.1 and 45.8/25.1, 1 x 4096 25.5/19.2 and
-// 33.5/20.9; heads of 64, 17 x 1100 9.6/11.7 and 15.1/13.3, 17 x 1500 10.8/11.0 and 17.0/13.6).  The output's bits may not
-// depend on whether the average is wanted, so one line serves both.
+// rows from kLongMinL on.  The output's bits may not depend on whether the average is wanted, so one line serves calls without and
+// with it, and heads of 64 and of 128.  Beyond it the tiled kernels were never the slower (us, few-row / tiled kernels, without and
+// with the average; 32 heads of 128: 16 x 1536 13.7/13.1 and 20.9/15.4, 47 x 1792 16.5/15.3 and 26.5/19.2, 40 x 4096 26.9/21.6 and
+// 46.1/25.6; 32 heads of 64: 16 x 1536 11.4/10.8 and 17.0/13.5, 47 x 1792 13.3/12.5 and 19.9/17.3; GQA alike).  It is on the safe side:
+// between 1025 keys and the line they are up to 7 us faster with the average, but without it up to 2 us slower from 17 rows on (heads
+// of 128, 47 x 1025 11.5/13.6, 47 x 1536 13.9/15.4; of 64, 47 x 1100 9.9/11.0) and level up to 16 (16 x 1100 11.8/11.5, of 64 9.7/10.0).
 constexpr int kLongMinM = 48, kOneTile = 16, kOneTileMinL = 1536, kLongMinL = 1792;
 bool attention_is_tiled(const Tunables& t, int dtype, int m, int L) {
   if (dtype != kBF16) return false;

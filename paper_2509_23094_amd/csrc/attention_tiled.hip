@@ -13,8 +13,7 @@
 //             When the grid would not fill the chip the key range is split; every split writes
 //             an unnormalised fp32 partial with its running maximum and sum, and a merge
 //             kernel combines them in a fixed order (bit-reproducible, no atomics).
-//   A-bar     one workgroup = 64 query rows x 16*KA keys, looping over the heads with the K
-//             block of each head staged through LDS; exp(s - lse) accumulates in registers.
+//   A-bar     from the probabilities that the forward kernel leaves behind (EMIT), in the launch that also merges the splits.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -31,9 +30,6 @@ constexpr int kBlockKeys = 64;
 // power of two (the head average reads the same piece of every head at once)
 constexpr int kPtildePad = 64;
 
-// low halves of (a, b) / high halves of (a, b) in one register: one byte-permute instruction each
-__device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
-__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 // two floats -> one register of two bf16 (round to nearest even): a single packed conversion
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -85,9 +81,10 @@ __device__ __forceinline__ TileId tile_of(int bid, int q_blocks, int n_heads, in
 // LDS (ds_read_b64_tr_b16).  Loads and stores retire in one queue, which is waited for once, in the middle of a
 // block: the rows were requested at its start, the last block's probability stores behind the last wait.
 // 1024 queries x 2048 keys, 32 heads, no average: 50 us, 0.69 PFLOP/s, in 256 workgroups of 4 waves.  Rows through registers
-// took 92 us a layer for 4 x 228 x 3072 with the average (now 83) and 47 for 777 x 777 without (now 28, unsplit): the compiler
-// had moved their loads behind the scores and their wait in front of everything stored.  What is left: the probabilities
-// (half of the time of a call with the average), and 1 to 2 waves per SIMD between whose phases a third of the time is idle.
+// took 94 us a layer for 4 x 228 x 3072 with the average (now 83), and for 777 x 777 without, unsplit, 31 (now 23; in the two splits
+// it took then 51 with the merge): the compiler had moved their loads behind the scores and their wait in front of everything
+// stored.  What is left: the probabilities (half of the time of a call with the average), the wait in mid-block (a row has half a block
+// to arrive), and 1 to 2 waves per SIMD between whose phases a third of the time is idle.
 // DMA = false brings the rows through registers: buffers that are not 16-byte aligned.
 __device__ __forceinline__ u32x2 lds_read_transposed(const unsigned char* p) {
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;

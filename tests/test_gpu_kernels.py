@@ -95,7 +95,8 @@ ATTN_CASES = [
     ("bf16", 5, 5, 128, 300, 16, "few"),          # 5 kv heads: plain placement
     ("bf16", 28, 4, 128, 1824, 93, "default"),    # the long-generation decode step late on: too long for the
                                                   # per-head probability rows, so the tiled kernels from 48 rows on
-    ("bf16", 28, 4, 128, 1824, 40, "default"),    # same length, fewer rows
+    ("bf16", 28, 4, 128, 1824, 40, "default"),    # same length, fewer rows: the tiled kernels as well
+    ("bf16", 28, 4, 128, 1824, 40, "few"),        # and the few-row kernels with their second launch
     ("f32", 4, 4, 64, 128, 73, ""),               # the small fp32 model's geometry
     ("f32", 4, 2, 8, 19, 5, ""),
 ]
@@ -806,11 +807,12 @@ def test_attention_parity_staged_rows(B, H, Hkv, dh, L, m):
 
 
 @pytest.mark.parametrize("dtype,m,N,K", [("bf16", 1, 16, 392), ("bf16", 97, 1007, 1160), ("bf16", 113, 2600, 392), ("bf16", 145, 333, 1032),
-                                         ("f32", 77, 257, 68), ("f32", 120, 1000, 516), ("f32", 33, 26001, 196)])
+                                         ("f32", 77, 2505, 68), ("f32", 120, 1000, 516), ("f32", 33, 26001, 196)])
 def test_linear_parity_staged_weights(B, dtype, m, N, K):
     """Row-major weights staged through LDS (unsplit contractions of three chunks and more, float with five row tiles or a full
     round of workgroups): ragged last chunk and last rows, three slots, two slots (many rows, 10 waves) and none; and weights
     that are not 16-byte aligned, which take the loads in operand order: the same bits."""
+    assert dtype == "bf16" or B.d2c_plan_projection(dtype, m, N, K, True)["waves"] != 4          # not the one-tile kernel's
     tun = {"gemm_max_splits": 1}
     test_linear_parity(B, dtype, m, N, K, tunables=tun)
     if dtype == "bf16":
@@ -907,7 +909,8 @@ def test_refresh_layer_f32_one_tile_per_wave(B, wd, m):
                                          ("bf16", 256, 300, 4096), ("bf16", 300, 1030, 2048), ("f32", 40, 3000, 1024), ("f32", 130, 200, 2048)])
 def test_linear_rows_a_power_of_two_apart(B, dtype, m, N, K):
     """Row-major weights whose workgroups start their walks over k at different chunks."""
-    test_linear_parity(B, dtype, m, N, K)
+    for rot in (1, 3):
+        test_linear_parity(B, dtype, m, N, K, tunables={"gemm_rot": rot})
 
 
 @pytest.mark.parametrize("H,Hkv,dh,L,m", [(32, 32, 128, 1536, 16), (32, 32, 128, 1536, 17), (28, 4, 128, 1791, 47), (28, 4, 128, 1792, 17),
