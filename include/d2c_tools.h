@@ -67,8 +67,8 @@ int d2c_ctx_set_tunable(d2c_ctx* ctx, const char* name, int32_t value);
  * contraction (the gate/up projection with the gated epilogue).  Writes
  * shape[0..6] = row tiles per workgroup (16 rows each), column tiles per wave, waves per workgroup, splits of
  * the contraction, contraction elements per split, row blocks (of the workgroup's row tiles), workgroups of the launch.
- * In float, up to 128 rows of a short contraction are one row tile per workgroup of 4 waves.  Of 8 waves with 3 or 4 column tiles each, half take the upper and half the lower half of the row tiles; else all waves
- * take all of them.
+ * In float, up to 128 rows of a short contraction are one row tile per workgroup of 4 waves.  Of 8 waves with 3 or 4
+ * column tiles each, half take the upper and half the lower half of the row tiles; else all waves take all of them.
  * Returns D2C_EINVAL for a null pointer, a dtype other than D2C_F32 / D2C_BF16 or non-positive sizes. */
 int d2c_plan_projection(int32_t dtype, int32_t m, int32_t N, int32_t K, int32_t single_split, int32_t shape[7]);
 
