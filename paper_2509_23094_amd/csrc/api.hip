@@ -38,11 +38,12 @@ bool d2c::set_tunable(Tunables& t, const char* name, int value) {
 }
 
 // ---- d2c_select_static: Eq. 1's per-chunk (max, argmax, sum) triples live in this file-scope device array
-// instead of a context's workspace, so the call needs no context and never allocates.  Each GPU holds its
-// own copy of the array at its own address; the address is looked up once per device.
+// instead of a context's workspace, so the call needs no context and never allocates.  Behind them lies the result of the
+// selection's first half.  Each GPU holds its own copy of the array at its own address; the address is looked up once per device.
 constexpr int kStaticMaxRows = D2C_STATIC_MAX_ROWS;
 constexpr size_t kStaticFloats = (size_t)kStaticMaxRows * 64 * 3;        // 64 = most chunks per vocabulary row
-static __device__ __align__(256) float scratch[kStaticFloats];
+constexpr size_t kStaticPreFloats = 8192;                                // >= select_pre_floats(), checked at the call
+static __device__ __align__(256) float scratch[kStaticFloats + kStaticPreFloats];
 
 struct d2c_ctx {
   d2c_dims dims{};
@@ -90,6 +91,7 @@ struct d2c_ctx {
   void* head_a = nullptr;       // T [head_rows, d]
   float* logits = nullptr;      // [head_rows, vocab]
   float* conf_part = nullptr;   // per-chunk (max, argmax, sum) triples of Eq. 1 for every row of a group
+  float* sel_pre = nullptr;     // first halves of the selections of one launch, select_pre_floats() each
   int head_rows = 0;
   float* rope_cos = nullptr;    // [max_seq, head_dim/2]
   float* rope_sin = nullptr;
@@ -474,6 +476,7 @@ int d2c_init_tuned(const d2c_dims* dims, const d2c_weights* w, const d2c_tunable
       (rc = ws_alloc(c, &c->head_a, (size_t)c->head_rows * d * ts)) ||
       (rc = ws_alloc(c, &c->logits, (size_t)c->head_rows * D.vocab * 4)) ||
       (rc = ws_alloc(c, &c->conf_part, confidence_scratch_floats(c->max_rows, D.vocab) * 4)) ||
+      (rc = ws_alloc(c, &c->sel_pre, (size_t)select_max_batch() * select_pre_floats() * 4)) ||
       (rc = ws_alloc(c, &c->rope_cos, Lm * (D.head_dim / 2) * 4)) ||
       (rc = ws_alloc(c, &c->rope_sin, Lm * (D.head_dim / 2) * 4)))
     return bail(rc);
@@ -632,11 +635,12 @@ int d2c_select(d2c_ctx* c, const d2c_params* p, const float* logits, const int32
   if (prompt_len < 0 || prompt_len > L) return fail(c, D2C_EINVAL, "prompt_len outside [0, L]");
   hipStream_t st = (hipStream_t)stream;
   if (n_rows > c->dims.max_seq) return fail(c, D2C_ESHAPE, "n_rows exceeds max_seq of the context");
-  D2C_HIP(c, launch_confidence_chunks(logits, n_rows, c->dims.vocab, c->conf_part, st));
+  const bool split = n_rows > 0 && p->cand_mode == 0;
   SelectArgs a{p->sigma, p->k, p->p, p->block_len, p->n_unmask, p->cand_mode, p->threshold, p->conf_decode,
                tokens, is_masked, L, prompt_len,
                conf, pred, influence, mstar, u_set, decode_idx, s_next, s_rows_next, counts, score_out,
-               c->conf_part, logit_pos, nullptr, n_rows, confidence_chunks(c->dims.vocab)};
+               c->conf_part, logit_pos, nullptr, n_rows, confidence_chunks(c->dims.vocab), split ? c->sel_pre : nullptr};
+  D2C_HIP(c, launch_confidence_chunks(logits, n_rows, c->dims.vocab, c->conf_part, st, &a, split ? 1 : 0));
   D2C_HIP(c, launch_select(&a, 1, st));
   return D2C_OK;
 }
@@ -658,17 +662,18 @@ int d2c_select_static(const d2c_params* p, int32_t vocab, const float* logits, c
   if (L <= 0 || L > select_max_len())
     return fail(nullptr, D2C_ESHAPE, "L outside (0, " + std::to_string(select_max_len()) + "]");
   if (prompt_len < 0 || prompt_len > L) return fail(nullptr, D2C_EINVAL, "prompt_len outside [0, L]");
-  if (confidence_scratch_floats(n_rows, vocab) > kStaticFloats) return fail(nullptr, D2C_ESHAPE, "scratch array too small");
+  if (confidence_scratch_floats(n_rows, vocab) > kStaticFloats || select_pre_floats() > kStaticPreFloats) return fail(nullptr, D2C_ESHAPE, "scratch array too small");
   float* sp = nullptr;
   if ((rc = static_scratch(&sp))) return rc;
   hipStream_t st = (hipStream_t)stream;
   // every (row, chunk) triple that the merge reads is written by the chunk kernel of this call: nothing in
   // the array has to start at zero, whatever the last call left there
-  D2C_HIP(nullptr, launch_confidence_chunks(logits, n_rows, vocab, sp, st));
+  const bool split = n_rows > 0 && p->cand_mode == 0;
   SelectArgs a{p->sigma, p->k, p->p, p->block_len, p->n_unmask, p->cand_mode, p->threshold, p->conf_decode,
                tokens, is_masked, L, prompt_len,
                conf, pred, influence, mstar, u_set, decode_idx, s_next, s_rows_next, counts, score_out,
-               sp, logit_pos, nullptr, n_rows, confidence_chunks(vocab)};
+               sp, logit_pos, nullptr, n_rows, confidence_chunks(vocab), split ? sp + kStaticFloats : nullptr};
+  D2C_HIP(nullptr, launch_confidence_chunks(logits, n_rows, vocab, sp, st, &a, split ? 1 : 0));
   D2C_HIP(nullptr, launch_select(&a, 1, st));
   return D2C_OK;
 }
@@ -877,6 +882,22 @@ int d2c_step(d2c_ctx* c, const d2c_params* p, d2c_seq_state* seqs, int32_t batch
     int fill = 0;
     const int n_chunks = confidence_chunks(D.vocab);
     size_t conf_rows = 0;                         // rows of the group whose chunk triples are in conf_part
+    // the selections of the group's sequences share launches (one workgroup per sequence)
+    std::vector<SelectArgs> sel;
+    size_t all_rows = 0;
+    for (int i = 0; i < n_seg; ++i) {
+      d2c_seq_state& s = seqs[group[i]];
+      sel.push_back(SelectArgs{p->sigma, p->k, p->p, p->block_len, p->n_unmask, p->cand_mode, p->threshold, p->conf_decode,
+                               s.tokens, s.is_masked, s.L,
+                               s.prompt_len, s.conf, s.pred, s.influence, s.mstar, s.u_set, s.decode_idx, s.s_idx, s.s_rows,
+                               s.counts, s.score,
+                               c->conf_part + all_rows * n_chunks * 3, s.s_rows, s.s_idx, s.n_rows, n_chunks, nullptr});
+      all_rows += (size_t)s.n_rows;
+    }
+    // their halves that need no logits run beside the last chunks of Eq. 1, if the influence is there by then
+    const bool split = p->cand_mode == 0 && side == st && all_rows > 0 && n_seg <= select_max_batch();
+    if (split)
+      for (int i = 0; i < n_seg; ++i) sel[i].pre = c->sel_pre + (size_t)i * select_pre_floats();
     auto flush = [&]() -> int {
       if (fill == 0) return D2C_OK;
       GemmPlan pl;
@@ -885,7 +906,8 @@ int d2c_step(d2c_ctx* c, const d2c_params* p, d2c_seq_state* seqs, int32_t batch
       if (rc2) return rc2;
       // the chunk triples of a group's rows stay until the selection, which merges them: the rows of all pieces in order
       D2C_TIMED(c, st, D2C_PROF_SELECT, 0.0,
-                launch_confidence_chunks(c->logits, fill, D.vocab, c->conf_part + conf_rows * n_chunks * 3, st));
+                launch_confidence_chunks(c->logits, fill, D.vocab, c->conf_part + conf_rows * n_chunks * 3, st, sel.data(),
+                                         split && conf_rows + fill == all_rows ? n_seg : 0));
       conf_rows += fill;
       for (const Piece& pc : pieces) {
         d2c_seq_state& s = seqs[group[pc.seg]];
@@ -915,22 +937,8 @@ int d2c_step(d2c_ctx* c, const d2c_params* p, d2c_seq_state* seqs, int32_t batch
     // join: the selection is the first consumer of the influence scores, so the chain also runs beside the
     // LM head and Eq. 1
     if (side != st) D2C_HIP(c, hipStreamWaitEvent(st, c->side_done, 0));
-    // the selections of the group's sequences share launches (one workgroup per sequence)
-    std::vector<SelectArgs> sel;
-    conf_rows = 0;
-    for (int i = 0; i < n_seg; ++i) {
-      d2c_seq_state& s = seqs[group[i]];
-      sel.push_back(SelectArgs{p->sigma, p->k, p->p, p->block_len, p->n_unmask, p->cand_mode, p->threshold, p->conf_decode,
-                               s.tokens, s.is_masked, s.L,
-                               s.prompt_len, s.conf, s.pred, s.influence, s.mstar, s.u_set, s.decode_idx, s.s_idx, s.s_rows,
-                               s.counts, s.score,
-                               c->conf_part + conf_rows * n_chunks * 3, s.s_rows, s.s_idx, s.n_rows, n_chunks});
-      conf_rows += (size_t)s.n_rows;
-      if ((int)sel.size() == select_max_batch() || i + 1 == n_seg) {
-        D2C_TIMED(c, st, D2C_PROF_SELECT, 0.0, launch_select(sel.data(), (int)sel.size(), st));
-        sel.clear();
-      }
-    }
+    for (int i = 0; i < n_seg; i += select_max_batch())
+      D2C_TIMED(c, st, D2C_PROF_SELECT, 0.0, launch_select(sel.data() + i, std::min(select_max_batch(), n_seg - i), st));
     for (int i = 0; i < n_seg; ++i) {
       d2c_seq_state& s = seqs[group[i]];
       D2C_HIP(c, hipMemcpyAsync(c->counts_host + (size_t)group[i] * D2C_N_COUNTS, s.counts,

@@ -183,7 +183,6 @@ hipError_t launch_influence_chain(const ChainCall* calls, int n_calls, size_t la
 // part: confidence_scratch_floats(n_rows, vocab) floats
 int confidence_chunks(int vocab);                       // 1..64
 size_t confidence_scratch_floats(size_t n_rows, int vocab);
-hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st);
 struct SelectArgs {
   float sigma; int k; float p; int block_len; int n_unmask; int cand_mode; float threshold; int conf_decode;
   int32_t* tokens; uint8_t* is_masked; int L; int prompt_len;
@@ -193,7 +192,14 @@ struct SelectArgs {
   // logit rows of this call whose chunks are still to be merged (n_rows may be 0); a row's position is
   // via ? via[pos[row]] : pos[row].  pos and via may be the s_rows_next / s_next that the call overwrites.
   const float* part; const int32_t *pos, *via; int n_rows, n_chunks;
+  // result of the selection's half that needs no logits, select_pre_floats() floats, 8-byte aligned: written by the chunks' launch,
+  // read by launch_select.  null (for all sequences of a launch): launch_select does that half as well
+  void* pre;
 };
+size_t select_pre_floats();
+// first: n_first (up to select_max_batch()) selections with cand_mode 0 whose first half this launch does too (n_rows > 0 then)
+hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st,
+                                    const SelectArgs* first = nullptr, int n_first = 0);
 int select_max_len();
 // n independent sequences (n <= select_max_batch), one workgroup each
 int select_max_batch();

@@ -29,16 +29,20 @@ constexpr int kConfThreads = 256;
 constexpr int kConfMaxChunks = 64;
 constexpr int kConfChunk = 8192;              // entries per chunk, as long as 64 chunks cover the vocabulary
 
-__global__ __launch_bounds__(kConfThreads) void confidence_chunk_kernel(const float* __restrict__ logits, int vocab,
-                                                                        int chunk, int n_chunks,
-                                                                        float* __restrict__ part) {
-  __shared__ float s_val[kConfThreads / 64];
-  __shared__ int s_idx[kConfThreads / 64];
-  __shared__ float s_sum[kConfThreads / 64];
-  const int row = blockIdx.y, ck = blockIdx.x;
+// One chunk by four waves of a workgroup; the barriers inside are the whole workgroup's, whose waves all have a chunk.
+struct ConfLds {
+  float val[kConfThreads / 64];
+  int idx[kConfThreads / 64];
+  float sum[kConfThreads / 64];
+};
+__device__ __forceinline__ void confidence_chunk(const float* __restrict__ logits, int vocab, int chunk, int n_chunks,
+                                                 float* __restrict__ part, int row, int ck, ConfLds& lds) {
+  float (&s_val)[kConfThreads / 64] = lds.val;
+  int (&s_idx)[kConfThreads / 64] = lds.idx;
+  float (&s_sum)[kConfThreads / 64] = lds.sum;
   const float* x = logits + (size_t)row * vocab;
   const int lo = ck * chunk, hi = min(vocab, lo + chunk);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x % kConfThreads, wave = tid >> 6, lane = tid & 63;
   float best = -INFINITY;
   int bidx = 0x7fffffff;
   for (int v = lo + tid; v < hi; v += kConfThreads) {       // ascending per thread: a tie keeps the lower index
@@ -77,17 +81,15 @@ __global__ __launch_bounds__(kConfThreads) void confidence_chunk_kernel(const fl
 // The same for chunks of exactly 8192 entries of 16-byte aligned rows (vocab % 4 == 0): a thread keeps its 32
 // entries in registers (eight 16-byte loads issued together), so the row is read once and the kernel is one
 // memory latency long.  Entry order per thread is ascending (piece, then element), as the tie rule needs.
-__global__ __launch_bounds__(kConfThreads) void confidence_chunk_vec_kernel(const float* __restrict__ logits,
-                                                                            int vocab, int n_chunks,
-                                                                            float* __restrict__ part) {
+__device__ __forceinline__ void confidence_chunk_vec(const float* __restrict__ logits, int vocab, int n_chunks,
+                                                     float* __restrict__ part, int row, int ck, ConfLds& lds) {
   constexpr int kChunk = kConfChunk, kPieces = kChunk / (4 * kConfThreads);
-  __shared__ float s_val[kConfThreads / 64];
-  __shared__ int s_idx[kConfThreads / 64];
-  __shared__ float s_sum[kConfThreads / 64];
-  const int row = blockIdx.y, ck = blockIdx.x;
+  float (&s_val)[kConfThreads / 64] = lds.val;
+  int (&s_idx)[kConfThreads / 64] = lds.idx;
+  float (&s_sum)[kConfThreads / 64] = lds.sum;
   const float* x = logits + (size_t)row * vocab;
   const int lo = ck * kChunk;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x % kConfThreads, wave = tid >> 6, lane = tid & 63;
   f32x4 val[kPieces];
 #pragma unroll
   for (int p = 0; p < kPieces; ++p) {
@@ -762,7 +764,8 @@ struct SelectBatch {
 
 // Eq. 1's chunks of a row -> confidence and prediction, by 32 lanes (64 with more than 32 chunks), two rows of a wave at a
 // time; kSelT threads, at most kMergeMaxRows rows.  A row's sum is a scan over its lanes: the same bits for any number of rows.
-__device__ void merge_rows(const SelectArgs& a, int wave) {
+// conf_s, pred_s (optional): the same by position in LDS.
+__device__ void merge_rows(const SelectArgs& a, int wave, float* conf_s, int* pred_s) {
   const int lane = threadIdx.x & 63;
   const int width = a.n_chunks <= 32 ? 32 : 64, per = 64 / width;
   const int li = lane & (width - 1), sub = width == 32 ? lane >> 5 : 0;
@@ -815,8 +818,13 @@ __device__ void merge_rows(const SelectArgs& a, int wave) {
       }));
       const int to = __shfl(where, (q + sub) & 63, kWave);
       if (on && li == 0) {
-        a.conf[to] = 1.0f / sum;
+        const float conf = 1.0f / sum;
+        a.conf[to] = conf;
         a.pred[to] = (int)bidx;
+        if (conf_s) {
+          conf_s[to] = conf;
+          pred_s[to] = (int)bidx;
+        }
       }
     }
   }
@@ -827,71 +835,42 @@ __global__ __launch_bounds__(kSelT) void confidence_merge_kernel(SelectArgs a) {
   a.part += (size_t)row0 * a.n_chunks * 3;
   a.pos += row0;
   a.n_rows = min(kMergeLaunchRows, a.n_rows - row0);
-  merge_rows(a, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  merge_rows(a, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nullptr, nullptr);
 }
 
-// One workgroup per sequence (blockIdx.x); the sequences are independent.  Latency is what bounds it (a few KB of
+// One workgroup per sequence; the sequences are independent.  Latency is what bounds the selection (a few KB of
 // input), so it is built from few barriers: the sets live as bitmaps of 64-position words in LDS (wave w of the
 // workgroup ballots word e * waves + w for its e-th position), every wave turns a bitmap into counts and compaction
 // offsets by itself (lane = word), and both selections look for a threshold key by radix (sel_radix) instead of sorting.
 // Eq. 3's sum stops where the Gaussian is exactly zero in float.  Measured against a bitonic sort, rank counting, a
 // scan per set and 16 waves (Eq. 1's merge then took another 5 / 7.5 us launch): L 512, 16 logit rows, 32 candidates
 // 30.4 -> 14.8 us; L 3071, 200 logit rows, 737 candidates 327 -> 33 us.
-// PER positions a thread: 4 up to 2048 positions, 8 up to 4096.
+// It has two halves.  The first (sel_first: Eq. 3's sums, and stage 2 where its candidates are the known tokens) needs no
+// logits: it runs beside Eq. 1's chunks as workgroups of their launch and leaves its result in a SelPre.  The second (sel_second)
+// merges the chunks, ranks, and emits the sets.  Chunks and selection one after the other, against halves: L 512, 16 logit rows of
+// 126464 5.0 + 13.5 us -> 7.9 (the first half is the longer one) + 6.4; L 3071, 200 rows of 152064 22.6 + 32.5 -> 25.3 + 20.0.
+// A call without logit rows, with cand_mode 1 or in a group of more sequences than a launch takes runs both in one kernel.
+// PER positions a thread: 1, 2, 4 or 8 for up to 512, 1024, 2048, 4096 positions.
+struct SelPre {                                // what the first half leaves for the second
+  u64 mask[64], u[64];                         // masked positions, stage-2 set: bitmaps
+  float density[kSelMaxL];                     // Eq. 3, per candidate in ascending order
+};
+
+// The current block and its masked tokens (every wave for itself; lane = word of the bitmap); at most ML of them go into cand.
+struct SelBlock {
+  int lo, hi, n_masked, n;
+};
 template <int PER>
-__global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) {
-  constexpr int T = kSelT, NW = kSelNW, ML = PER * T;
-  __shared__ u64 w_mask[64], w_mst[64], w_dec[64], w_u[64], w_tie[64];
-  __shared__ u64 w_known[3 * kKnownPad];                   // known positions, with kKnownPad empty words on either side
-  __shared__ __align__(16) float phi[ML + 32];
-  __shared__ float density[ML];
-  __shared__ uint16_t cand[ML];
-  __shared__ u64 rkey[kRankMax], dkey[kRankMax];
-  __shared__ SelRadix radix;
-  __shared__ int n_small;
-
-  const SelectArgs& a = batch.seq[blockIdx.x];
-  const int L = a.L;
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+__device__ __forceinline__ SelBlock sel_block(const SelectArgs& a, u64 mask_w, uint16_t* cand, int wave) {
+  constexpr int T = kSelT, NW = kSelNW;
+  const int tid = threadIdx.x, lane = tid & 63, L = a.L;
   const u64 below = low_mask(lane);
-  int buf = 0;
-
-  // ---- mask flags, the Gaussian of Eq. 3, and Eq. 1's chunks of this call's logit rows
-  float inf[PER];
-  for (int i = tid; i < 64; i += T) {
-    if (i >= PER * NW) w_mask[i] = 0ull;
-    w_mst[i] = w_dec[i] = w_u[i] = w_tie[i] = 0ull;
-  }
-  for (int i = tid; i < 256; i += T) radix.hist[0][i] = 0ull;
-  for (int i = tid; i < 3 * kKnownPad; i += T)
-    if (i < kKnownPad || i >= kKnownPad + PER * NW) w_known[i] = 0ull;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int j = e * T + tid;
-    const bool f = j < L && a.is_masked[j] != 0;
-    inf[e] = j < L ? a.influence[j] : 0.f;
-    const u64 word = __ballot(f), known = __ballot(j < L && !f);
-    if (lane == 0) {
-      w_mask[e * NW + wave] = word;
-      w_known[kKnownPad + e * NW + wave] = known;
-    }
-    if (j < L && a.score_out) a.score_out[j] = 0.f;
-  }
-  const float inv2s2 = 1.0f / (2.0f * a.sigma * a.sigma);
-  // exp(-x) is zero in float from x = 104 on, subnormals included: distances of cut and more add nothing
-  const int cut = (int)fminf((float)L, ceilf(sqrtf(105.0f / inv2s2)) + 1.0f);
-  const int n_win = (cut + 31) >> 5;
-  for (int d = tid; d < n_win * 32; d += T) phi[d] = d < cut ? expf(-((float)d * (float)d) * inv2s2) : 0.f;
-  if (a.part) merge_rows(a, wave);
-  __syncthreads();
-
-  // ---- current block and its masked tokens (every wave for itself; lane = word of the bitmap)
-  const u64 mask_w = w_mask[lane];
+  SelBlock s;
   uint32_t n_masked_u;
   (void)wave_before((uint32_t)__popcll(mask_w), &n_masked_u);
-  const int n_masked = (int)n_masked_u;
-  int lo = L, hi = L;
-  if (n_masked > 0) {
+  s.n_masked = (int)n_masked_u;
+  s.lo = s.hi = L;
+  if (s.n_masked > 0) {
     const int fw = __builtin_ctzll(__ballot(mask_w != 0ull));
     const int first_masked = fw * 64 + __builtin_ctzll(lane_of(mask_w, fw));
     // blocks are counted from the end of the prompt in both directions (floor division): a masked
@@ -900,171 +879,37 @@ __global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) 
     const int diff = first_masked - a.prompt_len;
     const int b = diff >= 0 ? diff / a.block_len : -((-diff + a.block_len - 1) / a.block_len);
     const int64_t lo_raw = (int64_t)a.prompt_len + (int64_t)b * a.block_len;
-    lo = (int)max((int64_t)0, lo_raw);
-    hi = (int)min((int64_t)L, lo_raw + a.block_len);
+    s.lo = (int)max((int64_t)0, lo_raw);
+    s.hi = (int)min((int64_t)L, lo_raw + a.block_len);
   }
-  const u64 cand_w = mask_w & low_mask(hi - lane * 64) & ~low_mask(lo - lane * 64);
-  uint32_t n1_u;
-  const uint32_t cand_before = wave_before((uint32_t)__popcll(cand_w), &n1_u);
-  const int n1 = (int)n1_u;
+  const u64 cand_w = mask_w & low_mask(s.hi - lane * 64) & ~low_mask(s.lo - lane * 64);
+  uint32_t n_u;
+  const uint32_t before_w = wave_before((uint32_t)__popcll(cand_w), &n_u);
+  s.n = (int)n_u;
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
     const int word = e * NW + wave;
     const u64 bits = lane_of(cand_w, word);
-    const int before = (int)lane_of(cand_before, word);
+    const int before = (int)lane_of(before_w, word);
     if (bits >> lane & 1ull) cand[before + __popcll(bits & below)] = (uint16_t)(e * T + tid);
   }
-  __syncthreads();
+  return s;
+}
 
-  // ---- phase 1: Eq. 3 on the masked tokens of the current block, score = D(i) * s^i; thread t holds candidates
-  // t, t + T, ..  A wave takes 64 candidates (one a lane) and a share of the distances, 32 at a time: the known positions
-  // at those distances are two 32-bit windows of the bitmap, phi is the same for every lane, and a term costs three
-  // instructions.  Far distances are added first (the terms grow), left and right, even and odd apart.
-  const int n1p = (n1 + 63) & ~63;
-  const int shares = n1 > 0 ? max(1, min(min(8, n_win), ML / n1p)) : 1;
-  for (int item = wave; item < (n1p >> 6) * shares; item += NW) {
-    const int q = item % shares, c = (item / shares) * 64 + lane;
-    const int i = cand[min(c, n1 - 1)];
-    float sum[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int w = q + ((n_win - 1 - q) / shares) * shares; w >= 0; w -= shares) {
-      const int d0 = w * 32;
-      auto window = [&](int p) {                               // known flags of positions p .. p + 31
-        const unsigned at_bit = (unsigned)(p + kKnownPad * 64);
-        const u64 lo_w = w_known[at_bit >> 6], hi_w = w_known[(at_bit >> 6) + 1];
-        const unsigned sh = at_bit & 63u;
-        return (uint32_t)(lo_w >> sh) | (sh ? (uint32_t)(hi_w << (64u - sh)) : 0u);
-      };
-      const uint32_t right = window(i + d0), left = window(i - d0 - 31);
-#pragma unroll
-      for (int b = 31; b >= 0; --b) {
-        const uint32_t f = __float_as_uint(phi[d0 + b]);
-        sum[(b & 1) * 2] += __uint_as_float(f & (uint32_t)((int32_t)(right << (31 - b)) >> 31));
-        sum[(b & 1) * 2 + 1] += __uint_as_float(f & (uint32_t)((int32_t)(left << b) >> 31));
-      }
-    }
-    density[q * n1p + c] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-  }
-  int at[PER];
-  float cf[PER];
-  unsigned clive = 0u;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int c = e * T + tid;
-    at[e] = 0;
-    cf[e] = 0.f;
-    if (c < n1) {
-      clive |= 1u << e;
-      at[e] = cand[c];
-      cf[e] = a.conf[at[e]];
-    }
-  }
-  __syncthreads();
-
-  // ---- phase 2: Eq. 4 (top-k) and the decode set.  The decode set ranks the same scores, or the confidences alone
-  // (conf_decode), and with a threshold also takes every candidate whose confidence exceeds it.
-  uint32_t sb[PER], db[PER];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    sb[e] = db[e] = 0u;
-    if (clive >> e & 1u) {
-      float dsum = 0.f;
-      for (int q = shares - 1; q >= 0; --q) dsum += density[q * n1p + e * T + tid];
-      const float score = dsum * cf[e];
-      sb[e] = __float_as_uint(score);
-      db[e] = a.conf_decode ? __float_as_uint(cf[e]) : sb[e];
-      if (a.score_out) a.score_out[at[e]] = score;
-    }
-  }
-  unsigned in_m = a.k >= n1 ? clive : 0u, in_d = a.n_unmask >= n1 ? clive : 0u;
-  const bool cut_m = a.k > 0 && a.k < n1, cut_d = a.n_unmask > 0 && a.n_unmask < n1;
-  if (n1 <= kRankMax) {
-    if (cut_m || cut_d) {                                    // rank by counting (n1 <= T: at most one candidate a thread)
-      if (tid < n1) {
-        rkey[tid] = make_key(sb[0], at[0]);
-        dkey[tid] = make_key(db[0], at[0]);
-      }
-      __syncthreads();
-      if (tid < n1) {
-        const u64 mine = rkey[tid], dmine = dkey[tid];
-        int rank = 0, drank = 0;
-        for (int o = 0; o < n1; ++o) {
-          rank += rkey[o] > mine ? 1 : 0;
-          drank += dkey[o] > dmine ? 1 : 0;
-        }
-        if (cut_m && rank < a.k) in_m |= 1u;
-        if (cut_d && drank < a.n_unmask) in_d |= 1u;
-      }
-    }
-  } else {
-    // the count-th largest key by radix; candidates with an equal key are taken in ascending order
-    auto top = [&](const uint32_t (&kb)[PER], int count) {
-      u64 ones[PER], sum, above;
-      uint32_t any, all, t;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) ones[e] = 1ull;
-      sel_reduce(kb, clive, ones, radix, &sum, &any, &all);
-      sel_radix(kb, clive, ones, any, all, (u64)(count - 1), radix, &buf, &t, &above);
-      const int ties = count - (int)above;                   // >= 1
-#pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const u64 word = __ballot((clive >> e & 1u) && kb[e] == t);
-        if (lane == 0) w_tie[e * NW + wave] = word;
-      }
-      __syncthreads();
-      const u64 tie_w = w_tie[lane];
-      uint32_t n_tie;
-      const uint32_t tie_before = wave_before((uint32_t)__popcll(tie_w), &n_tie);
-      unsigned f = 0u;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const int word = e * NW + wave;
-        const u64 bits = lane_of(tie_w, word);
-        const int rank = (int)lane_of(tie_before, word) + __popcll(bits & below);
-        if ((clive >> e & 1u) && (kb[e] > t || (kb[e] == t && rank < ties))) f |= 1u << e;
-      }
-      __syncthreads();                                       // w_tie and the reduction slots are used again
-      return f;
-    };
-    if (cut_m) in_m = top(sb, a.k);
-    if (cut_d && !a.conf_decode && cut_m && a.n_unmask <= a.k && a.k <= kRankMax) {
-      // the same ranking, and the decode set lies inside M*: count ranks among those k
-      if (tid == 0) n_small = 0;
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < PER; ++e)
-        if (in_m >> e & 1u) rkey[atomicAdd(&n_small, 1)] = make_key(sb[e], at[e]);      // exactly k of them, in any order
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < PER; ++e)
-        if (in_m >> e & 1u) {
-          const u64 mine = make_key(sb[e], at[e]);
-          int rank = 0;
-          for (int o = 0; o < a.k; ++o) rank += rkey[o] > mine ? 1 : 0;
-          if (rank < a.n_unmask) in_d |= 1u << e;
-        }
-    } else if (cut_d) {
-      in_d = top(db, a.n_unmask);
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < PER; ++e)
-    if (clive >> e & 1u) {
-      const u64 bit = 1ull << (at[e] & 63);
-      if (in_m >> e & 1u) atomicOr(&w_mst[at[e] >> 6], bit);
-      if ((in_d >> e & 1u) || (a.threshold > 0.f && cf[e] > a.threshold)) atomicOr(&w_dec[at[e] >> 6], bit);
-    }
-  __syncthreads();
-
-  // ---- phases 3, 4: the smallest set of stage-2 candidates, by descending influence (lowest index first among
-  // equals), whose mass exceeds floor(p * total)
-  const u64 mst_w = w_mst[lane], dec_w = w_dec[lane];
+// Phases 3, 4: the smallest set of stage-2 candidates (the positions outside the bitmap `out`), by descending influence
+// (lowest index first among equals), whose mass exceeds floor(p * total).  Leaves the set in w_u; ends on a barrier.
+template <int PER>
+__device__ __forceinline__ void sel_stage2(const SelectArgs& a, const float (&inf)[PER], u64 out_w, SelRadix& radix, int* buf, u64* w_tie,
+                                           u64* w_u, int wave) {
+  constexpr int T = kSelT, NW = kSelNW;
+  const int tid = threadIdx.x, lane = tid & 63, L = a.L;
+  const u64 below = low_mask(lane);
   uint32_t kb[PER];
   u64 mass[PER];
   unsigned live = 0u;
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    const int word = e * NW + wave;
-    const u64 out = lane_of(a.cand_mode == 0 ? mask_w : mst_w, word);
+    const u64 out = lane_of(out_w, e * NW + wave);
     kb[e] = __float_as_uint(inf[e]);
     mass[e] = 0ull;
     if (e * T + tid < L && !(out >> lane & 1ull)) {
@@ -1079,14 +924,14 @@ __global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) 
     sel_reduce(kb, live, mass, radix, &total, &any, &all);
     const u64 thr = (u64)floor((double)a.p * __ull2double_rn(total));
     if (total > thr) {
-      sel_radix(kb, live, mass, any, all, thr, radix, &buf, &t, &above);
+      sel_radix(kb, live, mass, any, all, thr, radix, buf, &t, &above);
 #pragma unroll
       for (int e = 0; e < PER; ++e) {
         const u64 word = __ballot((live >> e & 1u) && kb[e] == t);
         if (lane == 0) w_tie[e * NW + wave] = word;
       }
       __syncthreads();
-      const u64 tie_w = w_tie[lane];
+      const u64 tie_w = lane < PER * NW ? w_tie[lane] : 0ull;
       uint32_t n_tie;
       const uint32_t tie_before = wave_before((uint32_t)__popcll(tie_w), &n_tie);
       u64 ties = 1ull;                                         // how many of the equal keys; a division only for a run
@@ -1107,10 +952,255 @@ __global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) 
     if (lane == 0) w_u[e * NW + wave] = word;
   }
   __syncthreads();
+}
+
+template <int PER>
+struct SelFirstLds {
+  // room for shares of the sums; not less than for 2048 positions, so that a candidate's sum has one order up to there
+  static constexpr int kDensity = PER * kSelT < 2048 ? 2048 : PER * kSelT;
+  alignas(16) float phi[PER * kSelT + 32];
+  float density[kDensity];
+  u64 known[3 * kKnownPad];                    // known positions, with kKnownPad empty words on either side
+  u64 mask[64], tie[64], u[64];
+  uint16_t cand[PER * kSelT];
+  SelRadix radix;
+};
+
+// The half without logits.  Leaves the bitmaps mask and, with cand_mode 0, u in sh and every candidate's Eq. 3 sum in
+// its first share's place; ends on a barrier.  Returns the radix buffer to go on with.
+template <int PER>
+__device__ __forceinline__ int sel_first(const SelectArgs& a, SelFirstLds<PER>& sh, int wave) {
+  constexpr int T = kSelT, NW = kSelNW, ML = SelFirstLds<PER>::kDensity;
+  const int L = a.L, tid = threadIdx.x, lane = tid & 63;
+  int buf = 0;
+  // ---- mask flags and the Gaussian of Eq. 3
+  float inf[PER];
+  for (int i = tid; i < 256; i += T) sh.radix.hist[0][i] = 0ull;
+  for (int i = tid; i < 3 * kKnownPad; i += T)
+    if (i < kKnownPad || i >= kKnownPad + PER * NW) sh.known[i] = 0ull;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int j = e * T + tid;
+    const bool f = j < L && a.is_masked[j] != 0;
+    inf[e] = j < L ? a.influence[j] : 0.f;
+    const u64 word = __ballot(f), known = __ballot(j < L && !f);
+    if (lane == 0) {
+      sh.mask[e * NW + wave] = word;
+      sh.known[kKnownPad + e * NW + wave] = known;
+    }
+  }
+  for (int i = PER * NW + tid; i < 64; i += T) sh.mask[i] = sh.u[i] = 0ull;
+  const float inv2s2 = 1.0f / (2.0f * a.sigma * a.sigma);
+  // exp(-x) is zero in float from x = 104 on, subnormals included: distances of cut and more add nothing
+  const int cut = (int)fminf((float)L, ceilf(sqrtf(105.0f / inv2s2)) + 1.0f);
+  const int n_win = (cut + 31) >> 5;
+  for (int d = tid; d < n_win * 32; d += T) sh.phi[d] = d < cut ? expf(-((float)d * (float)d) * inv2s2) : 0.f;
+  __syncthreads();
+  const u64 mask_w = sh.mask[lane];
+  const int n1 = sel_block<PER>(a, mask_w, sh.cand, wave).n;
+  __syncthreads();
+
+  // ---- phase 1: Eq. 3 on the masked tokens of the current block.  A wave takes 64 candidates (one a lane) and a share of
+  // the distances, 32 at a time: the known positions at those distances are two 32-bit windows of the bitmap, phi is the
+  // same for every lane, and a term costs three instructions.  Far distances are added first (the terms grow), left and
+  // right, even and odd apart.
+  const int n1p = (n1 + 63) & ~63;
+  const int shares = n1 > 0 ? max(1, min(min(8, n_win), ML / n1p)) : 1;
+  for (int item = wave; item < (n1p >> 6) * shares; item += NW) {
+    const int q = item % shares, c = (item / shares) * 64 + lane;
+    const int i = sh.cand[min(c, n1 - 1)];
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int w = q + ((n_win - 1 - q) / shares) * shares; w >= 0; w -= shares) {
+      const int d0 = w * 32;
+      auto window = [&](int p) {                               // known flags of positions p .. p + 31
+        const unsigned at_bit = (unsigned)(p + kKnownPad * 64);
+        const u64 lo_w = sh.known[at_bit >> 6], hi_w = sh.known[(at_bit >> 6) + 1];
+        const unsigned s = at_bit & 63u;
+        return (uint32_t)(lo_w >> s) | (s ? (uint32_t)(hi_w << (64u - s)) : 0u);
+      };
+      const uint32_t right = window(i + d0), left = window(i - d0 - 31);
+#pragma unroll
+      for (int b = 31; b >= 0; --b) {
+        const uint32_t f = __float_as_uint(sh.phi[d0 + b]);
+        sum[(b & 1) * 2] += __uint_as_float(f & (uint32_t)((int32_t)(right << (31 - b)) >> 31));
+        sum[(b & 1) * 2 + 1] += __uint_as_float(f & (uint32_t)((int32_t)(left << b) >> 31));
+      }
+    }
+    sh.density[q * n1p + c] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+  }
+  if (a.cand_mode == 0) sel_stage2<PER>(a, inf, mask_w, sh.radix, &buf, sh.tie, sh.u, wave);
+  else __syncthreads();
+  for (int c = tid; c < n1; c += T) {
+    float sum = 0.f;
+    for (int q = shares - 1; q >= 0; --q) sum += sh.density[q * n1p + c];
+    sh.density[c] = sum;                                       // share 0 of c is read by this thread alone
+  }
+  __syncthreads();
+  return buf;
+}
+
+template <int PER>
+struct SelSecondLds {
+  float conf[PER * kSelT];
+  int pred[PER * kSelT];
+  uint16_t cand[PER * kSelT];
+  u64 tie[64], mst[64], dec[64], u[64];
+  u64 rkey[kRankMax], dkey[kRankMax];
+  SelRadix radix;
+  int n_small;
+};
+
+// The half behind Eq. 1.  pre: the first half's result in memory, or null: it runs here, in `first`.
+template <int PER>
+__device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER>& sh, const SelPre* pre, SelFirstLds<PER>* first, int wave) {
+  constexpr int T = kSelT, NW = kSelNW;
+  const int L = a.L, tid = threadIdx.x, lane = tid & 63;
+  const u64 below = low_mask(lane);
+  int buf = 0;
+  u64 mask_w = 0ull, u_w = 0ull;
+  float dens[PER];
+  if (pre) {
+    mask_w = pre->mask[lane];
+    u_w = pre->u[lane];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) dens[e] = pre->density[e * T + tid];      // of candidate e T + tid, if there are so many
+  }
+  for (int i = tid; i < 64; i += T) sh.mst[i] = sh.dec[i] = sh.u[i] = sh.tie[i] = 0ull;
+  for (int i = tid; i < 256; i += T) sh.radix.hist[0][i] = 0ull;
+  // confidences and predictions so far, then Eq. 1's chunks of this call's logit rows over them
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int j = e * T + tid;
+    if (j < L) {
+      sh.conf[j] = a.conf[j];
+      sh.pred[j] = a.pred[j];
+      if (a.score_out) a.score_out[j] = 0.f;
+    }
+  }
+  __syncthreads();
+  if (a.part) merge_rows(a, wave, sh.conf, sh.pred);
+  if (!pre) {
+    (void)sel_first<PER>(a, *first, wave);
+    mask_w = first->mask[lane];
+    if (a.cand_mode == 0) u_w = first->u[lane];
+  }
+  const SelBlock blk = sel_block<PER>(a, mask_w, sh.cand, wave);
+  const int n1 = blk.n;
+  __syncthreads();
+
+  // ---- phase 2: Eq. 4 (top-k) and the decode set on D(i) * s^i; thread t holds candidates t, t + T, ..  The decode set ranks
+  // the same scores, or the confidences alone (conf_decode), and with a threshold also takes every candidate whose confidence
+  // exceeds it.
+  int at[PER];
+  float cf[PER];
+  unsigned clive = 0u;
+  uint32_t sb[PER], db[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int c = e * T + tid;
+    at[e] = 0;
+    cf[e] = 0.f;
+    sb[e] = db[e] = 0u;
+    if (c < n1) {
+      clive |= 1u << e;
+      at[e] = sh.cand[c];
+      cf[e] = sh.conf[at[e]];
+      const float score = (pre ? dens[e] : first->density[c]) * cf[e];
+      sb[e] = __float_as_uint(score);
+      db[e] = a.conf_decode ? __float_as_uint(cf[e]) : sb[e];
+      if (a.score_out) a.score_out[at[e]] = score;
+    }
+  }
+  unsigned in_m = a.k >= n1 ? clive : 0u, in_d = a.n_unmask >= n1 ? clive : 0u;
+  const bool cut_m = a.k > 0 && a.k < n1, cut_d = a.n_unmask > 0 && a.n_unmask < n1;
+  if (n1 <= kRankMax) {
+    if (cut_m || cut_d) {                                    // rank by counting (n1 <= T: at most one candidate a thread)
+      if (tid < n1) {
+        sh.rkey[tid] = make_key(sb[0], at[0]);
+        sh.dkey[tid] = make_key(db[0], at[0]);
+      }
+      __syncthreads();
+      if (tid < n1) {
+        const u64 mine = sh.rkey[tid], dmine = sh.dkey[tid];
+        int rank = 0, drank = 0;
+        for (int o = 0; o < n1; ++o) {
+          rank += sh.rkey[o] > mine ? 1 : 0;
+          drank += sh.dkey[o] > dmine ? 1 : 0;
+        }
+        if (cut_m && rank < a.k) in_m |= 1u;
+        if (cut_d && drank < a.n_unmask) in_d |= 1u;
+      }
+    }
+  } else {
+    // the count-th largest key by radix; candidates with an equal key are taken in ascending order
+    auto top = [&](const uint32_t (&kb)[PER], int count) {
+      u64 ones[PER], sum, above;
+      uint32_t any, all, t;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) ones[e] = 1ull;
+      sel_reduce(kb, clive, ones, sh.radix, &sum, &any, &all);
+      sel_radix(kb, clive, ones, any, all, (u64)(count - 1), sh.radix, &buf, &t, &above);
+      const int ties = count - (int)above;                   // >= 1
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const u64 word = __ballot((clive >> e & 1u) && kb[e] == t);
+        if (lane == 0) sh.tie[e * NW + wave] = word;
+      }
+      __syncthreads();
+      const u64 tie_w = sh.tie[lane];
+      uint32_t n_tie;
+      const uint32_t tie_before = wave_before((uint32_t)__popcll(tie_w), &n_tie);
+      unsigned f = 0u;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const int word = e * NW + wave;
+        const u64 bits = lane_of(tie_w, word);
+        const int rank = (int)lane_of(tie_before, word) + __popcll(bits & below);
+        if ((clive >> e & 1u) && (kb[e] > t || (kb[e] == t && rank < ties))) f |= 1u << e;
+      }
+      __syncthreads();                                       // tie and the reduction slots are used again
+      return f;
+    };
+    if (cut_m) in_m = top(sb, a.k);
+    if (cut_d && !a.conf_decode && cut_m && a.n_unmask <= a.k && a.k <= kRankMax) {
+      // the same ranking, and the decode set lies inside M*: count ranks among those k
+      if (tid == 0) sh.n_small = 0;
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < PER; ++e)
+        if (in_m >> e & 1u) sh.rkey[atomicAdd(&sh.n_small, 1)] = make_key(sb[e], at[e]);      // exactly k of them, in any order
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < PER; ++e)
+        if (in_m >> e & 1u) {
+          const u64 mine = make_key(sb[e], at[e]);
+          int rank = 0;
+          for (int o = 0; o < a.k; ++o) rank += sh.rkey[o] > mine ? 1 : 0;
+          if (rank < a.n_unmask) in_d |= 1u << e;
+        }
+    } else if (cut_d) {
+      in_d = top(db, a.n_unmask);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (clive >> e & 1u) {
+      const u64 bit = 1ull << (at[e] & 63);
+      if (in_m >> e & 1u) atomicOr(&sh.mst[at[e] >> 6], bit);
+      if ((in_d >> e & 1u) || (a.threshold > 0.f && cf[e] > a.threshold)) atomicOr(&sh.dec[at[e] >> 6], bit);
+    }
+  __syncthreads();
+  const u64 mst_w = sh.mst[lane], dec_w = sh.dec[lane];
+  if (a.cand_mode != 0) {                                    // stage 2's candidates: everything outside M*
+    float inf[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) inf[e] = e * T + tid < L ? a.influence[e * T + tid] : 0.f;
+    sel_stage2<PER>(a, inf, mst_w, sh.radix, &buf, sh.tie, sh.u, wave);
+    u_w = sh.u[lane];
+  }
 
   // ---- phase 5: unmask (Eq. 2), emit M*, I_t, U, S_{t+1} = M* u I_t u U and its still-masked rows: all offsets from
   // the bitmaps (two counts of at most 4096 to a register)
-  const u64 u_w = w_u[lane];
   const u64 s_w = mst_w | dec_w | u_w, row_w = s_w & mask_w & ~dec_w;
   uint32_t tot_a, tot_b, tot_c;
   const uint32_t pre_a = wave_before((uint32_t)__popcll(mst_w) | (uint32_t)__popcll(dec_w) << 16, &tot_a);
@@ -1125,7 +1215,7 @@ __global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) 
     if (m_b >> lane & 1ull) a.mstar[(pa & 0xffffu) + __popcll(m_b & below)] = j;
     if (d_b >> lane & 1ull) {
       a.decode_idx[(pa >> 16) + __popcll(d_b & below)] = j;
-      a.tokens[j] = a.pred[j];
+      a.tokens[j] = sh.pred[j];
       a.is_masked[j] = 0;
     }
     if (u_b >> lane & 1ull) a.u_set[(pb & 0xffffu) + __popcll(u_b & below)] = j;
@@ -1141,10 +1231,53 @@ __global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) 
     a.counts[2] = (int)(tot_b >> 16);
     a.counts[3] = (int)(tot_a >> 16);
     a.counts[4] = (int)tot_c;
-    a.counts[5] = n_masked - (int)(tot_a >> 16);
-    a.counts[6] = lo;
-    a.counts[7] = hi;
+    a.counts[5] = blk.n_masked - (int)(tot_a >> 16);
+    a.counts[6] = blk.lo;
+    a.counts[7] = blk.hi;
   }
+}
+
+template <int PER, bool SPLIT>
+__global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) {
+  __shared__ SelSecondLds<PER> sh;
+  const SelectArgs& a = batch.seq[blockIdx.x];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (SPLIT) {
+    sel_second<PER>(a, sh, static_cast<const SelPre*>(a.pre), nullptr, wave);
+  } else {
+    __shared__ SelFirstLds<PER> first;
+    sel_second<PER>(a, sh, nullptr, &first, wave);
+  }
+}
+
+// Eq. 1's chunks, and in front of them the halves without logits of n_first selections: one workgroup each, which runs as long
+// as the chunks of a few dozen rows or longer, so it goes first.  A workgroup has the selection's 8 waves; four make a chunk.
+// Six waves a SIMD: with 117 registers, four, the loads in flight did not fill the memory's queue (200 rows 28.5 us, 25.3 now).
+template <int PER, bool VEC>
+__global__ __launch_bounds__(kSelT, 6) void confidence_select_kernel(const float* __restrict__ logits, int vocab, int chunk, int n_chunks,
+                                                                  int n_rows, float* __restrict__ part, const SelectBatch batch,
+                                                                  int n_first) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.x < n_first) {
+    __shared__ SelFirstLds<PER> sh;
+    const SelectArgs& a = batch.seq[blockIdx.x];
+    SelPre* pre = static_cast<SelPre*>(a.pre);
+    (void)sel_first<PER>(a, sh, wave);
+    const int tid = threadIdx.x;
+    if (tid < 64) {
+      pre->mask[tid] = sh.mask[tid];
+      pre->u[tid] = sh.u[tid];
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e) pre->density[e * kSelT + tid] = sh.density[e * kSelT + tid];     // those behind the last are not used
+    return;
+  }
+  __shared__ ConfLds lds[kSelT / kConfThreads];
+  const int half = wave / (kConfThreads / 64), item = ((int)blockIdx.x - n_first) * 2 + half;
+  const int at = min(item, n_rows * n_chunks - 1);           // an odd count: the last chunk twice, the same numbers
+  const int row = at / n_chunks, ck = at - row * n_chunks;
+  if constexpr (VEC) confidence_chunk_vec(logits, vocab, n_chunks, part, row, ck, lds[half]);
+  else confidence_chunk(logits, vocab, chunk, n_chunks, part, row, ck, lds[half]);
 }
 
 // Step-0 state: S_0 = all rows, s_rows = masked rows, conf = 0, pred = 0.
@@ -1182,19 +1315,47 @@ int confidence_chunks(int vocab) {
 
 size_t confidence_scratch_floats(size_t n_rows, int vocab) { return n_rows * confidence_chunks(vocab) * 3; }
 
-hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st) {
-  if (n_rows <= 0) return hipSuccess;
-  if (vocab <= 0 || part == nullptr) return hipErrorInvalidValue;
+size_t select_pre_floats() { return sizeof(SelPre) / sizeof(float); }
+
+// positions a thread of the selection for sequences of up to max_L positions
+static int sel_per(int max_L) { return max_L <= kSelT ? 1 : max_L <= 2 * kSelT ? 2 : max_L <= 4 * kSelT ? 4 : 8; }
+
+hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st, const SelectArgs* first,
+                                    int n_first) {
+  if (n_rows <= 0) return n_first > 0 ? hipErrorInvalidValue : hipSuccess;
+  if (vocab <= 0 || part == nullptr || n_first < 0 || n_first > kSelMaxBatch) return hipErrorInvalidValue;
+  SelectBatch batch;
+  int max_L = 1;
+  for (int i = 0; i < n_first; ++i) {
+    if (first[i].L <= 0 || first[i].L > kSelMaxL || first[i].block_len <= 0 || first[i].prompt_len < 0 ||
+        first[i].prompt_len > first[i].L || first[i].cand_mode != 0 || !first[i].pre)
+      return hipErrorInvalidValue;
+    batch.seq[i] = first[i];
+    max_L = std::max(max_L, first[i].L);
+  }
+  for (int i = n_first; i < kSelMaxBatch; ++i) batch.seq[i] = SelectArgs{};
   int chunk = kConfChunk;
   while ((vocab + chunk - 1) / chunk > kConfMaxChunks) chunk *= 2;
   const int n_chunks = confidence_chunks(vocab);
-  if (chunk == kConfChunk && vocab % 4 == 0 && vocab >= 4 && (uintptr_t)logits % 16 == 0)
-    hipLaunchKernelGGL(confidence_chunk_vec_kernel, dim3(n_chunks, n_rows), dim3(kConfThreads), 0, st, logits, vocab,
-                       n_chunks, part);
-  else
-    hipLaunchKernelGGL(confidence_chunk_kernel, dim3(n_chunks, n_rows), dim3(kConfThreads), 0, st, logits, vocab, chunk,
-                       n_chunks, part);
-  return hipGetLastError();
+  const dim3 grid(n_first + (unsigned)(((size_t)n_rows * n_chunks + 1) / 2)), threads(kSelT);
+  const bool vec = chunk == kConfChunk && vocab % 4 == 0 && vocab >= 4 && (uintptr_t)logits % 16 == 0;
+#define D2C_CONF(PER_)                                                                                                         \
+  do {                                                                                                                         \
+    if (vec)                                                                                                                   \
+      hipLaunchKernelGGL((confidence_select_kernel<PER_, true>), grid, threads, 0, st, logits, vocab, chunk, n_chunks, n_rows, \
+                         part, batch, n_first);                                                                                \
+    else                                                                                                                       \
+      hipLaunchKernelGGL((confidence_select_kernel<PER_, false>), grid, threads, 0, st, logits, vocab, chunk, n_chunks,        \
+                         n_rows, part, batch, n_first);                                                                        \
+    return hipGetLastError();                                                                                                  \
+  } while (0)
+  switch (sel_per(max_L)) {
+    case 1: D2C_CONF(1);
+    case 2: D2C_CONF(2);
+    case 4: D2C_CONF(4);
+    default: D2C_CONF(8);
+  }
+#undef D2C_CONF
 }
 
 bool rollout_in_place(int layer, int m) { return layer == 0 || m <= kRollStripMax; }
@@ -1299,6 +1460,7 @@ hipError_t launch_select(const SelectArgs* args, int n, hipStream_t st) {
       return hipErrorInvalidValue;
     if (a.n_rows < 0 || (a.n_rows > 0 && (!a.part || !a.pos || a.n_chunks <= 0 || a.n_chunks > kConfMaxChunks)))
       return hipErrorInvalidValue;
+    if ((a.pre != nullptr) != (args[0].pre != nullptr) || (a.pre && a.cand_mode != 0)) return hipErrorInvalidValue;
     batch.seq[i] = a;
     if (a.n_rows == 0) batch.seq[i].part = nullptr;
     if (a.n_rows > kMergeMaxRows) {
@@ -1311,11 +1473,19 @@ hipError_t launch_select(const SelectArgs* args, int n, hipStream_t st) {
     max_L = std::max(max_L, a.L);
   }
   for (int i = n; i < kSelMaxBatch; ++i) batch.seq[i] = args[0];        // never read: the grid has n workgroups
-  if (max_L <= 4 * kSelT)
-    hipLaunchKernelGGL(select_kernel<4>, dim3(n), dim3(kSelT), 0, st, batch);
-  else
-    hipLaunchKernelGGL(select_kernel<8>, dim3(n), dim3(kSelT), 0, st, batch);
-  return hipGetLastError();
+#define D2C_SELECT(PER_)                                                                                  \
+  do {                                                                                                    \
+    if (args[0].pre) hipLaunchKernelGGL((select_kernel<PER_, true>), dim3(n), dim3(kSelT), 0, st, batch); \
+    else hipLaunchKernelGGL((select_kernel<PER_, false>), dim3(n), dim3(kSelT), 0, st, batch);            \
+    return hipGetLastError();                                                                             \
+  } while (0)
+  switch (sel_per(max_L)) {
+    case 1: D2C_SELECT(1);
+    case 2: D2C_SELECT(2);
+    case 4: D2C_SELECT(4);
+    default: D2C_SELECT(8);
+  }
+#undef D2C_SELECT
 }
 
 hipError_t launch_seq_reset(const uint8_t* is_masked, int L, int32_t* s_idx, int32_t* s_rows, float* conf,

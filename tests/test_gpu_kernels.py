@@ -531,6 +531,30 @@ def test_select_parity_at_the_edges(B, case):
     test_select_parity(B, case)
 
 
+@pytest.mark.parametrize("L", [1, 64, 512, 513, 1024, 1025, 2048, 2049, 4096])
+def test_select_halves_in_one_launch_and_in_two(B, L):
+    """With logit rows the half of the selection that needs none runs beside Eq. 1, in another launch: the same sets and the same
+    bits as in one launch (no logit rows; the confidences those of the first call)."""
+    say(f"select in halves L={L}")
+    V = 8196
+    wd = W.ModelDims(1, 64, 4, 4, 16, 80, V, dtype="f32")
+    mdl = W.model_weights(W.ModelDims(1, 64, 4, 4, 16, 80, 8, dtype="f32"), 0)
+    mdl["tok_emb"] = mdl["lm_head"] = np.zeros((V, 64), np.float32)
+    ctx = B.Context(wd, mdl, L)
+    rng = np.random.default_rng(L)
+    for P, blk, k, nu, p, sigma, cdec in ((0, L, 300, 5, 0.3, 10.0, 0), (L // 3, 64, 8, 1, 0.1, 25.0, 1), (L // 2, 16, 0, 2, 1.0, 1e5, 0)):
+        is_masked = rng.random(L) < 0.6; is_masked[:P] = False; is_masked[L - 1] = True
+        y = np.where(is_masked, wd.mask_id, 3).astype(np.int32)
+        pos = np.flatnonzero(is_masked)[:5]
+        prm = B.make_params(sigma, k, p, blk, nu, 0, conf_decode=cdec)
+        conf, c = rng.random(L).astype(np.float32), W.skewed_influence(L, L)
+        two, _ = _run_select(B, ctx, prm, W.logits_rows(L, len(pos), V), pos, y, is_masked, P, conf, np.zeros(L, np.int32), c)
+        one, _ = _run_select(B, ctx, prm, np.zeros((0, V), np.float32), pos[:0], y, is_masked, P, two["conf"], two["pred"], c)
+        for name in two:
+            np.testing.assert_array_equal(two[name], one[name], err_msg=name)
+    ctx.close()
+
+
 @pytest.mark.parametrize("L,n_masked", [(640, 600), (3000, 2900)])
 def test_select_ties_beyond_the_counting_limit(B, L, n_masked):
     """More than 256 candidates, runs of equal scores and of equal influence: the lowest index of a run goes first."""
