@@ -49,12 +49,37 @@ constexpr int kStageSlots = NT != 1 ? 0
                                                                                                      : 0;
 
 // silu(g) * u with the quotient from the reciprocal unit and one correction from its own remainder (Markstein's method), as
-// exact as the division that it replaces: relative error against 64 bits over |g| < 16 at most 1.5e-7, 4e-8 on average, both.
-// The exponential unit alone (arguments rounded after the product with log2(e)) reaches 1e-6 and is not used.
-__device__ __forceinline__ float gated(float g, float u) {
-  if (!(fabsf(g) < 87.0f)) return g / (1.0f + expf(-g)) * u;   // the steps below need finite terms
-  const float d = 1.0f + expf(-g), inv = __builtin_amdgcn_rcpf(d), q = g * inv;
+// exact as the division that it replaces.
+__device__ __forceinline__ float gate_of(float g, float e, float u) {      // e = exp(-g), finite
+  const float d = 1.0f + e, inv = __builtin_amdgcn_rcpf(d), q = g * inv;
   return copysignf(fmaf(fmaf(-d, q, g), inv, q), g) * u;       // the correction of -0 would lose its sign
+}
+__device__ __forceinline__ float gated(float g, float u) {
+  if (!(fabsf(g) < 87.0f)) return g / (1.0f + expf(-g)) * u;   // the steps above need finite terms
+  return gate_of(g, expf(-g), u);
+}
+// The same for |g| < 87: exp(-g) = 2^n 2^f with n + f = -g log2(e), n whole and f in two parts.  Without the library's range
+// checks the values of a lane are one stretch of code without branches, which overlaps their latencies.  Relative error against
+// 64 bits over |g| < 16 at most 1.5e-7, 3.2e-8 on average, over |g| < 87 1.8e-7 and 1.9e-8: as of g / (1 + expf(-g)).
+__device__ __forceinline__ float gated_finite(float g, float u) {
+  constexpr float kL2e = -1.44269502162933349609375f, kL2eLo = -1.92596303350e-8f;      // -log2(e): nearest float, what is left
+  const float n = __builtin_rintf(g * kL2e), f = fmaf(g, kL2eLo, fmaf(g, kL2e, -n));
+  return gate_of(g, __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)n), u);
+}
+// Four values of a lane; the wave takes the general form if any of its gates is not finite and below 87.
+__device__ __forceinline__ f32x4 gated4(const f32x4& g, const f32x4& u) {
+  bool wide = false;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) wide = wide || !(fabsf(g[j]) < 87.0f);
+  f32x4 o;
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(wide) != 0, 0)) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = gated(g[j], u[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = gated_finite(g[j], u[j]);
+  }
+  return o;
 }
 
 template <typename T, int MT, int NT, int WAVES, int MODE>
@@ -575,41 +600,55 @@ __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restric
   __builtin_amdgcn_s_waitcnt(0x70 | 0xf00);                  // no staging may write LDS after the workgroup has left
 
   if constexpr (MODE == kPreSwiglu) {
-    // column tiles alternate gate, up, gate, up ..
-    const int F = N >> 1, first = n_base >> 4;                // first column tile of the wave
-    auto put = [&](int pair, int mt, const f32x4& gate, const f32x4& up) {
-      const int col = pair * 16 + r;
-      if (col >= F) return;
+    // column tiles alternate gate, up, gate, up ..  The gated values go through LDS (idle now) and out in 16-byte pieces of
+    // rows: 2-byte stores from the accumulators, a branch and the library's exponential for each, took 5-8 us of the kernel
+    // (860 rows x 24576 x 4096, zeros 139 -> 131 us; with real data, where power bounds the clock, 162 -> 158; in steps 4-5 %).
+    constexpr int kCols = 32 * NT, kPitch = kCols + 8;        // hidden columns of the workgroup
+    constexpr int kXch = NT % 2 == 0 ? 0 : 4 * MT * 1024;
+    static_assert(kXch + 2 * MT * 16 * kPitch * 2 <= 2 * kBuf, "the output tile and the exchanged tiles fit the staging buffers");
+    const int F = N >> 1;
+    bf16* const tile = reinterpret_cast<bf16*>(lds + kXch);
+    auto put = [&](int pair, int mt, const f32x4& gate, const f32x4& up) {      // pair: of the workgroup's
+      const f32x4 o = gated4(gate, up);
+      bf16* dst = tile + (part * (MT * 16) + mt * 16 + g * 4) * kPitch + pair * 16 + r;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = row0 + mt * 16 + g * 4 + j;
-        if (row < m) act[(size_t)row * F + col] = (bf16)gated(gate[j], up[j]);
-      }
+      for (int j = 0; j < 4; ++j) dst[j * kPitch] = (bf16)o[j];
     };
+    __syncthreads();
     if constexpr (NT % 2 == 0) {                              // every pair sits in one wave
 #pragma unroll
       for (int p = 0; p < NT / 2; ++p)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) put((first >> 1) + p, mt, acc[mt][2 * p], acc[mt][2 * p + 1]);
+        for (int mt = 0; mt < MT; ++mt) put(quarter * (NT / 2) + p, mt, acc[mt][2 * p], acc[mt][2 * p + 1]);
     } else {
-      // three tiles: an even quarter holds (gate, up) and the gate of a pair whose up tile is its neighbour's first, which
-      // comes over through LDS (idle now); the neighbour's other two tiles are a pair of their own
+      // three tiles: an even quarter holds a pair and the gate tile of another, whose up tile is its neighbour's first; they
+      // exchange halves of these two tiles.  The neighbour's other two are a pair of their own.
+      static_assert(NT == 3, "pairs across two waves");
+      constexpr int kHalf = MT / 2;
       f32x4* xch = reinterpret_cast<f32x4*>(lds) + (part * 2 + (quarter >> 1)) * (MT * 64);      // [MT][64]
-      __syncthreads();
-      if (quarter & 1) {
+      const int first = (quarter >> 1) * 3;
+      const bool odd = quarter & 1;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) xch[mt * 64 + lane] = acc[mt][0];
-      }
+      for (int mt = 0; mt < MT; ++mt)
+        if (odd == (mt < kHalf)) xch[mt * 64 + lane] = odd ? acc[mt][0] : acc[mt][2];
       __syncthreads();
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        if (quarter & 1) {
-          put((first + 1) >> 1, mt, acc[mt][1], acc[mt][2]);
-        } else {
-          put(first >> 1, mt, acc[mt][0], acc[mt][1]);
-          put((first >> 1) + 1, mt, acc[mt][2], xch[mt * 64 + lane]);
+        if (odd) put(first + 2, mt, acc[mt][1], acc[mt][2]);
+        else put(first, mt, acc[mt][0], acc[mt][1]);
+        if (odd != (mt < kHalf)) {
+          const f32x4 other = xch[mt * 64 + lane];
+          put(first + 1, mt, odd ? other : acc[mt][2], odd ? acc[mt][0] : other);
         }
       }
+    }
+    __syncthreads();
+    constexpr int kPieces = kCols / 8;
+    for (int i = tid; i < 2 * MT * 16 * kPieces; i += 512) {
+      const int row_t = i / kPieces, piece = i - row_t * kPieces;
+      const int row = bz * (MT * 32) + row_t, col = bx * kCols + piece * 8;
+      if (row < m && col < F)
+        *reinterpret_cast<u32x4*>(act + (size_t)row * F + col) = *reinterpret_cast<const u32x4*>(tile + row_t * kPitch + piece * 8);
     }
     return;
   }

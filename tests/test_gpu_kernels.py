@@ -784,6 +784,28 @@ def test_refresh_layer_parity_many_rows(B, m, kernel):
                           tunables={"gemm_wide_tiles": kernel})
 
 
+@pytest.mark.parametrize("m,F", [(257, 1280), (300, 208), (449, 1024)])
+def test_gated_epilogue_of_large_gates(B, m, F):
+    """Gates far beyond 87, where exp(-g) leaves the range of a float, beside ordinary ones: whole waves of either, and mixed ones."""
+    say(f"gated epilogue, large gates m={m} F={F}")
+    wd = W.ModelDims(1, 512, 4, 4, 128, F, 64, dtype="bf16")
+    mdl = W.model_weights(wd, 0)
+    gate = mdl["layers"][0]["w_gate_up"]
+    gate[: F // 3] *= 400.0                                                 # gates with a standard deviation of 180
+    gate[F // 2: F: 7] *= 100.0
+    mdl["layers"][0]["w_gate_up"] = W.round_bf16(gate)
+    ctx = B.Context(wd, mdl, m, tunables={"gemm_wide_tiles": 2})
+    S, h0 = np.arange(m, dtype=np.int32), W.hidden_rows(4, m, wd.d_model, std=0.5)
+    kc, vc = (np.zeros((m, wd.d_kv)) for _ in range(2))
+    hidden, kd, vd = torch.from_numpy(h0).cuda(), B.to_device(kc, "bf16"), B.to_device(vc, "bf16")
+    ctx.d2c_refresh_layer(0, hidden, torch.from_numpy(S).cuda(), S, kd, vd, m, None, None)
+    torch.cuda.synchronize()
+    h_ref, _ = O.refresh_layer(oracle_dims(wd), mdl["layers"][0], h0, S, kc, vc)
+    for r in range(m):
+        assert rel_l2(host(hidden)[r], h_ref[r]) < TOL["bf16"], f"hidden row {r}"
+    ctx.close()
+
+
 @pytest.mark.parametrize("m,N,K", [(300, 520, 512), (449, 264, 2304), (230, 520, 640)])
 def test_linear_many_rows_unaligned(B, m, N, K):
     """Activations that are not 16-byte aligned cannot be staged straight into LDS: gemm_wide_kernel's splits by another kernel
