@@ -497,7 +497,9 @@ __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restric
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int r = lane & 15, g = lane >> 4;
-  const int part = wave >> 2, quarter = wave & 3;             // row chunk of the pair, 64-column quarter
+  // row chunk of the pair, 64-column quarter: the two waves of a quarter sit on different SIMDs, so that they go at one pace
+  // and the second finds the weights in the L1 (on one SIMD they took turns: a third more requests to the L2)
+  const int part = (wave >> 1) & 1, quarter = (wave & 1) | ((wave >> 2) << 1);
   const int row0 = (bz * 2 + part) * (MT * 16);
   const int k_begin = by * k_per_split;
   const int k_end = min(K, k_begin + k_per_split);
