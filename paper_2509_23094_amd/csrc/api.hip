@@ -68,6 +68,7 @@ struct d2c_ctx {
   std::vector<void*> allocs;
   int64_t ws_bytes = 0;
   float* hidden = nullptr;      // [max_rows, d]
+  float* h_mid = nullptr;       // [128 rows, d] (float contexts): residual rows between attention and FFN where gemm_fuses
   void* a_norm = nullptr;       // T [max_seq, d]
   void* q = nullptr;            // T [n_layers, max_seq, d_q]: one slot per layer (a second stream may read it later)
   void* attn_o = nullptr;       // T [max_seq, d_q]
@@ -253,10 +254,25 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
   GemmPlan pl;
   size_t stride;
   int rc;
-  if (!a_ready)
-    D2C_TIMED(c, st, D2C_PROF_ROWWISE, 0.0,
-              launch_add_norm(dt, hidden, nullptr, 0, 0, d, M, d, c->attn_norm[layer], D.rms_eps, c->a_norm, st));
-  if ((rc = project(c, c->a_norm, d, c->wqkv[layer], M, dq + 2 * dkv, d, &pl, &stride, st)) != D2C_OK) return rc;
+  // small float layers: the norm, RoPE and the cache update are part of the projection (one launch instead of three)
+  std::vector<RopeCall> all_ropes;
+  for (int b = 0; b < n_seg; ++b)
+    if (segs[b].m > 0) all_ropes.push_back(RopeCall{segs[b].idx, segs[b].k_cache, segs[b].v_cache, segs[b].off, segs[b].m});
+  pl = plan_gemm(c->tun, dt, M, dq + 2 * dkv, d, false, !c->pre);
+  const bool fuse_qkv = c->pre && gemm_fuses(dt, pl) && rope_fuses(D.head_dim, (int)all_ropes.size());
+  if (fuse_qkv) {
+    const NormFuse norm{hidden, nullptr, 0, 0, 0, c->attn_norm[layer], D.rms_eps, nullptr};
+    const RopeFuse rope{c->bqkv.empty() ? nullptr : c->bqkv[layer], all_ropes.data(), (int)all_ropes.size(), D.n_heads, D.n_kv_heads,
+                        D.head_dim, c->rope_cos, c->rope_sin, (float*)q};
+    D2C_TIMED(c, st, D2C_PROF_GEMM, (double)(dq + 2 * dkv) * d * ts,
+              launch_gemm_tile_fused(pl, a_ready ? nullptr : &norm, (const float*)c->a_norm, d, c->wqkv[layer], pre_chunks(c, d), &rope,
+                                     nullptr, 0, nullptr, M, dq + 2 * dkv, d, st));
+  } else {
+    if (!a_ready)
+      D2C_TIMED(c, st, D2C_PROF_ROWWISE, 0.0,
+                launch_add_norm(dt, hidden, hidden, nullptr, 0, 0, d, M, d, c->attn_norm[layer], D.rms_eps, c->a_norm, st));
+    if ((rc = project(c, c->a_norm, d, c->wqkv[layer], M, dq + 2 * dkv, d, &pl, &stride, st)) != D2C_OK) return rc;
+  }
   // RoPE and cache update per sequence; the few-row attention per sequence as well, the LDS-tiled attention of
   // the sequences with many rows in batched launches (they write the head average themselves, on this stream)
   std::vector<TiledCall> tiled;
@@ -272,7 +288,7 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
   };
   // RoPE + cache update of consecutive non-empty slices in one launch (their rows are consecutive in the
   // compact buffers; an empty slice in between does not break the run)
-  {
+  if (!fuse_qkv) {
     std::vector<RopeCall> ropes;
     auto flush_rope = [&]() -> int {
       if (ropes.empty()) return D2C_OK;
@@ -286,10 +302,8 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
       ropes.clear();
       return D2C_OK;
     };
-    for (int b = 0; b < n_seg; ++b) {
-      const Seg& g = segs[b];
-      if (g.m <= 0) continue;
-      ropes.push_back(RopeCall{g.idx, g.k_cache, g.v_cache, g.off, g.m});
+    for (const RopeCall& rcall : all_ropes) {
+      ropes.push_back(rcall);
       if ((int)ropes.size() == rope_max_batch() && (rc = flush_rope())) return rc;
     }
     if ((rc = flush_rope())) return rc;
@@ -325,21 +339,32 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
     for (int b = 0; b < n_seg; ++b) {
       const Seg& g = segs[b];
       if (g.m <= 0 || !g.abar) continue;
-      if (!attention_is_tiled(c->tun, dt, g.m, g.L))
+      const bool few = !attention_is_tiled(c->tun, dt, g.m, g.L), first = few && layer == 0;      // first: the same launch
+      if (few)
         D2C_TIMED(c, side, D2C_PROF_ATTN_AVG, 0.0,
                   launch_attention_avg(c->tun, dt, q + (size_t)g.off * dq * ts, g.k_cache, lse + (size_t)D.n_heads * g.off,
-                                       g.m, g.L, D.n_heads, D.n_kv_heads, D.head_dim, g.abar, side));
-      if (g.roll)
+                                       g.m, g.L, D.n_heads, D.n_kv_heads, D.head_dim, g.abar, side, first ? g.roll : nullptr, g.idx));
+      if (g.roll && !first)
         D2C_TIMED(c, side, D2C_PROF_ROLLOUT, 0.0,
                   launch_rollout(g.abar, g.roll, c->roll, g.idx, g.m, g.L, layer == 0, side));
     }
   }
   if ((rc = project(c, c->attn_o, dq, c->wo[layer], M, d, dq, &pl, &stride, st)) != D2C_OK) return rc;
-  D2C_TIMED(c, st, D2C_PROF_ROWWISE, 0.0,
-            launch_add_norm(dt, hidden, c->partial, pl.splits, stride, d, M, d, c->ffn_norm[layer], D.rms_eps,
-                            c->a_norm, st));
-  if (c->fused_swiglu) {
-    pl = plan_gemm(c->tun, dt, M, 2 * F, d, true);
+  const GemmPlan gate = plan_gemm(c->tun, dt, M, 2 * F, d, true);
+  const float* h_mid = hidden;                       // the residual rows behind the attention
+  const bool fuse_gate = c->fused_swiglu && gemm_fuses(dt, gate);
+  if (!fuse_gate)
+    D2C_TIMED(c, st, D2C_PROF_ROWWISE, 0.0,
+              launch_add_norm(dt, hidden, hidden, c->partial, pl.splits, stride, d, M, d, c->ffn_norm[layer], D.rms_eps,
+                              c->a_norm, st));
+  if (fuse_gate) {
+    const NormFuse norm{hidden, c->partial, pl.splits, stride, d, c->ffn_norm[layer], D.rms_eps, c->h_mid};
+    h_mid = c->h_mid;
+    D2C_TIMED(c, st, D2C_PROF_GEMM, 2.0 * F * d * tsize(c),
+              launch_gemm_tile_fused(gate, &norm, nullptr, d, c->w_gate_up[layer], pre_chunks(c, d), nullptr, nullptr, 0,
+                                     (float*)c->act, M, 2 * F, d, st));
+  } else if (c->fused_swiglu) {
+    pl = gate;
     D2C_TIMED(c, st, D2C_PROF_GEMM, 2.0 * F * d * tsize(c),
               launch_gemm_swiglu(dt, pl, c->a_norm, d, c->w_gate_up[layer], pre_chunks(c, d), c->act, F, M, d, st));
   } else {
@@ -349,7 +374,7 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
   }
   if ((rc = project(c, c->act, F, c->w_down[layer], M, d, F, &pl, &stride, st)) != D2C_OK) return rc;
   D2C_TIMED(c, st, D2C_PROF_ROWWISE, 0.0,
-            launch_add_norm(dt, hidden, c->partial, pl.splits, stride, d, M, d, next_gain, D.rms_eps,
+            launch_add_norm(dt, h_mid, hidden, c->partial, pl.splits, stride, d, M, d, next_gain, D.rms_eps,
                             next_gain ? c->a_norm : nullptr, st));
   return D2C_OK;
 }
@@ -467,6 +492,8 @@ int d2c_init_tuned(const d2c_dims* dims, const d2c_weights* w, const d2c_tunable
     return bail(rc);
   c->rollout_bytes = c->ws_bytes - ws0;
   c->attn_scratch_bytes = (int64_t)std::max<size_t>(1, c->attn_part_floats) * 4;
+  // gemm_tile_kernel takes at most 128 rows
+  if (D.dtype == D2C_F32 && (rc = ws_alloc(c, &c->h_mid, std::min<size_t>(Lr, 128) * d * 4))) return bail(rc);
   if ((rc = ws_alloc(c, &c->hidden, Lr * d * 4)) || (rc = ws_alloc(c, &c->a_norm, Lr * d * ts)) ||
       (rc = ws_alloc(c, &c->q, (size_t)D.n_layers * Lr * dq * ts)) || (rc = ws_alloc(c, &c->attn_o, Lr * dq * ts)) ||
       (rc = ws_alloc(c, &c->act, Lr * F * ts)) ||

@@ -449,8 +449,8 @@ __device__ __forceinline__ float exp_of(const float*, float x) { return expf(x);
 template <typename T, int DH, bool STAGED>
 __global__ __launch_bounds__(kThreads) void attn_avg_kernel(const T* __restrict__ q, const T* __restrict__ k_cache,
                                                             const float* __restrict__ lse, int m, int L, int n_heads,
-                                                            int n_kv_heads, float scale,
-                                                            float* __restrict__ attn_avg) {
+                                                            int n_kv_heads, float scale, float* __restrict__ attn_avg,
+                                                            float* __restrict__ roll, const int32_t* __restrict__ idx) {
   constexpr int KS = Frag<T>::kStep, E = Frag<T>::kElems;
   constexpr int NS = DH / KS;
   __shared__ f32x4 part[kWaves][64];
@@ -571,6 +571,13 @@ __global__ __launch_bounds__(kThreads) void attn_avg_kernel(const T* __restrict_
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     if (key0 + 4 * g + j < L) dst[j] = sum[j] * inv_h;
+  if (roll) {                                               // the first layer's rollout block: W^(1) itself
+    const int own = idx[q0 + r];
+    float* c = roll + (size_t)(q0 + r) * L + key0 + 4 * g;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (key0 + 4 * g + j < L) c[j] = 0.5f * (sum[j] * inv_h + (own == key0 + 4 * g + j ? 1.f : 0.f));
+  }
 }
 
 // fp32 forward for head dimensions 64 and 128: the bf16 kernel's shape (one workgroup per 16-query tile and head, 8
@@ -756,7 +763,8 @@ __global__ __launch_bounds__(kThreads) void attn_avg_f32_kernel(const float* __r
                                                                 const float* __restrict__ k_cache,
                                                                 const float* __restrict__ lse, int m, int L,
                                                                 int n_heads, int n_kv_heads, int head_dim,
-                                                                float scale, float* __restrict__ attn_avg) {
+                                                                float scale, float* __restrict__ attn_avg,
+                                                                float* __restrict__ roll, const int32_t* __restrict__ idx) {
   const int row = blockIdx.x;
   const int dq = n_heads * head_dim, dkv = n_kv_heads * head_dim, group = n_heads / n_kv_heads;
   const float inv_h = 1.0f / (float)n_heads;
@@ -770,6 +778,7 @@ __global__ __launch_bounds__(kThreads) void attn_avg_f32_kernel(const float* __r
       acc += expf(s * scale - lse[(size_t)head * m + row]);
     }
     attn_avg[(size_t)row * L + j] = acc * inv_h;
+    if (roll) roll[(size_t)row * L + j] = 0.5f * (acc * inv_h + (idx[row] == j ? 1.f : 0.f));
   }
 }
 
@@ -823,7 +832,7 @@ bool f32_tiles(int head_dim, const void* q, const void* k_cache, const void* v_c
 
 template <typename T, int DH>
 hipError_t launch_avg(const void* q, const void* k_cache, const float* lse, int m, int L, int n_heads,
-                      int n_kv_heads, float* attn_avg, hipStream_t st) {
+                      int n_kv_heads, float* attn_avg, hipStream_t st, float* roll, const int32_t* idx) {
   const float scale = 1.0f / sqrtf((float)DH);
   const int key_blocks = (L + 15) / 16;
   if constexpr (sizeof(T) == 2) {
@@ -835,12 +844,12 @@ hipError_t launch_avg(const void* q, const void* k_cache, const float* lse, int 
     if (pays && (((uintptr_t)q | (uintptr_t)k_cache) & 15) == 0 && (size_t)L * n_kv_heads * DH * 2 < (1ull << 31) &&
         (size_t)m * n_heads * DH * 2 < (1ull << 31)) {
       hipLaunchKernelGGL((attn_avg_kernel<T, DH, true>), dim3((m + 15) / 16, key_blocks), dim3(kThreads), 0, st, (const T*)q,
-                         (const T*)k_cache, lse, m, L, n_heads, n_kv_heads, scale, attn_avg);
+                         (const T*)k_cache, lse, m, L, n_heads, n_kv_heads, scale, attn_avg, roll, idx);
       return hipGetLastError();
     }
   }
   hipLaunchKernelGGL((attn_avg_kernel<T, DH, false>), dim3((m + 15) / 16, key_blocks), dim3(kThreads), 0, st, (const T*)q,
-                     (const T*)k_cache, lse, m, L, n_heads, n_kv_heads, scale, attn_avg);
+                     (const T*)k_cache, lse, m, L, n_heads, n_kv_heads, scale, attn_avg, roll, idx);
   return hipGetLastError();
 }
 
@@ -927,20 +936,21 @@ hipError_t launch_attention_fwd(const Tunables& t, int dtype, const void* q, con
 }
 
 hipError_t launch_attention_avg(const Tunables& t, int dtype, const void* q, const void* k_cache, const float* lse, int m, int L,
-                                int n_heads, int n_kv_heads, int head_dim, float* attn_avg, hipStream_t st) {
+                                int n_heads, int n_kv_heads, int head_dim, float* attn_avg, hipStream_t st, float* roll,
+                                const int32_t* idx) {
   if (m <= 0) return hipSuccess;
-  if (L <= 0 || n_heads % n_kv_heads || attention_is_tiled(t, dtype, m, L)) return hipErrorInvalidValue;
+  if (L <= 0 || n_heads % n_kv_heads || attention_is_tiled(t, dtype, m, L) || (roll && !idx)) return hipErrorInvalidValue;
   if (dtype == kBF16) {
-    if (head_dim == 128) return launch_avg<bf16, 128>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st);
-    if (head_dim == 64) return launch_avg<bf16, 64>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st);
+    if (head_dim == 128) return launch_avg<bf16, 128>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st, roll, idx);
+    if (head_dim == 64) return launch_avg<bf16, 64>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st, roll, idx);
     return hipErrorInvalidValue;
   }
   if (f32_tiles(head_dim, q, k_cache, nullptr))
-    return head_dim == 128 ? launch_avg<float, 128>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st)
-                           : launch_avg<float, 64>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st);
+    return head_dim == 128 ? launch_avg<float, 128>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st, roll, idx)
+                           : launch_avg<float, 64>(q, k_cache, lse, m, L, n_heads, n_kv_heads, attn_avg, st, roll, idx);
   const float scale = 1.0f / sqrtf((float)head_dim);
   hipLaunchKernelGGL(attn_avg_f32_kernel, dim3(m), dim3(kThreads), 0, st, (const float*)q, (const float*)k_cache, lse,
-                     m, L, n_heads, n_kv_heads, head_dim, scale, attn_avg);
+                     m, L, n_heads, n_kv_heads, head_dim, scale, attn_avg, roll, idx);
   return hipGetLastError();
 }
 

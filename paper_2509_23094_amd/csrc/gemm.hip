@@ -707,10 +707,33 @@ constexpr int kTileChunks = 4;
 // columns, FFN 80 to 2816, 1-128 rows, with this rule against without: 1.0 to 2.5 times as fast, none slower (768 columns, 17 rows 62 ->
 // 56 us, 1024 columns, 16 rows 53 -> 49).  Row-major, 223 sizes of 1-128 rows x 64-4096 columns x 64-2048: 1.5 to 4 times, 2.4 on average.
 constexpr int kTileWgs = 192;
-template <int NC, int MODE>
+// NORM, ROPE (one split, pre-tiled): the launches around such a projection are as long as it is, and a workgroup holds whole rows of
+// its activations and, with heads of 64 columns and less, whole heads.  NORM: the activations are made here, every workgroup of a
+// row tile for itself (16 rows, a few KB), and the first one leaves the updated residual rows in another buffer than the one that
+// the others read.  ROPE: the output goes through LDS, and q, K and V rows leave turned, as launch_qkv_rope_scatter writes them.
+// 37 rows of the small model, launches and the gaps between them apart: norm + QKV + RoPE 3.1 + 3.8 + 3.6 us -> 6.6, norm +
+// gate/up 3.4 + 4.1 -> 7.3; two layers with 22 launches 91 us a call, 76 with 17.
+struct NormArgs {
+  const float *h, *P;
+  int n_splits;
+  size_t split_stride;
+  int ldp;
+  const float* gain;
+  float eps;
+  float* h_out;
+};
+struct RopeArgs {
+  RopeSeqs seqs;
+  const float *bias, *cos, *sin;
+  int dq, dkv, head_dim;
+  float* q_out;
+};
+template <int NC, int MODE, bool NORM, bool ROPE>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
                                                         float* __restrict__ P, int ldp, size_t split_stride, int m, int N, int K,
-                                                        int k_per_split, float* __restrict__ act) {
+                                                        int k_per_split, float* __restrict__ act, const NormArgs norm,
+                                                        const RopeArgs rope) {
+  static_assert(MODE != kRowMajor || !(NORM || ROPE), "fused with pre-tiled weights only");
   constexpr int E = 4, KS = 16, KC = 64;
   constexpr int kPieces = NC * 16;                                  // 16-byte pieces of a row
   constexpr int kPitch = kPieces + 1;                               // in LDS: neighbouring rows on other banks
@@ -739,12 +762,58 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict_
     for (int i = 0; i < NC * kSteps; ++i)
       b[i].raw = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane * 16 + i * 1024, 0, 0));
   }
+  // what the output's rows need: the chain of position and angles is over by the time the product is
+  constexpr int kTurn = ROPE ? 2 : 1;                    // pairs of a thread: two of the 32 of a row's 64 columns
+  const int t_row = threadIdx.x >> 4;
+  int t_pos = 0, t_c1[kTurn] = {}, t_half = 0;
+  float t_cos[kTurn], t_sin[kTurn];
+  float *k_row = nullptr, *v_row = nullptr;
+  if constexpr (ROPE) {
+    const int row = min(row0 + t_row, m - 1), sq = rope_seq_of(rope.seqs, row);
+    t_pos = rope.seqs.idx[sq][row - rope.seqs.off[sq]];
+    k_row = static_cast<float*>(rope.seqs.k_cache[sq]) + (size_t)t_pos * rope.dkv;
+    v_row = static_cast<float*>(rope.seqs.v_cache[sq]) + (size_t)t_pos * rope.dkv;
+    t_half = rope.head_dim >> 1;
+  }
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
     const int at = i * 256 + (int)threadIdx.x, k = k_begin + at % kPieces * E;
-    a_reg[i] = ld16(A + (size_t)min(row0 + at / kPieces, m - 1) * lda + min(k, K - E));
-    if (k >= k_end) a_reg[i] = u32x4{0u, 0u, 0u, 0u};
+    a_reg[i] = ld16((NORM ? norm.h + (size_t)min(row0 + at / kPieces, m - 1) * K : A + (size_t)min(row0 + at / kPieces, m - 1) * lda) +
+                    min(k, K - E));
   }
+  if constexpr (ROPE) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int pair = (threadIdx.x & 15) * 2 + e, head = pair / t_half, i = pair - head * t_half;
+      t_c1[e] = head * rope.head_dim + i;                // column of the block; its pair's other one is t_half further on
+      t_cos[e] = rope.cos[(size_t)t_pos * t_half + i];
+      t_sin[e] = rope.sin[(size_t)t_pos * t_half + i];
+    }
+  }
+  if constexpr (NORM) {
+    if (norm.n_splits > 0) {
+      f32x4 add[NC];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) add[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int s = 0; s < norm.n_splits; ++s)
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+          const int at = i * 256 + (int)threadIdx.x;
+          add[i] += __builtin_bit_cast(f32x4, ld16(norm.P + s * norm.split_stride + (size_t)min(row0 + at / kPieces, m - 1) * norm.ldp +
+                                                   min(at % kPieces * E, K - E)));
+        }
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const int at = i * 256 + (int)threadIdx.x, k = at % kPieces * E, row = row0 + at / kPieces;
+        const f32x4 v = __builtin_bit_cast(f32x4, a_reg[i]) + add[i];
+        if (norm.h_out != nullptr && blockIdx.x == 0 && row < m && k < K) *reinterpret_cast<f32x4*>(norm.h_out + (size_t)row * K + k) = v;
+        a_reg[i] = __builtin_bit_cast(u32x4, v);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i)
+    if (k_begin + (i * 256 + (int)threadIdx.x) % kPieces * E >= k_end) a_reg[i] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
     const int at = i * 256 + (int)threadIdx.x;
@@ -758,11 +827,35 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict_
       w_lds[(wave * 16 + row) * kPitch + piece] = k_begin + piece * E < k_end ? w_reg[i] : zero;
     }
   }
+  Frag<float> gain[NORM ? NC * kSteps : 1];
+  if constexpr (NORM) {
+#pragma unroll
+    for (int i = 0; i < NC * kSteps; ++i) gain[i].raw = ld16(norm.gain + min((i * 4 + g) * E, K - E));
+  }
   __syncthreads();
+  __shared__ float inv_s[NORM ? 16 : 1];
+  if constexpr (NORM) {
+    // 16 threads a row; the zeros behind the row's end add nothing
+    const int row = threadIdx.x >> 4, sub = threadIdx.x & 15;
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const f32x4 v = __builtin_bit_cast(f32x4, a_lds[row * kPitch + i * 16 + sub]);
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, kWave);
+    if (sub == 0) inv_s[row] = 1.0f / sqrtf(ss / (float)K + norm.eps);
+    __syncthreads();
+  }
   Frag<float> a[NC * kSteps];
 #pragma unroll
   for (int i = 0; i < NC * kSteps; ++i) {
     a[i].raw = a_lds[r * kPitch + i * 4 + g];
+    if constexpr (NORM) {
+      const f32x4 v = __builtin_bit_cast(f32x4, a[i].raw) * inv_s[r] * __builtin_bit_cast(f32x4, gain[i].raw);
+      a[i].raw = (i * 4 + g) * E < K ? __builtin_bit_cast(u32x4, v) : u32x4{0u, 0u, 0u, 0u};
+    }
     if (MODE == kRowMajor) b[i].raw = w_lds[(wave * 16 + r) * kPitch + i * 4 + g];
   }
   f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
@@ -784,6 +877,33 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict_
     }
     return;
   }
+  if constexpr (ROPE) {
+    __shared__ float turn[16][64 + 4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) turn[g * 4 + j][wave * 16 + r] = sum[j];
+    __syncthreads();
+    const int row = row0 + t_row;
+    if (row >= m) return;
+    float* const q_row = rope.q_out + (size_t)row * rope.dq;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int c1 = t_c1[e], n1 = blockIdx.x * 64 + c1;
+      if (n1 >= N) continue;
+      float x1 = 0.f, x2 = 0.f;
+      if (rope.bias) {
+        x1 = rope.bias[n1];
+        x2 = rope.bias[n1 + t_half];
+      }
+      x1 += turn[t_row][c1];
+      x2 += turn[t_row][c1 + t_half];
+      const bool value = n1 >= rope.dq + rope.dkv;        // value rows are not turned
+      const float o1 = value ? x1 : x1 * t_cos[e] - x2 * t_sin[e], o2 = value ? x2 : x2 * t_cos[e] + x1 * t_sin[e];
+      float* const dst = n1 < rope.dq ? q_row + n1 : value ? v_row + (n1 - rope.dq - rope.dkv) : k_row + (n1 - rope.dq);
+      dst[0] = o1;
+      dst[t_half] = o2;
+    }
+    return;
+  }
   const int col = n_base + r;
   if (col >= N) return;
   float* out = P + (size_t)blockIdx.z * split_stride;
@@ -794,14 +914,14 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict_
   }
 }
 
-template <int MODE>
+template <int MODE, bool NORM = false, bool ROPE = false>
 hipError_t launch_tile(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp, size_t split_stride, int m,
-                       int N, int K, hipStream_t st, void* act) {
+                       int N, int K, hipStream_t st, void* act, const NormArgs& norm = NormArgs{}, const RopeArgs& rope = RopeArgs{}) {
   const dim3 grid((N + 63) / 64, pl.row_chunks, pl.splits);
 #define D2C_TILE(nc_)                                                                                                           \
   if (pl.k_per_split <= nc_ * 64) {                                                                                             \
-    hipLaunchKernelGGL((gemm_tile_kernel<nc_, MODE>), grid, dim3(256), 0, st, (const float*)A, lda, (const float*)W, ldw, P, ldp, \
-                       split_stride, m, N, K, pl.k_per_split, (float*)act);                                                     \
+    hipLaunchKernelGGL((gemm_tile_kernel<nc_, MODE, NORM, ROPE>), grid, dim3(256), 0, st, (const float*)A, lda, (const float*)W,  \
+                       ldw, P, ldp, split_stride, m, N, K, pl.k_per_split, (float*)act, norm, rope);                            \
     return hipGetLastError();                                                                                                   \
   }
   D2C_TILE(1) D2C_TILE(2) D2C_TILE(3) D2C_TILE(4)
@@ -1221,6 +1341,40 @@ hipError_t launch_gemm_swiglu(int dtype, const GemmPlan& pl, const void* A, int 
   if (dtype == kBF16)
     return launch_nt<bf16, kPreSwiglu>(pl, A, lda, W, ldw, nullptr, 0, 0, m, 2 * F, K, st, act);
   return launch_nt<float, kPreSwiglu>(pl, A, lda, W, ldw, nullptr, 0, 0, m, 2 * F, K, st, act);
+}
+
+bool gemm_fuses(int dtype, const GemmPlan& pl) { return dtype == kF32 && pl.tile && pl.splits == 1; }
+bool rope_fuses(int head_dim, int n_calls) { return head_dim % 2 == 0 && 64 % head_dim == 0 && n_calls > 0 && n_calls <= kRopeMaxSeqs; }
+
+hipError_t launch_gemm_tile_fused(const GemmPlan& pl, const NormFuse* norm, const float* A, int lda, const void* W, int ldw,
+                                  const RopeFuse* rope, float* P, int ldp, float* act, int m, int N, int K, hipStream_t st) {
+  if (m <= 0 || N <= 0 || K <= 0 || K % 4 || !gemm_fuses(kF32, pl) || pl.row_chunks * 16 < m || pl.k_per_split < K ||
+      ldw != (K + 63) / 64 || (norm ? norm->n_splits > 0 && norm->ldp < K : lda % 4 != 0 || lda < K) || (rope && act) || (act && N % 32))
+    return hipErrorInvalidValue;
+  NormArgs na{};
+  if (norm) {
+    // h_out: others still read h, and without partial sums there is nothing to update
+    if (norm->h_out == norm->h || (norm->h_out && norm->n_splits == 0) || (norm->ldp | norm->split_stride) % 4) return hipErrorInvalidValue;
+    na = NormArgs{norm->h, norm->P, norm->n_splits, norm->split_stride, norm->ldp, norm->gain, norm->eps, norm->h_out};
+  }
+  const size_t stride = (size_t)m * ldp;
+  if (act)
+    return norm ? launch_tile<kPreSwiglu, true, false>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, act, na)
+                : launch_tile<kPreSwiglu>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, act);
+  if (rope) {
+    RopeArgs ra{};
+    const int dq = rope->n_heads * rope->head_dim, dkv = rope->n_kv_heads * rope->head_dim;
+    if (!rope_fuses(rope->head_dim, rope->n_calls) || !rope_seqs(rope->calls, rope->n_calls, ra.seqs) ||
+        ra.seqs.off[rope->n_calls] != m || N != dq + 2 * dkv)
+      return hipErrorInvalidValue;
+    ra.bias = rope->bias; ra.cos = rope->rope_cos; ra.sin = rope->rope_sin;
+    ra.dq = dq; ra.dkv = dkv; ra.head_dim = rope->head_dim; ra.q_out = rope->q_out;
+    return norm ? launch_tile<kPre, true, true>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, nullptr, na, ra)
+                : launch_tile<kPre, false, true>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, nullptr, na, ra);
+  }
+  if (!P || ldp < N) return hipErrorInvalidValue;
+  return norm ? launch_tile<kPre, true, false>(pl, A, lda, W, ldw, P, ldp, stride, m, N, K, st, nullptr, na)
+              : launch_tile<kPre>(pl, A, lda, W, ldw, P, ldp, stride, m, N, K, st, nullptr);
 }
 
 size_t preshuffled_bytes(int N, int K, int dtype) {

@@ -73,9 +73,10 @@ hipError_t launch_gemm_swiglu(int dtype, const GemmPlan& plan, const void* A, in
 // h[r,:] = emb[tokens[idx[r]],:];  a[r,:] = T(rmsnorm(h[r,:]) * gain)
 hipError_t launch_embed_norm(int dtype, const void* emb, const int32_t* tokens, const int32_t* idx, int m, int d,
                              const float* gain, float eps, float* h, void* a, hipStream_t st);
-// h[r,:] += bias? + sum_s P[s][r,:] (n_splits may be 0);  if a: a[r,:] = T(rmsnorm(h[r,:]) * gain)
-hipError_t launch_add_norm(int dtype, float* h, const float* P, int n_splits, size_t split_stride, int ldp, int m,
-                           int d, const float* gain, float eps, void* a, hipStream_t st);
+// h[r,:] = h_in[r,:] + sum_s P[s][r,:] (n_splits may be 0; then h is not written and h_in is h);
+// if a: a[r,:] = T(rmsnorm(h[r,:]) * gain)
+hipError_t launch_add_norm(int dtype, const float* h_in, float* h, const float* P, int n_splits, size_t split_stride, int ldp,
+                           int m, int d, const float* gain, float eps, void* a, hipStream_t st);
 // a[i,:] = T(rmsnorm(h[rows[i],:]) * gain)
 hipError_t launch_gather_norm(int dtype, const float* h, const int32_t* rows, int n_rows, int d, const float* gain,
                               float eps, void* a, hipStream_t st);
@@ -89,10 +90,50 @@ struct RopeCall {
   int off, m;
 };
 int rope_max_batch();
+// The sequences whose rows one launch covers: rows off .. off+m of the compact buffers belong to a sequence with its own
+// index set and caches.
+constexpr int kRopeMaxSeqs = 8;
+struct RopeSeqs {
+  const int32_t* idx[kRopeMaxSeqs];
+  void* k_cache[kRopeMaxSeqs];
+  void* v_cache[kRopeMaxSeqs];
+  int off[kRopeMaxSeqs + 1];          // off[n] = total rows
+  int n;
+};
+__device__ __forceinline__ int rope_seq_of(const RopeSeqs& sq, int r) {
+  int s = 0;
+  while (s + 1 < sq.n && r >= sq.off[s + 1]) ++s;
+  return s;
+}
+// false: too many, empty or not consecutive
+bool rope_seqs(const RopeCall* calls, int n_calls, RopeSeqs& out);
 hipError_t launch_qkv_rope_scatter(int dtype, const float* P, int n_splits, size_t split_stride, int ldp,
                                    const float* bias, const RopeCall* calls, int n_calls, int n_heads, int n_kv_heads,
                                    int head_dim, const float* rope_cos, const float* rope_sin, void* q_out,
                                    hipStream_t st);
+// What gemm_tile_kernel does beside the product where gemm_fuses (few rows, short contractions, float): the norm (with the
+// residual's update) of its activation rows in front, RoPE and the cache update of the QKV projection behind.  Pre-tiled weights.
+struct NormFuse {              // A = rmsnorm(h + sum_s P[s]) * gain, [m, K]; h_out (not h itself; null = not wanted) = h + sum_s P[s]
+  const float *h, *P;
+  int n_splits;
+  size_t split_stride;
+  int ldp;
+  const float* gain;
+  float eps;
+  float* h_out;
+};
+struct RopeFuse {              // as launch_qkv_rope_scatter's arguments; 64 must be a multiple of head_dim
+  const float* bias;
+  const RopeCall* calls;
+  int n_calls, n_heads, n_kv_heads, head_dim;
+  const float *rope_cos, *rope_sin;
+  float* q_out;
+};
+bool gemm_fuses(int dtype, const GemmPlan& plan);
+bool rope_fuses(int head_dim, int n_calls);
+// P = A W^T (norm null: A as given, [m, lda]); with rope nothing is written to P, with act the gated product to act[m, N / 2]
+hipError_t launch_gemm_tile_fused(const GemmPlan& plan, const NormFuse* norm, const float* A, int lda, const void* W, int ldw,
+                                  const RopeFuse* rope, float* P, int ldp, float* act, int m, int N, int K, hipStream_t st);
 // act[r,f] = T(silu(g) * u), g/u = split sums of columns f and F+f
 hipError_t launch_swiglu(int dtype, const float* P, int n_splits, size_t split_stride, int ldp, int m, int F,
                          void* act, hipStream_t st);
@@ -131,9 +172,11 @@ hipError_t launch_attention_fwd(const Tunables& t, int dtype, const void* q, con
 hipError_t launch_head_mean(const void* probs, size_t probs_layer_stride, float* abar, size_t abar_layer_stride,
                             int n_layers, int n_heads, int m, int L, hipStream_t st);
 // the second launch of the few-row kernels: attn_avg float [m, L] = mean over heads of
-// exp(q k / sqrt(dh) - lse); needs fwd's lse.  Not for attention_is_tiled shapes.
+// exp(q k / sqrt(dh) - lse); needs fwd's lse.  Not for attention_is_tiled shapes.  roll (optional): the rollout block of the
+// first layer as launch_rollout's, (attn_avg + one-hot at idx) / 2
 hipError_t launch_attention_avg(const Tunables& t, int dtype, const void* q, const void* k_cache, const float* lse, int m, int L,
-                                int n_heads, int n_kv_heads, int head_dim, float* attn_avg, hipStream_t st);
+                                int n_heads, int n_kv_heads, int head_dim, float* attn_avg, hipStream_t st, float* roll = nullptr,
+                                const int32_t* idx = nullptr);
 
 // the bf16 kernels for many query rows: forward over a split key range, then one launch that merges the
 // splits and (attn_avg != null) writes the head average.  Several sequences (up to attention_tiled_max_batch)

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kThreads) void embed_norm_kernel(const T* __restric
 }
 
 template <typename T>
-__global__ __launch_bounds__(kThreads) void add_norm_kernel(float* __restrict__ h, const float* __restrict__ P,
+__global__ __launch_bounds__(kThreads) void add_norm_kernel(const float* h_in, float* h, const float* __restrict__ P,
                                                             int n_splits, size_t split_stride, int ldp, int d,
                                                             const float* __restrict__ gain, float eps,
                                                             T* __restrict__ a) {
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kThreads) void add_norm_kernel(float* __restrict__ 
   float* hr = h + (size_t)r * d;
   float ss = 0.f;
   for (int c = threadIdx.x; c < d; c += kThreads) {
-    float v = hr[c];
+    float v = h_in[(size_t)r * d + c];
     float add = 0.f;
     for (int s = 0; s < n_splits; ++s) add += P[(size_t)s * split_stride + (size_t)r * ldp + c];
     v += add;
@@ -82,7 +82,7 @@ __device__ __forceinline__ void store4(bf16* dst, const f32x4& v) {
 // handful of rows); with four pieces per thread more rows are resident per compute unit, which is what many
 // rows need.
 template <typename T, int THREADS, int PIECES>
-__global__ __launch_bounds__(THREADS) void add_norm_vec_kernel(float* __restrict__ h, const float* __restrict__ P,
+__global__ __launch_bounds__(THREADS) void add_norm_vec_kernel(const float* h_in, float* h, const float* __restrict__ P,
                                                                int n_splits, size_t split_stride, int ldp, int d,
                                                                const float* __restrict__ gain, float eps,
                                                                T* __restrict__ a) {
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(THREADS) void add_norm_vec_kernel(float* __restrict
   for (int p = 0; p < PIECES; ++p) {
     const int c = (threadIdx.x + p * THREADS) * 4;
     v[p] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (c < d) v[p] = *reinterpret_cast<const f32x4*>(hr + c);
+    if (c < d) v[p] = *reinterpret_cast<const f32x4*>(h_in + (size_t)r * d + c);
   }
   if (n_splits > 0) {
 #pragma unroll
@@ -166,22 +166,6 @@ __global__ __launch_bounds__(kThreads) void gather_norm_kernel(const float* __re
   const float inv = 1.0f / sqrtf(block_sum(ss, red) / (float)d + eps);
   T* ar = a + (size_t)blockIdx.x * d;
   for (int c = threadIdx.x; c < d; c += kThreads) ar[c] = from_f32<T>(hr[c] * inv * gain[c]);
-}
-
-// The sequences whose rows one RoPE / cache-update launch covers: rows off .. off+m of the compact buffers
-// belong to a sequence with its own index set and caches.
-constexpr int kRopeMaxSeqs = 8;
-struct RopeSeqs {
-  const int32_t* idx[kRopeMaxSeqs];
-  void* k_cache[kRopeMaxSeqs];
-  void* v_cache[kRopeMaxSeqs];
-  int off[kRopeMaxSeqs + 1];          // off[n] = total rows
-  int n;
-};
-__device__ __forceinline__ int rope_seq_of(const RopeSeqs& sq, int r) {
-  int s = 0;
-  while (s + 1 < sq.n && r >= sq.off[s + 1]) ++s;
-  return s;
 }
 
 // One workgroup per selected row.  Columns of the fused projection: n_heads
@@ -379,15 +363,16 @@ hipError_t launch_embed_norm(int dtype, const void* emb, const int32_t* tokens, 
   return hipGetLastError();
 }
 
-hipError_t launch_add_norm(int dtype, float* h, const float* P, int n_splits, size_t split_stride, int ldp, int m,
-                           int d, const float* gain, float eps, void* a, hipStream_t st) {
+hipError_t launch_add_norm(int dtype, const float* h_in, float* h, const float* P, int n_splits, size_t split_stride, int ldp,
+                           int m, int d, const float* gain, float eps, void* a, hipStream_t st) {
+  if (n_splits == 0 && h_in != h) return hipErrorInvalidValue;
   if (m <= 0) return hipSuccess;
   if (d % 4 == 0 && d <= 4096 && ldp % 4 == 0 && split_stride % 4 == 0) {
 #define D2C_ADD_NORM_VEC(THREADS, PIECES)                                                                          \
   D2C_DISPATCH(dtype,                                                                                             \
-               hipLaunchKernelGGL((add_norm_vec_kernel<bf16, THREADS, PIECES>), dim3(m), dim3(THREADS), 0, st, h, P,   \
+               hipLaunchKernelGGL((add_norm_vec_kernel<bf16, THREADS, PIECES>), dim3(m), dim3(THREADS), 0, st, h_in, h, P,   \
                                   n_splits, split_stride, ldp, d, gain, eps, (bf16*)a),                           \
-               hipLaunchKernelGGL((add_norm_vec_kernel<float, THREADS, PIECES>), dim3(m), dim3(THREADS), 0, st, h, P,  \
+               hipLaunchKernelGGL((add_norm_vec_kernel<float, THREADS, PIECES>), dim3(m), dim3(THREADS), 0, st, h_in, h, P,  \
                                   n_splits, split_stride, ldp, d, gain, eps, (float*)a))
     if (d <= 1024) {
       D2C_ADD_NORM_VEC(256, 1);
@@ -400,9 +385,9 @@ hipError_t launch_add_norm(int dtype, float* h, const float* P, int n_splits, si
     return hipGetLastError();
   }
   D2C_DISPATCH(dtype,
-               hipLaunchKernelGGL(add_norm_kernel<bf16>, dim3(m), dim3(kThreads), 0, st, h, P, n_splits, split_stride,
+               hipLaunchKernelGGL(add_norm_kernel<bf16>, dim3(m), dim3(kThreads), 0, st, h_in, h, P, n_splits, split_stride,
                                   ldp, d, gain, eps, (bf16*)a),
-               hipLaunchKernelGGL(add_norm_kernel<float>, dim3(m), dim3(kThreads), 0, st, h, P, n_splits,
+               hipLaunchKernelGGL(add_norm_kernel<float>, dim3(m), dim3(kThreads), 0, st, h_in, h, P, n_splits,
                                   split_stride, ldp, d, gain, eps, (float*)a));
   return hipGetLastError();
 }
@@ -431,20 +416,10 @@ hipError_t launch_qkv_rope_scatter(int dtype, const float* P, int n_splits, size
                                    int head_dim, const float* rope_cos, const float* rope_sin, void* q_out,
                                    hipStream_t st) {
   if (n_calls <= 0) return hipSuccess;
-  if (n_calls > kRopeMaxSeqs || head_dim % 2) return hipErrorInvalidValue;
+  if (head_dim % 2) return hipErrorInvalidValue;
   RopeSeqs sq;
-  memset(&sq, 0, sizeof(sq));
-  int m = 0;
-  for (int i = 0; i < n_calls; ++i) {
-    if (calls[i].m <= 0 || calls[i].off != m) return hipErrorInvalidValue;      // consecutive, non-empty slices
-    sq.idx[i] = calls[i].idx;
-    sq.k_cache[i] = calls[i].k_cache;
-    sq.v_cache[i] = calls[i].v_cache;
-    sq.off[i] = m;
-    m += calls[i].m;
-  }
-  sq.off[n_calls] = m;
-  sq.n = n_calls;
+  if (!rope_seqs(calls, n_calls, sq)) return hipErrorInvalidValue;
+  const int m = sq.off[n_calls];
   // the vector kernel reads P, the bias and the RoPE table in 16-byte pieces
   if (head_dim % 8 == 0 && ldp % 4 == 0 && split_stride % 4 == 0 && (uintptr_t)P % 16 == 0 &&
       (bias == nullptr || (uintptr_t)bias % 16 == 0)) {
@@ -470,6 +445,23 @@ hipError_t launch_qkv_rope_scatter(int dtype, const float* P, int n_splits, size
 }
 
 int rope_max_batch() { return kRopeMaxSeqs; }
+
+bool rope_seqs(const RopeCall* calls, int n_calls, RopeSeqs& sq) {
+  if (n_calls <= 0 || n_calls > kRopeMaxSeqs) return false;
+  memset(&sq, 0, sizeof(sq));
+  int m = 0;
+  for (int i = 0; i < n_calls; ++i) {
+    if (calls[i].m <= 0 || calls[i].off != m) return false;
+    sq.idx[i] = calls[i].idx;
+    sq.k_cache[i] = calls[i].k_cache;
+    sq.v_cache[i] = calls[i].v_cache;
+    sq.off[i] = m;
+    m += calls[i].m;
+  }
+  sq.off[n_calls] = m;
+  sq.n = n_calls;
+  return true;
+}
 
 hipError_t launch_swiglu(int dtype, const float* P, int n_splits, size_t split_stride, int ldp, int m, int F,
                          void* act, hipStream_t st) {

@@ -246,6 +246,26 @@ def _refresh_layer_parity(B, name, wd, L, m, tunables=None):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,H,Hkv,dh,F,L,m", [(256, 4, 4, 64, 688, 128, 1), (256, 4, 2, 64, 688, 150, 128), (60, 6, 3, 2, 80, 40, 17),
+                                              (132, 3, 1, 32, 48, 70, 33), (20, 2, 1, 16, 16, 20, 16), (192, 6, 2, 4, 208, 300, 127)])
+def test_refresh_layer_parity_fused_norm_and_rope(B, d, H, Hkv, dh, F, L, m):
+    """Float layers whose projections make the norm in front and RoPE and the cache update behind: ragged contractions, column
+    blocks with several heads and with a last head cut off, one row and all eight row tiles; and what a bias adds."""
+    wd = W.ModelDims(1, d, H, Hkv, dh, F, 64, dtype="f32")
+    _refresh_layer_parity(B, f"f32 d={d} heads {H}/{Hkv} x {dh}", wd, L, m)
+    mdl = W.model_weights(wd, 0)
+    mdl["layers"][0]["bqkv"] = W.hidden_rows(9, 1, wd.d_q + 2 * wd.d_kv)[0]
+    ctx = B.Context(wd, mdl, L)
+    S, h0 = W.distinct_sorted_rows(3, L, m), W.hidden_rows(4, m, d, std=0.5)
+    kc, vc = (W.hidden_rows(5, L, wd.d_kv, extra=e).astype(np.float64) for e in (1, 2))
+    hidden, kd, vd = torch.from_numpy(h0).cuda(), B.to_device(kc, "f32"), B.to_device(vc, "f32")
+    ctx.d2c_refresh_layer(0, hidden, torch.from_numpy(S).cuda(), S, kd, vd, L, None, None)
+    torch.cuda.synchronize()
+    h_ref, _ = O.refresh_layer(oracle_dims(wd), mdl["layers"][0], h0, S, kc, vc)
+    assert rel_l2(host(hidden), h_ref) < TOL["f32"] and rel_l2(host(kd), kc) < TOL["f32"] and rel_l2(host(vd), vc) < TOL["f32"]
+    ctx.close()
+
+
 def test_refresh_layer_rollout_chain_and_influence(B):
     """Three layers in a row on the same rows: the compact rollout block and c_j against the literal L x L rollout."""
     wd = W.ModelDims(3, 256, 4, 4, 64, 688, 64, dtype="f32")
