@@ -209,6 +209,58 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
     }
   };
 
+  // The products of one chunk: activation fragments from LDS, b_of(step, column tile) the weights.  In bf16 from 2 row tiles on
+  // the fragments are read kAhead of them ahead of their use and the scheduler is told to keep it so: left alone it waits for each
+  // read in front of its step, with 7 row tiles 28 LDS latencies a chunk, longer than the chunk's weights take (97 rows x 3584 x
+  // 18944 38.8 -> 33 us, x 37888 x 3584 66 -> 57, x 4608 x 3584 13.3 -> 12.4; 128 x 24576 x 4096 60 -> 54; 200, two column tiles a
+  // wave, 78 -> 71; 69 rows 3 %, 46 rows 1 %; one row tile loses: 16 x 152064 x 3584 180 -> 184).  A barrier for the scheduler
+  // behind the chunk costs half of that: the next chunk's way into LDS has to start beside the last products.  Four ahead cost
+  // the second workgroup on a compute unit its registers in several rounds of 8 waves (112 x 126464 x 4096 221 us before, three
+  // ahead 218, four 229).
+  auto chunk_steps = [&](const unsigned char* abuf, auto b_of) {
+    auto read_af = [&](int i) {
+      Frag<T> f;
+      f.raw = *reinterpret_cast<const u32x4*>(&abuf[((i % MT) * 16 + r) * kRowStride + ((i / MT) * 4 + g) * 16]);
+      return f;
+    };
+    constexpr int NI = kSteps * MT;
+    if constexpr (sizeof(T) == 2 && MT >= 2) {
+      constexpr int kAhead = WAVES == 8 || WAVES == 6 ? 3 : 4;
+      Frag<T> af[kAhead], bf[NT];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) af[i] = read_af(i);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        if (i % MT == 0) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) bf[nt] = b_of(i / MT, nt);
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) mfma16(acc[i % MT][nt], af[i % kAhead], bf[nt]);
+        if (i + kAhead < NI) af[i % kAhead] = read_af(i + kAhead);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, NT, 0);
+        if (i + kAhead < NI) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s) {
+        Frag<T> bf[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) bf[nt] = b_of(s, nt);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const Frag<T> af = read_af(s * MT + mt);
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) mfma16(acc[mt][nt], af, bf[nt]);
+        }
+      }
+    }
+  };
+
   if (n_chunks <= 0) return;
   if constexpr (NT >= 4) {
     // Many rows: 128 x 64 outputs per wave, one wave per SIMD.  Nothing else hides latencies here, so the
@@ -332,18 +384,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
         const int kc = chunk_k(c);
         u32x4 wv[kSteps];
         lds_read_staged(wv, wbuf + woff[0], wbuf + woff[1], wbuf + woff[2], wbuf + woff[3]);
-#pragma unroll
-        for (int s = 0; s < kSteps; ++s) {
+        chunk_steps(abuf, [&](int s, int) {
           const unsigned keep = (c < n_chunks && kc + s * KS + g * E < k_end) ? 0xffffffffu : 0u;
           Frag<T> bf;
           bf.raw = wv[s] & u32x4{keep, keep, keep, keep};
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            Frag<T> af;
-            af.raw = *reinterpret_cast<const u32x4*>(&abuf[(mt * 16 + r) * kRowStride + (s * 4 + g) * 16]);
-            mfma16(acc[mt][0], af, bf);
-          }
-        }
+          return bf;
+        });
         fence();
         store_a(areg[(u + 1) & 1], (u + 1) & 1);
         __builtin_amdgcn_s_waitcnt(0xc07f);                // lgkmcnt(0): the stores; what is on its way stays so
@@ -376,21 +422,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
       __builtin_amdgcn_sched_barrier(0);   // the requests stay ahead of this iteration's arithmetic
       const unsigned char* abuf = lds[u & 1];
       const int kc = chunk_k(c);
-#pragma unroll
-      for (int s = 0; s < kSteps; ++s) {
-        const unsigned keep = (c < n_chunks && kc + s * KS + g * E < k_end) ? 0xffffffffu : 0u;   // zero in the tail of the last chunk and past it
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          Frag<T> af;
-          af.raw = *reinterpret_cast<const u32x4*>(&abuf[(mt * 16 + r) * kRowStride + (s * 4 + g) * 16]);
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            Frag<T> bf;
-            bf.raw = breg[u][nt][s].raw & u32x4{keep, keep, keep, keep};
-            mfma16(acc[mt][nt], af, bf);
-          }
-        }
-      }
+      chunk_steps(abuf, [&](int s, int nt) {     // zero in the tail of the last chunk and past it
+        const unsigned keep = (c < n_chunks && kc + s * KS + g * E < k_end) ? 0xffffffffu : 0u;
+        Frag<T> bf;
+        bf.raw = breg[u][nt][s].raw & u32x4{keep, keep, keep, keep};
+        return bf;
+      });
       // activation chunk c+1 was requested one iteration ago: its latency is behind us
       store_a(areg[(u + 1) & 1], (u + 1) & 1);
       __syncthreads();
