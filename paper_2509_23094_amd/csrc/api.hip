@@ -492,9 +492,10 @@ int d2c_init_tuned(const d2c_dims* dims, const d2c_weights* w, const d2c_tunable
     return bail(rc);
   c->rollout_bytes = c->ws_bytes - ws0;
   c->attn_scratch_bytes = (int64_t)std::max<size_t>(1, c->attn_part_floats) * 4;
-  // gemm_tile_kernel takes at most 128 rows
-  if (D.dtype == D2C_F32 && (rc = ws_alloc(c, &c->h_mid, std::min<size_t>(Lr, 128) * d * 4))) return bail(rc);
-  if ((rc = ws_alloc(c, &c->hidden, Lr * d * 4)) || (rc = ws_alloc(c, &c->a_norm, Lr * d * ts)) ||
+  // what is small shares an allocation: each takes about 0.1 ms
+  const size_t mid_rows = D.dtype == D2C_F32 ? std::min<size_t>(Lr, 128) : 0;      // gemm_tile_kernel takes at most 128
+  const size_t pre_floats = (size_t)select_max_batch() * select_pre_floats();
+  if ((rc = ws_alloc(c, &c->hidden, (Lr + mid_rows) * d * 4)) || (rc = ws_alloc(c, &c->a_norm, Lr * d * ts)) ||
       (rc = ws_alloc(c, &c->q, (size_t)D.n_layers * Lr * dq * ts)) || (rc = ws_alloc(c, &c->attn_o, Lr * dq * ts)) ||
       (rc = ws_alloc(c, &c->act, Lr * F * ts)) ||
       (rc = ws_alloc(c, &c->lse, (size_t)D.n_layers * D.n_heads * Lr * 4)) ||
@@ -502,11 +503,12 @@ int d2c_init_tuned(const d2c_dims* dims, const d2c_weights* w, const d2c_tunable
       (rc = ws_alloc(c, &c->partial, pf * 4)) ||
       (rc = ws_alloc(c, &c->head_a, (size_t)c->head_rows * d * ts)) ||
       (rc = ws_alloc(c, &c->logits, (size_t)c->head_rows * D.vocab * 4)) ||
-      (rc = ws_alloc(c, &c->conf_part, confidence_scratch_floats(c->max_rows, D.vocab) * 4)) ||
-      (rc = ws_alloc(c, &c->sel_pre, (size_t)select_max_batch() * select_pre_floats() * 4)) ||
+      (rc = ws_alloc(c, &c->sel_pre, (pre_floats + confidence_scratch_floats(c->max_rows, D.vocab)) * 4)) ||
       (rc = ws_alloc(c, &c->rope_cos, Lm * (D.head_dim / 2) * 4)) ||
       (rc = ws_alloc(c, &c->rope_sin, Lm * (D.head_dim / 2) * 4)))
     return bail(rc);
+  c->h_mid = c->hidden + Lr * d;
+  c->conf_part = c->sel_pre + pre_floats;
   c->counts_host_cap = 64;
   if (hipHostMalloc((void**)&c->counts_host, sizeof(int32_t) * D2C_N_COUNTS * c->counts_host_cap) != hipSuccess)
     return bail(fail(c, D2C_ENOMEM, "hipHostMalloc failed"));
