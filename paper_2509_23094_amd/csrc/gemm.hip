@@ -1146,9 +1146,10 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   pl.mt = tiles <= 8 ? (tiles < 1 ? 1 : tiles) : 8;
   pl.row_chunks = tiles <= 8 ? 1 : (tiles + 7) / 8;
   // 129-192 rows in bf16: still one row chunk (10 or 12 row tiles).  Two row chunks pull every weight tile
-  // through the L1 of two compute units, and that pull rate, not HBM, is what bounds the kernel; beyond 12
-  // row tiles the LDS reads of one column tile per wave cost more than the second pull (measured per layer
-  // at the LLaDA shape: 140 rows 170 vs 196 us, 166 rows 192 vs 200 us, 200 rows 214 vs 200 us).
+  // through the L1 of two compute units; beyond 12 row tiles the LDS reads of one column tile per wave cost more than the second
+  // pull (measured per layer at the LLaDA shape, one chunk and two: 144 rows 154 and 163 us, 160 rows 159 and 163; with 12 tiles
+  // they are close since the fragments are read ahead: 176 rows 172 and 168, 192 rows 177 and 169; the Dream shape's 37888 x 3584
+  // and 3584 x 18944 together 144 rows 146 and 156, 176 rows 168 and 159).
   if (tiles > 8 && tiles <= 12 && dtype == kBF16 && t.gemm_tall_chunk && (t.gemm_waves == 0 || t.gemm_waves == 8)) {
     pl.mt = tiles + (tiles & 1);
     pl.row_chunks = 1;
