@@ -49,7 +49,8 @@ constexpr int kStageSlots = NT != 1 ? 0
                                                                                                      : 0;
 
 // silu(g) * u with the quotient from the reciprocal unit and one correction from its own remainder (Markstein's method), as
-// exact as the division that it replaces.
+// exact as the division that it replaces: relative error against 64 bits over |g| < 16 at most 1.5e-7, 4e-8 on average, both.
+// The exponential unit alone (arguments rounded after the product with log2(e)) reaches 1e-6 and is not used.
 __device__ __forceinline__ float gate_of(float g, float e, float u) {      // e = exp(-g), finite
   const float d = 1.0f + e, inv = __builtin_amdgcn_rcpf(d), q = g * inv;
   return copysignf(fmaf(fmaf(-d, q, g), inv, q), g) * u;       // the correction of -0 would lose its sign
@@ -58,15 +59,8 @@ __device__ __forceinline__ float gated(float g, float u) {
   if (!(fabsf(g) < 87.0f)) return g / (1.0f + expf(-g)) * u;   // the steps above need finite terms
   return gate_of(g, expf(-g), u);
 }
-// The same for |g| < 87: exp(-g) = 2^n 2^f with n + f = -g log2(e), n whole and f in two parts.  Without the library's range
-// checks the values of a lane are one stretch of code without branches, which overlaps their latencies.  Relative error against
-// 64 bits over |g| < 16 at most 1.5e-7, 3.2e-8 on average, over |g| < 87 1.8e-7 and 1.9e-8: as of g / (1 + expf(-g)).
-__device__ __forceinline__ float gated_finite(float g, float u) {
-  constexpr float kL2e = -1.44269502162933349609375f, kL2eLo = -1.92596303350e-8f;      // -log2(e): nearest float, what is left
-  const float n = __builtin_rintf(g * kL2e), f = fmaf(g, kL2eLo, fmaf(g, kL2e, -n));
-  return gate_of(g, __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)n), u);
-}
-// Four values of a lane; the wave takes the general form if any of its gates is not finite and below 87.
+// Four values of a lane.  Where all gates of the wave are finite and below 87 this is one stretch of code without branches, which
+// overlaps their latencies.  Both sides give an ordinary gate the same bits: a value depends on its own gate alone.
 __device__ __forceinline__ f32x4 gated4(const f32x4& g, const f32x4& u) {
   bool wide = false;
 #pragma unroll
@@ -77,7 +71,7 @@ __device__ __forceinline__ f32x4 gated4(const f32x4& g, const f32x4& u) {
     for (int j = 0; j < 4; ++j) o[j] = gated(g[j], u[j]);
   } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = gated_finite(g[j], u[j]);
+    for (int j = 0; j < 4; ++j) o[j] = gate_of(g[j], expf(-g[j]), u[j]);
   }
   return o;
 }
@@ -640,8 +634,8 @@ __global__ __launch_bounds__(512, 1) void gemm_wide_kernel(const bf16* __restric
 
   if constexpr (MODE == kPreSwiglu) {
     // column tiles alternate gate, up, gate, up ..  The gated values go through LDS (idle now) and out in 16-byte pieces of
-    // rows: 2-byte stores from the accumulators, a branch and the library's exponential for each, took 5-8 us of the kernel
-    // (860 rows x 24576 x 4096, zeros 139 -> 131 us; with real data, where power bounds the clock, 162 -> 158; in steps 4-5 %).
+    // rows: 2-byte stores from the accumulators, with a branch for each, took 5-8 us of the kernel (rows x 24576 x 4096, fastest
+    // of 40 launches, the 2 % of the waves' order included: 860 rows 159 -> 151 us, 512 rows 91.6 -> 87.4; steps of many rows 3 %).
     constexpr int kCols = 32 * NT, kPitch = kCols + 8;        // hidden columns of the workgroup
     constexpr int kXch = NT % 2 == 0 ? 0 : 4 * MT * 1024;
     static_assert(kXch + 2 * MT * 16 * kPitch * 2 <= 2 * kBuf, "the output tile and the exchanged tiles fit the staging buffers");

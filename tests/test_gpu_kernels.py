@@ -826,6 +826,36 @@ def test_gated_epilogue_of_large_gates(B, m, F):
     ctx.close()
 
 
+@pytest.mark.parametrize("m,F", [(300, 16400), (457, 16400), (200, 16400), (250, 16400)])
+def test_gated_epilogue_of_a_row_depends_on_that_row_alone(B, m, F):
+    """A row of each 16 gets gates beyond 87: every other row keeps its bits.  The rows meet in no other place: without q, K and V
+    of their own all of them attend alike.  300 and 457 rows: pairs of column tiles across two waves; 200 and 250: inside one.
+    As many values as it takes for the last place of a float to show, which changes one bf16 value in 65536."""
+    say(f"gated epilogue, rows apart m={m} F={F}")
+    wd = W.ModelDims(1, 256, 4, 4, 64, F, 64, dtype="bf16")
+    mdl = W.model_weights(wd, 0)
+    layer = mdl["layers"][0]
+    layer["wqkv"][:] = 0.0
+    layer["wo"][0] = 0.0                                                    # column 0 of the residual stays what it is
+    layer["w_gate_up"][:F, 0] = W.round_bf16(W.hidden_rows(7, 1, F, std=20.0)[0])      # and adds to the gates where it is not 0
+    ctx = B.Context(wd, mdl, m, tunables={"gemm_wide_tiles": 2})
+    S, moved = np.arange(m, dtype=np.int32), np.arange(5, m, 16)
+    idx, others = torch.from_numpy(S).cuda(), np.setdiff1d(S, moved)
+    for seed in range(8):
+        h0, got = W.hidden_rows(seed, m, wd.d_model, std=0.5), []
+        for x in (0.0, 20.0):
+            h0[:, 0] = 0.0
+            h0[moved, 0] = x
+            hidden = torch.from_numpy(h0).cuda()
+            kd, vd = (B.to_device(np.zeros((m, wd.d_kv)), "bf16") for _ in range(2))
+            ctx.d2c_refresh_layer(0, hidden, idx, S, kd, vd, m, None, None)
+            torch.cuda.synchronize()
+            got.append(host(hidden))
+        np.testing.assert_array_equal(got[0][others], got[1][others], err_msg=f"rows of draw {seed}")
+        assert (got[0][moved] != got[1][moved]).any(axis=1).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("m,N,K", [(300, 520, 512), (449, 264, 2304), (230, 520, 640)])
 def test_linear_many_rows_unaligned(B, m, N, K):
     """Activations that are not 16-byte aligned cannot be staged straight into LDS: gemm_wide_kernel's splits by another kernel
