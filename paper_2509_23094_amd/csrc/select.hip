@@ -856,7 +856,7 @@ struct SelPre {                                // what the first half leaves for
   float density[kSelMaxL];                     // Eq. 3, per candidate in ascending order
 };
 
-// The current block and its masked tokens (every wave for itself; lane = word of the bitmap); at most ML of them go into cand.
+// The current block and its masked tokens (every wave for itself; lane = word of the bitmap); their positions go into cand.
 struct SelBlock {
   int lo, hi, n_masked, n;
 };
@@ -966,15 +966,24 @@ struct SelFirstLds {
   SelRadix radix;
 };
 
+// A thread's influence scores.  score_out may be the same buffer: they are read before anything is written there.
+template <int PER>
+__device__ __forceinline__ void sel_influence(const SelectArgs& a, float (&inf)[PER]) {
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int j = e * kSelT + (int)threadIdx.x;
+    inf[e] = j < a.L ? a.influence[j] : 0.f;
+  }
+}
+
 // The half without logits.  Leaves the bitmaps mask and, with cand_mode 0, u in sh and every candidate's Eq. 3 sum in
 // its first share's place; ends on a barrier.  Returns the radix buffer to go on with.
 template <int PER>
-__device__ __forceinline__ int sel_first(const SelectArgs& a, SelFirstLds<PER>& sh, int wave) {
+__device__ __forceinline__ int sel_first(const SelectArgs& a, const float (&inf)[PER], SelFirstLds<PER>& sh, int wave) {
   constexpr int T = kSelT, NW = kSelNW, ML = SelFirstLds<PER>::kDensity;
   const int L = a.L, tid = threadIdx.x, lane = tid & 63;
   int buf = 0;
   // ---- mask flags and the Gaussian of Eq. 3
-  float inf[PER];
   for (int i = tid; i < 256; i += T) sh.radix.hist[0][i] = 0ull;
   for (int i = tid; i < 3 * kKnownPad; i += T)
     if (i < kKnownPad || i >= kKnownPad + PER * NW) sh.known[i] = 0ull;
@@ -982,7 +991,6 @@ __device__ __forceinline__ int sel_first(const SelectArgs& a, SelFirstLds<PER>& 
   for (int e = 0; e < PER; ++e) {
     const int j = e * T + tid;
     const bool f = j < L && a.is_masked[j] != 0;
-    inf[e] = j < L ? a.influence[j] : 0.f;
     const u64 word = __ballot(f), known = __ballot(j < L && !f);
     if (lane == 0) {
       sh.mask[e * NW + wave] = word;
@@ -1058,7 +1066,8 @@ __device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER
   const u64 below = low_mask(lane);
   int buf = 0;
   u64 mask_w = 0ull, u_w = 0ull;
-  float dens[PER];
+  float dens[PER], inf[PER];
+  if (!pre) sel_influence<PER>(a, inf);
   if (pre) {
     mask_w = pre->mask[lane];
     u_w = pre->u[lane];
@@ -1080,7 +1089,7 @@ __device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER
   __syncthreads();
   if (a.part) merge_rows(a, wave, sh.conf, sh.pred);
   if (!pre) {
-    (void)sel_first<PER>(a, *first, wave);
+    (void)sel_first<PER>(a, inf, *first, wave);
     mask_w = first->mask[lane];
     if (a.cand_mode == 0) u_w = first->u[lane];
   }
@@ -1191,10 +1200,7 @@ __device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER
     }
   __syncthreads();
   const u64 mst_w = sh.mst[lane], dec_w = sh.dec[lane];
-  if (a.cand_mode != 0) {                                    // stage 2's candidates: everything outside M*
-    float inf[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) inf[e] = e * T + tid < L ? a.influence[e * T + tid] : 0.f;
+  if (!pre && a.cand_mode != 0) {                            // stage 2's candidates: everything outside M*
     sel_stage2<PER>(a, inf, mst_w, sh.radix, &buf, sh.tie, sh.u, wave);
     u_w = sh.u[lane];
   }
@@ -1262,7 +1268,9 @@ __global__ __launch_bounds__(kSelT, 6) void confidence_select_kernel(const float
     __shared__ SelFirstLds<PER> sh;
     const SelectArgs& a = batch.seq[blockIdx.x];
     SelPre* pre = static_cast<SelPre*>(a.pre);
-    (void)sel_first<PER>(a, sh, wave);
+    float inf[PER];
+    sel_influence<PER>(a, inf);
+    (void)sel_first<PER>(a, inf, sh, wave);
     const int tid = threadIdx.x;
     if (tid < 64) {
       pre->mask[tid] = sh.mask[tid];

@@ -329,7 +329,7 @@ def test_refresh_layer_empty_and_errors(B):
 
 
 # ------------------------------------------------------------------ selection
-def _run_select(B, ctx, prm, logits, logit_pos, y, is_masked, P, conf, pred, c):
+def _run_select(B, ctx, prm, logits, logit_pos, y, is_masked, P, conf, pred, c, score_over_influence=False):
     L = len(y)
     dev = "cuda"
     t = {
@@ -340,7 +340,7 @@ def _run_select(B, ctx, prm, logits, logit_pos, y, is_masked, P, conf, pred, c):
     for name in ("mstar", "u_set", "decode_idx", "s_next", "s_rows_next"):
         t[name] = torch.full((L,), -1, dtype=torch.int32, device=dev)
     t["counts"] = torch.zeros(B.N_COUNTS, dtype=torch.int32, device=dev)
-    t["score"] = torch.zeros(L, dtype=torch.float32, device=dev)
+    t["score"] = t["influence"] if score_over_influence else torch.zeros(L, dtype=torch.float32, device=dev)
     lg = torch.from_numpy(logits).to(dev) if len(logit_pos) else None
     lp = torch.from_numpy(logit_pos.astype(np.int32)).to(dev) if len(logit_pos) else None
     ctx.d2c_select(prm, lg, lp, len(logit_pos), t["tokens"], t["is_masked"], L, P, t["conf"], t["pred"], t["influence"],
@@ -572,6 +572,29 @@ def test_select_halves_in_one_launch_and_in_two(B, L):
         one, _ = _run_select(B, ctx, prm, np.zeros((0, V), np.float32), pos[:0], y, is_masked, P, two["conf"], two["pred"], c)
         for name in two:
             np.testing.assert_array_equal(two[name], one[name], err_msg=name)
+    ctx.close()
+
+
+@pytest.mark.parametrize("rows", [0, 5])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("L", [100, 700, 2100])
+def test_select_scores_over_the_influence(B, L, mode, rows):
+    """score_out may be the influence's own buffer: the influence is read before the scores are written."""
+    say(f"select, scores over the influence L={L} mode={mode} rows={rows}")
+    V = 1024
+    wd = W.ModelDims(1, 64, 4, 4, 16, 80, V, dtype="f32")
+    ctx = B.Context(wd, W.model_weights(wd, 0), L)
+    rng = np.random.default_rng(L)
+    is_masked = rng.random(L) < 0.5; is_masked[: L // 3] = False; is_masked[L - 1] = True
+    y = np.where(is_masked, wd.mask_id, 3).astype(np.int32)
+    pos = np.flatnonzero(is_masked)[:rows]
+    prm = B.make_params(10.0, 8, 0.3, 64, 1, mode)
+    conf, c = rng.random(L).astype(np.float32), W.skewed_influence(L, L)
+    args = (B, ctx, prm, W.logits_rows(L, rows, V), pos, y, is_masked, L // 3, conf, np.zeros(L, np.int32), c)
+    apart, over = (_run_select(*args, score_over_influence=o)[0] for o in (False, True))
+    for name in apart:
+        if name != "influence":
+            np.testing.assert_array_equal(apart[name], over[name], err_msg=name)
     ctx.close()
 
 
