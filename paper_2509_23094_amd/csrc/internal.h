@@ -240,7 +240,7 @@ struct SelectArgs {
   void* pre;
 };
 size_t select_pre_floats();
-// first: n_first (up to select_max_batch()) selections with cand_mode 0 whose first half this launch does too (n_rows > 0 then)
+// first: n_first (up to select_max_batch(), or 0) selections with cand_mode 0 whose first half this launch does too (n_rows > 0 then)
 hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st,
                                     const SelectArgs* first = nullptr, int n_first = 0);
 int select_max_len();

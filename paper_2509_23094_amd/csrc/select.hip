@@ -1256,6 +1256,17 @@ __global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) 
   }
 }
 
+// Eq. 1's chunks alone, one a workgroup: where the launch has no first half beside them (pieces of a group but the last, cand_mode 1,
+// a second stream, many sequences).  Memory bounds it; the barriers of two chunks and the registers of a first half cost 4 us on 256
+// rows of 126464 (the Eq. 1 and selection launches of 1200 masked rows 159 us in the kernel below, 144 in this one).
+template <bool VEC>
+__global__ __launch_bounds__(kConfThreads) void confidence_chunk_kernel(const float* __restrict__ logits, int vocab, int chunk, int n_chunks,
+                                                                        float* __restrict__ part) {
+  __shared__ ConfLds lds;
+  if constexpr (VEC) confidence_chunk_vec(logits, vocab, n_chunks, part, blockIdx.y, blockIdx.x, lds);
+  else confidence_chunk(logits, vocab, chunk, n_chunks, part, blockIdx.y, blockIdx.x, lds);
+}
+
 // Eq. 1's chunks, and in front of them the halves without logits of n_first selections: one workgroup each, which runs as long
 // as the chunks of a few dozen rows or longer, so it goes first.  A workgroup has the selection's 8 waves; four make a chunk.
 // Six waves a SIMD: with 117 registers, four, the loads in flight did not fill the memory's queue (200 rows 28.5 us, 25.3 now).
@@ -1332,6 +1343,16 @@ hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, 
                                     int n_first) {
   if (n_rows <= 0) return n_first > 0 ? hipErrorInvalidValue : hipSuccess;
   if (vocab <= 0 || part == nullptr || n_first < 0 || n_first > kSelMaxBatch) return hipErrorInvalidValue;
+  int chunk = kConfChunk;
+  while ((vocab + chunk - 1) / chunk > kConfMaxChunks) chunk *= 2;
+  const int n_chunks = confidence_chunks(vocab);
+  const bool vec = chunk == kConfChunk && vocab % 4 == 0 && vocab >= 4 && (uintptr_t)logits % 16 == 0;
+  if (n_first == 0) {
+    const dim3 grid(n_chunks, n_rows), threads(kConfThreads);
+    if (vec) hipLaunchKernelGGL(confidence_chunk_kernel<true>, grid, threads, 0, st, logits, vocab, chunk, n_chunks, part);
+    else hipLaunchKernelGGL(confidence_chunk_kernel<false>, grid, threads, 0, st, logits, vocab, chunk, n_chunks, part);
+    return hipGetLastError();
+  }
   SelectBatch batch;
   int max_L = 1;
   for (int i = 0; i < n_first; ++i) {
@@ -1342,11 +1363,7 @@ hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, 
     max_L = std::max(max_L, first[i].L);
   }
   for (int i = n_first; i < kSelMaxBatch; ++i) batch.seq[i] = SelectArgs{};
-  int chunk = kConfChunk;
-  while ((vocab + chunk - 1) / chunk > kConfMaxChunks) chunk *= 2;
-  const int n_chunks = confidence_chunks(vocab);
   const dim3 grid(n_first + (unsigned)(((size_t)n_rows * n_chunks + 1) / 2)), threads(kSelT);
-  const bool vec = chunk == kConfChunk && vocab % 4 == 0 && vocab >= 4 && (uintptr_t)logits % 16 == 0;
 #define D2C_CONF(PER_)                                                                                                         \
   do {                                                                                                                         \
     if (vec)                                                                                                                   \

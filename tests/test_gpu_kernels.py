@@ -575,6 +575,33 @@ def test_select_halves_in_one_launch_and_in_two(B, L):
     ctx.close()
 
 
+@pytest.mark.parametrize("rows", [1, 3, 6])
+@pytest.mark.parametrize("V", [40, 8192, 8196, 20001, 40000])
+def test_select_chunks_beside_a_first_half_and_alone(B, V, rows):
+    """Eq. 1's chunks in the launch that does the first half as well (cand_mode 0) and in one of their own (1): odd and even counts
+    of chunks, whole and ragged ones, rows that 16-byte loads take and rows that they do not.  Same bits, and the oracle's values."""
+    say(f"select chunks V={V} rows={rows}")
+    L = 64
+    wd = W.ModelDims(1, 64, 4, 4, 16, 80, V, dtype="f32")
+    mdl = W.model_weights(W.ModelDims(1, 64, 4, 4, 16, 80, 8, dtype="f32"), 0)
+    mdl["tok_emb"] = mdl["lm_head"] = np.zeros((V, 64), np.float32)
+    ctx = B.Context(wd, mdl, L)
+    is_masked = np.arange(L) >= 32
+    y, pos = np.where(is_masked, wd.mask_id, 3).astype(np.int32), np.arange(32, 32 + rows)
+    logits, zero = W.logits_rows(V, rows, V), np.zeros(L, np.int32)
+    conf, pred = [], []
+    for mode in (0, 1):
+        res, _ = _run_select(B, ctx, B.make_params(10.0, 4, 0.3, 32, 1, mode), logits, pos, y, is_masked, 32, zero, zero, W.skewed_influence(L, L))
+        conf.append(res["conf"]), pred.append(res["pred"])
+    np.testing.assert_array_equal(conf[0], conf[1])
+    np.testing.assert_array_equal(pred[0], pred[1])
+    x = logits.astype(np.float64)
+    np.testing.assert_array_equal(pred[0][pos], x.argmax(1))
+    ref = 1.0 / np.exp(x - x.max(1, keepdims=True)).sum(1)
+    np.testing.assert_allclose(conf[0][pos], ref, rtol=1e-5)          # sums of up to 40000 positive floats in chunks
+    ctx.close()
+
+
 @pytest.mark.parametrize("rows", [0, 5])
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("L", [100, 700, 2100])
