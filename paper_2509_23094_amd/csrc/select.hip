@@ -10,6 +10,7 @@
 // the lowest index.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -849,7 +850,8 @@ __global__ __launch_bounds__(kSelT) void confidence_merge_kernel(SelectArgs a) {
 // logits: it runs beside Eq. 1's chunks as workgroups of their launch and leaves its result in a SelPre.  The second (sel_second)
 // merges the chunks, ranks, and emits the sets.  Chunks and selection one after the other, against halves: L 512, 16 logit rows of
 // 126464 5.0 + 13.5 us -> 7.9 (the first half is the longer one) + 6.4; L 3071, 200 rows of 152064 22.6 + 32.5 -> 25.3 + 20.0.
-// A call without logit rows, with cand_mode 1 or in a group of more sequences than a launch takes runs both in one kernel.
+// A call without logit rows, with cand_mode 1 or in a group of more sequences than a launch takes runs both in one kernel, with the
+// block found once and the confidences read where they are needed (L 3071 without rows 30.5 us a call; as two halves behind each other 31.9).
 // PER positions a thread: 1, 2, 4 or 8 for up to 512, 1024, 2048, 4096 positions.
 struct SelPre {                                // what the first half leaves for the second
   u64 mask[64], u[64];                         // masked positions, stage-2 set: bitmaps
@@ -966,24 +968,21 @@ struct SelFirstLds {
   SelRadix radix;
 };
 
-// A thread's influence scores.  score_out may be the same buffer: they are read before anything is written there.
+// What a thread has of the first half.  In a whole selection conf is requested behind Eq. 1's merge and used behind Eq. 3.
 template <int PER>
-__device__ __forceinline__ void sel_influence(const SelectArgs& a, float (&inf)[PER]) {
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int j = e * kSelT + (int)threadIdx.x;
-    inf[e] = j < a.L ? a.influence[j] : 0.f;
-  }
-}
+struct SelOwn {
+  float density[PER];                          // Eq. 3 of candidates t, t + T, ..
+  float inf[PER];                              // influence at positions t, t + T, ..
+  float conf[PER];                             // confidence of candidates t, t + T, ..
+};
 
-// The half without logits.  Leaves the bitmaps mask and, with cand_mode 0, u in sh and every candidate's Eq. 3 sum in
-// its first share's place; ends on a barrier.  Returns the radix buffer to go on with.
-template <int PER>
-__device__ __forceinline__ int sel_first(const SelectArgs& a, const float (&inf)[PER], SelFirstLds<PER>& sh, int wave) {
+// The half without logits.  Leaves the candidates and the bitmaps mask and, with cand_mode 0, u in sh, behind a barrier.  WHOLE: the
+// other half follows in this kernel; Eq. 1's chunks are merged here, the scores cleared.  buf: the radix buffer to go on with.
+template <int PER, bool WHOLE>
+__device__ __forceinline__ SelBlock sel_first(const SelectArgs& a, SelFirstLds<PER>& sh, SelOwn<PER>& mine, int& buf, int wave) {
   constexpr int T = kSelT, NW = kSelNW, ML = SelFirstLds<PER>::kDensity;
   const int L = a.L, tid = threadIdx.x, lane = tid & 63;
-  int buf = 0;
-  // ---- mask flags and the Gaussian of Eq. 3
+  // ---- mask flags and the Gaussian of Eq. 3.  score_out may be the influence's buffer: that is read first
   for (int i = tid; i < 256; i += T) sh.radix.hist[0][i] = 0ull;
   for (int i = tid; i < 3 * kKnownPad; i += T)
     if (i < kKnownPad || i >= kKnownPad + PER * NW) sh.known[i] = 0ull;
@@ -991,11 +990,13 @@ __device__ __forceinline__ int sel_first(const SelectArgs& a, const float (&inf)
   for (int e = 0; e < PER; ++e) {
     const int j = e * T + tid;
     const bool f = j < L && a.is_masked[j] != 0;
+    mine.inf[e] = j < L ? a.influence[j] : 0.f;
     const u64 word = __ballot(f), known = __ballot(j < L && !f);
     if (lane == 0) {
       sh.mask[e * NW + wave] = word;
       sh.known[kKnownPad + e * NW + wave] = known;
     }
+    if (WHOLE && j < L && a.score_out) a.score_out[j] = 0.f;
   }
   for (int i = PER * NW + tid; i < 64; i += T) sh.mask[i] = sh.u[i] = 0ull;
   const float inv2s2 = 1.0f / (2.0f * a.sigma * a.sigma);
@@ -1003,10 +1004,19 @@ __device__ __forceinline__ int sel_first(const SelectArgs& a, const float (&inf)
   const int cut = (int)fminf((float)L, ceilf(sqrtf(105.0f / inv2s2)) + 1.0f);
   const int n_win = (cut + 31) >> 5;
   for (int d = tid; d < n_win * 32; d += T) sh.phi[d] = d < cut ? expf(-((float)d * (float)d) * inv2s2) : 0.f;
+  if (WHOLE && a.part) merge_rows(a, wave, nullptr, nullptr);
   __syncthreads();
   const u64 mask_w = sh.mask[lane];
-  const int n1 = sel_block<PER>(a, mask_w, sh.cand, wave).n;
+  const SelBlock blk = sel_block<PER>(a, mask_w, sh.cand, wave);
+  const int n1 = blk.n;
   __syncthreads();
+  if constexpr (WHOLE) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int i = e * T + tid;
+      mine.conf[e] = i < n1 ? a.conf[sh.cand[i]] : 0.f;
+    }
+  }
 
   // ---- phase 1: Eq. 3 on the masked tokens of the current block.  A wave takes 64 candidates (one a lane) and a share of
   // the distances, 32 at a time: the known positions at those distances are two 32-bit windows of the bitmap, phi is the
@@ -1036,66 +1046,70 @@ __device__ __forceinline__ int sel_first(const SelectArgs& a, const float (&inf)
     }
     sh.density[q * n1p + c] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
   }
-  if (a.cand_mode == 0) sel_stage2<PER>(a, inf, mask_w, sh.radix, &buf, sh.tie, sh.u, wave);
+  if (a.cand_mode == 0) sel_stage2<PER>(a, mine.inf, mask_w, sh.radix, &buf, sh.tie, sh.u, wave);
   else __syncthreads();
-  for (int c = tid; c < n1; c += T) {
-    float sum = 0.f;
-    for (int q = shares - 1; q >= 0; --q) sum += sh.density[q * n1p + c];
-    sh.density[c] = sum;                                       // share 0 of c is read by this thread alone
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int c = e * T + tid;
+    mine.density[e] = 0.f;
+    if (c < n1)
+      for (int q = shares - 1; q >= 0; --q) mine.density[e] += sh.density[q * n1p + c];
   }
-  __syncthreads();
-  return buf;
+  return blk;
 }
 
-template <int PER>
 struct SelSecondLds {
+  u64 tie[64], mst[64], dec[64], u[64];
+  u64 rkey[kRankMax], dkey[kRankMax];
+  int n_small;
+};
+// and with the first half's result from memory: what else that half has
+template <int PER>
+struct SelSplitLds {
   float conf[PER * kSelT];
   int pred[PER * kSelT];
   uint16_t cand[PER * kSelT];
-  u64 tie[64], mst[64], dec[64], u[64];
-  u64 rkey[kRankMax], dkey[kRankMax];
   SelRadix radix;
-  int n_small;
 };
 
-// The half behind Eq. 1.  pre: the first half's result in memory, or null: it runs here, in `first`.
-template <int PER>
-__device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER>& sh, const SelPre* pre, SelFirstLds<PER>* first, int wave) {
+// The half behind Eq. 1, and all of it with SPLIT false (own: SelFirstLds then, SelSplitLds otherwise).
+template <int PER, bool SPLIT, typename Own>
+__device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds& sh, Own& own, int wave) {
   constexpr int T = kSelT, NW = kSelNW;
   const int L = a.L, tid = threadIdx.x, lane = tid & 63;
   const u64 below = low_mask(lane);
   int buf = 0;
-  u64 mask_w = 0ull, u_w = 0ull;
-  float dens[PER], inf[PER];
-  if (!pre) sel_influence<PER>(a, inf);
-  if (pre) {
+  u64 mask_w, u_w = 0ull;
+  SelOwn<PER> mine;
+  SelBlock blk;
+  for (int i = tid; i < 64; i += T) sh.mst[i] = sh.dec[i] = sh.u[i] = sh.tie[i] = 0ull;
+  if constexpr (SPLIT) {
+    const SelPre* pre = static_cast<const SelPre*>(a.pre);
     mask_w = pre->mask[lane];
     u_w = pre->u[lane];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) dens[e] = pre->density[e * T + tid];      // of candidate e T + tid, if there are so many
-  }
-  for (int i = tid; i < 64; i += T) sh.mst[i] = sh.dec[i] = sh.u[i] = sh.tie[i] = 0ull;
-  for (int i = tid; i < 256; i += T) sh.radix.hist[0][i] = 0ull;
-  // confidences and predictions so far, then Eq. 1's chunks of this call's logit rows over them
+    for (int e = 0; e < PER; ++e) mine.density[e] = pre->density[e * T + tid];      // of candidate e T + tid, if there are so many
+    for (int i = tid; i < 256; i += T) own.radix.hist[0][i] = 0ull;
+    // confidences and predictions so far, then Eq. 1's chunks of this call's logit rows over them
 #pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int j = e * T + tid;
-    if (j < L) {
-      sh.conf[j] = a.conf[j];
-      sh.pred[j] = a.pred[j];
-      if (a.score_out) a.score_out[j] = 0.f;
+    for (int e = 0; e < PER; ++e) {
+      const int j = e * T + tid;
+      if (j < L) {
+        own.conf[j] = a.conf[j];
+        own.pred[j] = a.pred[j];
+        if (a.score_out) a.score_out[j] = 0.f;
+      }
     }
+    __syncthreads();
+    if (a.part) merge_rows(a, wave, own.conf, own.pred);
+    blk = sel_block<PER>(a, mask_w, own.cand, wave);
+    __syncthreads();
+  } else {
+    blk = sel_first<PER, true>(a, own, mine, buf, wave);
+    mask_w = own.mask[lane];
+    if (a.cand_mode == 0) u_w = own.u[lane];
   }
-  __syncthreads();
-  if (a.part) merge_rows(a, wave, sh.conf, sh.pred);
-  if (!pre) {
-    (void)sel_first<PER>(a, inf, *first, wave);
-    mask_w = first->mask[lane];
-    if (a.cand_mode == 0) u_w = first->u[lane];
-  }
-  const SelBlock blk = sel_block<PER>(a, mask_w, sh.cand, wave);
   const int n1 = blk.n;
-  __syncthreads();
 
   // ---- phase 2: Eq. 4 (top-k) and the decode set on D(i) * s^i; thread t holds candidates t, t + T, ..  The decode set ranks
   // the same scores, or the confidences alone (conf_decode), and with a threshold also takes every candidate whose confidence
@@ -1112,9 +1126,10 @@ __device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER
     sb[e] = db[e] = 0u;
     if (c < n1) {
       clive |= 1u << e;
-      at[e] = sh.cand[c];
-      cf[e] = sh.conf[at[e]];
-      const float score = (pre ? dens[e] : first->density[c]) * cf[e];
+      at[e] = own.cand[c];
+      if constexpr (SPLIT) cf[e] = own.conf[at[e]];
+      else cf[e] = mine.conf[e];
+      const float score = mine.density[e] * cf[e];
       sb[e] = __float_as_uint(score);
       db[e] = a.conf_decode ? __float_as_uint(cf[e]) : sb[e];
       if (a.score_out) a.score_out[at[e]] = score;
@@ -1147,8 +1162,8 @@ __device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER
       uint32_t any, all, t;
 #pragma unroll
       for (int e = 0; e < PER; ++e) ones[e] = 1ull;
-      sel_reduce(kb, clive, ones, sh.radix, &sum, &any, &all);
-      sel_radix(kb, clive, ones, any, all, (u64)(count - 1), sh.radix, &buf, &t, &above);
+      sel_reduce(kb, clive, ones, own.radix, &sum, &any, &all);
+      sel_radix(kb, clive, ones, any, all, (u64)(count - 1), own.radix, &buf, &t, &above);
       const int ties = count - (int)above;                   // >= 1
 #pragma unroll
       for (int e = 0; e < PER; ++e) {
@@ -1200,8 +1215,8 @@ __device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER
     }
   __syncthreads();
   const u64 mst_w = sh.mst[lane], dec_w = sh.dec[lane];
-  if (!pre && a.cand_mode != 0) {                            // stage 2's candidates: everything outside M*
-    sel_stage2<PER>(a, inf, mst_w, sh.radix, &buf, sh.tie, sh.u, wave);
+  if (!SPLIT && a.cand_mode != 0) {                          // stage 2's candidates: everything outside M*
+    sel_stage2<PER>(a, mine.inf, mst_w, own.radix, &buf, sh.tie, sh.u, wave);
     u_w = sh.u[lane];
   }
 
@@ -1221,7 +1236,8 @@ __device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER
     if (m_b >> lane & 1ull) a.mstar[(pa & 0xffffu) + __popcll(m_b & below)] = j;
     if (d_b >> lane & 1ull) {
       a.decode_idx[(pa >> 16) + __popcll(d_b & below)] = j;
-      a.tokens[j] = sh.pred[j];
+      if constexpr (SPLIT) a.tokens[j] = own.pred[j];
+      else a.tokens[j] = a.pred[j];
       a.is_masked[j] = 0;
     }
     if (u_b >> lane & 1ull) a.u_set[(pb & 0xffffu) + __popcll(u_b & below)] = j;
@@ -1245,15 +1261,9 @@ __device__ __forceinline__ void sel_second(const SelectArgs& a, SelSecondLds<PER
 
 template <int PER, bool SPLIT>
 __global__ __launch_bounds__(kSelT) void select_kernel(const SelectBatch batch) {
-  __shared__ SelSecondLds<PER> sh;
-  const SelectArgs& a = batch.seq[blockIdx.x];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if constexpr (SPLIT) {
-    sel_second<PER>(a, sh, static_cast<const SelPre*>(a.pre), nullptr, wave);
-  } else {
-    __shared__ SelFirstLds<PER> first;
-    sel_second<PER>(a, sh, nullptr, &first, wave);
-  }
+  __shared__ SelSecondLds sh;
+  __shared__ std::conditional_t<SPLIT, SelSplitLds<PER>, SelFirstLds<PER>> own;
+  sel_second<PER, SPLIT>(batch.seq[blockIdx.x], sh, own, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // Eq. 1's chunks alone, one a workgroup: where the launch has no first half beside them (pieces of a group but the last, cand_mode 1,
@@ -1279,16 +1289,16 @@ __global__ __launch_bounds__(kSelT, 6) void confidence_select_kernel(const float
     __shared__ SelFirstLds<PER> sh;
     const SelectArgs& a = batch.seq[blockIdx.x];
     SelPre* pre = static_cast<SelPre*>(a.pre);
-    float inf[PER];
-    sel_influence<PER>(a, inf);
-    (void)sel_first<PER>(a, inf, sh, wave);
+    SelOwn<PER> mine;
+    int buf = 0;
+    (void)sel_first<PER, false>(a, sh, mine, buf, wave);
     const int tid = threadIdx.x;
     if (tid < 64) {
       pre->mask[tid] = sh.mask[tid];
       pre->u[tid] = sh.u[tid];
     }
 #pragma unroll
-    for (int e = 0; e < PER; ++e) pre->density[e * kSelT + tid] = sh.density[e * kSelT + tid];     // those behind the last are not used
+    for (int e = 0; e < PER; ++e) pre->density[e * kSelT + tid] = mine.density[e];      // those behind the last are not used
     return;
   }
   __shared__ ConfLds lds[kSelT / kConfThreads];
