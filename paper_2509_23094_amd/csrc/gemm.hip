@@ -208,9 +208,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(
   // read in front of its step, with 7 row tiles 28 LDS latencies a chunk, longer than the chunk's weights take (97 rows x 3584 x
   // 18944 38.8 -> 33 us, x 37888 x 3584 66 -> 57, x 4608 x 3584 13.3 -> 12.4; 128 x 24576 x 4096 60 -> 54; 200, two column tiles a
   // wave, 78 -> 71; 69 rows 3 %, 46 rows 1 %; one row tile loses: 16 x 152064 x 3584 180 -> 184).  A barrier for the scheduler
-  // behind the chunk costs half of that: the next chunk's way into LDS has to start beside the last products.  Four ahead cost
-  // the second workgroup on a compute unit its registers in several rounds of 8 waves (112 x 126464 x 4096 221 us before, three
-  // ahead 218, four 229).
+  // behind the chunk costs half of that: the next chunk's way into LDS has to start beside the last products.  Four ahead in 8 waves
+  // cost the second workgroup on a compute unit its registers (112 x 126464 x 4096 229 us).  So do three with 7 and 8 row tiles (129
+  // and 132 registers), which shows in the head's several rounds only (us without / three / two ahead: 112 x 126464 x 4096 214 / 216 /
+  // 210, 128 rows 218 / 221 / 225; x 152064 x 3584 243.6 / 242.8 / 237.5 and 251.1 / 250.5 / 255.5), while a layer's single rounds
+  // gain (LLaDA layer of 112 rows 152.6 / 146.8 / 148.7, of 128 159 / 153 / 155.6).
   auto chunk_steps = [&](const unsigned char* abuf, auto b_of) {
     auto read_af = [&](int i) {
       Frag<T> f;
