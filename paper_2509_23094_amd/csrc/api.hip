@@ -266,7 +266,7 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
                         D.head_dim, c->rope_cos, c->rope_sin, (float*)q};
     D2C_TIMED(c, st, D2C_PROF_GEMM, (double)(dq + 2 * dkv) * d * ts,
               launch_gemm_tile_fused(pl, a_ready ? nullptr : &norm, (const float*)c->a_norm, d, c->wqkv[layer], pre_chunks(c, d), &rope,
-                                     nullptr, 0, nullptr, M, dq + 2 * dkv, d, st));
+                                     nullptr, M, dq + 2 * dkv, d, st));
   } else {
     if (!a_ready)
       D2C_TIMED(c, st, D2C_PROF_ROWWISE, 0.0,
@@ -361,7 +361,7 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
     const NormFuse norm{hidden, c->partial, pl.splits, stride, d, c->ffn_norm[layer], D.rms_eps, c->h_mid};
     h_mid = c->h_mid;
     D2C_TIMED(c, st, D2C_PROF_GEMM, 2.0 * F * d * tsize(c),
-              launch_gemm_tile_fused(gate, &norm, nullptr, d, c->w_gate_up[layer], pre_chunks(c, d), nullptr, nullptr, 0,
+              launch_gemm_tile_fused(gate, &norm, nullptr, d, c->w_gate_up[layer], pre_chunks(c, d), nullptr,
                                      (float*)c->act, M, 2 * F, d, st));
   } else if (c->fused_swiglu) {
     pl = gate;

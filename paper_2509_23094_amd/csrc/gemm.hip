@@ -746,15 +746,6 @@ constexpr int kTileWgs = 192;
 // the others read.  ROPE: the output goes through LDS, and q, K and V rows leave turned, as launch_qkv_rope_scatter writes them.
 // 37 rows of the small model, launches and the gaps between them apart: norm + QKV + RoPE 3.1 + 3.8 + 3.6 us -> 6.6, norm +
 // gate/up 3.4 + 4.1 -> 7.3; two layers with 22 launches 91 us a call, 76 with 17.
-struct NormArgs {
-  const float *h, *P;
-  int n_splits;
-  size_t split_stride;
-  int ldp;
-  const float* gain;
-  float eps;
-  float* h_out;
-};
 struct RopeArgs {
   RopeSeqs seqs;
   const float *bias, *cos, *sin;
@@ -764,7 +755,7 @@ struct RopeArgs {
 template <int NC, int MODE, bool NORM, bool ROPE>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
                                                         float* __restrict__ P, int ldp, size_t split_stride, int m, int N, int K,
-                                                        int k_per_split, float* __restrict__ act, const NormArgs norm,
+                                                        int k_per_split, float* __restrict__ act, const NormFuse norm,
                                                         const RopeArgs rope) {
   static_assert(MODE != kRowMajor || !(NORM || ROPE), "fused with pre-tiled weights only");
   constexpr int E = 4, KS = 16, KC = 64;
@@ -949,7 +940,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const float* __restrict_
 
 template <int MODE, bool NORM = false, bool ROPE = false>
 hipError_t launch_tile(const GemmPlan& pl, const void* A, int lda, const void* W, int ldw, float* P, int ldp, size_t split_stride, int m,
-                       int N, int K, hipStream_t st, void* act, const NormArgs& norm = NormArgs{}, const RopeArgs& rope = RopeArgs{}) {
+                       int N, int K, hipStream_t st, void* act, const NormFuse& norm = NormFuse{}, const RopeArgs& rope = RopeArgs{}) {
   const dim3 grid((N + 63) / 64, pl.row_chunks, pl.splits);
 #define D2C_TILE(nc_)                                                                                                           \
   if (pl.k_per_split <= nc_ * 64) {                                                                                             \
@@ -1381,34 +1372,24 @@ bool gemm_fuses(int dtype, const GemmPlan& pl) { return dtype == kF32 && pl.tile
 bool rope_fuses(int head_dim, int n_calls) { return head_dim % 2 == 0 && 64 % head_dim == 0 && n_calls > 0 && n_calls <= kRopeMaxSeqs; }
 
 hipError_t launch_gemm_tile_fused(const GemmPlan& pl, const NormFuse* norm, const float* A, int lda, const void* W, int ldw,
-                                  const RopeFuse* rope, float* P, int ldp, float* act, int m, int N, int K, hipStream_t st) {
+                                  const RopeFuse* rope, float* act, int m, int N, int K, hipStream_t st) {
   if (m <= 0 || N <= 0 || K <= 0 || K % 4 || !gemm_fuses(kF32, pl) || pl.row_chunks * 16 < m || pl.k_per_split < K ||
-      ldw != (K + 63) / 64 || (norm ? norm->n_splits > 0 && norm->ldp < K : lda % 4 != 0 || lda < K) || (rope && act) || (act && N % 32))
+      ldw != (K + 63) / 64 || (norm ? norm->n_splits > 0 && norm->ldp < K : lda % 4 != 0 || lda < K) || !rope == !act ||
+      (act && (!norm || N % 32)))
     return hipErrorInvalidValue;
-  NormArgs na{};
-  if (norm) {
-    // h_out: others still read h, and without partial sums there is nothing to update
-    if (norm->h_out == norm->h || (norm->h_out && norm->n_splits == 0) || (norm->ldp | norm->split_stride) % 4) return hipErrorInvalidValue;
-    na = NormArgs{norm->h, norm->P, norm->n_splits, norm->split_stride, norm->ldp, norm->gain, norm->eps, norm->h_out};
-  }
-  const size_t stride = (size_t)m * ldp;
-  if (act)
-    return norm ? launch_tile<kPreSwiglu, true, false>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, act, na)
-                : launch_tile<kPreSwiglu>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, act);
-  if (rope) {
-    RopeArgs ra{};
-    const int dq = rope->n_heads * rope->head_dim, dkv = rope->n_kv_heads * rope->head_dim;
-    if (!rope_fuses(rope->head_dim, rope->n_calls) || !rope_seqs(rope->calls, rope->n_calls, ra.seqs) ||
-        ra.seqs.off[rope->n_calls] != m || N != dq + 2 * dkv)
-      return hipErrorInvalidValue;
-    ra.bias = rope->bias; ra.cos = rope->rope_cos; ra.sin = rope->rope_sin;
-    ra.dq = dq; ra.dkv = dkv; ra.head_dim = rope->head_dim; ra.q_out = rope->q_out;
-    return norm ? launch_tile<kPre, true, true>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, nullptr, na, ra)
-                : launch_tile<kPre, false, true>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, nullptr, na, ra);
-  }
-  if (!P || ldp < N) return hipErrorInvalidValue;
-  return norm ? launch_tile<kPre, true, false>(pl, A, lda, W, ldw, P, ldp, stride, m, N, K, st, nullptr, na)
-              : launch_tile<kPre>(pl, A, lda, W, ldw, P, ldp, stride, m, N, K, st, nullptr);
+  // h_out: others still read h, and without partial sums there is nothing to update
+  if (norm && (norm->h_out == norm->h || (norm->h_out && norm->n_splits == 0) || (norm->ldp | norm->split_stride) % 4))
+    return hipErrorInvalidValue;
+  if (act) return launch_tile<kPreSwiglu, true, false>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, act, *norm);
+  RopeArgs ra{};
+  const int dq = rope->n_heads * rope->head_dim, dkv = rope->n_kv_heads * rope->head_dim;
+  if (!rope_fuses(rope->head_dim, rope->n_calls) || !rope_seqs(rope->calls, rope->n_calls, ra.seqs) ||
+      ra.seqs.off[rope->n_calls] != m || N != dq + 2 * dkv)
+    return hipErrorInvalidValue;
+  ra.bias = rope->bias; ra.cos = rope->rope_cos; ra.sin = rope->rope_sin;
+  ra.dq = dq; ra.dkv = dkv; ra.head_dim = rope->head_dim; ra.q_out = rope->q_out;
+  return norm ? launch_tile<kPre, true, true>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, nullptr, *norm, ra)
+              : launch_tile<kPre, false, true>(pl, A, lda, W, ldw, nullptr, 0, 0, m, N, K, st, nullptr, NormFuse{}, ra);
 }
 
 size_t preshuffled_bytes(int N, int K, int dtype) {

@@ -131,9 +131,9 @@ struct RopeFuse {              // as launch_qkv_rope_scatter's arguments; 64 mus
 };
 bool gemm_fuses(int dtype, const GemmPlan& plan);
 bool rope_fuses(int head_dim, int n_calls);
-// P = A W^T (norm null: A as given, [m, lda]); with rope nothing is written to P, with act the gated product to act[m, N / 2]
+// A W^T (norm null: A as given, [m, lda]) turned and written by rope, or (with norm) the gated product to act[m, N / 2]
 hipError_t launch_gemm_tile_fused(const GemmPlan& plan, const NormFuse* norm, const float* A, int lda, const void* W, int ldw,
-                                  const RopeFuse* rope, float* P, int ldp, float* act, int m, int N, int K, hipStream_t st);
+                                  const RopeFuse* rope, float* act, int m, int N, int K, hipStream_t st);
 // act[r,f] = T(silu(g) * u), g/u = split sums of columns f and F+f
 hipError_t launch_swiglu(int dtype, const float* P, int n_splits, size_t split_stride, int ldp, int m, int F,
                          void* act, hipStream_t st);
