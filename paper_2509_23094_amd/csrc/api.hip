@@ -352,7 +352,7 @@ int layer_impl(d2c_ctx* c, int layer, float* hidden, const Seg* segs, int n_seg,
   if ((rc = project(c, c->attn_o, dq, c->wo[layer], M, d, dq, &pl, &stride, st)) != D2C_OK) return rc;
   const GemmPlan gate = plan_gemm(c->tun, dt, M, 2 * F, d, true);
   const float* h_mid = hidden;                       // the residual rows behind the attention
-  const bool fuse_gate = c->fused_swiglu && gemm_fuses(dt, gate);
+  const bool fuse_gate = c->fused_swiglu && gemm_fuses(dt, gate) && norm_fuses(pl.splits, d, fuse_qkv);
   if (!fuse_gate)
     D2C_TIMED(c, st, D2C_PROF_ROWWISE, 0.0,
               launch_add_norm(dt, hidden, hidden, c->partial, pl.splits, stride, d, M, d, c->ffn_norm[layer], D.rms_eps,

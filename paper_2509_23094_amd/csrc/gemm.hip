@@ -745,7 +745,9 @@ constexpr int kTileWgs = 192;
 // row tile for itself (16 rows, a few KB), and the first one leaves the updated residual rows in another buffer than the one that
 // the others read.  ROPE: the output goes through LDS, and q, K and V rows leave turned, as launch_qkv_rope_scatter writes them.
 // 37 rows of the small model, launches and the gaps between them apart: norm + QKV + RoPE 3.1 + 3.8 + 3.6 us -> 6.6, norm +
-// gate/up 3.4 + 4.1 -> 7.3; two layers with 22 launches 91 us a call, 76 with 17.
+// gate/up 3.4 + 4.1 -> 7.3; two layers with 22 launches 91 us a call, 76 with 17.  Layers of 64 to 256 columns with 4 to 32 heads of
+// 64, FFN 80 to 2816, 1-128 rows, the QKV projection so against three launches (graph): 4 to 21 % of the layer, none slower; the norm
+// alone by the rule of norm_fuses.
 struct RopeArgs {
   RopeSeqs seqs;
   const float *bias, *cos, *sin;
@@ -1369,6 +1371,16 @@ hipError_t launch_gemm_swiglu(int dtype, const GemmPlan& pl, const void* A, int 
 }
 
 bool gemm_fuses(int dtype, const GemmPlan& pl) { return dtype == kF32 && pl.tile && pl.splits == 1; }
+// Every column block adds up the splits of its rows for itself.  Device us of a layer with the norm inside gate/up less without
+// (1-128 rows, FFN 80-2816, launches from a graph; the launch itself costs the host about 2):
+//   splits      1      2      4      8
+//   K =  64   -1.2   -1.8   -1.7   -0.1
+//   K = 128   -1.0   -1.0   -0.9   +1.2
+//   K = 192   -0.5   -0.5   -0.3   +1.5
+//   K = 256   +0.6   +1.3   +2.5   +7.4   (32 heads of 64: 36 rows 38 us without, 46 with)
+// With 256 columns it is taken for the host's sake, and only where the fused QKV projection gives the device more (3-5 us a layer)
+// than this takes: heads of 128, which are not fused, lost 2-5 % in a graph.
+bool norm_fuses(int n_splits, int K, bool qkv_fused) { return n_splits <= (K <= 64 ? 8 : K <= 192 ? 4 : qkv_fused ? 2 : 0); }
 bool rope_fuses(int head_dim, int n_calls) { return head_dim % 2 == 0 && 64 % head_dim == 0 && n_calls > 0 && n_calls <= kRopeMaxSeqs; }
 
 hipError_t launch_gemm_tile_fused(const GemmPlan& pl, const NormFuse* norm, const float* A, int lda, const void* W, int ldw,

@@ -131,6 +131,8 @@ struct RopeFuse {              // as launch_qkv_rope_scatter's arguments; 64 mus
 };
 bool gemm_fuses(int dtype, const GemmPlan& plan);
 bool rope_fuses(int head_dim, int n_calls);
+// whether the norm that also sums so many splits is the faster inside the projection; qkv_fused: the layer's QKV projection is fused
+bool norm_fuses(int n_splits, int K, bool qkv_fused);
 // A W^T (norm null: A as given, [m, lda]) turned and written by rope, or (with norm) the gated product to act[m, N / 2]
 hipError_t launch_gemm_tile_fused(const GemmPlan& plan, const NormFuse* norm, const float* A, int lda, const void* W, int ldw,
                                   const RopeFuse* rope, float* act, int m, int N, int K, hipStream_t st);

@@ -246,6 +246,15 @@ def _refresh_layer_parity(B, name, wd, L, m, tunables=None):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,H,dh,F,m", [(64, 32, 64, 208, 17), (128, 16, 64, 80, 33), (128, 32, 64, 208, 17), (192, 16, 64, 208, 16),
+                                        (192, 8, 128, 80, 5), (252, 8, 64, 80, 70), (256, 4, 128, 80, 20), (256, 12, 64, 208, 40),
+                                        (256, 32, 64, 208, 31)])
+def test_refresh_layer_parity_split_sums_in_the_norm_and_apart(B, d, H, dh, F, m):
+    """Small float layers whose O projection has 2 to 8 splits: summed inside gate/up's norm, or by a launch in front of it where
+    that is the faster, behind a QKV projection with the norm inside or (heads of 128) without."""
+    _refresh_layer_parity(B, f"f32 d={d} heads {H} x {dh}", W.ModelDims(1, d, H, H, dh, F, 64, dtype="f32"), m + 20, m)
+
+
 @pytest.mark.parametrize("d,H,Hkv,dh,F,L,m", [(256, 4, 4, 64, 688, 128, 1), (256, 4, 2, 64, 688, 150, 128), (60, 6, 3, 2, 80, 40, 17),
                                               (132, 3, 1, 32, 48, 70, 33), (20, 2, 1, 16, 16, 20, 16), (192, 6, 2, 4, 208, 300, 127)])
 def test_refresh_layer_parity_fused_norm_and_rope(B, d, H, Hkv, dh, F, L, m):
