@@ -176,7 +176,8 @@ int d2c_select(d2c_ctx* ctx, const d2c_params* params,
  * d2c_select, with the vocabulary size passed in place of the context.  The call allocates nothing (no
  * hipMalloc / hipFree, no context, no workspace): the only scratch its kernels need -- Eq. 1's per-chunk
  * (max, argmax, sum) triples and the half of the selection that runs beside them -- lives in an array inside
- * the library's device code, 224 KiB per GPU, held until the process ends.  Limits: n_rows <= D2C_STATIC_MAX_ROWS and L <= 4096, else D2C_ESHAPE.
+ * the library's device code, 209 KiB per GPU, held until the process ends.
+ * Limits: n_rows <= D2C_STATIC_MAX_ROWS and L <= 4096, else D2C_ESHAPE.
  * Every call on a GPU shares that GPU's one array (nothing in it has to be cleared between calls): calls
  * that overlap in time on one GPU, on any streams, race; issue them one after the other.
  * d2c_last_error(NULL) holds the text of its last error. */

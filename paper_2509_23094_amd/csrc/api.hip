@@ -42,8 +42,7 @@ bool d2c::set_tunable(Tunables& t, const char* name, int value) {
 // selection's first half.  Each GPU holds its own copy of the array at its own address; the address is looked up once per device.
 constexpr int kStaticMaxRows = D2C_STATIC_MAX_ROWS;
 constexpr size_t kStaticFloats = (size_t)kStaticMaxRows * 64 * 3;        // 64 = most chunks per vocabulary row
-constexpr size_t kStaticPreFloats = 8192;                                // >= select_pre_floats(), checked at the call
-static __device__ __align__(256) float scratch[kStaticFloats + kStaticPreFloats];
+static __device__ __align__(256) float scratch[kStaticFloats + kSelPreFloats];
 
 struct d2c_ctx {
   d2c_dims dims{};
@@ -92,7 +91,7 @@ struct d2c_ctx {
   void* head_a = nullptr;       // T [head_rows, d]
   float* logits = nullptr;      // [head_rows, vocab]
   float* conf_part = nullptr;   // per-chunk (max, argmax, sum) triples of Eq. 1 for every row of a group
-  float* sel_pre = nullptr;     // first halves of the selections of one launch, select_pre_floats() each
+  float* sel_pre = nullptr;     // first halves of the selections of one launch, kSelPreFloats each
   int head_rows = 0;
   float* rope_cos = nullptr;    // [max_seq, head_dim/2]
   float* rope_sin = nullptr;
@@ -494,7 +493,7 @@ int d2c_init_tuned(const d2c_dims* dims, const d2c_weights* w, const d2c_tunable
   c->attn_scratch_bytes = (int64_t)std::max<size_t>(1, c->attn_part_floats) * 4;
   // what is small shares an allocation: each takes about 0.1 ms
   const size_t mid_rows = D.dtype == D2C_F32 ? std::min<size_t>(Lr, 128) : 0;      // gemm_tile_kernel takes at most 128
-  const size_t pre_floats = (size_t)select_max_batch() * select_pre_floats();
+  const size_t pre_floats = (size_t)select_max_batch() * kSelPreFloats;
   if ((rc = ws_alloc(c, &c->hidden, (Lr + mid_rows) * d * 4)) || (rc = ws_alloc(c, &c->a_norm, Lr * d * ts)) ||
       (rc = ws_alloc(c, &c->q, (size_t)D.n_layers * Lr * dq * ts)) || (rc = ws_alloc(c, &c->attn_o, Lr * dq * ts)) ||
       (rc = ws_alloc(c, &c->act, Lr * F * ts)) ||
@@ -691,7 +690,7 @@ int d2c_select_static(const d2c_params* p, int32_t vocab, const float* logits, c
   if (L <= 0 || L > select_max_len())
     return fail(nullptr, D2C_ESHAPE, "L outside (0, " + std::to_string(select_max_len()) + "]");
   if (prompt_len < 0 || prompt_len > L) return fail(nullptr, D2C_EINVAL, "prompt_len outside [0, L]");
-  if (confidence_scratch_floats(n_rows, vocab) > kStaticFloats || select_pre_floats() > kStaticPreFloats) return fail(nullptr, D2C_ESHAPE, "scratch array too small");
+  if (confidence_scratch_floats(n_rows, vocab) > kStaticFloats) return fail(nullptr, D2C_ESHAPE, "scratch array too small");
   float* sp = nullptr;
   if ((rc = static_scratch(&sp))) return rc;
   hipStream_t st = (hipStream_t)stream;
@@ -926,7 +925,7 @@ int d2c_step(d2c_ctx* c, const d2c_params* p, d2c_seq_state* seqs, int32_t batch
     // their halves that need no logits run beside the last chunks of Eq. 1, if the influence is there by then
     const bool split = p->cand_mode == 0 && side == st && all_rows > 0 && n_seg <= select_max_batch();
     if (split)
-      for (int i = 0; i < n_seg; ++i) sel[i].pre = c->sel_pre + (size_t)i * select_pre_floats();
+      for (int i = 0; i < n_seg; ++i) sel[i].pre = c->sel_pre + (size_t)i * kSelPreFloats;
     auto flush = [&]() -> int {
       if (fill == 0) return D2C_OK;
       GemmPlan pl;

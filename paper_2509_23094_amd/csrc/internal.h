@@ -237,11 +237,11 @@ struct SelectArgs {
   // logit rows of this call whose chunks are still to be merged (n_rows may be 0); a row's position is
   // via ? via[pos[row]] : pos[row].  pos and via may be the s_rows_next / s_next that the call overwrites.
   const float* part; const int32_t *pos, *via; int n_rows, n_chunks;
-  // result of the selection's half that needs no logits, select_pre_floats() floats, 8-byte aligned: written by the chunks' launch,
+  // result of the selection's half that needs no logits, kSelPreFloats floats, 8-byte aligned: written by the chunks' launch,
   // read by launch_select.  null (for all sequences of a launch): launch_select does that half as well
   void* pre;
 };
-size_t select_pre_floats();
+constexpr size_t kSelPreFloats = 256 + 4096;      // two bitmaps of 64 words, a float per position of the longest sequence
 // first: n_first (up to select_max_batch(), or 0) selections with cand_mode 0 whose first half this launch does too (n_rows > 0 then)
 hipError_t launch_confidence_chunks(const float* logits, int n_rows, int vocab, float* part, hipStream_t st,
                                     const SelectArgs* first = nullptr, int n_first = 0);

@@ -1344,7 +1344,7 @@ int confidence_chunks(int vocab) {
 
 size_t confidence_scratch_floats(size_t n_rows, int vocab) { return n_rows * confidence_chunks(vocab) * 3; }
 
-size_t select_pre_floats() { return sizeof(SelPre) / sizeof(float); }
+static_assert(sizeof(SelPre) == kSelPreFloats * sizeof(float), "what callers keep for a first half");
 
 // positions a thread of the selection for sequences of up to max_L positions
 static int sel_per(int max_L) { return max_L <= kSelT ? 1 : max_L <= 2 * kSelT ? 2 : max_L <= 4 * kSelT ? 4 : 8; }
