@@ -885,6 +885,37 @@ def test_gated_epilogue_of_large_gates(B, m, F):
     ctx.close()
 
 
+@pytest.mark.parametrize("m,F", [(200, 208), (200, 1040), (250, 208), (250, 1040)])
+def test_refresh_layer_parity_gated_pairs_in_one_wave(B, m, F):
+    """193-256 rows in the kernel for many rows: four column tiles a wave, 7 and 8 row tiles, cut-off rows and column blocks."""
+    _refresh_layer_parity(B, f"bf16-{m}-rows-{F}", W.ModelDims(1, 512, 4, 4, 128, F, 64, dtype="bf16"), m + 30, m,
+                          tunables={"gemm_wide_tiles": 2})
+
+
+@pytest.mark.parametrize("m,F", [(257, 1280), (300, 208), (449, 1024), (200, 208), (250, 1040)])
+def test_gated_epilogue_of_ordinary_gates_beside_large_ones(B, m, F):
+    """Every seventh hidden column has gates far beyond 87 and half of the output columns do not see those: the ordinary gates of
+    mixed waves on their own.  200 and 250 rows: four column tiles a wave, the others three."""
+    say(f"gated epilogue, ordinary gates beside large ones m={m} F={F}")
+    wd = W.ModelDims(1, 512, 4, 4, 128, F, 64, dtype="bf16")
+    mdl = W.model_weights(wd, 0)
+    layer, half = mdl["layers"][0], wd.d_model // 2
+    layer["w_gate_up"][0:F:7] = W.round_bf16(layer["w_gate_up"][0:F:7] * 400.0)
+    layer["w_down"][:half, 0:F:7] = 0.0
+    layer["w_down"][:half] *= 16.0                                          # 2^4: the values stay bf16; the FFN is most of the sum
+    ctx = B.Context(wd, mdl, m, tunables={"gemm_wide_tiles": 2})
+    S, h0 = np.arange(m, dtype=np.int32), W.hidden_rows(4, m, wd.d_model, std=0.5)
+    kc, vc = (np.zeros((m, wd.d_kv)) for _ in range(2))
+    hidden, kd, vd = torch.from_numpy(h0).cuda(), B.to_device(kc, "bf16"), B.to_device(vc, "bf16")
+    ctx.d2c_refresh_layer(0, hidden, torch.from_numpy(S).cuda(), S, kd, vd, m, None, None)
+    torch.cuda.synchronize()
+    h_ref, _ = O.refresh_layer(oracle_dims(wd), layer, h0, S, kc, vc)
+    for r in range(m):
+        assert rel_l2(host(hidden)[r, :half], h_ref[r, :half]) < TOL["bf16"], f"hidden row {r}"
+        assert rel_l2(host(hidden)[r, half:], h_ref[r, half:]) < TOL["bf16"], f"hidden row {r}, large gates"
+    ctx.close()
+
+
 @pytest.mark.parametrize("m,F", [(300, 16400), (457, 16400), (200, 16400), (250, 16400)])
 def test_gated_epilogue_of_a_row_depends_on_that_row_alone(B, m, F):
     """A row of each 16 gets gates beyond 87: every other row keeps its bits.  The rows meet in no other place: without q, K and V

@@ -369,6 +369,37 @@ def test_step_grouped_projections_match_separate_calls(B):
     ctx_1.close()
 
 
+@pytest.mark.parametrize("cand_mode", [0, 1])
+def test_step_more_sequences_than_a_launch_takes(B, cand_mode):
+    """Ten sequences in one group, more than RoPE and the selection take in a launch: both halves of a selection in one kernel, the
+    QKV projection's output turned by launches of its own.  At step 0 the group's masked rows go through the head in pieces."""
+    wd = W.DIMS["C1"]
+    mdl = W.model_weights(wd, 3)
+    for lw in mdl["layers"]:
+        for name in ("wqkv", "wo", "w_gate_up", "w_down"):
+            lw[name] = lw[name] * np.float32(4.0)
+    sus = [W.DecodeSetup(8 + 3 * b, 24 + 2 * (b % 4), 16, 1, k=8, p=0.5) for b in range(10)]
+    gp = B.make_params(10.0, 8, 0.5, 16, 1, cand_mode)
+    ctx_g, ctx_1 = B.Context(wd, mdl, 72, max_batch=10), B.Context(wd, mdl, 72)
+    grouped, single = [], []
+    for b, su in enumerate(sus):
+        y0, m0 = W.initial_sequence(wd, su, 11, seq=b)
+        grouped.append(B.Sequence_(ctx_g, y0, m0, su.prompt_len))
+        single.append(B.Sequence_(ctx_1, y0, m0, su.prompt_len))
+    for t in range(5):
+        say(f"group of ten, cand_mode={cand_mode} t={t}")
+        ctx_g.d2c_step(gp, grouped)
+        for a, b in zip(grouped, single):
+            ctx_1.d2c_step(gp, [b])
+            assert (a.n_s, a.n_rows, a.n_masked) == (b.n_s, b.n_rows, b.n_masked)
+            assert torch.equal(a.s_idx[: a.n_s], b.s_idx[: b.n_s]) and torch.equal(a.s_rows[: a.n_rows], b.s_rows[: b.n_rows])
+            assert torch.equal(a.tokens, b.tokens) and torch.equal(a.is_masked, b.is_masked) and torch.equal(a.pred, b.pred)
+            for name in ("k_cache", "v_cache", "conf", "influence"):
+                assert rel_l2(host(getattr(a, name)), host(getattr(b, name))) < TOL["f32"], name
+    ctx_g.close()
+    ctx_1.close()
+
+
 def test_step_llada_shape_reduced_depth(B):
     """LLaDA-8B geometry at full width and full vocabulary, 2 of the 32 layers: step 0 (all 512 rows)
     and two d2Cache steps, teacher-forced."""
