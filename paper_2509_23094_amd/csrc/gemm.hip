@@ -1134,11 +1134,11 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   const int tiles = (m + 15) / 16;
   pl.mt = tiles <= 8 ? (tiles < 1 ? 1 : tiles) : 8;
   pl.row_chunks = tiles <= 8 ? 1 : (tiles + 7) / 8;
-  // 129-192 rows in bf16: still one row chunk (10 or 12 row tiles).  Two row chunks pull every weight tile
-  // through the L1 of two compute units; beyond 12 row tiles the LDS reads of one column tile per wave cost more than the second
-  // pull (measured per layer at the LLaDA shape, one chunk and two: 144 rows 154 and 163 us, 160 rows 159 and 163; with 12 tiles
-  // they are close since the fragments are read ahead: 176 rows 172 and 168, 192 rows 177 and 169; the Dream shape's 37888 x 3584
-  // and 3584 x 18944 together 144 rows 146 and 156, 176 rows 168 and 159).
+  // 129-192 rows in bf16: still one row chunk (10 or 12 row tiles).  Two row chunks pull every weight tile through the L1 of two
+  // compute units (us per layer at the LLaDA shape, one chunk and two: 144 rows 154 and 163, 160 rows 159 and 163; the Dream shape's
+  // 37888 x 3584 and 3584 x 18944 together, 144 rows 146 and 156).  The line at 12 tiles dates from before the fragments were read
+  // ahead; with that two chunks are the faster from 161 rows on (176 rows 172 and 168, 192 rows 177 and 169, Dream 176 rows 168 and
+  // 159).  It still stands because it and the cost of a split below, too low from 129 rows on, decide this range together.
   if (tiles > 8 && tiles <= 12 && dtype == kBF16 && t.gemm_tall_chunk && (t.gemm_waves == 0 || t.gemm_waves == 8)) {
     pl.mt = tiles + (tiles & 1);
     pl.row_chunks = 1;
@@ -1189,7 +1189,8 @@ GemmPlan plan_gemm(const Tunables& t, int dtype, int m, int N, int K, bool singl
   // Few rows (one row chunk, one column tile per wave): the kernel streams fastest when every compute unit
   // holds one workgroup of equal size, so the waves per workgroup and the split count are chosen together.
   // Cost of a shape = rounds of workgroups over the 256 units x (waves x chunks per split), +4 % per
-  // additional split (its partial is written and read again).  Measured at 48-69 rows: LLaDA QKV 25.1 ->
+  // additional split (its partial is written and read again; 4 % is too little from 129 rows on: 140 x 12288 x 4096 in 8 splits
+  // 43.6 us, 128 rows in 2 28.5).  Measured at 48-69 rows: LLaDA QKV 25.1 ->
   // 22.5 us (6 waves x 2 splits = 256 workgroups instead of 8 x 2 = 192), Dream gate/up 68.6 -> 51.5 us
   // (10 waves = 237 workgroups in one round instead of 296 in two); 4-wave workgroups were slower at every
   // shape and are not searched.

@@ -16,7 +16,7 @@ struct Tunables {
   int gemm_target_wgs = 384;   // aim for at least this many groups of 4 waves per GEMM
   int gemm_max_splits = 8;
   int gemm_wide_min_rows = 257; // these from this many rows on (fewer: see the end of plan_gemm)
-  int gemm_tall_chunk = 1;      // 129-192 bf16 rows as ONE row chunk of 10 or 12 row tiles
+  int gemm_tall_chunk = 1;      // 129-192 bf16 rows as ONE row chunk of 10 or 12 row tiles (see plan_gemm)
   int gemm_wide_tiles = 1;     // many bf16 rows, 128 x 64 outputs per wave: 0 = never, 1 = the faster by plan_gemm's estimate,
                                // 2 = gemm_wide_kernel, 3 = gemm_rows_kernel with four column tiles
   int gemm_wide_mt = 0;        // row tiles per row chunk of these: 6, 7, 8; 0 = by shape
